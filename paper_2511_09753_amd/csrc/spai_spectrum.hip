@@ -13,9 +13,10 @@
 // distance from each to an eigenvalue of S.  Ritz values are Rayleigh quotients, so
 // lambda_min(S) <= theta_min and theta_max <= lambda_max(S).
 //
-// Device work: one thread per row for S v (ascending stored order), the basis products
-// as fixed row chunks summed in a fixed order (deterministic), the basis kept as n x
-// (steps + 1) doubles.  The host reads three scalars per step.
+// Device work: a workgroup owns a block of rows and takes it 256 rows at a time; each
+// launch forms w for its rows (S v, or w - V h) and, from the same w in LDS, the partial
+// products with every basis vector.  Partials are summed in a fixed order (deterministic).
+// alpha, beta and the stopping test stay on the device; the host looks every 64 steps.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,64 +31,220 @@ namespace spai {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kChunks = 512;        // row chunks of the partial basis products
+constexpr int kLzThreads = 1024;
+constexpr int kLzRows = 256;        // rows of w in LDS at a time
+constexpr int kLzBlocks = 256;      // at most: one workgroup per compute unit
 constexpr int kMaxSteps = 2048;
 
-__global__ void k_lz_spmv(PcgMat S, const double* __restrict__ x, double* __restrict__ y) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= S.n) return;
-  double acc = 0.0;
-  const int64_t e = S.row_end(i);
-  for (int64_t q = S.row_begin(i); q < e; ++q) {
-    const int c = S.col[q];
-    if (c >= 0) acc += S.v(q) * x[c];
-  }
-  y[i] = acc;
-}
+struct LzState {
+  double scale;                     // max_i (|alpha_i| + beta_i)
+  int steps, stop;                  // steps taken; 1: invariant subspace or a non-finite step
+};
 
-// part[t * kChunks + c] = sum over the rows of chunk c of V[i, t] w[i]
-__global__ __launch_bounds__(kThreads) void k_lz_dots(const double* __restrict__ V, int64_t ldv,
-                                                      int64_t n, const double* __restrict__ w,
-                                                      double* __restrict__ part) {
-  __shared__ double sh[kThreads];
-  const int c = blockIdx.x, t = blockIdx.y;
-  const int64_t per = (n + kChunks - 1) / kChunks;
-  const int64_t lo = (int64_t)c * per, hi = std::min<int64_t>(n, lo + per);
-  const double* v = V + (int64_t)t * ldv;
-  double acc = 0.0;
-  for (int64_t i = lo + threadIdx.x; i < hi; i += kThreads) acc += v[i] * w[i];
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int d = kThreads / 2; d >= 1; d >>= 1) {
-    if ((int)threadIdx.x < d) sh[threadIdx.x] += sh[threadIdx.x + d];
+// One pass over the rows of a workgroup.  kLzMult: w = S v_{k-1}; kLzSub, kLzNorm: w -= V h
+// (k basis vectors).  Then part[t * gridDim.x + block] = sum over its rows of V[i, t] w[i]
+// (kLzNorm: part[block] = sum of w[i]^2).
+// Bound by reading the basis (8 n k bytes) and, where that is small, by latency: a row's sum
+// takes four threads (entries, or basis vectors, in strides of four), so that a tile of 256
+// rows keeps 1024 threads loading; a wave then owns every sixteenth group of four basis
+// vectors and reads their 256 rows as 16 coalesced loads against w in registers.  Forming w
+// and the products in one launch saves a pass over w.  At n = 262,144 (14 entries per row,
+// 100 steps, 50 vectors on average) kLzMult takes 46 us where a thread per row (its entries
+// read 14 apart, one dependent load after another) and a launch for the products took 146;
+// kLzSub 33 against 38, kLzNorm 22 against 25, and the serial sums of the partials 4.6
+// against 15: 115 us a step against 330.  One workgroup of 16 waves per compute unit: capping
+// the registers at 64 for two spilled and took 1.5 times as long.
+enum { kLzMult = 0, kLzSub = 1, kLzNorm = 2 };
+template <int MODE>
+__global__ __launch_bounds__(kLzThreads) void k_lz_pass(PcgMat S, const double* __restrict__ V,
+                                                        int64_t ldv, int k, int64_t n,
+                                                        int64_t per,
+                                                        const double* __restrict__ h,
+                                                        double* __restrict__ w,
+                                                        double* __restrict__ part,
+                                                        const LzState* st) {
+  if (st->stop) return;
+  __shared__ double s_w[kLzRows];
+  __shared__ double s_red[kLzThreads];
+  __shared__ double s_acc[MODE == kLzNorm ? 1 : kMaxSteps + 1];
+  constexpr int kWaves = kLzThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int64_t lo = (int64_t)blockIdx.x * per, hi = lo + per < n ? lo + per : n;
+  double nrm = 0.0;
+  if constexpr (MODE != kLzNorm)
+    for (int t = tid; t < k; t += kLzThreads) s_acc[t] = 0.0;
+  for (int64_t base = lo; base < hi; base += kLzRows) {
+    if constexpr (MODE == kLzMult) {
+      const int64_t i = base + (tid >> 2);
+      const int l = tid & 3;
+      const double* __restrict__ x = V + (int64_t)(k - 1) * ldv;
+      double acc = 0.0;
+      if (i < hi) {
+        const int64_t e = S.row_end(i);
+        for (int64_t q0 = S.row_begin(i) + l; q0 < e; q0 += 16) {
+          int c[4];
+          double v[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int64_t q = q0 + 4 * u;
+            c[u] = -1;
+            v[u] = 0.0;
+            if (q < e) {
+              c[u] = S.col[q];
+              v[u] = S.v(q);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (c[u] >= 0) acc += v[u] * x[c[u]];
+        }
+      }
+      acc += __shfl_xor(acc, 1, 64);
+      acc += __shfl_xor(acc, 2, 64);
+      if (l == 0) {
+        s_w[tid >> 2] = acc;                       // 0 past the last row
+        if (i < hi) w[i] = acc;
+      }
+    } else {
+      const int r = tid & (kLzRows - 1), g = tid / kLzRows;
+      const int64_t i = base + r;
+      const int64_t ic = i < hi ? i : hi - 1;
+      const double* __restrict__ v = V + ic;
+      double acc = 0.0;
+      int t = g;
+      for (; t + 28 < k; t += 32) {                // eight loads in flight
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = v[(int64_t)(t + 4 * u) * ldv];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += x[u] * h[t + 4 * u];
+      }
+      for (; t < k; t += 4) acc += v[(int64_t)t * ldv] * h[t];
+      s_red[tid] = acc;
+      __syncthreads();
+      if (g == 0) {
+        const double sub = (s_red[r] + s_red[kLzRows + r]) +
+                           (s_red[2 * kLzRows + r] + s_red[3 * kLzRows + r]);
+        const double x = i < hi ? w[i] - sub : 0.0;
+        if (i < hi) w[i] = x;
+        if constexpr (MODE == kLzNorm) nrm += x * x;
+        else s_w[r] = x;
+      }
+    }
     __syncthreads();
+    if constexpr (MODE != kLzNorm) {
+      // four basis vectors per wave at a time, 16 loads in flight; their four sums over
+      // the wave in one transposed tree (7 exchanges instead of 24), vector t in lane 16 t
+      double x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = s_w[lane + 64 * u];
+      const double* __restrict__ vb = V + base + lane;
+      for (int t0 = 4 * wv; t0 < k; t0 += 4 * kWaves) {
+        double a[4];
+        if (base + kLzRows <= hi && t0 + 4 <= k) {
+          double v[4][4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[t][u] = vb[(int64_t)(t0 + t) * ldv + 64 * u];
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            a[t] = (v[t][0] * x[0] + v[t][1] * x[1]) + (v[t][2] * x[2] + v[t][3] * x[3]);
+        } else {                                   // the last rows, the last vectors
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              v[u] = t0 + t < k && base + lane + 64 * u < hi ? vb[(int64_t)(t0 + t) * ldv + 64 * u]
+                                                             : 0.0;
+            a[t] = (v[0] * x[0] + v[1] * x[1]) + (v[2] * x[2] + v[3] * x[3]);
+          }
+        }
+        const bool up = lane >= 32, up16 = (lane & 16) != 0;
+        const double b0 = (up ? a[2] : a[0]) + __shfl_xor(up ? a[0] : a[2], 32, 64);
+        const double b1 = (up ? a[3] : a[1]) + __shfl_xor(up ? a[1] : a[3], 32, 64);
+        double c = (up16 ? b1 : b0) + __shfl_xor(up16 ? b0 : b1, 16, 64);
+#pragma unroll
+        for (int d = 8; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+        const int t = t0 + (lane >> 4);
+        if ((lane & 15) == 0 && t < k) s_acc[t] += c;   // a basis vector belongs to one wave
+      }
+      __syncthreads();
+    }
   }
-  if (threadIdx.x == 0) part[(int64_t)t * kChunks + c] = sh[0];
+  if constexpr (MODE == kLzNorm) {
+    s_red[tid] = nrm;
+    __syncthreads();
+    for (int d = kLzThreads / 2; d >= 1; d >>= 1) {
+      if (tid < d) s_red[tid] += s_red[tid + d];
+      __syncthreads();
+    }
+    if (tid == 0) part[blockIdx.x] = s_red[0];
+  } else {
+    __syncthreads();
+    for (int t = tid; t < k; t += kLzThreads) part[(int64_t)t * gridDim.x + blockIdx.x] = s_acc[t];
+  }
 }
 
-// h[t] = sum_c part[t * kChunks + c], c ascending
-__global__ void k_lz_sum(const double* __restrict__ part, int k, double* __restrict__ h) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+// sum of p[0 .. m) over one wave in a fixed order, on every lane
+__device__ __forceinline__ double lz_sum(const double* __restrict__ p, int m) {
+  double a = 0.0;
+#pragma unroll 4
+  for (int c = threadIdx.x & 63; c < m; c += 64) a += p[c];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) a += __shfl_xor(a, d, 64);
+  return a;
+}
+
+// h[t] = sum_c part[t * m + c], one wave per basis vector
+__global__ __launch_bounds__(kThreads) void k_lz_sum(const double* __restrict__ part, int k, int m,
+                                                     double* __restrict__ h) {
+  const int t = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (t >= k) return;
-  double acc = 0.0;
-  for (int c = 0; c < kChunks; ++c) acc += part[(int64_t)t * kChunks + c];
-  h[t] = acc;
+  const double a = lz_sum(part + (int64_t)t * m, m);
+  if ((threadIdx.x & 63) == 0) h[t] = a;
 }
 
-// w[i] -= sum_{t<k} V[i, t] h[t]
-__global__ void k_lz_sub(const double* __restrict__ V, int64_t ldv, int k, int64_t n,
-                         const double* __restrict__ h, double* __restrict__ w) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double acc = 0.0;
-  for (int t = 0; t < k; ++t) acc += V[i + (int64_t)t * ldv] * h[t];
-  w[i] -= acc;
+// the end of step j: beta_j from the partials of ||w||^2 (every workgroup sums them, in one
+// order), v_{j+1} = w / beta_j where a step follows (next), and on workgroup 0 alpha_j and
+// the stopping test
+__global__ __launch_bounds__(kThreads) void k_lz_next(const double* __restrict__ w, int64_t n,
+                                                      const double* __restrict__ part, int m,
+                                                      const double* __restrict__ h1,
+                                                      const double* __restrict__ h2, int j,
+                                                      double* __restrict__ next,
+                                                      double* __restrict__ alpha,
+                                                      double* __restrict__ beta, LzState* st) {
+  if (st->stop) return;                            // a workgroup that sees this step's own
+                                                   // stop leaves v_{j+1}, which nobody reads
+  const double nb = lz_sum(part, m);
+  const double b = sqrt(nb > 0.0 ? nb : nb == nb ? 0.0 : nb);
+  if (next)
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kThreads)
+      next[i] = w[i] / b;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const double a = h1[j] + h2[j];
+    alpha[j] = a;
+    beta[j] = b;
+    const double sc = fmax(st->scale, fabs(a) + b);
+    st->scale = sc;
+    st->steps = j + 1;
+    if (!isfinite(a) || !isfinite(b) || b <= 1e-12 * sc) st->stop = 1;
+  }
 }
 
 __global__ void k_lz_div(const double* __restrict__ w, double b, int64_t n,
                          double* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = w[i] / b;
+}
+
+__global__ void k_lz_start(LzState* st) {
+  st->scale = 0.0;
+  st->steps = 0;
+  st->stop = 0;
 }
 
 // ---- host: the tridiagonal T_k
@@ -190,53 +347,63 @@ int lanczos_run(const PcgMat& S, int steps, const double* dv0, double* out, int*
   DevPool pool;
   pool.limit = pool_limit;
   int rc;
-  double *V, *w, *part, *h1, *h2, *nb;
+  // rows per workgroup and workgroups
+  const int64_t per = std::max<int64_t>(kLzRows, ((n + kLzBlocks - 1) / kLzBlocks + 63) / 64 * 64);
+  const int nb = (int)((n + per - 1) / per);
+  double *V, *w, *part, *h1, *h2, *ab;
+  LzState* st;
   if ((rc = pool.alloc(&V, n * (int64_t)(K + 1))) || (rc = pool.alloc(&w, n)) ||
-      (rc = pool.alloc(&part, (int64_t)kChunks * (K + 1))) || (rc = pool.alloc(&h1, K + 1)) ||
-      (rc = pool.alloc(&h2, K + 1)) || (rc = pool.alloc(&nb, 1)))
+      (rc = pool.alloc(&part, (int64_t)nb * (K + 1))) || (rc = pool.alloc(&h1, K + 1)) ||
+      (rc = pool.alloc(&h2, K + 1)))
     return rc;
-  const dim3 rows((unsigned)((n + kThreads - 1) / kThreads)), bs(kThreads);
-  auto dots = [&](const double* Vb, int k, const double* x, double* h) {
-    hipLaunchKernelGGL(k_lz_dots, dim3(kChunks, k), bs, 0, s, Vb, ldv, n, x, part);
-    hipLaunchKernelGGL(k_lz_sum, dim3((k + kThreads - 1) / kThreads), bs, 0, s, part, k, h);
+  // alpha, beta and the state: in the basis's last column, which no step writes
+  static_assert(sizeof(LzState) == 2 * sizeof(double), "the state takes two doubles");
+  ab = V + n * (int64_t)K;
+  if (n < 2 * (int64_t)K + 2 && (rc = pool.alloc(&ab, 2 * (int64_t)K + 2))) return rc;
+  st = (LzState*)ab;
+  double *d_alpha = ab + 2, *d_beta = d_alpha + K;
+  const dim3 rows((unsigned)((n + kThreads - 1) / kThreads)), bs(kThreads), lb(kLzThreads);
+  auto sum = [&](int k, double* h) {
+    hipLaunchKernelGGL(k_lz_sum, dim3((k + kThreads / 64 - 1) / (kThreads / 64)), bs, 0, s, part, k,
+                       nb, h);
   };
+  hipLaunchKernelGGL(k_lz_start, dim3(1), dim3(1), 0, s, st);
   // v_0 = v0 / ||v0||
   double nrm2 = 0.0;
-  dots(dv0, 1, dv0, nb);
-  HIPCHK(hipMemcpyAsync(&nrm2, nb, sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(w, dv0, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
+  hipLaunchKernelGGL(k_lz_pass<kLzNorm>, dim3(nb), lb, 0, s, S, V, ldv, 0, n, per, h1, w, part, st);
+  sum(1, h1);
+  HIPCHK(hipMemcpyAsync(&nrm2, h1, sizeof(double), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   if (!(nrm2 > 0.0) || !std::isfinite(nrm2))
     return fail(SPAI_ERR_ARG, "spectrum: start vector zero or not finite");
-  hipLaunchKernelGGL(k_lz_div, rows, bs, 0, s, dv0, std::sqrt(nrm2), n, V);
-  std::vector<double> alpha, beta;
-  double scale = 0.0;
-  int done = 0;
+  hipLaunchKernelGGL(k_lz_div, rows, bs, 0, s, w, std::sqrt(nrm2), n, V);
+  LzState hst{};
   for (int j = 0; j < K; ++j) {
-    const double* vj = V + (int64_t)j * ldv;
-    hipLaunchKernelGGL(k_lz_spmv, rows, bs, 0, s, S, vj, w);
-    dots(V, j + 1, w, h1);
-    hipLaunchKernelGGL(k_lz_sub, rows, bs, 0, s, V, ldv, j + 1, n, h1, w);
-    dots(V, j + 1, w, h2);
-    hipLaunchKernelGGL(k_lz_sub, rows, bs, 0, s, V, ldv, j + 1, n, h2, w);
-    dots(w, 1, w, nb);
+    const int k = j + 1;
+    hipLaunchKernelGGL(k_lz_pass<kLzMult>, dim3(nb), lb, 0, s, S, V, ldv, k, n, per, h1, w, part, st);
+    sum(k, h1);
+    hipLaunchKernelGGL(k_lz_pass<kLzSub>, dim3(nb), lb, 0, s, S, V, ldv, k, n, per, h1, w, part, st);
+    sum(k, h2);
+    hipLaunchKernelGGL(k_lz_pass<kLzNorm>, dim3(nb), lb, 0, s, S, V, ldv, k, n, per, h2, w, part, st);
+    hipLaunchKernelGGL(k_lz_next, dim3(std::min<unsigned>(rows.x, 1024)), bs, 0, s, w, n, part, nb,
+                       h1, h2, j, k < K ? V + (int64_t)k * ldv : nullptr, d_alpha, d_beta, st);
     HIPCHK(hipGetLastError());
-    double hj[3];
-    HIPCHK(hipMemcpyAsync(&hj[0], h1 + j, sizeof(double), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&hj[1], h2 + j, sizeof(double), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&hj[2], nb, sizeof(double), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    const double a = hj[0] + hj[1];
-    const double b = std::sqrt(std::max(hj[2], 0.0));
-    if (!std::isfinite(a) || !std::isfinite(b)) return fail(SPAI_ERR_NONFINITE, "spectrum: non-finite step");
-    alpha.push_back(a);
-    beta.push_back(b);
-    scale = std::max(scale, std::fabs(a) + b);
-    done = j + 1;
-    if (b <= 1e-12 * scale) break;     // invariant subspace: T_k's eigenvalues are exact
-    if (j + 1 < K)
-      hipLaunchKernelGGL(k_lz_div, rows, bs, 0, s, w, b, n, V + (int64_t)(j + 1) * ldv);
+    if (k == K || k % 64 == 0) {       // an invariant subspace ends the process early
+      HIPCHK(hipMemcpyAsync(&hst, st, sizeof(LzState), hipMemcpyDeviceToHost, s));
+      HIPCHK(hipStreamSynchronize(s));
+      if (hst.stop) break;
+    }
   }
+  std::vector<double> alpha((size_t)hst.steps), beta((size_t)hst.steps);
+  HIPCHK(hipMemcpyAsync(alpha.data(), d_alpha, sizeof(double) * hst.steps, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(beta.data(), d_beta, sizeof(double) * hst.steps, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  const double scale = hst.scale;
+  const int done = hst.steps;
+  for (int j = 0; j < done; ++j)
+    if (!std::isfinite(alpha[j]) || !std::isfinite(beta[j]))
+      return fail(SPAI_ERR_NONFINITE, "spectrum: non-finite step");
   const int k = done;
   std::vector<double> a(alpha.begin(), alpha.begin() + k), b(beta.begin(), beta.begin() + k);
   const double bl = b[k - 1];

@@ -48,43 +48,149 @@ __device__ __forceinline__ unsigned long long lanemask_lt() {
   return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-// fixed-tree butterfly sum: every lane gets the bitwise-identical total
+// ---- lane exchanges in registers ------------------------------------------------------
+// The value of lane i ^ D (every lane of the wave active), without the LDS pipe: __shfl_xor
+// becomes ds_bpermute, over 100 cycles of latency a step, where these are one to three VALU
+// instructions (DPP within a row of 16 lanes, gfx950's permlane swaps across rows).
+template <int CTRL>
+__device__ __forceinline__ int lane_dpp(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+}
+// permlane swaps of v with itself: lo holds the lower row's (half's) value on both sides of
+// the exchange, hi the upper one's
+__device__ __forceinline__ void lane_swap16(int v, int& lo, int& hi) {
+  const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+  lo = (int)r[0];
+  hi = (int)r[1];
+}
+__device__ __forceinline__ void lane_swap32(int v, int& lo, int& hi) {
+  const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  lo = (int)r[0];
+  hi = (int)r[1];
+}
+template <int D>
+__device__ __forceinline__ int lane_xor(int v) {
+  static_assert(D == 1 || D == 2 || D == 4 || D == 8 || D == 16 || D == 32, "a power of two");
+  if constexpr (D == 1) return lane_dpp<0xB1>(v);            // quad_perm [1, 0, 3, 2]
+  else if constexpr (D == 2) return lane_dpp<0x4E>(v);       // quad_perm [2, 3, 0, 1]
+  else if constexpr (D == 4) return lane_dpp<0x1B>(lane_dpp<0x141>(v));  // i ^ 7, then i ^ 3
+  else if constexpr (D == 8) return lane_dpp<0x128>(v);      // row_ror 8
+  else {
+    int lo, hi;
+    if constexpr (D == 16) lane_swap16(v, lo, hi); else lane_swap32(v, lo, hi);
+    return (threadIdx.x & D) ? lo : hi;
+  }
+}
+template <int D>
+__device__ __forceinline__ double lane_xor(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = lane_xor<D>((int)(b & 0xffffffffll)), hi = lane_xor<D>((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+template <int D>
+__device__ __forceinline__ long long lane_xor(long long b) {
+  const int lo = lane_xor<D>((int)(b & 0xffffffffll)), hi = lane_xor<D>((int)(b >> 32));
+  return ((long long)hi << 32) | (long long)(unsigned)lo;
+}
+// v + the value of lane i ^ D: the sum of the two sides, so no side has to be picked
+template <int D>
+__device__ __forceinline__ double lane_xor_add(double v) {
+  if constexpr (D < 16) {
+    return v + lane_xor<D>(v);
+  } else {
+    const long long b = __double_as_longlong(v);
+    int l0, h0, l1, h1;
+    if constexpr (D == 16) {
+      lane_swap16((int)(b & 0xffffffffll), l0, l1);
+      lane_swap16((int)(b >> 32), h0, h1);
+    } else {
+      lane_swap32((int)(b & 0xffffffffll), l0, l1);
+      lane_swap32((int)(b >> 32), h0, h1);
+    }
+    return __longlong_as_double(((long long)h0 << 32) | (long long)(unsigned)l0) +
+           __longlong_as_double(((long long)h1 << 32) | (long long)(unsigned)l1);
+  }
+}
+template <int D>
+__device__ __forceinline__ int lane_xor_add(int v) {
+  if constexpr (D < 16) {
+    return v + lane_xor<D>(v);
+  } else {
+    int lo, hi;
+    if constexpr (D == 16) lane_swap16(v, lo, hi); else lane_swap32(v, lo, hi);
+    return lo + hi;
+  }
+}
+
+// fixed-tree butterfly sum (xor 32, 16, 8, 4, 2, 1): every lane gets the bitwise-identical
+// total
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, SPAI_WAVE);
-  return v;
+  v = lane_xor_add<32>(v);
+  v = lane_xor_add<16>(v);
+  v = lane_xor_add<8>(v);
+  v = lane_xor_add<4>(v);
+  v = lane_xor_add<2>(v);
+  return lane_xor_add<1>(v);
 }
 __device__ __forceinline__ int wave_sum_int(int v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, SPAI_WAVE);
-  return v;
+  v = lane_xor_add<1>(v);
+  v = lane_xor_add<2>(v);
+  v = lane_xor_add<4>(v);
+  v = lane_xor_add<8>(v);
+  v = lane_xor_add<16>(v);
+  return lane_xor_add<32>(v);
 }
 __device__ __forceinline__ long long wave_sum_ll(long long v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, SPAI_WAVE);
-  return v;
+  v += lane_xor<1>(v);
+  v += lane_xor<2>(v);
+  v += lane_xor<4>(v);
+  v += lane_xor<8>(v);
+  v += lane_xor<16>(v);
+  return v + lane_xor<32>(v);
 }
-// lane l's value of a 64-bit per-lane register, as a wave-uniform value (l constant)
+__device__ __forceinline__ double wave_max(double v) {
+  v = fmax(v, lane_xor<32>(v));
+  v = fmax(v, lane_xor<16>(v));
+  v = fmax(v, lane_xor<8>(v));
+  v = fmax(v, lane_xor<4>(v));
+  v = fmax(v, lane_xor<2>(v));
+  return fmax(v, lane_xor<1>(v));
+}
+// lane l's value of a 64-bit per-lane register, as a wave-uniform value (l wave-uniform)
 __device__ __forceinline__ int64_t wave_read64(int64_t v, int l) {
   const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(uint64_t)v, l);
   const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)((uint64_t)v >> 32), l);
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
+// lane l's double (l wave-uniform)
+__device__ __forceinline__ double wave_readf(double v, int l) {
+  return __longlong_as_double(wave_read64(__double_as_longlong(v), l));
+}
 __device__ __forceinline__ int wave_max_int(int v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v = max(v, __shfl_xor(v, d, SPAI_WAVE));
-  return v;
+  v = max(v, lane_xor<1>(v));
+  v = max(v, lane_xor<2>(v));
+  v = max(v, lane_xor<4>(v));
+  v = max(v, lane_xor<8>(v));
+  int lo, hi;
+  lane_swap16(v, lo, hi);
+  lane_swap32(max(lo, hi), lo, hi);
+  return max(lo, hi);
 }
 
-// inclusive prefix sum over the wave
+// inclusive prefix sum over the wave: four shifts within the rows of 16 lanes, then each
+// odd row adds the row before it and the upper half the lower half's total
 __device__ __forceinline__ int wave_incl_scan(int v) {
-  const int l = lane_id();
-#pragma unroll
-  for (int d = 1; d < SPAI_WAVE; d <<= 1) {
-    int t = __shfl_up(v, d, SPAI_WAVE);
-    if (l >= d) v += t;
-  }
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr 1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // 2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // 4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast 15 into rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast 31 into rows 2, 3
   return v;
+}
+// lane 63's value of a scan: the wave's total, wave-uniform
+__device__ __forceinline__ int wave_last(int v) {
+  return __builtin_amdgcn_readlane(v, SPAI_WAVE - 1);
 }
 
 __device__ __forceinline__ unsigned hash_key(int k) {
@@ -253,6 +359,18 @@ __device__ inline void bitonic_sort_int(int* a, int S) {
   }
 }
 
+// lane_xor with a distance that unrolling makes a constant
+__device__ __forceinline__ int lane_xor_var(int v, int d) {
+  switch (d) {
+    case 1: return lane_xor<1>(v);
+    case 2: return lane_xor<2>(v);
+    case 4: return lane_xor<4>(v);
+    case 8: return lane_xor<8>(v);
+    case 16: return lane_xor<16>(v);
+    default: return lane_xor<32>(v);
+  }
+}
+
 // Ascending bitonic sort of 64 * C keys held in registers: element c * 64 + lane is
 // v[c].  Fully unrolled so every register index is a compile-time constant.
 template <int C>
@@ -277,7 +395,7 @@ __device__ __forceinline__ void wave_bitonic(int (&v)[C]) {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
           const int i = c * 64 + lane;
-          const int o = __shfl_xor(v[c], j, SPAI_WAVE);
+          const int o = lane_xor_var(v[c], j);
           const bool asc = ((i & k) == 0);
           const bool lower = ((i & j) == 0);
           v[c] = (lower == asc) ? min(v[c], o) : max(v[c], o);
@@ -503,6 +621,48 @@ __device__ __forceinline__ int oh_compact(unsigned* T, int end) {
   return cnt;
 }
 
+// ---- clash-free cells: a multiplicative hash whose multiplier is picked per column (row)
+// so that no two of its keys share a cell; a lookup is then one read with no probing
+constexpr int kBtCells = 1024;
+constexpr int kBtMuls = 16;
+
+// odd 24-bit multipliers (a column retries with the next one while two of its rows
+// share a cell)
+__device__ __forceinline__ unsigned bt_mul(int a) {
+  switch (a & 15) {
+    case 0: return 0x9E3779u;
+    case 1: return 0x85EBCBu;
+    case 2: return 0xC2B2AFu;
+    case 3: return 0x27D4EBu;
+    case 4: return 0x165667u;
+    case 5: return 0xD3A265u;
+    case 6: return 0xFD7047u;
+    case 7: return 0xB55A4Fu;
+    case 8: return 0x7FEB35u;
+    case 9: return 0x846CA7u;
+    case 10: return 0x2C1B3Du;
+    case 11: return 0x297A2Du;
+    case 12: return 0xA136ABu;
+    case 13: return 0x9E6C63u;
+    case 14: return 0x1B8735u;
+    default: return 0xCC9E2Du;
+  }
+}
+
+// multiplicative hash on 24-bit words: the top 10 of the low 24 bits of row * m, from
+// one full-rate 24-bit multiply.  A cluster of nearby rows (a column of a matrix with
+// local couplings) spreads over the cells almost like a linear map, so the first
+// multiplier seldom clashes.  Rows equal in their low 24 bits share a cell under every
+// multiplier; a column holding two such rows goes to the next tier.
+// (The multiply is written out: left to itself the compiler sees that only the low 24
+// bits of the operands matter, drops the 24-bit form and emits the quarter-rate 32-bit
+// multiply instead.)
+__device__ __forceinline__ unsigned bt_cell(int row, unsigned m) {
+  unsigned p;
+  asm("v_mul_u32_u24 %0, %1, %2" : "=v"(p) : "v"(row), "v"(m));
+  return (p >> 14) & (unsigned)(kBtCells - 1);
+}
+
 // Sum of six values over the wave as a fixed transpose tree: the first three halving
 // steps exchange half of the live values (six padded to eight), the last three add the
 // single remaining value; every step pairs lanes by xor, so the order of the additions
@@ -517,7 +677,7 @@ __device__ __forceinline__ void wave_sum6(double (&v)[6]) {
   for (int c = 0; c < 4; ++c) {
     const double send = up32 ? a[c] : a[c + 4];
     const double keep = up32 ? a[c + 4] : a[c];
-    b[c] = keep + __shfl_xor(send, 32, SPAI_WAVE);
+    b[c] = keep + lane_xor<32>(send);
   }
   // xor 16: keep two of the four
   const bool up16 = (lane & 16) != 0;
@@ -526,7 +686,7 @@ __device__ __forceinline__ void wave_sum6(double (&v)[6]) {
   for (int c = 0; c < 2; ++c) {
     const double send = up16 ? b[c] : b[c + 2];
     const double keep = up16 ? b[c + 2] : b[c];
-    d[c] = keep + __shfl_xor(send, 16, SPAI_WAVE);
+    d[c] = keep + lane_xor<16>(send);
   }
   // xor 8: keep one of the two
   const bool up8 = (lane & 8) != 0;
@@ -534,13 +694,14 @@ __device__ __forceinline__ void wave_sum6(double (&v)[6]) {
   {
     const double send = up8 ? d[0] : d[1];
     const double keep = up8 ? d[1] : d[0];
-    e = keep + __shfl_xor(send, 8, SPAI_WAVE);
+    e = keep + lane_xor<8>(send);
   }
-#pragma unroll
-  for (int dd = 4; dd >= 1; dd >>= 1) e += __shfl_xor(e, dd, SPAI_WAVE);
+  e = lane_xor_add<4>(e);
+  e = lane_xor_add<2>(e);
+  e = lane_xor_add<1>(e);
   // value q = 4 (lane bit 5) + 2 (bit 4) + (bit 3) lives in lane 8 q (and its group)
 #pragma unroll
-  for (int q = 0; q < 6; ++q) v[q] = __shfl(e, 8 * q, SPAI_WAVE);
+  for (int q = 0; q < 6; ++q) v[q] = wave_readf(e, 8 * q);
 }
 
 // Columns of a grid-stride loop.  The columns are split into 8 contiguous ranges,

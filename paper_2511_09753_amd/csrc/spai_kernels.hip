@@ -69,52 +69,13 @@ struct Carve {
 // column among kBtMuls odd constants so that no two rows of one list share a cell; a
 // lookup is then one cell read plus one entry read per list, with no probing and no
 // branches.
-constexpr int kBtCells = 1024;
-constexpr int kBtMuls = 16;
 constexpr int kBtNone = -2;           // the sentinel's row (ELL padding asks for -1)
-
-// odd 24-bit multipliers (a column retries with the next one while two of its rows
-// share a cell)
-__device__ __forceinline__ unsigned bt_mul(int a) {
-  switch (a & 15) {
-    case 0: return 0x9E3779u;
-    case 1: return 0x85EBCBu;
-    case 2: return 0xC2B2AFu;
-    case 3: return 0x27D4EBu;
-    case 4: return 0x165667u;
-    case 5: return 0xD3A265u;
-    case 6: return 0xFD7047u;
-    case 7: return 0xB55A4Fu;
-    case 8: return 0x7FEB35u;
-    case 9: return 0x846CA7u;
-    case 10: return 0x2C1B3Du;
-    case 11: return 0x297A2Du;
-    case 12: return 0xA136ABu;
-    case 13: return 0x9E6C63u;
-    case 14: return 0x1B8735u;
-    default: return 0xCC9E2Du;
-  }
-}
 
 template <typename T>
 struct BtEnt {
   int row;
   T val;
 };
-
-// multiplicative hash on 24-bit words: the top 10 of the low 24 bits of row * m, from
-// one full-rate 24-bit multiply.  A cluster of nearby rows (a column of a matrix with
-// local couplings) spreads over the cells almost like a linear map, so the first
-// multiplier seldom clashes.  Rows equal in their low 24 bits share a cell under every
-// multiplier; a column holding two such rows goes to the next tier.
-// (The multiply is written out: left to itself the compiler sees that only the low 24
-// bits of the operands matter, drops the 24-bit form and emits the quarter-rate 32-bit
-// multiply instead.)
-__device__ __forceinline__ unsigned bt_cell(int row, unsigned m) {
-  unsigned p;
-  asm("v_mul_u32_u24 %0, %1, %2" : "=v"(p) : "v"(row), "v"(m));
-  return (p >> 14) & (unsigned)(kBtCells - 1);
-}
 
 // a value masked to zero in the iterate's type, then widened: the opaque copy keeps the
 // compiler from widening first and masking both halves of the double
@@ -241,7 +202,7 @@ __device__ inline int degree_prefix(const Csr& A, const int* rows, int cnt, int*
     }
     const int inc = wave_incl_scan(d);
     if (e < cnt) pre[e] = run + inc;
-    run += __shfl(inc, SPAI_WAVE - 1, SPAI_WAVE);
+    run += wave_last(inc);
   }
   return run;
 }
@@ -731,7 +692,7 @@ void launch_zero_cols(int64_t n, Cols<T> X, hipStream_t s) {
 // upper bound of nnz(r_j): 1 + sum_{l in supp(m_j)} deg(l).  Eight lanes per column read
 // its entries together (two per lane in flight) and add their degrees with shuffles: an
 // integer sum, the same in any order.
-constexpr int kBoundLanes = 8;
+constexpr int kBoundLanes = 8;   // the three exchanges below
 template <typename T>
 __global__ __launch_bounds__(256) void k_bound_resid(Csr A, Pair<T> Mp, int64_t* ub, int64_t n,
                                                      const DevState* st) {
@@ -753,8 +714,9 @@ __global__ __launch_bounds__(256) void k_bound_resid(Csr A, Pair<T> Mp, int64_t*
       s += A.rowptr[l + 1] - A.rowptr[l];
     }
   }
-#pragma unroll
-  for (int d = 1; d < kBoundLanes; d <<= 1) s += __shfl_xor(s, d, SPAI_WAVE);   // all lanes
+  s += lane_xor<1>(s);                               // all lanes
+  s += lane_xor<2>(s);
+  s += lane_xor<4>(s);
   if (j < n && g == 0) ub[j] = 1 + s;
 }
 
@@ -1845,14 +1807,12 @@ __device__ inline double kth_largest_cols(const int32_t* idx, const T* val, int 
     if (__popcll(um) > b) {
       int r = 0;
       for (int f = 0; f < cnt; ++f) {
-        const double y = __shfl(x, f, SPAI_WAVE);
+        const double y = wave_readf(x, f);
         if ((um >> f) & 1ull) r += (y > x) || (y == x && f < lane);
       }
       if (use && r == b) t = x;
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) t = fmax(t, __shfl_xor(t, d, SPAI_WAVE));
-    return t;
+    return wave_max(t);
   }
   int m = 0;
   for (int e = lane_id(); e < cnt; e += SPAI_WAVE) m += idx[e] != skip;
@@ -1871,9 +1831,7 @@ __device__ inline double kth_largest_cols(const int32_t* idx, const T* val, int 
       if (r == b) t = x;
     }
   }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) t = fmax(t, __shfl_xor(t, d, SPAI_WAVE));
-  return t;
+  return wave_max(t);
 }
 
 template <typename T, bool GS>
@@ -1965,10 +1923,10 @@ __device__ __forceinline__ void update_body(Csr A, Pair<T> Mp, Cols<T> R, Pair<T
         s_nbbeg[t] = M.beg[l];
       }
       const unsigned long long dj = __ballot(l == (int)j);
-      if (dj) ajj = __shfl(av, __ffsll((long long)dj) - 1, SPAI_WAVE);
+      if (dj) ajj = wave_readf(av, __ffsll((long long)dj) - 1);
       const int inc = wave_incl_scan(len);
       if (t < deg) s_nboff[t] = onb + run + inc - len;
-      run += __shfl(inc, SPAI_WAVE - 1, SPAI_WAVE);
+      run += wave_last(inc);
     }
     if (lane == 0) s_nboff[deg] = onb + run;
     const int ltot = onb + (nb_lds ? run : 0);
@@ -2457,7 +2415,7 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
       continue;
     }
     const unsigned long long dj = __ballot(nl == (int)j);
-    const double ajj = dj ? __shfl(av, __ffsll((long long)dj) - 1, SPAI_WAVE) : 0.0;
+    const double ajj = dj ? wave_readf(av, __ffsll((long long)dj) - 1) : 0.0;
     const int Hc = next_pow2((int)min<int64_t>(max<int64_t>(ub, 64), (int64_t)H));
     const int ksh = 32 - log2_pow2(Hc);
     const int kend = Hc + kOhOver;
@@ -2518,7 +2476,7 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
       }
     // neighbour products in ascending l: one round per neighbour, distinct ranks inside
     for (int t = 0; t < deg; ++t) {
-      const double a_t = __shfl(av, t, SPAI_WAVE);
+      const double a_t = wave_readf(av, t);
       // the entries of m_t: distinct rows, so distinct ranks (a lane's slots too)
 #pragma unroll
       for (int k = 0; k < NS; ++k)
@@ -2760,7 +2718,7 @@ __device__ __forceinline__ Group64 group_load(const Cols<T>& X, int64_t j0, int6
   }
   const int inc = wave_incl_scan(g.cl);
   g.ex = inc - g.cl;
-  g.T = __shfl(inc, SPAI_WAVE - 1, SPAI_WAVE);
+  g.T = wave_last(inc);
   return g;
 }
 
@@ -2924,7 +2882,7 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_sel_collect(Pair<T> Xp, const dou
     __syncthreads();
     unsigned long long base = 0;
     if (lane == 0 && cnt) base = atomicAdd(&st->sel_count, (unsigned long long)cnt);
-    base = __shfl(base, 0, SPAI_WAVE);
+    base = (unsigned long long)wave_read64((int64_t)base, 0);
     for (int i = lane; i < cnt; i += SPAI_WAVE) selbuf[base + i] = stage[i];
     __syncthreads();
     cnt = 0;
@@ -3371,7 +3329,7 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_compact(Pair<T> Xp, int kind, int
           X.idx[pos] = idx[u];
           X.val[pos] = val[u];
         }
-        const int cn = __shfl_down(c, 1, SPAI_WAVE);
+        const int cn = __builtin_amdgcn_update_dpp(c, c, 0x130, 0xf, 0xf, false);   // lane + 1's
         const bool last = ok && (lane == SPAI_WAVE - 1 || x + 1 >= g.T || cn != c);
         __syncthreads();
         if (last) s_run[c] = base + before + (keep ? 1 : 0);

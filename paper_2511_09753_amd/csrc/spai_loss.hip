@@ -3,10 +3,11 @@
 // With R = I - A M:  df = -2 (R, dA M + A dM)_F, so
 //   d f / d A = -2 R M^T   restricted to supp(A),
 //   d f / d M = -2 A^T R   restricted to supp(M)   (= -2 A R of Section 2 for symmetric A).
-// Neither A M nor R is stored: the row kernel rebuilds row i of R from the rows of M
-// selected by A's row i (giving f and d f / d A), the column kernel rebuilds column j
-// of R from column j of M (giving d f / d M).  Both keep one row/column per 64-lane
-// wavefront in LDS and sum in fixed orders, so the results are deterministic.
+// Neither A M nor R is stored.  Row i of R is rebuilt from the rows of M selected by A's
+// row i, which gives f and d f / d A; column j of R is row j of R^T = I - M^T A^T, so the
+// same kernel on M^T and A^T (symmetric patterns, values gathered through the transpose
+// map) gives d f / d M.  One row per 64-lane wavefront, every sum in a fixed order, so the
+// results are deterministic.
 #include <hip/hip_runtime.h>
 
 #include <map>
@@ -16,6 +17,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "spai.h"
@@ -45,31 +47,32 @@ struct Pat {                    // CSR pattern
   const int32_t* col;
 };
 
-// position of (col[q], row(q)) for every stored entry q of a symmetric pattern; an
-// entry without its mirror maps to itself and raises err bit 2
-__global__ void k_transpose_map(Pat P, int64_t* tmap, int* err) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// position of (col[q], row(q)) for every stored entry q of a symmetric pattern, in tmap
+// and / or the value there, in tval; an entry without its mirror maps to itself and raises
+// err bit 2.  Sixteen lanes share a row, so that the binary searches of a row (four or five
+// dependent loads) run side by side: 2.4M + 6.6M entries took 158 us a thread per row.
+constexpr int kMapLanes = 16;
+template <typename T>
+__global__ __launch_bounds__(256) void k_transpose(Pat P, int64_t* tmap, const T* val, T* tval,
+                                                   int* err) {
+  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kMapLanes;
   if (i >= P.n) return;
-  for (int64_t q = P.rowptr[i]; q < P.rowptr[i + 1]; ++q) {
+  const int64_t e = P.rowptr[i + 1];
+  for (int64_t q = P.rowptr[i] + threadIdx.x % kMapLanes; q < e; q += kMapLanes) {
     const int32_t k = P.col[q];
-    int64_t lo = P.rowptr[k], hi = P.rowptr[k + 1];
+    int64_t lo = P.rowptr[k];
+    const int64_t end = P.rowptr[k + 1];
+    int64_t hi = end;
     while (lo < hi) {
       const int64_t mid = (lo + hi) >> 1;
       if (P.col[mid] < (int32_t)i) lo = mid + 1; else hi = mid;
     }
-    if (lo < P.rowptr[k + 1] && P.col[lo] == (int32_t)i) {
-      tmap[q] = lo;
-    } else {
-      tmap[q] = q;
-      atomicOr(err, 2);
-    }
+    int64_t at = q;
+    if (lo < end && P.col[lo] == (int32_t)i) at = lo;
+    else atomicOr(err, 2);
+    if (tmap) tmap[q] = at;
+    if (tval) tval[q] = val[at];
   }
-}
-
-template <typename T>
-__global__ void k_gather(const T* src, const int64_t* map, T* dst, int64_t nnz) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < nnz) dst[q] = src[map[q]];
 }
 
 __global__ void k_to_f32(const double* a, float* b, int64_t nnz) {
@@ -77,11 +80,231 @@ __global__ void k_to_f32(const double* a, float* b, int64_t nnz) {
   if (q < nnz) b[q] = (float)a[q];
 }
 
-// row kernel: rowpart[i] = ||R(i,:)||^2 and, if gA, gA[q] = -2 dL (R M^T)(i, col q)
-template <typename T>
-__global__ __launch_bounds__(SPAI_WAVE) void k_loss_rows(Pat A, const T* Av, Pat M, const T* Mv,
-                                                         double* rowpart, double* gA, double dL,
-                                                         int* err, int L, int H, int DG) {
+// Row i of I - X Y, with X and Y in CSR: rowpart[i] = ||row||^2 and, with gX set,
+// gX[q] = -2 dL (row) . (row col(q) of Y) for the entries q of X's row i.  (A, M) gives f and
+// d f / d A; (M^T, A^T) gives d f / d M, X's values read and gX written through xmap (MAP).
+//
+// One wave per row.  The rows of Y that X's row selects are taken G lanes each (G = 16, 32
+// or 64, the first that holds the longest), 64 / G rows a round, at most kLossRounds rounds
+// held in registers: every load of a row is in flight together.  Their columns are mapped to
+// cells without clashes (no probing); the first entry of each cell, in the order of rounds and
+// lanes, takes the next rank, so the ranks do not depend on the order of the writes.  The
+// products are added into per-rank sums in LDS, one row of Y per lane group a round (distinct
+// columns, so distinct ranks), each group with sums of its own that are added last.  The row
+// of R then stays in LDS for the gradients, one group sum per entry of X.  Descriptors are
+// loaded one and two rows ahead.
+// Bound by instruction issue and LDS latency at 17 waves per compute unit (9 KB of LDS).
+// 512 x 512 nine-point graph, M on pattern(A^2) (9 rows of 25 entries, and 25 of 9): 290 us
+// for the value and with d f / d A, 469 us for d f / d M.  One instance per number of rounds
+// (297 and 486, at four waves per SIMD), against 405 and 622 with every round tested for and
+// 455 and 668 with sums over the wave through the LDS pipe as well; with the columns in an
+// ordered hash set 463 and 678; with binary searches in a 19 KB tile (8 waves per compute
+// unit) and an LDS sort 2600 and 2800.
+// A row outside this (more than 64 entries in X's row or a row of Y, more rounds or more
+// distinct columns than there is room for, a clash under every multiplier) is marked
+// rowpart[i] = -1 and left to k_loss_rows.
+constexpr int kLossRounds = 8;
+constexpr int kLossSums = 512;      // per-rank sums of all groups
+constexpr int kLossEntries = 509;   // entries of the selected rows together (k_loss_rows' limit)
+constexpr double kLossLeft = -1.0;  // rowpart of a row left to k_loss_rows
+
+template <typename T, bool MAP>
+__global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5))) void k_loss_lean(Pat X, const T* Xv, const int64_t* xmap,
+                                                         Pat Y, const T* Yv, double* rowpart,
+                                                         double* gX, double dL) {
+  // a lane without an entry in a round works on a place of its own behind the tables, so the
+  // rounds need no branches
+  __shared__ int cell[kBtCells + SPAI_WAVE];      // column, then first entry, then rank
+  __shared__ double sums[kLossSums + SPAI_WAVE];
+  const int lane = lane_id();
+  ColumnWalk w(X.n, blockIdx.x, gridDim.x);
+  struct Row {
+    int64_t qa = 0, yb = 0;
+    int deg = 0, l = -1, len = 0;
+    T a = (T)0;
+  };
+  auto ends = [&](int64_t i, Row& r) {            // the row's range in X
+    r = Row{};
+    if (i < w.end) {
+      r.qa = X.rowptr[i];
+      r.deg = (int)min<int64_t>(X.rowptr[i + 1] - r.qa, INT_MAX);
+    }
+  };
+  auto entries = [&](Row& r) {                    // its entries, one per lane
+    if (lane < r.deg) {
+      r.l = X.col[r.qa + lane];
+      r.a = MAP ? Xv[xmap[r.qa + lane]] : Xv[r.qa + lane];
+    }
+  };
+  auto spans = [&](Row& r) {                      // where their rows of Y sit
+    if (r.l >= 0) {
+      r.yb = Y.rowptr[r.l];
+      r.len = (int)min<int64_t>(Y.rowptr[r.l + 1] - r.yb, INT_MAX / SPAI_WAVE);
+    }
+  };
+  Row cur, nxt;
+  ends(w.begin, cur);
+  entries(cur);
+  spans(cur);
+  ends(w.begin + w.step, nxt);
+  for (int64_t i = w.begin; i < w.end; i += w.step) {
+    entries(nxt);
+    Row far;
+    ends(i + 2 * w.step, far);
+    // the rows of Y, G = 2^lg lanes each
+    const int lg = __ballot(cur.len > 32) ? 6 : __ballot(cur.len > 16) ? 5 : 4;
+    const int groups = SPAI_WAVE >> lg;
+    int rounds = (cur.deg + groups - 1) >> (6 - lg);
+    const int cap = kLossSums >> (6 - lg);                       // ranks a group has room for
+    const int g = lane >> lg, e = lane & ((1 << lg) - 1);
+    const double av = (double)cur.a;
+    bool left = cur.deg > SPAI_WAVE || rounds > kLossRounds || __ballot(cur.len > SPAI_WAVE);
+    if (!left && (cur.deg << lg) > kLossEntries) left = wave_sum_int(cur.len) > kLossEntries;
+    if (left) rounds = 0;                         // marked below
+    // one instance per number of rounds: no round is tested for
+    auto work = [&](auto rc) {
+      constexpr int RR = decltype(rc)::value;
+      int c[RR];
+      T v[RR];
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        const int t = (r << (6 - lg)) + g;                       // at most 63
+        const int64_t yb = __shfl(cur.yb, t, SPAI_WAVE);
+        const int len = __shfl(cur.len, t, SPAI_WAVE);           // 0 past the row's entries
+        c[r] = -1;
+        v[r] = (T)0;
+        if (e < len) {
+          c[r] = Y.col[yb + e];
+          v[r] = Yv[yb + e];
+        }
+      }
+      spans(nxt);
+      // an entry's cell, then the place of its sum
+      int at[RR];
+      int a = 0;
+      for (; a < kBtMuls; ++a) {
+        const unsigned m = bt_mul(a);
+        const int own = (int)bt_cell((int)i, m);
+#pragma unroll
+        for (int r = 0; r < RR; ++r) {
+          at[r] = c[r] >= 0 ? (int)bt_cell(c[r], m) : kBtCells + lane;
+          cell[at[r]] = c[r];
+        }
+        cell[own] = (int)i;                       // the same word from every lane
+        __syncthreads();
+        bool clash = cell[own] != (int)i;
+#pragma unroll
+        for (int r = 0; r < RR; ++r) clash |= cell[at[r]] != c[r];
+        __syncthreads();
+        if (__ballot(clash) == 0ull) {
+#pragma unroll
+          for (int r = 0; r < RR; ++r) cell[at[r]] = INT_MAX;
+          __syncthreads();
+          cell[own] = 0;                          // rank 0: the row's own column i
+          break;
+        }
+      }
+      if (a == kBtMuls) return false;
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < RR; ++r) atomicMin(&cell[at[r]], 1 + r * SPAI_WAVE + lane);
+      __syncthreads();
+      int mine[RR], nk = 1;
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        const bool first = c[r] >= 0 && cell[at[r]] == 1 + r * SPAI_WAVE + lane;
+        const unsigned long long bal = __ballot(first);
+        mine[r] = first ? nk + __popcll(bal & lanemask_lt()) : -1;
+        nk += __popcll(bal);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < RR; ++r) cell[mine[r] >= 0 ? at[r] : kBtCells + lane] = mine[r];
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        const int rk = cell[at[r]];
+        at[r] = c[r] >= 0 ? g * cap + rk : kLossSums + lane;
+      }
+      if (nk > cap) return false;
+      for (int q = 0; q < groups; ++q)
+        for (int k = lane; k < nk; k += SPAI_WAVE) sums[q * cap + k] = 0.0;
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < RR; ++r)
+        sums[at[r]] += __shfl(av, (r << (6 - lg)) + g, SPAI_WAVE) * (double)v[r];
+      __syncthreads();
+      double acc = 0.0;
+      for (int k = lane; k < nk; k += SPAI_WAVE) {
+        double s = sums[k];
+        if (groups >= 2) s += sums[cap + k];
+        if (groups == 4) s += sums[2 * cap + k] + sums[3 * cap + k];
+        const double rho = (k == 0 ? 1.0 : 0.0) - s;
+        sums[k] = rho;
+        acc += rho * rho;
+      }
+      acc = wave_sum(acc);
+      if (lane == 0) rowpart[i] = acc;
+      __syncthreads();
+      if (gX) {
+        double p[RR];
+#pragma unroll
+        for (int r = 0; r < RR; ++r) {
+          const double rho = sums[c[r] >= 0 ? at[r] - g * cap : 0];
+          p[r] = c[r] >= 0 ? rho * (double)v[r] : 0.0;
+        }
+        if (lg == 6)
+#pragma unroll
+          for (int r = 0; r < RR; ++r) p[r] = lane_xor_add<32>(p[r]);
+        if (lg >= 5)
+#pragma unroll
+          for (int r = 0; r < RR; ++r) p[r] = lane_xor_add<16>(p[r]);
+#pragma unroll
+        for (int r = 0; r < RR; ++r) p[r] = lane_xor_add<8>(p[r]);
+#pragma unroll
+        for (int r = 0; r < RR; ++r) p[r] = lane_xor_add<4>(p[r]);
+#pragma unroll
+        for (int r = 0; r < RR; ++r) p[r] = lane_xor_add<2>(p[r]);
+#pragma unroll
+        for (int r = 0; r < RR; ++r) p[r] = lane_xor_add<1>(p[r]);
+#pragma unroll
+        for (int r = 0; r < RR; ++r) {
+          const int t = (r << (6 - lg)) + g;
+          if (e == 0 && t < cur.deg) {
+            const int64_t q = cur.qa + t;
+            gX[MAP ? xmap[q] : q] = -2.0 * dL * p[r];
+          }
+        }
+        __syncthreads();
+      }
+      return true;
+    };
+    bool done = false;
+    switch (rounds) {
+      case 1: done = work(std::integral_constant<int, 1>{}); break;
+      case 2: done = work(std::integral_constant<int, 2>{}); break;
+      case 3: done = work(std::integral_constant<int, 3>{}); break;
+      case 4: done = work(std::integral_constant<int, 4>{}); break;
+      case 5: done = work(std::integral_constant<int, 5>{}); break;
+      case 6: done = work(std::integral_constant<int, 6>{}); break;
+      case 7: done = work(std::integral_constant<int, 7>{}); break;
+      case 8: done = work(std::integral_constant<int, 8>{}); break;
+      default: spans(nxt);                        // no entries, or more than this kernel takes
+    }
+    if (!done && lane == 0) rowpart[i] = kLossLeft;
+    cur = nxt;
+    nxt = far;
+  }
+}
+
+// The rows that k_loss_lean left (rowpart[i] = kLossLeft), in a larger LDS tile: sorted
+// keys, and the sums pulled with binary searches.  Up to DG entries in X's row and
+// L, H / 2 - 2 entries of Y; a row beyond that raises err bit 1.
+template <typename T, bool MAP>
+__global__ __launch_bounds__(SPAI_WAVE) void k_loss_rows(Pat X, const T* Xv, const int64_t* xmap,
+                                                         Pat Y, const T* Yv, double* rowpart,
+                                                         double* gX, double dL, int* err, int L,
+                                                         int H, int DG) {
   extern __shared__ char smem[];
   Carve2 cv(smem);
   int* s_li = cv.take<int>(L);
@@ -92,42 +315,41 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_loss_rows(Pat A, const T* Av, Pat
   double* s_a = cv.take<double>(DG);
   double* s_rho = cv.take<double>(H / 2);
   const int lane = lane_id();
-  ColumnWalk w(A.n, blockIdx.x, gridDim.x);
-  for (int64_t i = w.begin; i < w.end; i += w.step) {
-    const int64_t qa = A.rowptr[i];
-    const int deg = (int)(A.rowptr[i + 1] - qa);
+  auto body = [&](int64_t i) {
+    const int64_t qa = X.rowptr[i];
+    const int deg = (int)(X.rowptr[i + 1] - qa);
     int ltot = 0;
     for (int t = lane; t < deg; t += SPAI_WAVE) {
-      const int l = A.col[qa + t];
-      ltot += (int)(M.rowptr[l + 1] - M.rowptr[l]);
+      const int l = X.col[qa + t];
+      ltot += (int)(Y.rowptr[l + 1] - Y.rowptr[l]);
     }
     ltot = wave_sum_int(ltot);
     if (deg > DG || ltot > L || ltot + 2 >= H / 2) {
       if (lane == 0) atomicOr(err, 1);
-      continue;
+      return;
     }
     int run = 0;
     for (int base = 0; base < deg; base += SPAI_WAVE) {
       const int t = base + lane;
       int len = 0;
       if (t < deg) {
-        const int l = A.col[qa + t];
-        len = (int)(M.rowptr[l + 1] - M.rowptr[l]);
-        s_a[t] = (double)Av[qa + t];
+        const int l = X.col[qa + t];
+        len = (int)(Y.rowptr[l + 1] - Y.rowptr[l]);
+        s_a[t] = (double)(MAP ? Xv[xmap[qa + t]] : Xv[qa + t]);
       }
       const int inc = wave_incl_scan(len);
       if (t < deg) s_off[t] = run + inc - len;
-      run += __shfl(inc, SPAI_WAVE - 1, SPAI_WAVE);
+      run += wave_last(inc);
     }
     if (lane == 0) s_off[deg] = run;
     __syncthreads();
     for (int t = 0; t < deg; ++t) {
-      const int l = A.col[qa + t];
-      const int64_t b = M.rowptr[l];
+      const int l = X.col[qa + t];
+      const int64_t b = Y.rowptr[l];
       const int len = s_off[t + 1] - s_off[t];
       for (int e = lane; e < len; e += SPAI_WAVE) {
-        s_li[s_off[t] + e] = M.col[b + e];
-        s_lv[s_off[t] + e] = (double)Mv[b + e];
+        s_li[s_off[t] + e] = Y.col[b + e];
+        s_lv[s_off[t] + e] = (double)Yv[b + e];
       }
     }
     ks_clear(s_keys, H);
@@ -153,7 +375,7 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_loss_rows(Pat A, const T* Av, Pat
     acc = wave_sum(acc);
     if (lane == 0) rowpart[i] = acc;
     __syncthreads();
-    if (gA) {
+    if (gX) {
       for (int t = 0; t < deg; ++t) {
         const int o = s_off[t];
         const int len = s_off[t + 1] - o;
@@ -163,90 +385,17 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_loss_rows(Pat A, const T* Av, Pat
           g += s_rho[pos] * s_lv[o + e];
         }
         g = wave_sum(g);
-        if (lane == 0) gA[qa + t] = -2.0 * dL * g;
+        if (lane == 0) gX[MAP ? xmap[qa + t] : qa + t] = -2.0 * dL * g;
       }
     }
     __syncthreads();
-  }
-}
-
-// column kernel: gM at (k, j) for k in supp(M(:, j)) = -2 dL sum_u A(u,k) R(u,j)
-template <typename T>
-__global__ __launch_bounds__(SPAI_WAVE) void k_loss_cols(Pat A, const T* Av, const T* Atv, Pat M,
-                                                         const T* Mv, const int64_t* tmapM,
-                                                         double* gM, double dL, int* err, int L,
-                                                         int H) {
-  extern __shared__ char smem[];
-  Carve2 cv(smem);
-  int* s_mi = cv.take<int>(L);
-  int* s_pre = cv.take<int>(L);
-  int* s_keys = cv.take<int>(H);
-  int* s_sorted = cv.take<int>(H);
-  double* s_mv = cv.take<double>(L);
-  double* s_r = cv.take<double>(H / 2);
-  const int lane = lane_id();
-  ColumnWalk w(M.n, blockIdx.x, gridDim.x);
-  for (int64_t j = w.begin; j < w.end; j += w.step) {
-    const int64_t mb = M.rowptr[j];
-    const int lm = (int)(M.rowptr[j + 1] - mb);     // column j of M = row j pattern (symmetric)
-    if (lm > L) {
-      if (lane == 0) atomicOr(err, 1);
-      continue;
-    }
-    for (int e = lane; e < lm; e += SPAI_WAVE) {
-      s_mi[e] = M.col[mb + e];
-      s_mv[e] = (double)Mv[tmapM[mb + e]];          // M(l, j)
-    }
-    __syncthreads();
-    // products: neighbours of every l in supp(m_j)
-    int run = 0;
-    for (int base = 0; base < lm; base += SPAI_WAVE) {
-      const int e = base + lane;
-      int d = 0;
-      if (e < lm) {
-        const int l = s_mi[e];
-        d = (int)(A.rowptr[l + 1] - A.rowptr[l]);
-      }
-      const int inc = wave_incl_scan(d);
-      if (e < lm) s_pre[e] = run + inc;
-      run += __shfl(inc, SPAI_WAVE - 1, SPAI_WAVE);
-    }
-    if (run + 2 >= H / 2) {
-      if (lane == 0) atomicOr(err, 1);
-      __syncthreads();
-      continue;
-    }
-    ks_clear(s_keys, H);
-    __syncthreads();
-    if (lane == 0) ks_insert(s_keys, H, (int)j);
-    for (int p = lane; p < run; p += SPAI_WAVE) {
-      const int e = upper_bound_int(s_pre, lm, p);
-      const int before = e ? s_pre[e - 1] : 0;
-      ks_insert(s_keys, H, A.col[A.rowptr[s_mi[e]] + (p - before)]);
-    }
-    __syncthreads();
-    const int nu = ks_sorted(s_keys, H, s_sorted);
-    __syncthreads();
-    for (int t = lane; t < nu; t += SPAI_WAVE) {
-      const int u = s_sorted[t];
-      double s = 0.0;
-      for (int64_t q = A.rowptr[u]; q < A.rowptr[u + 1]; ++q) {
-        const int e = bsearch_idx(s_mi, lm, A.col[q]);
-        if (e >= 0) s += (double)Av[q] * s_mv[e];
-      }
-      s_r[t] = ((u == (int)j) ? 1.0 : 0.0) - s;
-    }
-    __syncthreads();
-    for (int e = lane; e < lm; e += SPAI_WAVE) {
-      const int k = s_mi[e];
-      double g = 0.0;
-      for (int64_t q = A.rowptr[k]; q < A.rowptr[k + 1]; ++q) {
-        const int pos = bsearch_idx(s_sorted, nu, A.col[q]);
-        if (pos >= 0) g += (double)Atv[q] * s_r[pos];   // A(u, k) R(u, j), u = col q
-      }
-      gM[tmapM[mb + e]] = -2.0 * dL * g;
-    }
-    __syncthreads();
+  };
+  // workgroup b owns rows b, b + gridDim.x, ...: neighbouring left rows go to different ones
+  for (int64_t i0 = blockIdx.x; i0 < X.n; i0 += (int64_t)SPAI_WAVE * gridDim.x) {
+    const int64_t i = i0 + (int64_t)lane * gridDim.x;
+    const bool mine = i < X.n && rowpart[i] == kLossLeft;
+    for (unsigned long long m = __ballot(mine); m; m &= m - 1)
+      body(i0 + (int64_t)(__ffsll((long long)m) - 1) * gridDim.x);
   }
 }
 
@@ -278,13 +427,25 @@ __global__ void k_sum_chunks(const double* part, int64_t n, int64_t chunk, doubl
   if (threadIdx.x == 0) out[blockIdx.x] = sh[0];
 }
 
-constexpr int kGridRows = 2048;
+constexpr int kGridRows = 256 * 17;       // k_loss_lean: the one-wave workgroups that fit (LDS)
+constexpr int kGridLeft = 2048;
+constexpr int kLeftL = 512, kLeftH = 1024;
 
-size_t rows_lds(int L, int H, int DG) {
-  return (size_t)L * 4 + (size_t)H * 8 + (size_t)(DG + 1) * 4 + (size_t)L * 8 + (size_t)DG * 8 +
-         (size_t)(H / 2) * 8 + 64;
+size_t left_lds(int DG) {
+  return (size_t)kLeftL * 4 + (size_t)kLeftH * 8 + (size_t)(DG + 1) * 4 + (size_t)kLeftL * 8 +
+         (size_t)DG * 8 + (size_t)(kLeftH / 2) * 8 + 64;
 }
-size_t cols_lds(int L, int H) { return (size_t)L * 8 + (size_t)H * 8 + (size_t)L * 8 + (size_t)(H / 2) * 8 + 64; }
+
+// both tiers of I - X Y; DG: the most entries a row of X may have
+template <typename T, bool MAP>
+void launch_rows(const Pat& X, const T* Xv, const int64_t* xmap, const Pat& Y, const T* Yv,
+                 double* rowpart, double* gX, double dL, int* err, int DG, hipStream_t s) {
+  hipLaunchKernelGGL((k_loss_lean<T, MAP>), dim3(kGridRows), dim3(SPAI_WAVE), 0, s, X, Xv, xmap, Y,
+                     Yv, rowpart, gX, dL);
+  hipLaunchKernelGGL((k_loss_rows<T, MAP>), dim3(kGridLeft), dim3(SPAI_WAVE), left_lds(DG), s, X, Xv,
+                     xmap, Y, Yv, rowpart, gX, dL, err, kLeftL, kLeftH, DG);
+}
+constexpr int kDegRows = 64, kDegCols = 256;   // entries in a row of A; in a column of M
 
 struct LossCall {
   DevPool pool;
@@ -311,12 +472,21 @@ struct LossCall {
         return rc;
       if (!A->on_device) return upload(hA, hM);
     }
-    if ((rc = pool.alloc(&err, 1))) return rc;
-    HIPCHK(hipMemsetAsync(err, 0, sizeof(int), s));
     pA = Pat{A->n, A->rowptr, A->colind};
     pM = Pat{M->n, M->rowptr, M->colind};
     Av64 = A->val;
     Mv64 = M->val;
+    return SPAI_OK;
+  }
+
+  // the call's scratch, one block with the error flag in front (an allocation and its release
+  // cost 30 to 400 us): `bytes` behind 256
+  int scratch(char** p, size_t bytes) {
+    int rc = pool.alloc(p, (int64_t)(256 + bytes));
+    if (rc) return rc;
+    err = (int*)*p;
+    *p += 256;
+    HIPCHK(hipMemsetAsync(err, 0, sizeof(int), s));
     return SPAI_OK;
   }
 
@@ -326,8 +496,7 @@ struct LossCall {
     int32_t *ca, *cm;
     double *va, *vm;
     if ((rc = pool.alloc(&ra, hA.n + 1)) || (rc = pool.alloc(&ca, hA.nnz)) || (rc = pool.alloc(&va, hA.nnz)) ||
-        (rc = pool.alloc(&rm, hM.n + 1)) || (rc = pool.alloc(&cm, hM.nnz)) || (rc = pool.alloc(&vm, hM.nnz)) ||
-        (rc = pool.alloc(&err, 1)))
+        (rc = pool.alloc(&rm, hM.n + 1)) || (rc = pool.alloc(&cm, hM.nnz)) || (rc = pool.alloc(&vm, hM.nnz)))
       return rc;
     HIPCHK(hipMemcpyAsync(ra, hA.rowptr.data(), 8 * (hA.n + 1), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(ca, hA.col.data(), 4 * hA.nnz, hipMemcpyHostToDevice, s));
@@ -335,7 +504,6 @@ struct LossCall {
     HIPCHK(hipMemcpyAsync(rm, hM.rowptr.data(), 8 * (hM.n + 1), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(cm, hM.col.data(), 4 * hM.nnz, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(vm, hM.val.data(), 8 * hM.nnz, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemsetAsync(err, 0, sizeof(int), s));
     pA = Pat{hA.n, ra, ca};
     pM = Pat{hM.n, rm, cm};
     Av64 = va;
@@ -343,25 +511,6 @@ struct LossCall {
     return SPAI_OK;
   }
 };
-
-template <typename T>
-int run_rows(LossCall& c, const T* Av, const T* Mv, double* rowpart, double* gA, double dL) {
-  const int L = 512, H = 1024, DG = 64;
-  hipLaunchKernelGGL(k_loss_rows<T>, dim3(kGridRows), dim3(SPAI_WAVE), rows_lds(L, H, DG), c.s, c.pA,
-                     Av, c.pM, Mv, rowpart, gA, dL, c.err, L, H, DG);
-  HIPCHK(hipGetLastError());
-  return SPAI_OK;
-}
-
-template <typename T>
-int run_cols(LossCall& c, const T* Av, const T* Atv, const T* Mv, const int64_t* tmapM, double* gM,
-             double dL) {
-  const int L = 256, H = 1024;
-  hipLaunchKernelGGL(k_loss_cols<T>, dim3(kGridRows), dim3(SPAI_WAVE), cols_lds(L, H), c.s, c.pA, Av,
-                     Atv, c.pM, Mv, tmapM, gM, dL, c.err, L, H);
-  HIPCHK(hipGetLastError());
-  return SPAI_OK;
-}
 
 template <typename T>
 int values(LossCall& c, const T** Av, const T** Mv) {
@@ -385,11 +534,12 @@ int loss_fwd_t(LossCall& c, double* Lout) {
   int rc;
   const T *Av, *Mv;
   if ((rc = values<T>(c, &Av, &Mv))) return rc;
-  double *rowpart, *chunks, *out;
+  char* blk;
   const int nch = 512;
-  if ((rc = c.pool.alloc(&rowpart, c.pA.n)) || (rc = c.pool.alloc(&chunks, nch)) || (rc = c.pool.alloc(&out, 1)))
-    return rc;
-  if ((rc = run_rows<T>(c, Av, Mv, rowpart, nullptr, 1.0))) return rc;
+  if ((rc = c.scratch(&blk, sizeof(double) * (size_t)(c.pA.n + nch + 1)))) return rc;
+  double *rowpart = (double*)blk, *chunks = rowpart + c.pA.n, *out = chunks + nch;
+  launch_rows<T, false>(c.pA, Av, nullptr, c.pM, Mv, rowpart, nullptr, 1.0, c.err, kDegRows, c.s);
+  HIPCHK(hipGetLastError());
   const int64_t chunk = (c.pA.n + nch - 1) / nch;
   const int nb = (int)((c.pA.n + chunk - 1) / chunk);
   hipLaunchKernelGGL(k_sum_chunks, dim3(nb), dim3(256), 0, c.s, rowpart, c.pA.n, chunk, chunks);
@@ -407,23 +557,30 @@ int loss_bwd_t(LossCall& c, double dL, double* gA, double* gM, bool host_out) {
   int rc;
   const T *Av, *Mv;
   if ((rc = values<T>(c, &Av, &Mv))) return rc;
-  double *rowpart, *dgA = gA, *dgM = gM;
-  if ((rc = c.pool.alloc(&rowpart, c.pA.n))) return rc;
+  double *dgA = gA, *dgM = gM;
+  char* blk;                            // row sums, and for gM the transpose map of M and A^T's values
+  const size_t n8 = sizeof(double) * (size_t)c.pA.n;
+  const size_t m8 = gM ? sizeof(int64_t) * (size_t)c.nnzM : 0, a8 = gM ? sizeof(T) * (size_t)c.nnzA : 0;
+  if ((rc = c.scratch(&blk, n8 + m8 + a8))) return rc;
+  double* rowpart = (double*)blk;
+  int64_t* tM = (int64_t*)(blk + n8);
+  T* Atv = (T*)(blk + n8 + m8);
   if (host_out) {
     if (gA && (rc = c.pool.alloc(&dgA, c.nnzA))) return rc;
     if (gM && (rc = c.pool.alloc(&dgM, c.nnzM))) return rc;
   }
-  if (gA && (rc = run_rows<T>(c, Av, Mv, rowpart, dgA, dL))) return rc;
+  if (gA)
+    launch_rows<T, false>(c.pA, Av, nullptr, c.pM, Mv, rowpart, dgA, dL, c.err, kDegRows, c.s);
   if (gM) {
-    int64_t *tA, *tM;
-    T* Atv;
-    if ((rc = c.pool.alloc(&tA, c.nnzA)) || (rc = c.pool.alloc(&tM, c.nnzM)) || (rc = c.pool.alloc(&Atv, c.nnzA)))
-      return rc;
-    hipLaunchKernelGGL(k_transpose_map, dim3((unsigned)((c.pA.n + 255) / 256)), dim3(256), 0, c.s, c.pA, tA, c.err);
-    hipLaunchKernelGGL(k_transpose_map, dim3((unsigned)((c.pM.n + 255) / 256)), dim3(256), 0, c.s, c.pM, tM, c.err);
-    hipLaunchKernelGGL(k_gather<T>, dim3((unsigned)((c.nnzA + 255) / 256)), dim3(256), 0, c.s, Av, tA, Atv, c.nnzA);
-    if ((rc = run_cols<T>(c, Av, Atv, Mv, tM, dgM, dL))) return rc;
+    const int64_t lanes = c.pA.n * kMapLanes;
+    const dim3 grid((unsigned)((lanes + 255) / 256)), bs(256);
+    hipLaunchKernelGGL(k_transpose<T>, grid, bs, 0, c.s, c.pA, (int64_t*)nullptr, Av, Atv, c.err);
+    hipLaunchKernelGGL(k_transpose<T>, grid, bs, 0, c.s, c.pM, tM, (const T*)nullptr, (T*)nullptr,
+                       c.err);
+    // rows of R^T = I - M^T A^T
+    launch_rows<T, true>(c.pM, Mv, tM, c.pA, Atv, rowpart, dgM, dL, c.err, kDegCols, c.s);
   }
+  HIPCHK(hipGetLastError());
   int herr = 0;
   HIPCHK(hipMemcpyAsync(&herr, c.err, sizeof(int), hipMemcpyDeviceToHost, c.s));
   if (host_out) {
@@ -519,10 +676,8 @@ extern "C" int spai_loss_fwd_noalloc(const spai_csr_t* A, const spai_csr_t* M, d
     const Pat pA{A->n, A->rowptr, A->colind}, pM{M->n, M->rowptr, M->colind};
     // the flag is cleared by a kernel (no memset node), so the call can be captured
     hipLaunchKernelGGL(k_zero_flag, dim3(1), dim3(1), 0, s, err);
-    const int Lt = 512, Ht = 1024, DG = 64;
-    hipLaunchKernelGGL(k_loss_rows<double>, dim3(kGridRows), dim3(SPAI_WAVE),
-                       rows_lds(Lt, Ht, DG), s, pA, A->val, pM, M->val, rowpart,
-                       (double*)nullptr, 1.0, err, Lt, Ht, DG);
+    launch_rows<double, false>(pA, A->val, nullptr, pM, M->val, rowpart, nullptr, 1.0, err,
+                               kDegRows, s);
     const int64_t chunk = (A->n + kNoAllocChunks - 1) / kNoAllocChunks;
     const int nb = (int)((A->n + chunk - 1) / chunk);
     hipLaunchKernelGGL(k_sum_chunks, dim3(nb), dim3(256), 0, s, rowpart, A->n, chunk, chunks);

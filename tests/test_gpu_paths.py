@@ -53,3 +53,66 @@ def test_lanczos_stops_in_an_invariant_subspace():
     lo, hi, _, _, k = S.spectrum(A, np.random.default_rng(0).standard_normal(600), steps=200)
     assert k == 3
     assert lo == pytest.approx(1.0, rel=1e-12) and hi == pytest.approx(5.0, rel=1e-12)
+
+
+def _pattern_with(n, long_row, per_row, seed):
+    """Symmetric pattern with about per_row entries a row and one row (and column) of
+    long_row entries, diagonal included."""
+    rng = np.random.default_rng(seed)
+    m = max(n * (per_row - 1) // 2, 1)
+    r, c = rng.integers(0, n, m), np.empty(m, dtype=np.int64)
+    c = (r + rng.integers(1, min(40, max(n - 1, 2)), m)) % n
+    k = rng.choice(n - 1, long_row - 1, replace=False) + 1 if long_row > 1 else np.empty(0, int)
+    U = sp.coo_matrix((np.ones(m + len(k)), (np.r_[r, np.zeros(len(k), int)], np.r_[c, k])),
+                      shape=(n, n)).tocsr()
+    P = (U + U.T + sp.identity(n)).tocsr()
+    P.sort_indices()
+    return P
+
+
+@pytest.mark.parametrize("n,rows_a,long_a,rows_m,long_m", [
+    (1, 1, 1, 1, 1),
+    (70, 3, 1, 5, 16),        # 16 lanes a row of M
+    (70, 3, 1, 5, 17),        # 32
+    (90, 3, 1, 5, 33),        # 64: eight rows of A's row at most
+    (90, 3, 30, 2, 1),        # a long row of A: many rounds
+    (200, 3, 1, 3, 64),       # the longest row that the lean kernel takes
+    (200, 3, 1, 3, 65),       # and the first that it leaves
+    (300, 5, 1, 12, 1),
+    (400, 2, 60, 2, 1),       # more than eight rounds: left
+    (600, 2, 1, 2, 240),      # a column of M near the tile's 256
+])
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_loss_rows_at_the_edges_of_their_tiles(n, rows_a, long_a, rows_m, long_m, precision):
+    """Value and both gradients (unsymmetric values) on patterns around the lane-group
+    widths, rounds and row lengths of the lean kernel and the rows that it leaves to the
+    larger tile.  float64: sums of at most a few hundred products in another order, 1e-12
+    of the largest entry; float32 values: 1e-5."""
+    S = _spai()
+    rng = np.random.default_rng(n + long_m)
+    A = _pattern_with(n, long_a, rows_a, 1)
+    M = _pattern_with(n, long_m, rows_m, 2)
+    A.data = rng.standard_normal(A.nnz)
+    M.data = 0.3 * rng.standard_normal(M.nnz)
+    tol = 1e-12 if precision == "f64" else 1e-5
+    o = S.Options(precision=precision)
+    assert S.loss_fwd(A, M, o) == pytest.approx(O.loss(A, M), rel=tol)
+    gA, gM = S.loss_bwd(A, M, dL=0.5, options=o)
+    oA, oM = O.loss_grad(A, M)
+    oA, oM = (0.5 * sp.csr_matrix(x)[tuple(p.nonzero())] for x, p in ((oA, A), (oM, M)))
+    oA, oM = np.asarray(oA).ravel(), np.asarray(oM).ravel()
+    assert np.max(np.abs(gA - oA)) <= tol * np.max(np.abs(oA))
+    assert np.max(np.abs(gM - oM)) <= tol * np.max(np.abs(oM))
+
+
+def test_loss_row_beyond_the_tile_is_refused():
+    """Rows that select 510 entries or more are refused, as before the lean kernel."""
+    S = _spai()
+    n = 600
+    A = _pattern_with(n, 64, 2, 3)
+    M = _pattern_with(n, 1, 12, 4)
+    longest = max(M[A.indices[A.indptr[i]:A.indptr[i + 1]]].nnz for i in range(n))
+    assert longest >= 510
+    with pytest.raises(S.SpaiError) as e:
+        S.loss_fwd(A, M)
+    assert e.value.code == -7

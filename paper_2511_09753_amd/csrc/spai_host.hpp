@@ -97,6 +97,8 @@ struct PcgWork {
   int64_t n = -1;
   int nrhs = 0;
   void* blk[9] = {};
+  DevPool tiny_pool;                   // the results of a solve in one workgroup (any size)
+  void* tiny = nullptr;
 };
 
 int pcg_run(const PcgMat& A, const PcgMat& M, int nrhs, const double* dB, double* dX, double rtol,

@@ -409,31 +409,143 @@ __global__ __launch_bounds__(kThreads) void k_spmm_pair(Mat A, const double* X, 
   }
 }
 
+// The sum of sh[k], k = t, t + R, ... below kThreads, from 0 in that order: 16 loads in
+// flight, the additions one after the other (the order is the result's).
+__device__ __forceinline__ double column_sum(const double* sh, int t, int R) {
+  double s = 0.0;
+  int k = t;
+  for (; k + 15 * R < kThreads; k += 16 * R) {
+    double v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = sh[k + u * R];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += v[u];
+  }
+  for (; k < kThreads; k += R) s += sh[k];
+  return s;
+}
+
+// A partial that another workgroup of the same launch will read goes past the L2 caches (each
+// XCD has its own), one word at a time: a device-scope fence would write back and invalidate
+// a whole L2 for every workgroup (74 us against 13 for a product of 256 workgroups).
+__device__ __forceinline__ void agent_store(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double agent_load(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// sum_b p[b * step], b < nblocks, on every lane of one wave, in the order and tree of
+// rows_sum / parts_sum: thread t of 256 adds b = t, t + 256, ..., then halves of the 256
+// are added; lane l holds threads l, l + 64, l + 128 and l + 192.
+__device__ __forceinline__ double blocks_sum_wave(const double* p, int64_t step, int nblocks) {
+  const int lane = threadIdx.x & 63;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int b0 = 0; b0 < nblocks; b0 += 2 * kThreads) {     // eight loads in flight
+    double v[2][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int b = b0 + h * kThreads + lane + 64 * q;
+        v[h][q] = b < nblocks ? agent_load(p + (int64_t)b * step) : 0.0;
+      }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] += v[h][q];
+  }
+  return wave_sum((s[0] + s[2]) + (s[1] + s[3]));
+}
+
+struct RhsState {
+  double bnorm, rz, pq, rr, alpha, beta;
+  double alpha_prev;                // the previous iteration's alpha (its x term may be pending)
+  int active, iters, status, pad;   // status 0 running, 1 converged, 2 maxiter, 4 indefinite
+};
+__device__ void rhs_alpha(RhsState& g, double pq, int* nactive);
+__device__ void rhs_conv(RhsState& g, double rr, double rtol, int* nactive);
+__device__ void rhs_beta(RhsState& g, double rz_new);
+
+// What the last workgroup of a product or of the r update does with the partials: the
+// right-hand sides' sums (part[r * rstep + b * bstep], nrhs of them, nblocks partials each)
+// and the scalar step that consumes them (0: alpha, 1: beta, 2: convergence).  ticket counts
+// the workgroups that have written theirs (null: a launch of its own sums them); the last
+// one leaves it at 0 for the next launch.  One launch less per reduction: where partials are
+// few (kFusedParts) the sums take less time than a launch, 2 to 4 us each of the three in an
+// iteration; beyond that one workgroup per right-hand side sums them faster.
+struct Finish {
+  int* ticket = nullptr;
+  RhsState* S = nullptr;
+  int* nactive = nullptr;
+  int step = 0, nrhs = 0;
+  int64_t rstep = 0, bstep = 0;
+  double rtol = 0.0;
+};
+constexpr int kFusedParts = 8192;
+constexpr int kFusedGrid = 512;     // and the workgroups that draw a ticket
+
+__device__ __forceinline__ void finish_blocks(const Finish& f, const double* part, int nblocks) {
+  __shared__ int last;
+  // this workgroup's partials (agent_store) have arrived before its ticket is drawn
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0)
+    last = __hip_atomic_fetch_add(f.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           (int)gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  for (int r = threadIdx.x >> 6; r < f.nrhs; r += blockDim.x >> 6) {
+    const double v = blocks_sum_wave(part + r * f.rstep, f.bstep, nblocks);
+    if ((threadIdx.x & 63) == 0) {
+      if (f.step == 0) rhs_alpha(f.S[r], v, f.nactive);
+      else if (f.step == 1) rhs_beta(f.S[r], v);
+      else rhs_conv(f.S[r], v, f.rtol, f.nactive);
+    }
+  }
+  if (threadIdx.x == 0) *f.ticket = 0;
+}
+
+// a launch that returns at once takes its scalar step all the same (every right-hand side has
+// stopped, so no sum is read): the step carries a pending x term on
+__device__ __forceinline__ void finish_stopped(const Finish& f) {
+  if (!f.ticket || blockIdx.x != 0 || (int)threadIdx.x >= f.nrhs) return;
+  if (f.step == 0) rhs_alpha(f.S[threadIdx.x], 0.0, f.nactive);
+  else if (f.step == 1) rhs_beta(f.S[threadIdx.x], 0.0);
+}
+
 // The product for at most 32 right-hand sides.  A wave of k_spmm_wave would leave
 // 64 - nrhs lanes idle; here R = pow2(nrhs) lanes share a row (lane r owns right-hand
-// side r), so a workgroup has kThreads / R rows in flight, and each lane sums its row's
-// entries in stored order, eight entries and their gathers issued together (the order
-// of k_spmm_wave: the rows of Y are the same bit for bit).  Positions are dealt as in
-// k_spmm_wave: eight contiguous XCD ranges, each workgroup a contiguous chunk of
-// narrow_chunk(R) positions, its lanes taking them kThreads / R at a time.  With dot
-// set, per-block partials of sum_i X[i, r] Y[i, r], stored transposed as there.
+// side r), and each lane sums its row's entries in stored order, eight entries and their
+// gathers issued together (the order of k_spmm_wave: the rows of Y are the same bit for
+// bit).  Positions are dealt as in k_spmm_wave: eight contiguous XCD ranges, each workgroup
+// a contiguous chunk of narrow_chunk(R) positions.  With dot set, per-block partials of
+// sum_i X[i, r] Y[i, r], stored transposed as there: thread (g, r) of 256 adds its rows g,
+// g + G, ..., then g runs over the G groups.
+// W = 4: 1024 threads take those rows side by side instead of 256 one after the other and
+// leave the terms in LDS for the same sums.  Where a launch has fewer workgroups than four
+// per compute unit the product is bound by the latency of a thread's rows (descriptor,
+// entries, gathers, one row after the other): 256 x 256 grid, 4 right-hand sides (256
+// workgroups) 12.4 us with its reduction, against 13.3 and a reduction of 4.1; with more
+// workgroups 256 threads keep more waves resident (registers).
 template <int R>
-constexpr int narrow_rpt() { return R / 4 > 4 ? R / 4 : 4; }   // rows per lane
+constexpr int narrow_rpt() { return R / 4 > 4 ? R / 4 : 4; }   // rows per thread of 256
 template <int R>
 constexpr int narrow_chunk() { return (kThreads / R) * narrow_rpt<R>(); }
 
-template <typename VT, int LAY, int R>
-__global__ __launch_bounds__(kThreads) void k_spmm_narrow(Mat A, const double* X, double* Y,
-                                                          int dot, int nrhs, int c0, int ld,
-                                                          const int32_t* order, double* part) {
+template <typename VT, int LAY, int R, int W>
+__global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double* X, double* Y,
+                                                             int dot, int nrhs, int c0, int ld,
+                                                             const int32_t* order, double* part,
+                                                             Finish fin) {
   static_assert(narrow_chunk<R>() >= (kThreads / 64) * kRowsPerWave,
                 "no more workgroups than the partial buffer holds");
-  if (A.gate && *A.gate == 0) return;                     // every right-hand side stopped
+  if (A.gate && *A.gate == 0) return finish_stopped(fin);  // every right-hand side stopped
   if (A.ran && c0 == 0 && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(A.ran, 1);
-  __shared__ double sh[kThreads];
   constexpr int G = kThreads / R;
   constexpr int RPT = narrow_rpt<R>();
-  const int t = threadIdx.x;
+  __shared__ double sh[W == 1 ? kThreads : RPT * kThreads];
+  const int t = threadIdx.x % kThreads;
   const int r = t % R, g = t / R;
   const int64_t xcd = blockIdx.x & 7, kb = blockIdx.x >> 3;
   const int64_t per = (A.n + 7) / 8;
@@ -445,10 +557,10 @@ __global__ __launch_bounds__(kThreads) void k_spmm_narrow(Mat A, const double* X
   // for a whole block; a wide block is taken R columns at a time)
   X += c0;
   Y += c0;
-  if (r < nrhs) {
-    for (int j = 0; j < RPT; ++j) {
-      const int64_t k = base + (int64_t)j * G + g;
-      if (k >= r1) break;
+  for (int j = threadIdx.x / kThreads; j < RPT; j += W) {
+    const int64_t k = base + (int64_t)j * G + g;
+    double term = 0.0;
+    if (r < nrhs && k < r1) {
       const int64_t i = order ? (int64_t)order[k] : k;
       const int64_t a = row_lo<LAY>(A, i), b = row_hi<LAY>(A, i);
       double y = 0.0, xd = 0.0;
@@ -483,18 +595,156 @@ __global__ __launch_bounds__(kThreads) void k_spmm_narrow(Mat A, const double* X
       if (dot) {
         // a row without a diagonal entry loads X[i, r] after all
         const double wx = found ? xd : X[i * ld + r];
-        acc += wx * y;
+        term = wx * y;
       }
+    }
+    if (W == 1) acc += term;              // (0 where there is no row: the sum as it is)
+    else sh[j * kThreads + t] = term;
+  }
+  if (!part) return;
+  if (W > 1) {
+    __syncthreads();
+    if (threadIdx.x < kThreads)
+#pragma unroll
+      for (int j = 0; j < RPT; ++j) acc += sh[j * kThreads + t];
+    __syncthreads();
+  }
+  if (threadIdx.x < kThreads) sh[t] = acc;
+  __syncthreads();
+  if (threadIdx.x < R && t < nrhs)
+    agent_store(&part[(int64_t)(c0 + t) * gridDim.x + blockIdx.x], column_sum(sh, t, R));
+  if (fin.ticket) finish_blocks(fin, part, (int)gridDim.x);
+}
+
+// The product for at most two right-hand sides: four lanes per row and right-hand side, lane
+// l of them holding entries 2 l and 2 l + 1 of each eight, so that a row's entries are read
+// side by side and a wave's load touches 16 rows' pieces instead of 64 (a thread per row reads
+// its entries 8 or more words from its neighbour's: the address unit, at one cache line per
+// lane and load, was what the product waited for).  A row's sum still runs over its entries in
+// stored order, from 0: lane 0 adds its two, hands the sum to lane 1, and so on; lane 3 ends
+// with it.  1024 threads take the G = 256 / R rows of a pass of k_spmm_narrow at a time, four
+// passes with their loads in flight together, and the partials are that kernel's: the same
+// bit for bit.  256 x 256 grid, one right-hand side (64 workgroups): z = M r 19.4 us against
+// 31.7, q = A p 12.9 against 17.1 (each with its reduction).  From three right-hand sides on a
+// thread per value is faster (four of them, 44.3 us an iteration against 47.1): its lanes
+// share their rows' loads already.
+constexpr int kQuadRhs = 2;         // padded right-hand sides
+template <int R>
+__device__ __forceinline__ double quad_shift(double v) {       // lane l's value to lane l + 1
+  const long long b = __double_as_longlong(v);
+  const int lo = lane_dpp<0x110 + R>((int)(b & 0xffffffffll));  // row_shr R
+  const int hi = lane_dpp<0x110 + R>((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+template <int R>
+__device__ __forceinline__ double quad_return(double v) {      // lane 3's value to lane 0
+  const long long b = __double_as_longlong(v);
+  const int lo = lane_dpp<0x100 + 3 * R>((int)(b & 0xffffffffll));  // row_shl 3 R
+  const int hi = lane_dpp<0x100 + 3 * R>((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+// y (in lane 0) plus the eight terms in order; the sum is lane 3's.  Every lane takes part.
+template <int R>
+__device__ __forceinline__ double quad_sum(int l, double y, double p0, double p1) {
+  double s = (y + p0) + p1;
+#pragma unroll
+  for (int k = 1; k < 4; ++k) {
+    const double t = (quad_shift<R>(s) + p0) + p1;
+    s = l == k ? t : s;
+  }
+  return s;
+}
+
+template <typename VT, int LAY, int R>
+__global__ __launch_bounds__(4 * kThreads) void k_spmm_quad(Mat A, const double* X, double* Y,
+                                                            int dot, int nrhs,
+                                                            const int32_t* order, double* part,
+                                                            Finish fin) {
+  if (A.gate && *A.gate == 0) return finish_stopped(fin);  // every right-hand side stopped
+  if (A.ran && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(A.ran, 1);
+  constexpr int G = kThreads / R;
+  constexpr int RPT = narrow_rpt<R>();
+  static_assert(R <= 4 && RPT == 4, "four lanes per value within 16");
+  __shared__ double sh[kThreads];
+  const int r = threadIdx.x % R, l = (threadIdx.x / R) & 3, g = threadIdx.x / (4 * R);
+  const int64_t xcd = blockIdx.x & 7, kb = blockIdx.x >> 3;
+  const int64_t per = (A.n + 7) / 8;
+  const int64_t r0 = xcd * per;
+  const int64_t r1 = r0 + per < A.n ? r0 + per : A.n;
+  const int64_t base = r0 + kb * (int64_t)narrow_chunk<R>();
+  const int rc = r < nrhs ? r : 0;
+  int64_t row[RPT], a[RPT], b[RPT];
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    const int64_t k = base + (int64_t)j * G + g;
+    row[j] = -1;
+    if (k < r1) row[j] = order ? (int64_t)order[k] : k;
+  }
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    a[j] = b[j] = 0;
+    if (row[j] >= 0) {
+      a[j] = row_lo<LAY>(A, row[j]);
+      b[j] = row_hi<LAY>(A, row[j]);
+    }
+  }
+  // entries q, q + 1 of a row that ends at e (column -1: none)
+  auto two = [&](int64_t q, int64_t e, int (&c)[2], VT (&v)[2]) {
+    typedef int i2 __attribute__((ext_vector_type(2), aligned(4)));
+    typedef VT v2 __attribute__((ext_vector_type(2), aligned(sizeof(VT))));
+    c[0] = c[1] = -1;
+    v[0] = v[1] = 0;
+    if (q + 1 < e) {
+      const i2 cc = *(const i2*)(A.col + q);
+      c[0] = cc.x;
+      c[1] = cc.y;
+      v2 vv;
+      if constexpr (sizeof(VT) == 4) vv = *(const v2*)(A.val32 + q);
+      else vv = *(const v2*)(A.val + q);
+      v[0] = vv.x;
+      v[1] = vv.y;
+    } else if (q < e) {
+      c[0] = A.col[q];
+      v[0] = entry_val<VT>(A, q);
+    }
+  };
+  int c[RPT][2];
+  VT v[RPT][2];
+  double xd[RPT], x[RPT][2];
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) two(a[j] + 2 * l, b[j], c[j], v[j]);
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    xd[j] = dot && row[j] >= 0 ? X[row[j] * nrhs + rc] : 0.0;
+    x[j][0] = c[j][0] >= 0 ? X[(int64_t)c[j][0] * nrhs + rc] : 0.0;
+    x[j][1] = c[j][1] >= 0 ? X[(int64_t)c[j][1] * nrhs + rc] : 0.0;
+  }
+  double acc = 0.0;
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    double p0 = c[j][0] >= 0 ? (double)v[j][0] * x[j][0] : 0.0;
+    double p1 = c[j][1] >= 0 ? (double)v[j][1] * x[j][1] : 0.0;
+    double y = quad_sum<R>(l, 0.0, p0, p1);
+    // rows longer than eight entries (the wave goes on together: lanes without one add 0)
+    for (int64_t q = 8; __ballot(a[j] + q < b[j]) != 0ull; q += 8) {
+      int cc[2];
+      VT vv[2];
+      two(a[j] + q + 2 * l, b[j], cc, vv);
+      p0 = cc[0] >= 0 ? (double)vv[0] * X[(int64_t)cc[0] * nrhs + rc] : 0.0;
+      p1 = cc[1] >= 0 ? (double)vv[1] * X[(int64_t)cc[1] * nrhs + rc] : 0.0;
+      y = quad_sum<R>(l, quad_return<R>(y), p0, p1);
+    }
+    if (l == 3 && r < nrhs && row[j] >= 0) {
+      Y[row[j] * nrhs + r] = y;
+      acc += xd[j] * y;
     }
   }
   if (!part) return;
-  sh[t] = acc;
+  if (l == 3) sh[g * R + r] = acc;
   __syncthreads();
-  if (t < R && t < nrhs) {
-    double sum = 0.0;
-    for (int w = 0; w < G; ++w) sum += sh[w * R + t];
-    part[(int64_t)(c0 + t) * gridDim.x + blockIdx.x] = sum;
-  }
+  if ((int)threadIdx.x < nrhs)
+    agent_store(&part[(int64_t)threadIdx.x * gridDim.x + blockIdx.x], column_sum(sh, threadIdx.x, R));
+  if (fin.ticket) finish_blocks(fin, part, (int)gridDim.x);
 }
 
 // per-block partials of sum_i A[i, r] B[i, r] (B may be A), optionally of (B - C)
@@ -522,11 +772,7 @@ __global__ __launch_bounds__(kThreads) void k_dot_rows(const double* Xa, const d
   }
   sh[t] = acc;
   __syncthreads();
-  if (t < cw) {
-    double s = 0.0;
-    for (int k = t; k < kThreads; k += R) s += sh[k];
-    part[(int64_t)blockIdx.x * nrhs + c0 + t] = s;
-  }
+  if (t < cw) part[(int64_t)blockIdx.x * nrhs + c0 + t] = column_sum(sh, t, R);
 }
 
 // one workgroup per right-hand side: fixed strided partial sums, then a fixed tree
@@ -590,12 +836,6 @@ __global__ __launch_bounds__(kThreads) void k_reduce_parts(const double* part, i
   if (threadIdx.x == 0) out[r] = v;
 }
 
-struct RhsState {
-  double bnorm, rz, pq, rr, alpha, beta;
-  double alpha_prev;                // the previous iteration's alpha (its x term may be pending)
-  int active, iters, status, pad;   // status 0 running, 1 converged, 2 maxiter, 4 indefinite
-};
-
 __global__ void k_init_rhs(RhsState* S, const double* bb, int nrhs, int* nactive) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= nrhs) return;
@@ -641,21 +881,26 @@ __device__ void rhs_alpha(RhsState& g, double pq, int* nactive) {
 // are loaded nontemporally, and x and the new p are stored so, as are the products'
 // outputs: they do not push out of the caches what a product gathers (the 64-right-hand-
 // side solve at 96^3 339 -> 330 ms; r, which the next product gathers, gained nothing).
-__global__ __launch_bounds__(kThreads) void k_axpy(double* __restrict__ rv,
-                                                   const double* __restrict__ q,
-                                                   const RhsState* __restrict__ S, int64_t n,
-                                                   int nrhs, int R, double* __restrict__ part,
-                                                   const int* __restrict__ gate) {
+// A block of partials belongs to kThreads threads; W of them share a workgroup (W = 4 where
+// its last workgroup finishes the reduction: one draws a ticket where four did, and tickets
+// of one address come one after the other, about 10 ns each).
+template <int W>
+__global__ __launch_bounds__(kThreads* W) void k_axpy(double* __restrict__ rv,
+                                                      const double* __restrict__ q,
+                                                      const RhsState* S, int64_t n, int nrhs,
+                                                      int R, int nblocks, double* part,
+                                                      const int* gate, Finish fin) {
   if (*gate == 0) return;                                  // every right-hand side stopped
-  __shared__ double sh[kThreads];
-  const int t = threadIdx.x;
+  __shared__ double sh[kThreads * W];
+  const int t = threadIdx.x % kThreads, wb = threadIdx.x / kThreads;
+  const int block = blockIdx.x * W + wb;
   const int r = t % R;
   const int rows_per = kThreads / R;
   const int roff = t / R;
   double acc = 0.0;
-  if (r < nrhs) {
+  if (r < nrhs && block < nblocks) {
     const double a = S[r].alpha;
-    for (int64_t base = (int64_t)blockIdx.x * rows_per; base < n; base += (int64_t)gridDim.x * rows_per) {
+    for (int64_t base = (int64_t)block * rows_per; base < n; base += (int64_t)nblocks * rows_per) {
       const int64_t i = base + roff;
       if (i < n) {
         const int64_t o = i * nrhs + r;
@@ -668,13 +913,11 @@ __global__ __launch_bounds__(kThreads) void k_axpy(double* __restrict__ rv,
       }
     }
   }
-  sh[t] = acc;
+  sh[threadIdx.x] = acc;
   __syncthreads();
-  if (t < nrhs) {
-    double s2 = 0.0;
-    for (int k = t; k < kThreads; k += R) s2 += sh[k];
-    part[(int64_t)blockIdx.x * nrhs + t] = s2;
-  }
+  if (t < nrhs && block < nblocks)
+    agent_store(&part[(int64_t)block * nrhs + t], column_sum(sh + wb * kThreads, t, R));
+  if (fin.ticket) finish_blocks(fin, part, nblocks);
 }
 
 // convergence of one right-hand side on the recursive residual: ||r|| <= rtol ||b||
@@ -845,6 +1088,396 @@ __global__ __launch_bounds__(kThreads) void k_fill(double* dst, double v, int64_
     dst[o] = v;
 }
 
+// ---- the whole solve in one workgroup -------------------------------------------------
+// A small solve is a chain of launches, seven an iteration at 2.5 to 7 us each with a few
+// rows of work in every one.  With at most kTinyElems values per block of vectors one
+// workgroup of 1024 threads runs all of it: the vectors that are gathered (p, r) and the
+// terms of the dots in LDS, x, z and q in registers of the thread that owns a position and a
+// right-hand side, barriers instead of launches.  Up to 1024 values (U = 1) the first eight
+// entries of a thread's rows of A and M stay in registers too.  Bound by the ordered sums
+// (chains of up to 256 dependent additions) and, with U = 4, the rows' entries from L2.
+// 17 x 17 and 32 x 32 grids, one right-hand side: 7 us an iteration against 63 and 50 launched
+// (32 with fused reductions).
+// Every sum is that of the launched kernels: the products' terms by XCD range and thread of
+// the 256 (one workgroup per range here), the rows' by blocks of kThreads / R rows, each
+// from 0 in order, and the partials by halves (an unlaunched workgroup's is 0).  The results
+// are the same bit for bit.
+constexpr int kTinyElems = 4096;
+constexpr int kTinyRows = 1024;     // beyond, one compute unit reads the rows too slowly: 4096
+                                    // rows and one right-hand side 58 us an iteration, launched 60
+constexpr int kTinyThreads = 1024;
+constexpr int kTinyRhs = 32;
+
+struct TinyOut {
+  int iters, status;
+  double bnorm, rr;                 // ||b||, sum of (b - A x)^2
+};
+
+// eight entries of a row from q0 (column -1: none)
+template <typename VT, int LAY>
+__device__ __forceinline__ void tiny_chunk(const Mat& A, int64_t q0, int64_t b, int (&cc)[8],
+                                           VT (&vv)[8]) {
+  if constexpr (LAY == kLayEll) {                 // aligned pieces of the padded row
+    const int4 c0 = *(const int4*)(A.col + q0), c1 = *(const int4*)(A.col + q0 + 4);
+    cc[0] = c0.x; cc[1] = c0.y; cc[2] = c0.z; cc[3] = c0.w;
+    cc[4] = c1.x; cc[5] = c1.y; cc[6] = c1.z; cc[7] = c1.w;
+    if constexpr (sizeof(VT) == 8) {
+#pragma unroll
+      for (int u = 0; u < 8; u += 2) {
+        const double2 v = *(const double2*)(A.val + q0 + u);
+        vv[u] = v.x;
+        vv[u + 1] = v.y;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) vv[u] = entry_val<VT>(A, q0 + u);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      cc[u] = -1;
+      vv[u] = 0;
+      if (q0 + u < b) {
+        cc[u] = A.col[q0 + u];
+        vv[u] = entry_val<VT>(A, q0 + u);
+      }
+    }
+  }
+}
+
+// a row of the product: its first eight entries are in (cc, vv)
+template <typename VT, int LAY>
+__device__ __forceinline__ double tiny_row(const Mat& A, int64_t i, const int (&c0)[8],
+                                           const VT (&v0)[8], const double* x, int nrhs, int r) {
+  double y = 0.0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    if (c0[u] >= 0) y += (double)v0[u] * x[c0[u] * nrhs + r];
+  if (c0[7] >= 0) {
+    const int64_t b = row_hi<LAY>(A, i);
+    for (int64_t q0 = row_lo<LAY>(A, i) + 8; q0 < b; q0 += 8) {
+      int cc[8];
+      VT vv[8];
+      tiny_chunk<VT, LAY>(A, q0, b, cc, vv);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (cc[u] >= 0) y += (double)vv[u] * x[cc[u] * nrhs + r];
+      if (cc[7] < 0) break;
+    }
+  }
+  return y;
+}
+
+// s = 0; s += ((t[g] + t[G + g]) + t[2 G + g]) + ... (J terms) for g < cnt in order, cnt a
+// multiple of eight, the next K g's loads ahead of the additions
+template <int J>
+__device__ __forceinline__ double tiny_chain(const double* t, int G, int cnt) {
+  constexpr int K = J == 1 ? 8 : J == 2 ? 4 : 2;
+  double s = 0.0;
+  double v[J][K];
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+#pragma unroll
+    for (int c = 0; c < K; ++c) v[j][c] = t[j * G + c];
+#pragma unroll 1
+  for (int g = K; g <= cnt; g += K) {
+    double w[J][K];
+    const int gn = g < cnt ? g : 0;               // (the last round's loads are not used)
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int c = 0; c < K; ++c) w[j][c] = t[j * G + gn + c];
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+      double a = v[0][c];
+#pragma unroll
+      for (int j = 1; j < J; ++j) a += v[j][c];
+      s += a;
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int c = 0; c < K; ++c) v[j][c] = w[j][c];
+  }
+  return s;
+}
+
+// Where the terms of the sums sit in LDS: each chain of additions contiguous (an odd number
+// of doubles from one chain to the next: different banks), zeros behind its last term.
+// By position: a chain per XCD range and right-hand side, J rows of G terms (thread g of the
+// 256 adds its J rows first) or, with a row per thread, one of `cnt`; by row: a chain per
+// block of G rows and right-hand side.
+struct TinyLay {
+  int G, J, cnt, lp, blocks;        // lp: doubles per chain by position (G + 1 by row)
+  int by_pos, by_row;               // doubles in all
+};
+__host__ __device__ inline TinyLay tiny_lay(int n, int nrhs, int R) {
+  TinyLay l;
+  const int per = (n + 7) / 8;
+  l.G = kThreads / R;
+  l.J = (per + l.G - 1) / l.G;
+  l.cnt = l.J > 1 ? l.G : (per + 7) / 8 * 8;
+  l.lp = l.J * l.cnt + 1;
+  l.blocks = (n + l.G - 1) / l.G;
+  l.by_pos = 8 * nrhs * l.lp;
+  l.by_row = l.blocks * nrhs * (l.G + 1);
+  return l;
+}
+constexpr int kTinyTerms = 5248;    // of each kind
+
+template <typename MT, int LAYA, int LAYM, int U>
+__global__ __launch_bounds__(kTinyThreads) void k_pcg_tiny(Mat A, Mat M, const double* __restrict__ B,
+                                                           double* __restrict__ X, int nrhs, int R,
+                                                           double rtol, int max_iter,
+                                                           const int32_t* order, TinyOut* out) {
+  __shared__ double s_p[kTinyThreads * U], s_r[kTinyThreads * U];
+  __shared__ double s_t[kTinyTerms], s_n[kTinyTerms];       // terms by position, by row
+  __shared__ RhsState S[kTinyRhs];
+  __shared__ int s_active;
+  const int tid = threadIdx.x;
+  const int n = (int)A.n, tot = n * nrhs;
+  const int per = (n + 7) / 8;
+  const TinyLay lay = tiny_lay(n, nrhs, R);
+  const int G = lay.G;              // rows of a pass of 256 threads
+  for (int k = tid; k < lay.by_pos; k += kTinyThreads) s_t[k] = 0.0;
+  for (int k = tid; k < lay.by_row; k += kTinyThreads) s_n[k] = 0.0;
+  __syncthreads();
+  // element e = tid + u kTinyThreads is position e / nrhs and right-hand side e mod nrhs: its
+  // row and right-hand side (-1: none), its x, and q or z
+  int place[U], tat[U], nat[U];     // and the places of its terms
+  double x[U], w[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int e = tid + u * kTinyThreads;
+    place[u] = -1;
+    tat[u] = nat[u] = 0;
+    if (e < tot) {
+      const int k = e / nrhs, r = e - k * nrhs;
+      const int i = order ? order[k] : k;
+      place[u] = i * kTinyRhs + r;
+      tat[u] = (r * 8 + k / per) * lay.lp + k % per;
+      nat[u] = (r * lay.blocks + i / G) * (G + 1) + i % G;
+    }
+    x[u] = w[u] = 0.0;
+  }
+  int ca[8], cm[8];                 // U = 1: the rows' first entries
+  double va[8];
+  MT vm[8];
+  if constexpr (U == 1) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      ca[c] = cm[c] = -1;
+      va[c] = 0.0;
+      vm[c] = 0;
+    }
+    if (place[0] >= 0) {
+      const int64_t i = place[0] / kTinyRhs;
+      const int64_t a = row_lo<LAYA>(A, i), m = row_lo<LAYM>(M, i);
+      if (a < row_hi<LAYA>(A, i)) tiny_chunk<double, LAYA>(A, a, row_hi<LAYA>(A, i), ca, va);
+      if (m < row_hi<LAYM>(M, i)) tiny_chunk<MT, LAYM>(M, m, row_hi<LAYM>(M, i), cm, vm);
+    }
+  }
+  // f(u, row, r, own): own the element by row.  (U > 1: the place is
+  // opaque each time, as left to itself the compiler keeps the addresses and entries of all
+  // the rows across the iterations, and spills them.)
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (place[u] >= 0) {
+        int pl = place[u];
+        if constexpr (U > 1) asm volatile("" : "+v"(pl));
+        const int i = pl / kTinyRhs, r = pl % kTinyRhs;
+        f(u, i, r, i * nrhs + r);
+      }
+  };
+  auto row_a = [&](int i, const double* v, int r) {
+    if constexpr (U > 1) {
+      const int64_t a = row_lo<LAYA>(A, i), b = row_hi<LAYA>(A, i);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) ca[c] = -1;
+      if (a < b) tiny_chunk<double, LAYA>(A, a, b, ca, va);
+    }
+    return tiny_row<double, LAYA>(A, i, ca, va, v, nrhs, r);
+  };
+  auto row_m = [&](int i, const double* v, int r) {
+    if constexpr (U > 1) {
+      const int64_t a = row_lo<LAYM>(M, i), b = row_hi<LAYM>(M, i);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) cm[c] = -1;
+      if (a < b) tiny_chunk<MT, LAYM>(M, a, b, cm, vm);
+    }
+    return tiny_row<MT, LAYM>(M, i, cm, vm, v, nrhs, r);
+  };
+  // the sums of s_t in the products' order (by position), step(r, sum) on one thread each ...
+  auto product_sums = [&](auto step) {
+    if (tid < 8 * nrhs) {
+      const int xcd = tid & 7, r = tid >> 3;
+      const double* t = s_t + tid * lay.lp;
+      double s = lay.J == 1   ? tiny_chain<1>(t, 0, lay.cnt)
+                 : lay.J == 2 ? tiny_chain<2>(t, G, G)
+                 : lay.J == 3 ? tiny_chain<3>(t, G, G)
+                              : tiny_chain<4>(t, G, G);
+      // lanes 8 r .. 8 r + 7 hold the eight workgroups' partials
+      s = lane_xor_add<4>(s);
+      s = lane_xor_add<2>(s);
+      s = lane_xor_add<1>(s);
+      if (xcd == 0) step(r, s);
+    }
+  };
+  // ... and of s_n in the order of a pass over the rows, from the last threads on
+  auto row_sums = [&](auto step) {
+    const int at = kTinyThreads - 1 - tid;
+    if (at < 32 * nrhs) {
+      const int blk = at & 31, r = at >> 5;
+      double s = 0.0;
+      if (blk < lay.blocks) s = tiny_chain<1>(s_n + (r * lay.blocks + blk) * (G + 1), 0, G);
+      s = lane_xor_add<16>(s);
+      s = lane_xor_add<8>(s);
+      s = lane_xor_add<4>(s);
+      s = lane_xor_add<2>(s);
+      s = lane_xor_add<1>(s);
+      if (blk == 0) step(r, s);
+    }
+  };
+  // x_0 = 0, r = b, z = M r, p = z
+  if (tid == 0) s_active = 0;
+  each([&](int u, int i, int r, int own) {
+    const double b = B[own];
+    s_r[own] = b;
+    s_n[nat[u]] = b * b;
+  });
+  __syncthreads();
+  each([&](int u, int i, int r, int own) {
+    w[u] = row_m(i, s_r, r);
+    s_p[own] = w[u];
+    s_t[tat[u]] = s_r[own] * w[u];
+  });
+  row_sums([&](int r, double bb) {
+    RhsState& g = S[r];
+    g = RhsState{};
+    g.bnorm = sqrt(bb);
+    if (g.bnorm == 0.0) {
+      g.status = 1;
+    } else {
+      g.active = 1;
+      atomicAdd(&s_active, 1);
+    }
+  });
+  __syncthreads();
+  product_sums([&](int r, double v) { S[r].rz = v; });
+  __syncthreads();
+  for (int it = 0; it < max_iter && s_active > 0; ++it) {
+    each([&](int u, int i, int r, int own) {      // q = A p, (p, q), alpha
+      w[u] = row_a(i, s_p, r);
+      s_t[tat[u]] = s_p[own] * w[u];
+    });
+    __syncthreads();
+    product_sums([&](int r, double v) { rhs_alpha(S[r], v, &s_active); });
+    __syncthreads();
+    each([&](int u, int i, int r, int own) {      // r -= alpha q, x += alpha p
+      const double a = S[r].alpha;
+      double rr = s_r[own];
+      if (a != 0.0) {
+        rr = rr - a * w[u];
+        s_r[own] = rr;
+        x[u] = x[u] + a * s_p[own];
+      }
+      s_n[nat[u]] = rr * rr;
+    });
+    __syncthreads();
+    each([&](int u, int i, int r, int own) {      // z = M r
+      w[u] = row_m(i, s_r, r);
+      s_t[tat[u]] = s_r[own] * w[u];
+    });
+    // ||r||^2 and the convergence test, while the first threads wait for z; then (r, z)
+    row_sums([&](int r, double v) { rhs_conv(S[r], v, rtol, &s_active); });
+    __syncthreads();
+    product_sums([&](int r, double v) { rhs_beta(S[r], v); });
+    __syncthreads();
+    each([&](int u, int i, int r, int own) {      // p = z + beta p
+      if (S[r].active) s_p[own] = w[u] + S[r].beta * s_p[own];
+    });
+    __syncthreads();
+  }
+  // x, and the true residual: p's place takes x for the product
+  each([&](int u, int i, int r, int own) {
+    X[own] = x[u];
+    s_p[own] = x[u];
+  });
+  __syncthreads();
+  each([&](int u, int i, int r, int own) {
+    const double d = B[own] - row_a(i, s_p, r);
+    s_n[nat[u]] = d * d;
+  });
+  __syncthreads();
+  row_sums([&](int r, double v) { out[r] = TinyOut{S[r].iters, S[r].status, S[r].bnorm, v}; });
+}
+
+// which solves: the vectors fit, and each XCD range is one workgroup of the narrow product
+// and the rows at most 32 blocks (so the partials above are all there are)
+static bool tiny_fits(int64_t n, int nrhs) {
+  if (nrhs > kTinyRhs || n > kTinyRows || n * nrhs > kTinyElems) return false;
+  int R = 1;
+  while (R < nrhs) R <<= 1;
+  const int rpt = R / 4 > 4 ? R / 4 : 4;
+  const TinyLay l = tiny_lay((int)n, nrhs, R);
+  return (n + 7) / 8 <= (int64_t)l.G * rpt && l.J <= 4 && l.blocks <= 32 &&
+         l.by_pos <= kTinyTerms && l.by_row <= kTinyTerms;
+}
+
+template <typename MT, int LAYA>
+static void launch_tiny(const Mat& A, const Mat& M, const double* B, double* X, int nrhs, int R,
+                        double rtol, int max_iter, const int32_t* order, TinyOut* out,
+                        hipStream_t s) {
+  auto go = [&](auto one, auto four) {
+    if (A.n * nrhs <= kTinyThreads)
+      hipLaunchKernelGGL(one, dim3(1), dim3(kTinyThreads), 0, s, A, M, B, X, nrhs, R, rtol, max_iter,
+                         order, out);
+    else
+      hipLaunchKernelGGL(four, dim3(1), dim3(kTinyThreads), 0, s, A, M, B, X, nrhs, R, rtol, max_iter,
+                         order, out);
+  };
+  constexpr int kFour = kTinyElems / kTinyThreads;
+  if (M.beg) go(k_pcg_tiny<MT, LAYA, kLayPad, 1>, k_pcg_tiny<MT, LAYA, kLayPad, kFour>);
+  else go(k_pcg_tiny<MT, LAYA, kLayCsr, 1>, k_pcg_tiny<MT, LAYA, kLayCsr, kFour>);
+}
+
+static int pcg_tiny(const Mat& A, const Mat& M, int nrhs, const double* B, double* X, double rtol,
+                    int max_iter, int* iters, double* relres, const int32_t* order, hipStream_t s,
+                    PcgWork* work) {
+  DevPool local;
+  TinyOut* out = nullptr;
+  int rc;
+  if (work && work->tiny) {
+    out = (TinyOut*)work->tiny;
+  } else {
+    DevPool& pool = work ? work->tiny_pool : local;
+    if ((rc = pool.alloc(&out, kTinyRhs))) return rc;
+    if (work) work->tiny = out;
+  }
+  int R = 1;
+  while (R < nrhs) R <<= 1;
+  auto by_a = [&](auto mt) {
+    using MT = decltype(mt);
+    if (A.eshift >= 0) launch_tiny<MT, kLayEll>(A, M, B, X, nrhs, R, rtol, max_iter, order, out, s);
+    else launch_tiny<MT, kLayCsr>(A, M, B, X, nrhs, R, rtol, max_iter, order, out, s);
+  };
+  if (M.val32) by_a(float{});
+  else by_a(double{});
+  HIPCHK(hipGetLastError());
+  TinyOut h[kTinyRhs];
+  HIPCHK(hipMemcpyAsync(h, out, sizeof(TinyOut) * nrhs, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  bool indef = false, unconv = false;
+  for (int r = 0; r < nrhs; ++r) {
+    if (iters) iters[r] = h[r].iters;
+    if (relres) relres[r] = h[r].bnorm > 0.0 ? std::sqrt(h[r].rr) / h[r].bnorm : 0.0;
+    if (h[r].status == 4) indef = true;
+    if (h[r].status == 0) unconv = true;
+  }
+  return indef ? PCG_INDEFINITE : unconv ? SPAI_MAXITER : SPAI_OK;
+}
+
 struct Solver {
   Mat A, M;
   Mat Ag, Mg;                        // A and M as the iterations use them (gated, counted)
@@ -863,6 +1496,8 @@ struct Solver {
   // workgroups of the x, p update: 5 per compute unit (20 waves; the 64-right-hand-side solve
   // at 96^3 took 352 ms, against 361 ms with the full 2048 and 363 ms with 3 per unit)
   int pupd_grid = kGrid;
+  int wide_grid = 1024;              // products with at most as many workgroups take 1024 threads
+  int* ticket = nullptr;             // of the fused reductions
   // optional timing of the products inside the iterations: HIP events recorded on the
   // solver's stream around each A p (kind 0) and M r (kind 1), read back per chunk
   PcgTiming* timing = nullptr;
@@ -870,20 +1505,43 @@ struct Solver {
   std::vector<int> ev_kind;
   int ev_used = 0;
 
+  // the last workgroup of a launch of nb workgroups finishes its reduction (step as in
+  // Finish; part[r * rstep + b * bstep]), where the partials are few
+  Finish finish(int step, int64_t nb, int64_t grid, int64_t rstep, int64_t bstep,
+                double rtol = 0.0) const {
+    Finish f;
+    if (nb * nrhs > kFusedParts || grid > kFusedGrid) return f;
+    f.ticket = ticket;
+    f.S = S;
+    f.nactive = nactive;
+    f.step = step;
+    f.nrhs = nrhs;
+    f.rstep = rstep;
+    f.bstep = bstep;
+    f.rtol = rtol;
+    return f;
+  }
+  int prod_step = -1;                // the scalar step of the product being launched (-1: none)
+  bool prod_done = false;            // its last workgroup takes that step
+
   // Y = K X with the per-RHS dots (X, Y) reduced into out and the scalar step `step` applied
   // to them in the same launch (0: alpha, 1: beta)
   void timed_spmm(int kind, const Mat& K, const double* X, double* Y, double* out, int step) {
     const bool rec = timing && ev_used + 2 <= (int)ev.size();
     if (rec) (void)hipEventRecord(ev[ev_used], s);
+    prod_step = step;
     if (K.val32) spmm_v<float>(K, X, Y, part);
     else spmm_v<double>(K, X, Y, part);
+    prod_step = -1;
     if (rec) {
       (void)hipEventRecord(ev[ev_used + 1], s);
       ev_kind[ev_used / 2] = kind;
       ev_used += 2;
     }
-    hipLaunchKernelGGL(k_reduce_rows_step, dim3(nrhs), dim3(kThreads), 0, s, part, spmm_grid, out,
-                       S, step, nactive);
+    if (!prod_done)
+      hipLaunchKernelGGL(k_reduce_rows_step, dim3(nrhs), dim3(kThreads), 0, s, part, spmm_grid, out,
+                         S, step, nactive);
+    prod_done = false;
   }
   // after a synchronisation: add the recorded product times to the totals
   // (calls: the products that did their work; a product of a solve whose right-hand sides
@@ -923,8 +1581,18 @@ struct Solver {
                    int cw = 0) {
     const int64_t per = (n + 7) / 8;
     spmm_grid = (int)(8 * ((per + narrow_chunk<R>() - 1) / narrow_chunk<R>()));
-    hipLaunchKernelGGL((k_spmm_narrow<VT, LAY, R>), dim3(spmm_grid), dim3(kThreads), 0, s, K, X,
-                       Y, pt ? 1 : 0, cw ? cw : nrhs, c0, nrhs, order, pt);
+    Finish f;
+    if (prod_step >= 0) f = finish(prod_step, spmm_grid, spmm_grid, spmm_grid, 1);
+    prod_done = f.ticket != nullptr;
+    if constexpr (R <= kQuadRhs) {
+      hipLaunchKernelGGL((k_spmm_quad<VT, LAY, R>), dim3(spmm_grid), dim3(4 * kThreads), 0, s, K, X, Y,
+                         pt ? 1 : 0, nrhs, order, pt, f);
+    } else if (spmm_grid <= wide_grid)
+      hipLaunchKernelGGL((k_spmm_narrow<VT, LAY, R, 4>), dim3(spmm_grid), dim3(4 * kThreads), 0, s, K,
+                         X, Y, pt ? 1 : 0, cw ? cw : nrhs, c0, nrhs, order, pt, f);
+    else
+      hipLaunchKernelGGL((k_spmm_narrow<VT, LAY, R, 1>), dim3(spmm_grid), dim3(kThreads), 0, s, K, X,
+                         Y, pt ? 1 : 0, cw ? cw : nrhs, c0, nrhs, order, pt, f);
   }
   template <typename VT, int LAY>
   void spmm_as(const Mat& K, const double* X, double* Y, double* pt) {
@@ -961,14 +1629,21 @@ struct Solver {
       hipLaunchKernelGGL(k_reduce_rows, dim3(nrhs), dim3(kThreads), 0, s, part, spmm_grid, out);
   }
 
+  // workgroups of a pass over the rows, kThreads / R of them at a time: at most kGrid, and
+  // none without rows (their partials would be zeros at the end of every sum)
+  int row_blocks(int R) const {
+    return (int)std::min<int64_t>(kGrid, (n * R + kThreads - 1) / kThreads);
+  }
+
   void dot(const double* Xa, const double* Xb, const double* Xc, double* out) {
+    const int nb = row_blocks(pow2(std::min(64, nrhs)));   // of the widest group of columns
     for (int c0 = 0; c0 < nrhs; c0 += 64) {
       const int cw = std::min(64, nrhs - c0);
       const int R = pow2(cw);
-      hipLaunchKernelGGL(k_dot_rows, dim3(kGrid), dim3(kThreads), 0, s, Xa, Xb, Xc, n, nrhs, c0, cw, R,
+      hipLaunchKernelGGL(k_dot_rows, dim3(nb), dim3(kThreads), 0, s, Xa, Xb, Xc, n, nrhs, c0, cw, R,
                          part);
     }
-    hipLaunchKernelGGL(k_reduce_parts, dim3(nrhs), dim3(kThreads), 0, s, part, kGrid, nrhs, out);
+    hipLaunchKernelGGL(k_reduce_parts, dim3(nrhs), dim3(kThreads), 0, s, part, nb, nrhs, out);
   }
 
   // one PCG iteration; each reduction applies the scalar step that consumes it.  odd:
@@ -979,21 +1654,30 @@ struct Solver {
     double* pc = two && odd ? p1 : p;                          // this iteration's p
     timed_spmm(0, Ag, pc, q, tmp, 0);                         // q = A p, (p, q), alpha
     if (nrhs <= 64) {                                            // r update fused with ||r||^2
-      hipLaunchKernelGGL(k_axpy, dim3(kGrid), dim3(kThreads), 0, s, r, q, S, n, nrhs, pow2(nrhs),
-                         part, nactive);
-      hipLaunchKernelGGL(k_reduce_parts_conv, dim3(nrhs), dim3(kThreads), 0, s, part, kGrid, nrhs,
-                         tmp, S, rtol, nactive);               // convergence test
+      const int nb = row_blocks(pow2(nrhs));
+      const int g4 = (nb + 3) / 4;
+      const Finish f = finish(2, nb, g4, 1, nrhs, rtol);
+      if (f.ticket)
+        hipLaunchKernelGGL(k_axpy<4>, dim3(g4), dim3(4 * kThreads), 0, s, r, q, S, n, nrhs, pow2(nrhs),
+                           nb, part, nactive, f);
+      else
+        hipLaunchKernelGGL(k_axpy<1>, dim3(nb), dim3(kThreads), 0, s, r, q, S, n, nrhs, pow2(nrhs), nb,
+                           part, nactive, f);
+      if (!f.ticket)
+        hipLaunchKernelGGL(k_reduce_parts_conv, dim3(nrhs), dim3(kThreads), 0, s, part, nb, nrhs, tmp,
+                           S, rtol, nactive);                  // convergence test
     } else {
       hipLaunchKernelGGL(k_axpy_wide, dim3(kGrid), dim3(kThreads), 0, s, r, q, S, n, nrhs);
       dot(r, r, nullptr, tmp);
       hipLaunchKernelGGL(k_conv, gs, bs, 0, s, S, tmp, rtol, nrhs, nactive);
     }
     timed_spmm(1, Mg, r, z, tmp, 1);                          // z = M r, (r, z), beta
+    const int ug = std::min(pupd_grid, row_blocks(pow2(std::min(64, nrhs))));
     if (two && !odd)                                             // p1 = z + beta p
-      hipLaunchKernelGGL(k_pupd_p, dim3(pupd_grid), dim3(kThreads), 0, s, p1, p, z, S, n, nrhs,
+      hipLaunchKernelGGL(k_pupd_p, dim3(ug), dim3(kThreads), 0, s, p1, p, z, S, n, nrhs,
                          pow2(nrhs));
     else if (two)                                                // x += both terms, p = z + beta p1
-      hipLaunchKernelGGL(k_pupd_x2, dim3(pupd_grid), dim3(kThreads), 0, s, p, p1, x, z, S, n,
+      hipLaunchKernelGGL(k_pupd_x2, dim3(ug), dim3(kThreads), 0, s, p, p1, x, z, S, n,
                          nrhs, pow2(nrhs));
     else
       hipLaunchKernelGGL(k_pupd_wide, dim3(kGrid), dim3(kThreads), 0, s, p, x, z, S, n, nrhs);
@@ -1038,6 +1722,9 @@ namespace spai {
 int pcg_run(const PcgMat& A, const PcgMat& M, int nrhs, const double* dB, double* dX, double rtol,
             int max_iter, int* iters, double* relres, const int32_t* order, hipStream_t s,
             PcgTiming* timing, PcgWork* work) {
+  // (A is ELL or CSR, M padded columns or CSR; the per-product timing wants the launches)
+  if (tiny_fits(A.n, nrhs) && !timing && !A.beg && !A.val32 && M.eshift < 0)
+    return pcg_tiny(A, M, nrhs, dB, dX, rtol, max_iter, iters, relres, order, s, work);
   int rc;
   DevPool local;
   DevPool& pool = work ? work->pool : local;
@@ -1076,7 +1763,7 @@ int pcg_run(const PcgMat& A, const PcgMat& M, int nrhs, const double* dB, double
         (nrhs <= 64 && (rc = pool.alloc(&S.p1, tot))) ||
         (rc = pool.alloc(&S.q, tot)) ||
         (rc = pool.alloc(&S.part, (int64_t)std::max<int64_t>(kGrid, Solver::spmm_blocks(S.n)) * nrhs)) ||
-        (rc = pool.alloc(&S.tmp, nrhs)) || (rc = pool.alloc(&S.S, nrhs)) || (rc = pool.alloc(&S.nactive, 3)))
+        (rc = pool.alloc(&S.tmp, nrhs)) || (rc = pool.alloc(&S.S, nrhs)) || (rc = pool.alloc(&S.nactive, 4)))
       return rc;
     if (work) {
       void* const b[9] = {S.r, S.z, S.p, S.p1, S.q, S.part, S.tmp, S.S, S.nactive};
@@ -1113,7 +1800,8 @@ int pcg_run(const PcgMat& A, const PcgMat& M, int nrhs, const double* dB, double
   S.Ag.gate = S.Mg.gate = S.nactive;
   S.Ag.ran = S.runs;
   S.Mg.ran = S.runs ? S.runs + 1 : nullptr;
-  HIPCHK(hipMemsetAsync(S.nactive, 0, 3 * sizeof(int), s));
+  S.ticket = S.nactive + 3;
+  HIPCHK(hipMemsetAsync(S.nactive, 0, 4 * sizeof(int), s));
   HIPCHK(hipMemsetAsync(S.S, 0, sizeof(RhsState) * nrhs, s));
   const dim3 gs((nrhs + 63) / 64), bs(64);
   // x_0 = 0, r = b, z = M r, p = z

@@ -116,3 +116,51 @@ def test_loss_row_beyond_the_tile_is_refused():
     with pytest.raises(S.SpaiError) as e:
         S.loss_fwd(A, M)
     assert e.value.code == -7
+
+
+@pytest.mark.parametrize("kind,n,nrhs", [
+    ("geo", 1, 1), ("geo", 2, 3), ("geo", 9, 32), ("geo", 257, 1), ("geo", 1024, 1),
+    ("geo", 1023, 4), ("geo", 585, 7), ("geo", 512, 8), ("geo", 273, 15), ("geo", 272, 15),
+    ("geo", 240, 17), ("geo", 129, 31), ("geo", 128, 32), ("grid", 32, 2), ("grid", 9, 5),
+    ("grid", 32, 4)])
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_pcg_in_one_workgroup_equals_the_launched_solve(kind, n, nrhs, precision):
+    """Small solves run in one workgroup; with phase timing the same solve is launched
+    product by product.  The sums are the same: bitwise equal, also where the terms' layout
+    is at its limits (rows per XCD range, blocks of rows, padded right-hand sides), at
+    iteration caps, and where a right-hand side is zero."""
+    S = _spai()
+    A = W.laplace2d(n) if kind == "grid" else \
+        W.geometric_graph(n, 3) if n > 2 else sp.csr_matrix(np.diag(np.arange(1.0, n + 1)))
+    n = A.shape[0]
+    B = W.rhs(n, nrhs, 11)
+    if nrhs > 4:
+        B[:, 3] = 0.0
+    out = []
+    for prof in (False, True):
+        h = S.SPAI(A, "lomr", "global", 2.0, True, max_iter=12,
+                   options=S.Options(precision=precision, profile=prof))
+        h.iterate(12)
+        out.append([h.pcg(B, rtol=1e-9, max_iter=m) for m in (0, 1, 2, 7, 10000)])
+        h.close()
+    for a, b in zip(*out):
+        assert a[3] == b[3]
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+        assert np.array_equal(a[2], b[2])
+
+
+@pytest.mark.parametrize("n", [1025, 2049, 8193, 16500])
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 5, 16, 31])
+def test_pcg_narrow_products_against_the_oracle(n, nrhs):
+    """Sizes around the chunks of the narrow products (up to 1024 rows a workgroup, eight
+    ranges) on irregular rows of up to about 25 entries.  Eight iterations, before a CG
+    recurrence lets rounding grow (with a nearly indefinite M the two drift apart by 1e-6 in
+    40): X is then a few sums of products away from B, 1e-12."""
+    S = _spai()
+    A = W.geometric_graph(n, n)
+    M = sp.csr_matrix(O.lomr(A, oracle_rule(A, "column", 1.0, True), 6).M)
+    B = W.rhs(n, nrhs, n + nrhs)
+    X, it, _, rc = S.pcg_solve(A, M, B, rtol=1e-8, max_iter=8)
+    Xo, ito, _ = O.pcg_block(A, M, B, rtol=1e-8, max_iter=8)
+    assert rc in (S.SPAI_OK, S.SPAI_MAXITER) and list(it) == list(ito)
+    assert np.max(np.abs(X - Xo)) <= 1e-12 * np.max(np.abs(Xo))

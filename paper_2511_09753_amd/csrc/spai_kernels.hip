@@ -1095,6 +1095,13 @@ static int per_cu_grid(int per) {
 }
 
 
+// workgroups of a large-tile pass: as many as are resident (two to four per compute unit,
+// LDS), so that wide columns fill the chip; where there are none they return at once
+template <typename K>
+static int large_grid(K kernel, size_t lds) {
+  return std::max(256, resident_grid(kernel, lds));
+}
+
 template <typename T>
 void launch_resid(const Csr& A, Pair<T> M, Cols<T> R, const int64_t* off, const int64_t* total,
                   double* colnorm, int weighted, double* colrz, BigList big, DevState* st,
@@ -1116,8 +1123,8 @@ void launch_resid(const Csr& A, Pair<T> M, Cols<T> R, const int64_t* off, const 
                        dim3(resident_grid(k_resid<T, false>, resid_lds(small, ell))),
                        dim3(SPAI_WAVE), resid_lds(small, ell), s, A, M, R, off, total, colnorm,
                        weighted, colrz, big, st, 0, small.L, small.H);
-  hipLaunchKernelGGL((k_resid<T, false>), dim3(256), dim3(SPAI_WAVE), resid_lds(large, ell), s, A, M,
-                     R, off, total, colnorm, weighted, colrz, big, st, 1, large.L, large.H);
+  hipLaunchKernelGGL((k_resid<T, false>), dim3(large_grid(k_resid<T, false>, resid_lds(large, ell))),
+                     dim3(SPAI_WAVE), resid_lds(large, ell), s, A, M, R, off, total, colnorm, weighted, colrz, big, st, 1, large.L, large.H);
   hipLaunchKernelGGL((k_resid<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), 0, s, A, M, R, off, total,
                      colnorm, weighted, colrz, big, st, 2, huge.L, huge.H);
 }
@@ -1501,8 +1508,8 @@ void launch_dots(const Csr& A, Cols<T> R, Pair<T> P, int useR, int useP, int wei
                        dim3(resident_grid(k_dots<T, false>, dots_lds(small, ell))),
                        dim3(SPAI_WAVE), dots_lds(small, ell), s, A, R, P, useR, useP, weighted,
                        colpart, big, st, 0, small.L, small.H);
-  hipLaunchKernelGGL((k_dots<T, false>), dim3(256), dim3(SPAI_WAVE), dots_lds(large, ell), s, A, R, P,
-                     useR, useP, weighted, colpart, big, st, 1, large.L, large.H);
+  hipLaunchKernelGGL((k_dots<T, false>), dim3(large_grid(k_dots<T, false>, dots_lds(large, ell))),
+                     dim3(SPAI_WAVE), dots_lds(large, ell), s, A, R, P, useR, useP, weighted, colpart, big, st, 1, large.L, large.H);
   hipLaunchKernelGGL((k_dots<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), 0, s, A, R, P, useR, useP,
                      weighted, colpart, big, st, 2, huge.L, huge.H);
 }
@@ -2658,8 +2665,9 @@ void launch_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, Up
                        dim3(resident_grid(k_update<T, false>, update_lds(small, true))),
                        dim3(SPAI_WAVE), update_lds(small, true), s, A, M, R, P, PT, md, off,
                        total, kcol, tM, tP, big, seg, st, 0, small.L, small.H, update_deg(small));
-  hipLaunchKernelGGL((k_update<T, false>), dim3(256), dim3(SPAI_WAVE), update_lds(large, false), s,
-                     A, M, R, P, PT, md, off, total, kcol, tM, tP, big, seg, st, 1, large.L,
+  hipLaunchKernelGGL((k_update<T, false>),
+                     dim3(large_grid(k_update<T, false>, update_lds(large, false))), dim3(SPAI_WAVE),
+                     update_lds(large, false), s, A, M, R, P, PT, md, off, total, kcol, tM, tP, big, seg, st, 1, large.L,
                      large.H, update_deg(large));
   hipLaunchKernelGGL((k_update<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), 0, s, A, M, R, P, PT,
                      md, off, total, kcol, tM, tP, big, seg, st, 2, huge.L, huge.H,
@@ -3207,8 +3215,8 @@ void launch_score(const Csr& A, Pair<T> M, double* sc, double* sig, BigList big,
   hipLaunchKernelGGL((k_score<T, false>), dim3(resident_grid(k_score<T, false>, score_lds(small, ell))),
                      dim3(SPAI_WAVE), score_lds(small, ell), s, A, M, sc, big, st, 0, small.L,
                      small.H);
-  hipLaunchKernelGGL((k_score<T, false>), dim3(256), dim3(SPAI_WAVE), score_lds(large, ell), s, A,
-                     M, sc, big, st, 1, large.L, large.H);
+  hipLaunchKernelGGL((k_score<T, false>), dim3(large_grid(k_score<T, false>, score_lds(large, ell))),
+                     dim3(SPAI_WAVE), score_lds(large, ell), s, A, M, sc, big, st, 1, large.L, large.H);
   hipLaunchKernelGGL((k_score<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), 0, s, A, M, sc, big, st,
                      2, huge.L, huge.H);
   const int ng = (int)std::min<int64_t>((n + 63) / 64, 1 << 30);

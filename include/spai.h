@@ -136,8 +136,8 @@ typedef struct {
                                (keep score > t + tie_eta |t|, t the (b+1)-th largest).
                                P keeps hard thresholding.  Requires SPAI_CAP_GLOBAL
                                and symmetrize = 1; default 0                      */
-  double floor_frac;        /* global cap on magnitudes, one matrix: the update
-                               writes only the candidates (off-diagonal ones for M)
+  double floor_frac;        /* global cap on magnitudes, one matrix of at least
+                               49152 columns: the update writes only the candidates (off-diagonal ones for M)
                                with |x| >= floor_frac times the previous iteration's
                                cut t, and counts the others; when this iteration's
                                cut does not clear the floor by the tie factor

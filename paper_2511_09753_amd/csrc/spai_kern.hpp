@@ -12,6 +12,7 @@ enum : int { kMR = 0, kCG = 1, kLOMR = 2 };
 // Frobenius dots produced per column by the SpGEMM-dots kernel:
 // 0 (R,AR)  1 (AR,AR)  2 (AR,AP)  3 (R,AP)  4 (AP,AP)  5 (P,AP)
 constexpr int kND = 6;
+constexpr int64_t kFloorRows = 49152;   // columns from which the global cap uses floors
 constexpr int kCntSlots = 65536;   // workgroup slots per traffic counter
 constexpr int kNCnt = 7;
 
@@ -56,7 +57,8 @@ struct DevState {
   // iteration in progress (-1: none), f = kept, seen, band of M (0-2) and of P (3-5)
   unsigned long long* rec;
   int rec_i, rec_cap;
-  int rec_next, rec_pad;          // the next iteration's record
+  int rec_next;                   // the next iteration's record
+  int sel_ticket;                 // workgroups done with a selection pass (0 between launches)
   // speculative floor of the global cap (magnitude keys, one matrix): the lean update
   // writes the off-diagonal candidates of M (all of P, P^T) only where |x| >= floor and
   // counts the others in below; the selection sets redo when its cut does not clear

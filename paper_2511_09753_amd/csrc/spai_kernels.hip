@@ -2679,7 +2679,6 @@ void launch_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, Up
 // bits of |x| (positive doubles order like their bit patterns)
 // ============================================================================
 
-constexpr int kSelThreads = 256;
 
 __device__ __forceinline__ unsigned long long mag_key(double v) {
   return (unsigned long long)__double_as_longlong(fabs(v));
@@ -2745,15 +2744,110 @@ __device__ __forceinline__ int64_t group_src(const Group64& g, int c, int x) {
   return __shfl(g.cb, c, SPAI_WAVE) + (int64_t)(x - __shfl(g.ex, c, SPAI_WAVE));
 }
 
+// Find, with one block (a power of two of at most 1024 threads, nbins a multiple of it),
+// the bin i holding the rank-th largest key of a histogram, at(i) its count of bin i, counted
+// from the top bin down: *bin = i, *above = keys in bins above i.  Each thread owns
+// nbins / blockDim consecutive bins (thread 0 the highest).
+template <typename F>
+__device__ inline void find_bin_desc(F at, int nbins, long long rank, long long* total, int* bin,
+                                     long long* above) {
+  __shared__ long long s_wave[16];
+  __shared__ int s_bin;
+  __shared__ long long s_above;
+  const int t = threadIdx.x, lane = lane_id();
+  const int per = nbins / (int)blockDim.x;
+  const int hi = nbins - 1 - t * per;            // this thread's bins: hi, hi-1, ..., hi-per+1
+  long long loc = 0;
+#pragma unroll 8
+  for (int k = 0; k < per; ++k) loc += (long long)at(hi - k);
+  const long long wsum = wave_sum_ll(loc);
+  if (lane == 0) s_wave[t >> 6] = wsum;
+  if (t == 0) { s_bin = -1; s_above = 0; }
+  __syncthreads();
+  long long before = 0, tot = 0;
+  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+    before += w < (t >> 6) ? s_wave[w] : 0;
+    tot += s_wave[w];
+  }
+  if (rank > before && rank <= before + wsum) {  // one wave (none where rank < 1 or > tot)
+    long long inc = loc;
+    for (int d = 1; d < 64; d <<= 1) {
+      const long long o = __shfl_up(inc, d, SPAI_WAVE);
+      if (lane >= d) inc += o;
+    }
+    before += inc - loc;
+    if (rank >= 1 && before < rank && before + loc >= rank) {
+      long long acc = before;
+      for (int k = 0; k < per; ++k) {
+        const long long c = (long long)at(hi - k);
+        if (acc + c >= rank) { s_bin = hi - k; s_above = acc; break; }
+        acc += c;
+      }
+    }
+  }
+  __syncthreads();
+  *total = tot;
+  *bin = s_bin;
+  *above = s_above;
+}
+
+// true in every thread of the last workgroup of a launch to come here, all of whose atomics
+// and agent-scope stores have then arrived; the histograms are read by it through agent-scope
+// loads, and it sets the ticket back
+__device__ __forceinline__ bool last_block(int* ticket) {
+  __shared__ int last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           (int)gridDim.x - 1;
+    if (last) *ticket = 0;
+  }
+  __syncthreads();
+  return last != 0;
+}
+__device__ __forceinline__ unsigned long long agent_count(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// the decision after the exponent histogram (one thread): bin holds the (b+1)-th largest of
+// `total` keys, `above` of them in higher bins; sets the threshold where nothing is selected
+__device__ inline void sel_exp_decide(long long b, long long total, int bin, long long above,
+                                      int signed_keys, double* thr, DevState* st) {
+  st->sel_count = 0;
+  st->sel_diag = 0;                 // for the next selection
+  if (b < 0) {                      // cap below the diagonal count: keep only the diagonal
+    st->sel_done = 1;
+    *thr = INFINITY;
+    thr[2] = INFINITY;
+    return;
+  }
+  if (total <= b) {                  // |supp| within the cap: nothing to drop
+    st->sel_done = 1;
+    *thr = signed_keys ? -INFINITY : 0.0;
+    thr[2] = *thr;
+    // candidates left out below a floor would have to be kept: run again without it
+    const bool isM = thr == &st->thrM;
+    if ((isM ? st->belowM : st->belowP) > 0) st->redo = 1;
+    return;
+  }
+  st->sel_prefix = (unsigned long long)bin << 52;
+  st->sel_rank = (b + 1) - above;
+  st->sel_done = 0;
+}
+
 // histogram of the top key bits (63..52; for magnitudes bit 63 is 0) of the candidates,
 // counting diagonal entries apart.  SC: the keys are the signed scores sc[] stored beside
 // the candidates instead of their magnitudes.  Four waves per workgroup share one LDS
 // histogram, each walking its own 64-column groups: the histogram's LDS no longer limits
-// the waves in flight (one wave per histogram allowed five per SIMD, 7% slower).
+// the waves in flight (one wave per histogram allowed five per SIMD, 7% slower).  The last
+// workgroup finds the exponent bin of the (b+1)-th largest, b = m - (diagonal count if
+// excluded), and clears the histogram for the passes over the collected keys.
 template <typename T, bool SC>
 __global__ __launch_bounds__(4 * SPAI_WAVE) void k_sel_hist_exp(Pair<T> Xp, const double* sc,
-                                                            int excl_diag,
-                                                            unsigned long long* hist, int64_t n,
+                                                            int excl_diag, int64_t m,
+                                                            unsigned long long* hist,
+                                                            double* thr, int64_t n,
                                                             DevState* st) {
   if (!st->any_active || !st->iter_active) return;
   constexpr int NB = SC ? 4096 : 2048;
@@ -2804,72 +2898,15 @@ __global__ __launch_bounds__(4 * SPAI_WAVE) void k_sel_hist_exp(Pair<T> Xp, cons
     if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
   diag = wave_sum_ll(diag);
   if (lane == 0 && diag) atomicAdd((unsigned long long*)&st->sel_diag, (unsigned long long)diag);
-}
-
-// Find, with one 1024-thread block, the bin i holding the rank-th largest key of a
-// histogram counted from the top bin down: *bin = i, *above = keys in bins above i.
-// Each thread owns nbins / 1024 consecutive bins (thread 0 the highest).
-__device__ inline void find_bin_desc(const unsigned long long* hist, int nbins, long long rank,
-                                     long long* total, int* bin, long long* above) {
-  __shared__ int64_t sh[1024];
-  __shared__ int s_bin;
-  __shared__ long long s_above, s_total;
-  const int t = threadIdx.x;
-  const int per = nbins / 1024;
-  const int hi = nbins - 1 - t * per;            // this thread's bins: hi, hi-1, ..., hi-per+1
-  long long loc = 0;
-  for (int k = 0; k < per; ++k) loc += (long long)hist[hi - k];
-  int64_t tot;
-  const int64_t before = block_excl_scan_i64(loc, sh, &tot);
-  if (t == 0) { s_total = tot; s_bin = -1; s_above = 0; }
-  __syncthreads();
-  if (rank >= 1 && before < rank && before + loc >= rank) {
-    long long acc = before;
-    for (int k = 0; k < per; ++k) {
-      const long long c = (long long)hist[hi - k];
-      if (acc + c >= rank) { s_bin = hi - k; s_above = acc; break; }
-      acc += c;
-    }
-  }
-  __syncthreads();
-  *total = s_total;
-  *bin = s_bin;
-  *above = s_above;
-}
-
-// find the exponent bin of the (b+1)-th largest; b = m - (diagonal count if excluded)
-__global__ __launch_bounds__(1024) void k_sel_find_exp(unsigned long long* hist,
-                                                       int excl_diag, int64_t m, int signed_keys,
-                                                       double* thr, DevState* st) {
-  if (!st->any_active || !st->iter_active) return;
-  const long long b = m - (excl_diag ? st->sel_diag : 0);
+  if (!last_block(&st->sel_ticket)) return;
+  const long long b =
+      m - (excl_diag ? (long long)agent_count((const unsigned long long*)&st->sel_diag) : 0);
   long long total, above;
   int bin;
-  const int nb = signed_keys ? 4096 : 2048;
-  find_bin_desc(hist, nb, b + 1, &total, &bin, &above);
-  // every read of the histogram is done (the search ends on a barrier): clear it for the
-  // first pass over the collected keys (the bins above nb were never written)
-  for (int i = threadIdx.x; i < nb; i += blockDim.x) hist[i] = 0;
-  if (threadIdx.x != 0) return;
-  st->sel_count = 0;
-  if (b < 0) {                      // cap below the diagonal count: keep only the diagonal
-    st->sel_done = 1;
-    *thr = INFINITY;
-    thr[2] = INFINITY;
-    return;
-  }
-  if (total <= b) {                  // |supp| within the cap: nothing to drop
-    st->sel_done = 1;
-    *thr = signed_keys ? -INFINITY : 0.0;
-    thr[2] = *thr;
-    // candidates left out below a floor would have to be kept: run again without it
-    const bool isM = thr == &st->thrM;
-    if ((isM ? st->belowM : st->belowP) > 0) st->redo = 1;
-    return;
-  }
-  st->sel_prefix = (unsigned long long)bin << 52;
-  st->sel_rank = (b + 1) - above;
-  st->sel_done = 0;
+  find_bin_desc([&](int i) { return agent_count(hist + i); }, NB, b + 1, &total, &bin, &above);
+  // every read of the histogram is done (the search ends on a barrier)
+  for (int i = threadIdx.x; i < NB; i += 4 * SPAI_WAVE) hist[i] = 0;
+  if (threadIdx.x == 0) sel_exp_decide(b, total, bin, above, SC ? 1 : 0, thr, st);
 }
 
 // keys whose exponent bin is the selected one, staged in LDS (one stage per one-wave
@@ -2938,68 +2975,178 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_sel_collect(Pair<T> Xp, const dou
   flush();
 }
 
-// histogram of 13 key bits at `shift` among the collected keys matching the prefix above
-__global__ __launch_bounds__(kSelThreads) void k_sel_hist_buf(const unsigned long long* selbuf,
-                                                              int shift,
-                                                              unsigned long long* hist,
-                                                              DevState* st) {
+// the threshold once every key bit is known (one thread)
+__device__ inline void sel_finish(double eta, int signed_keys, double* thr, DevState* st) {
+  double t;                            // the bits below hold no candidate's bit
+  if (signed_keys) {                   // keep score > t + eta |t|
+    t = ord_value(st->sel_prefix);
+    *thr = t + eta * fabs(t);
+  } else {                             // keep |x| > t (1 + eta)
+    t = __longlong_as_double((long long)st->sel_prefix);
+    *thr = t * (1.0 + eta);
+    // every candidate the cut keeps or counts in its tie band must have been written:
+    // t (1 - eta) must clear the floor under which candidates were left out
+    const bool isM = thr == &st->thrM;
+    const double fl = isM ? st->floorM : st->floorP;
+    if ((isM ? st->belowM : st->belowP) > 0 && t * (1.0 - eta) < fl) st->redo = 1;
+  }
+  thr[2] = t;                          // rawM / rawP, two doubles after thrM / thrP
+  st->sel_done = 1;
+}
+
+// histogram of 13 key bits at `shift` among the collected keys matching the prefix above; the
+// last workgroup finds the bin of the key sought and clears the histogram
+__global__ __launch_bounds__(1024) void k_sel_pass(const unsigned long long* selbuf, int shift,
+                                                   int last, double eta, int signed_keys,
+                                                   unsigned long long* hist, double* thr,
+                                                   DevState* st) {
   if (!st->any_active || !st->iter_active || st->sel_done) return;
   __shared__ unsigned int h[8192];
-  for (int i = threadIdx.x; i < 8192; i += kSelThreads) h[i] = 0;
-  __syncthreads();
   const unsigned long long cnt = st->sel_count;
-  const int hi = shift + 13;
-  const unsigned long long pre = st->sel_prefix >> hi;
-  for (unsigned long long i = (unsigned long long)blockIdx.x * kSelThreads + threadIdx.x; i < cnt;
-       i += (unsigned long long)gridDim.x * kSelThreads) {
-    const unsigned long long key = selbuf[i];
-    if ((key >> hi) == pre) atomicAdd(&h[(int)((key >> shift) & 8191ull)], 1u);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 8192; i += kSelThreads)
-    if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
-}
-
-__global__ __launch_bounds__(1024) void k_sel_find_buf(unsigned long long* hist, int shift,
-                                                       int last, double eta, int signed_keys,
-                                                       double* thr, DevState* st) {
-  if (!st->any_active || !st->iter_active || st->sel_done) return;
   const long long rank = st->sel_rank;
+  const unsigned long long prefix = st->sel_prefix;
+  if ((unsigned long long)blockIdx.x * 1024 < cnt) {
+    for (int i = threadIdx.x; i < 8192; i += 1024) h[i] = 0;
+    __syncthreads();
+    const int hi = shift + 13;
+    const unsigned long long pre = prefix >> hi;
+    for (unsigned long long i = (unsigned long long)blockIdx.x * 1024 + threadIdx.x; i < cnt;
+         i += (unsigned long long)gridDim.x * 1024) {
+      const unsigned long long key = selbuf[i];
+      if ((key >> hi) == pre) atomicAdd(&h[(int)((key >> shift) & 8191ull)], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 8192; i += 1024)
+      if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
+  }
+  if (!last_block(&st->sel_ticket)) return;
   long long total, above;
   int bin;
-  find_bin_desc(hist, 8192, rank, &total, &bin, &above);
-  for (int i = threadIdx.x; i < 8192; i += blockDim.x) hist[i] = 0;   // for the next pass
+  find_bin_desc([&](int i) { return agent_count(hist + i); }, 8192, rank, &total, &bin, &above);
+  for (int i = threadIdx.x; i < 8192; i += 1024) hist[i] = 0;     // for the next pass
   if (threadIdx.x != 0) return;
   if (bin >= 0) {
-    st->sel_prefix |= (unsigned long long)bin << shift;
+    st->sel_prefix = prefix | ((unsigned long long)bin << shift);
     st->sel_rank = rank - above;
   }
-  if (shift == last) {                 // the bits below hold no candidate's bit
-    double t;
-    if (signed_keys) {                 // keep score > t + eta |t|
-      t = ord_value(st->sel_prefix);
-      *thr = t + eta * fabs(t);
-    } else {                           // keep |x| > t (1 + eta)
-      t = __longlong_as_double((long long)st->sel_prefix);
-      *thr = t * (1.0 + eta);
-      // every candidate the cut keeps or counts in its tie band must have been written:
-      // t (1 - eta) must clear the floor under which candidates were left out
-      const bool isM = thr == &st->thrM;
-      const double fl = isM ? st->floorM : st->floorP;
-      if ((isM ? st->belowM : st->belowP) > 0 && t * (1.0 - eta) < fl) st->redo = 1;
+  if (shift == last) sel_finish(eta, signed_keys, thr, st);
+}
+
+// The whole selection of a small matrix in one workgroup, its 16 waves walking the columns:
+// a launch is most of what the passes above cost there (6 of them, 2.5 to 7 us each).  The keys of the selected exponent, in selbuf, pass by pass as in k_sel_hist_buf and
+// k_sel_find_buf, with the histogram in LDS.
+__device__ inline void sel_passes(const unsigned long long* selbuf, unsigned* h, int last,
+                                  double eta, int signed_keys, double* thr, DevState* st) {
+  const unsigned long long cnt = st->sel_count;
+  unsigned long long prefix = st->sel_prefix;
+  long long rank = st->sel_rank;
+  for (int shift = 39; shift >= last; shift -= 13) {
+    for (int i = threadIdx.x; i < 8192; i += 1024) h[i] = 0;
+    __syncthreads();
+    const int hi = shift + 13;
+    for (unsigned long long i = threadIdx.x; i < cnt; i += 1024) {
+      const unsigned long long key = selbuf[i];
+      if ((key >> hi) == (prefix >> hi)) atomicAdd(&h[(int)((key >> shift) & 8191ull)], 1u);
     }
-    thr[2] = t;                        // rawM / rawP, two doubles after thrM / thrP
-    st->sel_done = 1;
+    __syncthreads();
+    long long total, above;
+    int bin;
+    find_bin_desc([&](int i) { return h[i]; }, 8192, rank, &total, &bin, &above);
+    __syncthreads();
+    if (bin >= 0) {
+      prefix |= (unsigned long long)bin << shift;
+      rank -= above;
+    }
+  }
+  if (threadIdx.x == 0) {
+    st->sel_prefix = prefix;
+    st->sel_rank = rank;
+    sel_finish(eta, signed_keys, thr, st);
   }
 }
 
-__global__ void k_sel_reset(unsigned long long* hist, int nbins, DevState* st) {
-  for (int i = threadIdx.x; i < nbins; i += blockDim.x) hist[i] = 0;
+constexpr int64_t kSelSmallRows = 2048;
+template <typename T, bool SC>
+__global__ __launch_bounds__(1024) void k_sel_small(Pair<T> Xp, const double* sc, int excl_diag,
+                                                    int64_t m, unsigned long long* selbuf,
+                                                    int last, double eta, double* thr, int64_t n,
+                                                    DevState* st) {
+  if (!st->any_active || !st->iter_active) return;
+  __shared__ unsigned h[8192];
+  __shared__ unsigned s_cnt;
+  __shared__ int s_diag;
+  constexpr int NB = SC ? 4096 : 2048;
+  const int lane = lane_id(), wv = threadIdx.x / SPAI_WAVE;
+  for (int i = threadIdx.x; i < NB; i += 1024) h[i] = 0;
   if (threadIdx.x == 0) {
-    st->sel_diag = 0;
-    st->sel_count = 0;
-    st->sel_done = 0;
+    s_cnt = 0;
+    s_diag = 0;
   }
+  __syncthreads();
+  const Cols<T> X = Xp.nxt();
+  const int64_t ng = (n + 63) / 64;
+  // f(key) for every candidate that takes part (every lane calls it; take: this lane's does)
+  int diag = 0;
+  auto walk = [&](auto f) {
+    for (int64_t gi = wv; gi < ng; gi += 16) {
+      const Group64 g = group_load(X, gi * 64, n);
+      for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE * kGU) {
+        int col[kGU], idx[kGU];
+        T val[kGU];
+        double sv[kGU];
+#pragma unroll
+        for (int u = 0; u < kGU; ++u) {
+          const int x = x0 + u * SPAI_WAVE + lane;
+          const int xc = min(x, g.T - 1);            // all lanes shuffle together
+          const int c = group_col(g, xc);
+          const int64_t src = group_src(g, c, xc);
+          sv[u] = 0.0;
+          col[u] = -1;
+          idx[u] = -1;
+          val[u] = (T)0;
+          if (x < g.T) {
+            col[u] = c;
+            if (excl_diag) idx[u] = X.idx[src];
+            if constexpr (SC) sv[u] = sc[src]; else val[u] = X.val[src];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kGU; ++u) {
+          const bool dg = col[u] >= 0 && excl_diag && idx[u] == (int)(g.j0 + col[u]);
+          const unsigned long long key = SC ? ord_key(sv[u]) : mag_key((double)val[u]);
+          f(key, col[u] >= 0 && !dg, dg);
+        }
+      }
+    }
+  };
+  walk([&](unsigned long long key, bool take, bool dg) {
+    diag += dg;
+    if (take) atomicAdd(&h[(int)(key >> 52)], 1u);
+  });
+  diag = wave_sum_int(diag);
+  if (lane == 0 && diag) atomicAdd(&s_diag, diag);
+  __syncthreads();
+  const long long b = m - (excl_diag ? s_diag : 0);
+  long long total, above;
+  int bin;
+  find_bin_desc([&](int i) { return h[i]; }, NB, b + 1, &total, &bin, &above);
+  if (threadIdx.x == 0) sel_exp_decide(b, total, bin, above, SC ? 1 : 0, thr, st);
+  __syncthreads();
+  if (b < 0 || total <= b) return;
+  const unsigned long long want = (unsigned long long)bin;
+  walk([&](unsigned long long key, bool take, bool) {
+    take = take && (key >> 52) == want;
+    const unsigned long long bal = __ballot(take);
+    if (bal == 0ull) return;
+    unsigned base = 0;
+    if (lane == 0) base = atomicAdd(&s_cnt, (unsigned)__popcll(bal));
+    base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+    if (take) selbuf[base + __popcll(bal & lanemask_lt())] = key;
+  });
+  __syncthreads();
+  if (threadIdx.x == 0) st->sel_count = s_cnt;
+  __syncthreads();
+  sel_passes(selbuf, h, last, eta, SC ? 1 : 0, thr, st);
 }
 
 template <typename T>
@@ -3008,7 +3155,19 @@ void launch_global_select(Pair<T> X, int exclude_diag, int64_t m, double eta, in
                           DevState* st, hipStream_t s, const double* score) {
   double* thr = which == 0 ? &st->thrM : &st->thrP;
   const int sk = score ? 1 : 0;
-  hipLaunchKernelGGL(k_sel_reset, dim3(1), dim3(1024), 0, s, hist, 8192, st);
+  // float candidates widened to double have zero in the low 29 mantissa bits, so the
+  // passes over bits 0..25 would each select bin 0: they stop after bits 26..38
+  const int last = (sizeof(T) == 4 && !score) ? 26 : 0;
+  if (n <= kSelSmallRows) {
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, X, score, exclude_diag, m, selbuf, last, eta,
+                         thr, n, st);
+    };
+    if (score) go(k_sel_small<T, true>);
+    else go(k_sel_small<T, false>);
+    return;
+  }
+  // (the histogram is zero here: every search clears the bins that it has read)
   const int ng = (int)std::min<int64_t>((n + 63) / 64, 1 << 30);
   // the magnitude passes run below full occupancy, as the compaction does: 4 four-wave
   // histogram workgroups and 12 collecting waves per compute unit took 0.55 ms per
@@ -3017,15 +3176,13 @@ void launch_global_select(Pair<T> X, int exclude_diag, int64_t m, double eta, in
     hipLaunchKernelGGL(
         (k_sel_hist_exp<T, true>),
         dim3(std::min((ng + 3) / 4, resident_grid(k_sel_hist_exp<T, true>, 0, 4 * SPAI_WAVE))),
-        dim3(4 * SPAI_WAVE), 0, s, X, score, exclude_diag, hist, n, st);
+        dim3(4 * SPAI_WAVE), 0, s, X, score, exclude_diag, m, hist, thr, n, st);
   else
     hipLaunchKernelGGL(
         (k_sel_hist_exp<T, false>),
         dim3(std::min({(ng + 3) / 4, resident_grid(k_sel_hist_exp<T, false>, 0, 4 * SPAI_WAVE),
                        per_cu_grid(4)})),
-        dim3(4 * SPAI_WAVE), 0, s, X, score, exclude_diag, hist, n, st);
-  hipLaunchKernelGGL(k_sel_find_exp, dim3(1), dim3(1024), 0, s, hist, exclude_diag, m, sk, thr,
-                     st);
+        dim3(4 * SPAI_WAVE), 0, s, X, score, exclude_diag, m, hist, thr, n, st);
   if (score)
     hipLaunchKernelGGL((k_sel_collect<T, true>),
                        dim3(std::min(ng, resident_grid(k_sel_collect<T, true>, 0))),
@@ -3035,15 +3192,11 @@ void launch_global_select(Pair<T> X, int exclude_diag, int64_t m, double eta, in
                        dim3(std::min({ng, resident_grid(k_sel_collect<T, false>, 0),
                                       per_cu_grid(12)})),
                        dim3(SPAI_WAVE), 0, s, X, score, exclude_diag, selbuf, n, st);
-  // float candidates widened to double have zero in the low 29 mantissa bits, so the
-  // passes over bits 0..25 would each select bin 0: they stop after bits 26..38
-  const int last = (sizeof(T) == 4 && !score) ? 26 : 0;
-  for (int shift = 39; shift >= last; shift -= 13) {
-    hipLaunchKernelGGL(k_sel_hist_buf, dim3(256), dim3(kSelThreads), 0, s, selbuf, shift, hist,
-                       st);
-    hipLaunchKernelGGL(k_sel_find_buf, dim3(1), dim3(1024), 0, s, hist, shift, last, eta, sk,
+  // a workgroup without keys still draws its ticket, one after the other
+  const int ngp = (int)std::max<int64_t>(16, std::min<int64_t>(256, n / 512));
+  for (int shift = 39; shift >= last; shift -= 13)
+    hipLaunchKernelGGL(k_sel_pass, dim3(ngp), dim3(1024), 0, s, selbuf, shift, last, eta, sk, hist,
                        thr, st);
-  }
 }
 
 // ============================================================================

@@ -5,7 +5,7 @@ import scipy.sparse as sp
 
 from oracle import spai_oracle as O
 from paper_2511_09753_amd import workloads as W
-from tests.helpers import oracle_rule, require_gpu
+from tests.helpers import history_array, oracle_rule, pattern_diff, require_gpu, value_err
 
 pytestmark = pytest.mark.gpu
 
@@ -164,3 +164,44 @@ def test_pcg_narrow_products_against_the_oracle(n, nrhs):
     Xo, ito, _ = O.pcg_block(A, M, B, rtol=1e-8, max_iter=8)
     assert rc in (S.SPAI_OK, S.SPAI_MAXITER) and list(it) == list(ito)
     assert np.max(np.abs(X - Xo)) <= 1e-12 * np.max(np.abs(Xo))
+
+
+# the selection of a global cap takes one workgroup up to 2048 columns; the walks over the
+# candidates take groups of columns, the bounds tiles of 128 columns or more
+@pytest.mark.parametrize("n", [1, 7, 65, 127, 129, 513, 2047, 2048, 2049, 4101])
+@pytest.mark.parametrize("method", ["mr", "cg", "lomr"])
+@pytest.mark.parametrize("mode,value", [("global", 2.0), ("column", 3.0)])
+def test_builds_at_the_edges_of_the_size_rules(n, method, mode, value):
+    S = _spai()
+    A = W.geometric_graph(n, 11 + n)
+    h = S.SPAI(A, method, mode, value, True, max_iter=6)
+    _, hist, _ = h.iterate(6)
+    M = h.get()
+    h.close()
+    ref = O.run(method, A, oracle_rule(A, mode, value, True), 6)
+    want = np.asarray(ref.resid[1:len(hist) + 1])
+    assert len(hist) == ref.iters
+    # a converged residual (n = 1, 7) is rounding: absolute against the first
+    assert np.all(np.abs(np.asarray(hist) - want) <= 1e-10 * want + 1e-13 * ref.resid[0])
+    assert pattern_diff(M, ref.M) == (set(), set())
+    assert value_err(M, ref.M) <= 1e-9
+
+
+@pytest.mark.parametrize("method", ["mr", "cg", "lomr"])
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_floors_from_their_first_size_on(method, precision):
+    """50,653 columns (the floors start at 49,152): none, the default and floors that every
+    iteration fails give the same bits."""
+    S = _spai()
+    A = W.lognormal3d(37, 41)
+    runs = []
+    for frac in (0.0, 0.75, 4.0):
+        h = S.SPAI(A, method, "global", 2.0, True, max_iter=5,
+                   options=S.Options(precision=precision, floor_frac=frac))
+        _, hist, _ = h.iterate(5)
+        runs.append((hist, h.get(), history_array(h)))
+        h.close()
+    for hist, M, rec in runs[1:]:
+        assert np.array_equal(hist, runs[0][0])
+        assert (M != runs[0][1]).nnz == 0
+        assert np.array_equal(rec, runs[0][2])

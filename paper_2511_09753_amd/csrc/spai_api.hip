@@ -308,7 +308,7 @@ struct Engine : EngineBase {
   // (and Zn, Pi-weighted) and copied over R; Pi-weighted, R holds Z and Rraw holds R
   Cols<T> Rn{}, Zn{}, Rraw{};
   bool implicit = false;
-  int64_t *ub = nullptr, *off = nullptr, *total = nullptr, *scantmp = nullptr;
+  OffBuf ob;
   double *colpart = nullptr, *colnorm = nullptr, *red = nullptr, *red_rr = nullptr;
   double *colrz = nullptr, *red_rz = nullptr;   // (R, Z)_F per column / matrix (weighted)
   double *blockpart = nullptr, *cvec = nullptr, *hist = nullptr;
@@ -573,8 +573,8 @@ struct Engine : EngineBase {
     M.cur = &st->curM;
     P.cur = &st->curP;
     PT.cur = &st->curP;
-    if ((rc = dalloc(&ub, n)) || (rc = dalloc(&off, n)) || (rc = dalloc(&total, 1)) ||
-        (rc = dalloc(&scantmp, scan_tmp_elems(n))))
+    if ((rc = dalloc(&ob.loc, n)) || (rc = dalloc(&ob.tile, std::min<int64_t>(n, kOffTiles))) ||
+        (rc = dalloc(&ob.total, 1)))
       return rc;
     if ((rc = dalloc(&colpart, n * kND)) || (rc = dalloc(&colnorm, n)) ||
         (rc = dalloc(&red, (int64_t)nseg * kND)) || (rc = dalloc(&red_rr, nseg)) ||
@@ -957,8 +957,7 @@ struct Engine : EngineBase {
     const bool ell = A.eshift >= 0;
     constexpr size_t kMaxLds = 64 * 1024;
     // residual: R = I - A M on the current M (rewrites R with the same values)
-    launch_bound_resid<T>(A, M, ub, n, st, s);
-    launch_scan(ub, off, total, n, scantmp, s);
+    Offs off = launch_bound_resid<T>(A, M, ob, big[0], big[1], n, st, s);
     Tile bestR = tRs;
     double tR = 1e300, curR = 1e300;
     for (int L : {64, 128, 256})
@@ -967,7 +966,8 @@ struct Engine : EngineBase {
         if (H < 512 && !ell) continue;
         if (resid_tile_bytes(t, ell) > kMaxLds) continue;
         const double ms = timed([&] {
-          launch_resid<T>(A, M, R, off, total, colnorm, opts.jacobi, colrz, big[0], st, t, tRl,
+          launch_zero_counts(big[0], s);
+          launch_resid<T>(A, M, R, off, ob.total, colnorm, opts.jacobi, colrz, big[0], st, t, tRl,
                           tRh, s);
         });
         if (same_tile(t, tRs)) curR = ms;
@@ -986,6 +986,7 @@ struct Engine : EngineBase {
           if (waves != 1 && (H < 512 || L < 128)) continue;
           if (dots_tile_bytes(t, ell) > kMaxLds) continue;
           const double ms = timed([&] {
+            launch_zero_counts(big[1], s);
             launch_dots<T>(A, R, P, useR, useP, opts.jacobi, colpart, big[1], st, t, tDl, tDh, s);
           });
           if (same_tile(t, tDs)) curD = ms;
@@ -994,8 +995,7 @@ struct Engine : EngineBase {
     // update: the candidates of M (and P) written to the next buffers
     const UpdMode md = method == SPAI_MR ? mode(1, 1, 0, 0)
                        : method == SPAI_CG ? mode(1, 2, 0, 0) : mode(1, 1, 2, 1);
-    launch_bound_update<T>(A, M, R, P, PT, md, ub, n, st, s);
-    launch_scan(ub, off, total, n, scantmp, s);
+    off = launch_bound_update<T>(A, M, R, P, PT, md, ob, big[2], n, st, s);
     Tile bestU = tUs;
     double tU = 1e300, curU = 1e300;
     for (int L : {128, 256, 384, 512})
@@ -1006,7 +1006,8 @@ struct Engine : EngineBase {
           if (waves == 1 ? (A.eshift < 0 || L != 128) : (H < 512 || L < 256)) continue;
           if (update_tile_bytes(t) > kMaxLds) continue;
           const double ms = timed([&] {
-            launch_update<T>(A, M, R, P, PT, md, off, total, kcol, tM, tP, big[2], seg, st, t,
+            launch_zero_counts(big[2], s);
+            launch_update<T>(A, M, R, P, PT, md, off, ob.total, kcol, tM, tP, big[2], seg, st, t,
                              tUl, tUh, s);
           });
           if (same_tile(t, tUs)) curU = ms;
@@ -1110,23 +1111,26 @@ struct Engine : EngineBase {
     return md;
   }
 
+  void post(int setup) {
+    launch_post(method, seg, colnorm, opts.jacobi ? colrz : nullptr, n,
+                nseg > 1 ? seg_beg : nullptr, red_rr, red_rz, blockpart, tol, hist, hist_cap,
+                setup, st, s);
+  }
+
   void resid_step(int setup) {
     tb(SPAI_PH_BOUNDS);
-    launch_bound_resid<T>(A, M, ub, n, st, s);
-    launch_scan(ub, off, total, n, scantmp, s);
+    const Offs off = launch_bound_resid<T>(A, M, ob, big[0], big[1], n, st, s);
     te();
     tb(SPAI_PH_RESID);
-    if (implicit && opts.jacobi)         // R_0 itself, for the implicit updates
-      launch_resid<T>(A, M, Rraw, off, total, colnorm, 0, colrz, big[0], st, tRs, tRl, tRh, s);
-    launch_resid<T>(A, M, R, off, total, colnorm, opts.jacobi, colrz, big[0], st, tRs, tRl, tRh,
+    if (implicit && opts.jacobi) {       // R_0 itself, for the implicit updates
+      launch_resid<T>(A, M, Rraw, off, ob.total, colnorm, 0, colrz, big[0], st, tRs, tRl, tRh, s);
+      launch_zero_counts(big[0], s);
+    }
+    launch_resid<T>(A, M, R, off, ob.total, colnorm, opts.jacobi, colrz, big[0], st, tRs, tRl, tRh,
                     s);
     te();
     tb(SPAI_PH_SCALAR);
-    launch_reduce(colnorm, 1, n, seg, nseg > 1 ? seg_beg : nullptr, red_rr, blockpart, s);
-    if (opts.jacobi)
-      launch_reduce(colrz, 1, n, seg, nseg > 1 ? seg_beg : nullptr, red_rz, blockpart, s);
-    launch_scal_post(method, seg, red_rr, opts.jacobi ? red_rz : nullptr, tol, hist, hist_cap,
-                     setup, st, s);
+    post(setup);
     te();
   }
 
@@ -1134,25 +1138,20 @@ struct Engine : EngineBase {
   void implicit_step(int xsrc, int cidx) {
     Cols<T> Rin = opts.jacobi ? Rraw : R;
     tb(SPAI_PH_BOUNDS);
-    launch_bound_impl<T>(A, Rin, R, P, xsrc, ub, n, st, s);
-    launch_scan(ub, off, total, n, scantmp, s);
+    const Offs off = launch_bound_impl<T>(A, Rin, R, P, xsrc, ob, big[0], big[1], n, st, s);
     te();
     tb(SPAI_PH_RESID);
-    launch_resid_impl<T>(A, Rin, R, P, xsrc, cidx, seg, off, total, Rn, Zn, opts.jacobi, colnorm,
+    launch_resid_impl<T>(A, Rin, R, P, xsrc, cidx, seg, off, ob.total, Rn, Zn, opts.jacobi, colnorm,
                          colrz, big[0], st, tDs, tDl, tDh, s);
     if (opts.jacobi) {
-      launch_copy_cols<T>(Rn, Rraw, n, total, st, s);
-      launch_copy_cols<T>(Zn, R, n, total, st, s);
+      launch_copy_cols<T>(Rn, Rraw, n, ob.total, st, s);
+      launch_copy_cols<T>(Zn, R, n, ob.total, st, s);
     } else {
-      launch_copy_cols<T>(Rn, R, n, total, st, s);
+      launch_copy_cols<T>(Rn, R, n, ob.total, st, s);
     }
     te();
     tb(SPAI_PH_SCALAR);
-    launch_reduce(colnorm, 1, n, seg, nseg > 1 ? seg_beg : nullptr, red_rr, blockpart, s);
-    if (opts.jacobi)
-      launch_reduce(colrz, 1, n, seg, nseg > 1 ? seg_beg : nullptr, red_rz, blockpart, s);
-    launch_scal_post(method, seg, red_rr, opts.jacobi ? red_rz : nullptr, tol, hist, hist_cap, 0,
-                     st, s);
+    post(0);
     te();
   }
 
@@ -1161,18 +1160,16 @@ struct Engine : EngineBase {
     launch_dots<T>(A, R, P, useR, useP, opts.jacobi, colpart, big[1], st, tDs, tDl, tDh, s);
     te();
     tb(SPAI_PH_SCALAR);
-    launch_reduce(colpart, kND, n, seg, nseg > 1 ? seg_beg : nullptr, red, blockpart, s);
-    launch_scal_step(method, seg, red, st, s);
+    launch_step(method, seg, colpart, n, nseg > 1 ? seg_beg : nullptr, red, blockpart, st, s);
     te();
   }
 
   void update_step(UpdMode md) {
     tb(SPAI_PH_BOUNDS);
-    launch_bound_update<T>(A, M, R, P, PT, md, ub, n, st, s);
-    launch_scan(ub, off, total, n, scantmp, s);
+    const Offs off = launch_bound_update<T>(A, M, R, P, PT, md, ob, big[2], n, st, s);
     te();
     tb(SPAI_PH_UPDATE);
-    launch_update<T>(A, M, R, P, PT, md, off, total, kcol, tM, tP, big[2], seg, st, tUs, tUl, tUh,
+    launch_update<T>(A, M, R, P, PT, md, off, ob.total, kcol, tM, tP, big[2], seg, st, tUs, tUl, tUh,
                      s);
     te();
     const double* keyM = (global && md.doM && score) ? sigma : nullptr;
@@ -1192,8 +1189,8 @@ struct Engine : EngineBase {
         launch_global_select<T>(M, 1, m_global, opts.tie_eta, 0, selhist, selbuf, n, st, s, keyM);
       if (md.doP) launch_global_select<T>(P, 0, m_global, opts.tie_eta, 1, selhist, selbuf, n, st, s);
       if (floors) {
-        launch_redo_begin(st, s);
-        launch_update<T>(A, M, R, P, PT, md, off, total, kcol, tM, tP, big[2], seg, st, tUs, tUl,
+        launch_redo_begin(st, big[2], s);
+        launch_update<T>(A, M, R, P, PT, md, off, ob.total, kcol, tM, tP, big[2], seg, st, tUs, tUl,
                          tUh, s, true);
         if (md.doM)
           launch_global_select<T>(M, 1, m_global, opts.tie_eta, 0, selhist, selbuf, n, st, s);

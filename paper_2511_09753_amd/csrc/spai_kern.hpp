@@ -59,6 +59,8 @@ struct DevState {
   int rec_i, rec_cap;
   int rec_next;                   // the next iteration's record
   int sel_ticket;                 // workgroups done with a selection pass (0 between launches)
+  int off_ticket;                 // ... with a bounds pass
+  int red_ticket;                 // ... with a reduction
   // speculative floor of the global cap (magnitude keys, one matrix): the lean update
   // writes the off-diagonal candidates of M (all of P, P^T) only where |x| >= floor and
   // counts the others in below; the selection sets redo when its cut does not clear
@@ -98,6 +100,19 @@ struct BigList {
   int grid2 = 64;                  // workgroups of the huge-tile pass (scratch slices)
 };
 
+// where the columns of an output start: column j at loc[j] + tile[j >> shift]
+struct Offs {
+  const int64_t* loc;
+  const int64_t* tile;
+  int shift;
+  __device__ __forceinline__ int64_t operator[](int64_t j) const { return loc[j] + tile[j >> shift]; }
+  int64_t tiles(int64_t n) const { return (n + ((int64_t)1 << shift) - 1) >> shift; }
+};
+constexpr int kOffTiles = 512;
+struct OffBuf {                    // their storage: loc[n], tile[min(n, kOffTiles)], total[1]
+  int64_t *loc = nullptr, *tile = nullptr, *total = nullptr;
+};
+
 struct Tile {      // per-column tile
   int L, H;        // list entries, hash slots
   int DG = 0;      // update: neighbour columns (0: default)
@@ -121,9 +136,9 @@ struct UpdMode {
 };
 
 // ---------------- launchers (all enqueue on `s`) -----------------------------
-int64_t scan_tmp_elems(int64_t n);
-void launch_scan(const int64_t* in, int64_t* out, int64_t* total, int64_t n, int64_t* tmp,
-                 hipStream_t s);
+// the deferred-column counters of one tiered launch set to zero; launch_bound_* does it for
+// the passes that read its offsets (z0; z1: the dots', which the residual's bounds precede)
+void launch_zero_counts(const BigList& big, hipStream_t s);
 
 // per-segment sums of colpart[j * nd + d] in a fixed order -> red[seg * nd + d]
 void launch_reduce(const double* colpart, int nd, int64_t n, const Seg& seg,
@@ -140,10 +155,10 @@ template <typename T>
 void launch_zero_cols(int64_t n, Cols<T> X, hipStream_t s);
 
 template <typename T>
-void launch_bound_resid(const Csr& A, Pair<T> M, int64_t* ub, int64_t n, const DevState* st,
-                        hipStream_t s);
+Offs launch_bound_resid(const Csr& A, Pair<T> M, const OffBuf& o, const BigList& z0,
+                        const BigList& z1, int64_t n, DevState* st, hipStream_t s);
 template <typename T>
-void launch_resid(const Csr& A, Pair<T> M, Cols<T> R, const int64_t* off, const int64_t* total,
+void launch_resid(const Csr& A, Pair<T> M, Cols<T> R, Offs off, const int64_t* total,
                   double* colnorm, int weighted, double* colrz, BigList big, DevState* st,
                   Tile small, Tile large, Tile huge, hipStream_t s);
 
@@ -155,11 +170,12 @@ void launch_dots(const Csr& A, Cols<T> R, Pair<T> P, int useR, int useP, int wei
 // implicit residual R_{i+1} = R_i - c A X (no dropping): X is Xr (xsrc 0) or P.now()
 // (xsrc 1), c the segment's coef[cidx] (cidx -1: c = 1); Zout gets Pi R_{i+1} (weighted)
 template <typename T>
-void launch_bound_impl(const Csr& A, Cols<T> Rin, Cols<T> Xr, Pair<T> P, int xsrc, int64_t* ub,
-                       int64_t n, const DevState* st, hipStream_t s);
+Offs launch_bound_impl(const Csr& A, Cols<T> Rin, Cols<T> Xr, Pair<T> P, int xsrc,
+                       const OffBuf& o, const BigList& z0, const BigList& z1, int64_t n,
+                       DevState* st, hipStream_t s);
 template <typename T>
 void launch_resid_impl(const Csr& A, Cols<T> Rin, Cols<T> Xr, Pair<T> P, int xsrc, int cidx,
-                       const Seg& seg, const int64_t* off, const int64_t* total, Cols<T> Rout,
+                       const Seg& seg, Offs off, const int64_t* total, Cols<T> Rout,
                        Cols<T> Zout, int weighted, double* colnorm, double* colrz, BigList big,
                        DevState* st, Tile small, Tile large, Tile huge, hipStream_t s);
 template <typename T>
@@ -167,11 +183,12 @@ void launch_copy_cols(Cols<T> src, Cols<T> dst, int64_t n, const int64_t* total,
                       const DevState* st, hipStream_t s);
 
 template <typename T>
-void launch_bound_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, UpdMode md,
-                         int64_t* ub, int64_t n, const DevState* st, hipStream_t s);
+Offs launch_bound_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, UpdMode md,
+                         const OffBuf& o, const BigList& z0, int64_t n, DevState* st,
+                         hipStream_t s);
 template <typename T>
 void launch_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, UpdMode md,
-                   const int64_t* off, const int64_t* total, const int32_t* kcol, double* tM,
+                   Offs off, const int64_t* total, const int32_t* kcol, double* tM,
                    double* tP, BigList big, const Seg& seg, DevState* st, Tile small,
                    Tile large, Tile huge, hipStream_t s, bool second = false);
 // bytes of one workgroup's working set for a tile (the huge tier's scratch slice)
@@ -201,18 +218,22 @@ void launch_compact(Pair<T> X, int kind, int colcap, int sym, int global, const 
                     double eta, int64_t n, DevState* st, hipStream_t s,
                     const double* score = nullptr);
 
-void launch_scal_step(int method, const Seg& seg, const double* red, DevState* st,
-                      hipStream_t s);
-void launch_scal_post(int method, const Seg& seg, const double* red, const double* red_rz,
-                      double tol, double* hist, int hist_cap, int setup, DevState* st,
-                      hipStream_t s);
+// the sums of colpart over the columns (fixed order) and the step sizes from them
+void launch_step(int method, const Seg& seg, const double* colpart, int64_t n,
+                 const int64_t* seg_beg, double* red, double* blockpart, DevState* st,
+                 hipStream_t s);
+// the sums of colnorm (and, Pi-weighted, colrz) and the end of the iteration: record
+// ||R||, test the stopping rule, CG's beta
+void launch_post(int method, const Seg& seg, const double* colnorm, const double* colrz, int64_t n,
+                 const int64_t* seg_beg, double* red, double* red_rz, double* blockpart,
+                 double tol, double* hist, int hist_cap, int setup, DevState* st, hipStream_t s);
 extern int g_grid_cols;   // persistent grid of the per-column kernels (multiple of 8)
 // zero the drop record; the next iteration's record is `next`
 void launch_rec_clear(DevState* st, int next, hipStream_t s);
 // the second, floor-free pass of the update and the selection runs only where the first
 // pass's floors were too high: redo_begin masks the iteration unless st->redo (and clears
 // the floors), redo_end restores it; drop_finish sets the next iteration's floors
-void launch_redo_begin(DevState* st, hipStream_t s);
+void launch_redo_begin(DevState* st, const BigList& big, hipStream_t s);
 void launch_redo_end(DevState* st, hipStream_t s);
 // the new M (doM) and P (doP) become current; with floors, the next iteration's floors
 // are set from this iteration's cuts

@@ -369,6 +369,9 @@ __global__ void k_zero_counts(int* a, int* b) {
   *a = 0;
   *b = 0;
 }
+void launch_zero_counts(const BigList& big, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero_counts, dim3(1), dim3(1), 0, s, big.count, big.count2);
+}
 
 // clear the drop record (a kernel, not a memset node: the iteration may be captured)
 __global__ void k_rec_clear(DevState* st, int next) {
@@ -389,7 +392,9 @@ void launch_rec_clear(DevState* st, int next, hipStream_t s) {
 }
 
 // the floor-free second pass: masked unless the first pass's floors were too high
-__global__ void k_redo_begin(DevState* st) {
+__global__ void k_redo_begin(DevState* st, int* count, int* count2) {
+  *count = 0;                          // the update's deferred columns
+  *count2 = 0;
   st->saved_active = st->iter_active;
   st->iter_active = st->iter_active && st->redo;
   if (st->redo) {
@@ -410,100 +415,162 @@ __device__ void floor_next_body(DevState* st, int doM, int doP, double frac) {
   }
   st->redo = 0;
 }
-void launch_redo_begin(DevState* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_redo_begin, dim3(1), dim3(1), 0, s, st);
+void launch_redo_begin(DevState* st, const BigList& big, hipStream_t s) {
+  hipLaunchKernelGGL(k_redo_begin, dim3(1), dim3(1), 0, s, st, big.count, big.count2);
 }
 void launch_redo_end(DevState* st, hipStream_t s) {
   hipLaunchKernelGGL(k_redo_end, dim3(1), dim3(1), 0, s, st);
 }
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kScanThreads * kScanItems;
-
-__device__ inline int64_t block_excl_scan_i64(int64_t v, int64_t* sh, int64_t* total) {
-  const int t = threadIdx.x;
-  sh[t] = v;
+// true in every thread of the last workgroup of a launch to come here, all of whose atomics
+// and agent-scope stores have then arrived; the histograms are read by it through agent-scope
+// loads, and it sets the ticket back
+__device__ __forceinline__ bool last_block(int* ticket) {
+  __shared__ int last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  for (int d = 1; d < (int)blockDim.x; d <<= 1) {
-    int64_t add = (t >= d) ? sh[t - d] : 0;
-    __syncthreads();
-    sh[t] += add;
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           (int)gridDim.x - 1;
+    if (last) *ticket = 0;
   }
-  int64_t incl = sh[t];
-  *total = sh[blockDim.x - 1];
   __syncthreads();
-  return incl - v;
+  return last != 0;
+}
+__device__ __forceinline__ unsigned long long agent_count(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const int64_t* in, int64_t* out,
-                                                             int64_t n, int64_t* tile_sums) {
-  __shared__ int64_t sh[kScanThreads];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  int64_t loc[kScanItems];
-  int64_t run = 0;
+// ---- column offsets -----------------------------------------------------------------
+// A pass's output column j starts at the sum of the bounds of the columns before it.  One
+// launch computes bounds and offsets: workgroup b takes columns b 2^shift .. and writes
+// their offsets within the tile, the last workgroup sums the tiles (at most kOffTiles, so
+// their tickets, drawn one after the other at some 10 ns, take a few us), and the readers
+// add the two (Offs).  Three launches (tile scan, sums, addition) behind a fourth for the
+// bounds took 22 us at 36,000 columns.
+
+struct OffZero {                 // deferred-column counters cleared on the way
+  int* c[4];
+};
+
+static Offs make_offs(const OffBuf& o, int64_t n) {
+  int sh = 7;                                       // a workgroup takes 128 columns at once
+  while (((n + ((int64_t)1 << sh) - 1) >> sh) > kOffTiles) ++sh;
+  return Offs{o.loc, o.tile, sh};
+}
+
+// exclusive prefix over the workgroup's 128 columns of v, column c's in lanes 8 c .. 8 c + 7;
+// tot: their sum.  w: 16 words, used by one call between two barriers.
+__device__ __forceinline__ int64_t cols_excl_scan(int64_t v, int64_t* w, int64_t& tot) {
+  const int lane = lane_id(), wv = threadIdx.x >> 6;
+  int64_t inc = v;
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    const int64_t g = base + i;
-    const int64_t v = g < n ? in[g] : 0;
-    loc[i] = run;
-    run += v;
+  for (int d = 8; d < 64; d <<= 1) {
+    const int64_t o = __shfl_up(inc, d, SPAI_WAVE);
+    if (lane >= d) inc += o;
   }
-  int64_t tot;
-  const int64_t off = block_excl_scan_i64(run, sh, &tot);
+  if (lane == 63) w[wv] = inc;
+  __syncthreads();
+  int64_t before = 0;
+  tot = 0;
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    const int64_t g = base + i;
-    if (g < n) out[g] = off + loc[i];
+  for (int i = 0; i < 16; ++i) {
+    const int64_t x = w[i];
+    before += i < wv ? x : 0;
+    tot += x;
   }
-  if (threadIdx.x == 0) tile_sums[blockIdx.x] = tot;
+  return before + inc - v;
 }
 
-__global__ __launch_bounds__(1024) void k_scan_sums(int64_t* tile_sums, int64_t ntiles,
-                                                    int64_t* total) {
-  __shared__ int64_t sh[1024];
-  const int per = (int)((ntiles + 1023) / 1024);
-  const int64_t b = (int64_t)threadIdx.x * per;
+// bound(j, g): the bound of column j on all eight lanes g that share it (every lane of the
+// wave calls it, j may be >= n: then 0)
+template <typename F>
+__device__ __forceinline__ void offsets_of(F bound, int64_t n, int shift, int64_t* loc,
+                                           int64_t* tile, int64_t* total, DevState* st) {
+  __shared__ int64_t w[2][16];
+  const int64_t j0 = (int64_t)blockIdx.x << shift;
+  const int64_t j1 = min(n, j0 + ((int64_t)1 << shift));
+  const int g = threadIdx.x & 7;
   int64_t run = 0;
-  for (int i = 0; i < per; ++i)
-    if (b + i < ntiles) run += tile_sums[b + i];
-  int64_t tot;
-  const int64_t off = block_excl_scan_i64(run, sh, &tot);
-  int64_t acc = off;
-  for (int i = 0; i < per; ++i)
-    if (b + i < ntiles) {
-      const int64_t v = tile_sums[b + i];
-      tile_sums[b + i] = acc;
-      acc += v;
-    }
-  if (threadIdx.x == 0 && total) *total = tot;
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_scan_add(int64_t* out, int64_t n,
-                                                           const int64_t* tile_off) {
-  const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  const int64_t add = tile_off[blockIdx.x];
-  for (int i = threadIdx.x; i < kScanTile; i += kScanThreads) {
-    const int64_t g = base + i;
-    if (g < n) out[g] += add;
+  int par = 0;
+  for (int64_t b = j0; b < j1; b += 128, par ^= 1) {
+    const int64_t j = b + (threadIdx.x >> 3);
+    const int64_t v = bound(j, g);
+    int64_t tot;
+    const int64_t ex = cols_excl_scan(v, w[par], tot);
+    if (g == 0 && j < j1) loc[j] = run + ex;
+    run += tot;
   }
+  if (threadIdx.x == 0)
+    __hip_atomic_store(&tile[blockIdx.x], run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (!last_block(&st->off_ticket)) return;
+  int64_t before = 0;
+  for (int t0 = 0; t0 < (int)gridDim.x; t0 += 128, par ^= 1) {
+    const int t = t0 + (threadIdx.x >> 3);
+    const int64_t v =
+        t < (int)gridDim.x
+            ? (int64_t)agent_count((const unsigned long long*)&tile[t])
+            : 0;
+    int64_t tot;
+    const int64_t ex = cols_excl_scan(v, w[par], tot);
+    if (g == 0 && t < (int)gridDim.x) tile[t] = before + ex;
+    before += tot;
+  }
+  if (threadIdx.x == 0) *total = before;
 }
 
-int64_t scan_tmp_elems(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
-
-void launch_scan(const int64_t* in, int64_t* out, int64_t* total, int64_t n, int64_t* tmp,
-                 hipStream_t s) {
-  const int64_t ntiles = (n + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, out, n,
-                     tmp);
-  hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, tmp, ntiles, total);
-  hipLaunchKernelGGL(k_scan_add, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, out, n, tmp);
+__device__ __forceinline__ void off_zero(const OffZero& z) {
+  if (blockIdx.x == 0 && threadIdx.x < 4 && z.c[threadIdx.x]) *z.c[threadIdx.x] = 0;
 }
 
 // ---- fixed-order reduction of per-column partials ---------------------------
 constexpr int kRedBlocks = 512;
 constexpr int kRedThreads = 256;
+
+// The sums of a handle of one matrix in one launch: the columns in the chunks, and within a
+// chunk in the order, of k_reduce_chunks and k_reduce_final (the results are theirs), a wave
+// per chunk -- lane l holds the partial sums of that kernel's threads l, l + 64, l + 128 and
+// l + 192 -- and the last workgroup adds the chunks and takes the scalar step.  Four launches
+// less in an iteration (4 to 6 us each; two more for the second norm of the weighted forms).
+// wave w of the launch: chunks [0, nb) of `chunk` columns -> part[w * nd + d]
+template <int ND>
+__device__ __forceinline__ void chunk_sums(const double* colpart, int64_t n, int64_t chunk,
+                                           double* part) {
+  const int lane = lane_id();
+  const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t lo = w * chunk, hi = min(n, lo + chunk);
+  if (lo >= hi) return;
+  double s[4][ND];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int d = 0; d < ND; ++d) s[q][d] = 0.0;
+  constexpr int U = ND > 1 ? 1 : 2;                  // 256-column rounds in flight
+  for (int64_t j0 = lo; j0 < hi; j0 += 256 * U) {
+    double v[U][4][ND];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t j = j0 + u * 256 + q * 64 + lane;
+#pragma unroll
+        for (int d = 0; d < ND; ++d) v[u][q][d] = j < hi ? colpart[j * ND + d] : 0.0;
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (j0 + u * 256 + q * 64 + lane < hi) {
+#pragma unroll
+          for (int d = 0; d < ND; ++d) s[q][d] += v[u][q][d];
+        }
+  }
+#pragma unroll
+  for (int d = 0; d < ND; ++d) {
+    const double r = wave_sum((s[0][d] + s[2][d]) + (s[1][d] + s[3][d]));
+    if (lane == 0) agent_store(&part[w * ND + d], r);
+  }
+}
 
 // one block per chunk of columns (single segment) or per segment (batched)
 __global__ __launch_bounds__(kRedThreads) void k_reduce_chunks(const double* colpart, int nd,
@@ -692,47 +759,61 @@ void launch_zero_cols(int64_t n, Cols<T> X, hipStream_t s) {
 // upper bound of nnz(r_j): 1 + sum_{l in supp(m_j)} deg(l).  Eight lanes per column read
 // its entries together (two per lane in flight) and add their degrees with shuffles: an
 // integer sum, the same in any order.
-constexpr int kBoundLanes = 8;   // the three exchanges below
-template <typename T>
-__global__ __launch_bounds__(256) void k_bound_resid(Csr A, Pair<T> Mp, int64_t* ub, int64_t n,
-                                                     const DevState* st) {
-  if (!st->any_active) return;
-  const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kBoundLanes;
-  const int g = threadIdx.x % kBoundLanes;
-  const Cols<T> M = Mp.now();
-  long long s = 0;
-  if (j < n) {
-    const int64_t b = M.beg[j];
-    const int lm = M.len[j];
-    int e = g;
-    for (; e + kBoundLanes < lm; e += 2 * kBoundLanes) {
-      const int l0 = M.idx[b + e], l1 = M.idx[b + e + kBoundLanes];
-      s += (A.rowptr[l0 + 1] - A.rowptr[l0]) + (A.rowptr[l1 + 1] - A.rowptr[l1]);
-    }
-    if (e < lm) {
-      const int l = M.idx[b + e];
-      s += A.rowptr[l + 1] - A.rowptr[l];
-    }
-  }
+__device__ __forceinline__ int64_t eight_sum(long long s) {
   s += lane_xor<1>(s);                               // all lanes
   s += lane_xor<2>(s);
   s += lane_xor<4>(s);
-  if (j < n && g == 0) ub[j] = 1 + s;
+  return s;
+}
+
+// sum of the degrees of the rows of X's column j, this lane's share of eight
+template <typename T>
+__device__ __forceinline__ long long degrees_of(const Csr& A, const Cols<T>& X, int64_t j, int g) {
+  long long s = 0;
+  const int64_t b = X.beg[j];
+  const int lm = X.len[j];
+  int e = g;
+  for (; e + 8 < lm; e += 16) {
+    const int l0 = X.idx[b + e], l1 = X.idx[b + e + 8];
+    s += (A.rowptr[l0 + 1] - A.rowptr[l0]) + (A.rowptr[l1 + 1] - A.rowptr[l1]);
+  }
+  if (e < lm) {
+    const int l = X.idx[b + e];
+    s += A.rowptr[l + 1] - A.rowptr[l];
+  }
+  return s;
 }
 
 template <typename T>
-void launch_bound_resid(const Csr& A, Pair<T> M, int64_t* ub, int64_t n, const DevState* st,
-                        hipStream_t s) {
-  const int64_t threads = n * kBoundLanes;
-  hipLaunchKernelGGL(k_bound_resid<T>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, A,
-                     M, ub, n, st);
+__global__ __launch_bounds__(1024) void k_bound_resid(Csr A, Pair<T> Mp, int64_t n, int shift,
+                                                      int64_t* loc, int64_t* tile,
+                                                      int64_t* total, OffZero z, DevState* st) {
+  off_zero(z);
+  if (!st->any_active) return;
+  const Cols<T> M = Mp.now();
+  offsets_of(
+      [&](int64_t j, int g) -> int64_t {
+        const int64_t s = eight_sum(j < n ? degrees_of(A, M, j, g) : 0);
+        return j < n ? s + 1 : 0;
+      },
+      n, shift, loc, tile, total, st);
+}
+
+template <typename T>
+Offs launch_bound_resid(const Csr& A, Pair<T> M, const OffBuf& o, const BigList& z0,
+                        const BigList& z1, int64_t n, DevState* st, hipStream_t s) {
+  const Offs f = make_offs(o, n);
+  hipLaunchKernelGGL(k_bound_resid<T>, dim3((unsigned)f.tiles(n)), dim3(1024), 0, s, A, M, n,
+                     f.shift, o.loc, o.tile, o.total,
+                     OffZero{{z0.count, z0.count2, z1.count, z1.count2}}, st);
+  return f;
 }
 
 // five waves per SIMD: measured faster than the compiler's own choice (four) for this
 // kernel, with no spills
 template <typename T, bool GS>
 __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5, 5))) void k_resid(Csr A, Pair<T> Mp, Cols<T> R,
-                                                     const int64_t* off, const int64_t* total,
+                                                     Offs off, const int64_t* total,
                                                      double* colnorm, int weighted, double* colrz,
                                                      BigList big, DevState* st, int tier, int L,
                                                      int H) {
@@ -864,7 +945,7 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5, 5)
 // carries no diagonal tracking.
 template <typename T, bool WT>
 __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 5))) void k_resid_lean(Csr A, Pair<T> Mp, Cols<T> R,
-                                                          const int64_t* off,
+                                                          Offs off,
                                                           const int64_t* total, double* colnorm,
                                                           int weighted, double* colrz,
                                                           BigList big, DevState* st, int L,
@@ -1103,11 +1184,10 @@ static int large_grid(K kernel, size_t lds) {
 }
 
 template <typename T>
-void launch_resid(const Csr& A, Pair<T> M, Cols<T> R, const int64_t* off, const int64_t* total,
+void launch_resid(const Csr& A, Pair<T> M, Cols<T> R, Offs off, const int64_t* total,
                   double* colnorm, int weighted, double* colrz, BigList big, DevState* st,
                   Tile small, Tile large, Tile huge, hipStream_t s) {
   const bool ell = A.eshift >= 0;
-  hipLaunchKernelGGL(k_zero_counts, dim3(1), dim3(1), 0, s, big.count, big.count2);
   if (ell) {
     auto go = [&](auto KR) {
       hipLaunchKernelGGL((KR),
@@ -1490,7 +1570,6 @@ void launch_dots(const Csr& A, Cols<T> R, Pair<T> P, int useR, int useP, int wei
                  double* colpart, BigList big, DevState* st, Tile small, Tile large, Tile huge,
                  hipStream_t s) {
   const bool ell = A.eshift >= 0;
-  hipLaunchKernelGGL(k_zero_counts, dim3(1), dim3(1), 0, s, big.count, big.count2);
   if (small.waves == 1 && ell) {
     auto go = [&](auto KD) {
       hipLaunchKernelGGL((KD), dim3(resident_grid(KD, dots_lean_lds<T>(small))),
@@ -1535,33 +1614,36 @@ struct ImplSrc {
 };
 
 template <typename T>
-__global__ void k_bound_impl(Csr A, Cols<T> Rin, Cols<T> Xr, Pair<T> Pp, ImplSrc src, int64_t* ub,
-                             int64_t n, const DevState* st) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
+__global__ __launch_bounds__(1024) void k_bound_impl(Csr A, Cols<T> Rin, Cols<T> Xr, Pair<T> Pp,
+                                                     ImplSrc src, int64_t n, int shift,
+                                                     int64_t* loc, int64_t* tile, int64_t* total,
+                                                     OffZero z, DevState* st) {
+  off_zero(z);
   if (!st->any_active || !st->iter_active) return;
   const Cols<T> X = src.xsrc ? Pp.now() : Xr;
-  const int64_t b = X.beg[j];
-  const int lx = X.len[j];
-  int64_t s = Rin.len[j];
-  for (int e = 0; e < lx; ++e) {
-    const int l = X.idx[b + e];
-    s += A.rowptr[l + 1] - A.rowptr[l];
-  }
-  ub[j] = s;
+  offsets_of(
+      [&](int64_t j, int g) -> int64_t {
+        const int64_t s = eight_sum(j < n ? degrees_of(A, X, j, g) : 0);
+        return j < n ? s + Rin.len[j] : 0;
+      },
+      n, shift, loc, tile, total, st);
 }
 
 template <typename T>
-void launch_bound_impl(const Csr& A, Cols<T> Rin, Cols<T> Xr, Pair<T> P, int xsrc, int64_t* ub,
-                       int64_t n, const DevState* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_bound_impl<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, A, Rin,
-                     Xr, P, ImplSrc{xsrc, 0}, ub, n, st);
+Offs launch_bound_impl(const Csr& A, Cols<T> Rin, Cols<T> Xr, Pair<T> P, int xsrc,
+                       const OffBuf& o, const BigList& z0, const BigList& z1, int64_t n,
+                       DevState* st, hipStream_t s) {
+  const Offs f = make_offs(o, n);
+  hipLaunchKernelGGL(k_bound_impl<T>, dim3((unsigned)f.tiles(n)), dim3(1024), 0, s, A, Rin, Xr, P,
+                     ImplSrc{xsrc, 0}, n, f.shift, o.loc, o.tile, o.total,
+                     OffZero{{z0.count, z0.count2, z1.count, z1.count2}}, st);
+  return f;
 }
 
 template <typename T, bool GS>
 __global__ __launch_bounds__(SPAI_WAVE) void k_resid_impl(Csr A, Cols<T> Rin, Cols<T> Xr,
                                                           Pair<T> Pp, ImplSrc src, Seg seg,
-                                                          const int64_t* off,
+                                                          Offs off,
                                                           const int64_t* total, Cols<T> Rout,
                                                           Cols<T> Zout, int weighted,
                                                           double* colnorm, double* colrz,
@@ -1708,12 +1790,11 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_resid_impl(Csr A, Cols<T> Rin, Co
 
 template <typename T>
 void launch_resid_impl(const Csr& A, Cols<T> Rin, Cols<T> Xr, Pair<T> P, int xsrc, int cidx,
-                       const Seg& seg, const int64_t* off, const int64_t* total, Cols<T> Rout,
+                       const Seg& seg, Offs off, const int64_t* total, Cols<T> Rout,
                        Cols<T> Zout, int weighted, double* colnorm, double* colrz, BigList big,
                        DevState* st, Tile small, Tile large, Tile huge, hipStream_t s) {
   const bool ell = A.eshift >= 0;
   const ImplSrc src{xsrc, cidx};
-  hipLaunchKernelGGL(k_zero_counts, dim3(1), dim3(1), 0, s, big.count, big.count2);
   hipLaunchKernelGGL((k_resid_impl<T, false>),
                      dim3(resident_grid(k_resid_impl<T, false>, dots_lds(small, ell))),
                      dim3(SPAI_WAVE), dots_lds(small, ell), s, A, Rin, Xr, P, src, seg, off, total,
@@ -1769,10 +1850,11 @@ void launch_copy_cols(Cols<T> src, Cols<T> dst, int64_t n, const int64_t* total,
 
 // upper bound of the union of the lists of column j
 template <typename T>
-__global__ void k_bound_update(Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp, Pair<T> PTp, UpdMode md,
-                               int64_t* ub, int64_t n, const DevState* st) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
+__global__ __launch_bounds__(1024) void k_bound_update(Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp,
+                                                       Pair<T> PTp, UpdMode md, int64_t n,
+                                                       int shift, int64_t* loc, int64_t* tile,
+                                                       int64_t* total, OffZero z, DevState* st) {
+  off_zero(z);
   if (!st->any_active || !st->iter_active) return;
   const Cols<T> M = Mp.now();
   const Cols<T> P = Pp.now();
@@ -1780,21 +1862,32 @@ __global__ void k_bound_update(Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp, Pair<T>
   const bool needR = (md.doM && (md.x1 == 1 || md.x2 == 1)) || (md.doP && md.pR);
   const bool needP = (md.doM && (md.x1 == 2 || md.x2 == 2)) || (md.doP && md.pP);
   const bool mirror = md.sym != 0;   // R^T, P^T serve only the symmetrization
-  int64_t s = 1;
-  if (md.doM) s += M.len[j];
-  if (needR) s += R.len[j];
-  if (needP) s += P.len[j];
-  if (needP && mirror) s += PT.len[j];
-  if (needR && mirror)
-    for (int64_t q = A.rowptr[j]; q < A.rowptr[j + 1]; ++q) s += M.len[A.col[q]];
-  ub[j] = s;
+  offsets_of(
+      [&](int64_t j, int g) -> int64_t {
+        long long s = 0;
+        if (j < n) {
+          if (g == 0) s += 1;
+          if (g == 1 && md.doM) s += M.len[j];
+          if (g == 2 && needR) s += R.len[j];
+          if (g == 3 && needP) s += P.len[j];
+          if (g == 4 && needP && mirror) s += PT.len[j];
+          if (needR && mirror)
+            for (int64_t q = A.rowptr[j] + g; q < A.rowptr[j + 1]; q += 8) s += M.len[A.col[q]];
+        }
+        return eight_sum(s);
+      },
+      n, shift, loc, tile, total, st);
 }
 
 template <typename T>
-void launch_bound_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, UpdMode md,
-                         int64_t* ub, int64_t n, const DevState* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_bound_update<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, A, M,
-                     R, P, PT, md, ub, n, st);
+Offs launch_bound_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, UpdMode md,
+                         const OffBuf& o, const BigList& z0, int64_t n, DevState* st,
+                         hipStream_t s) {
+  const Offs f = make_offs(o, n);
+  hipLaunchKernelGGL(k_bound_update<T>, dim3((unsigned)f.tiles(n)), dim3(1024), 0, s, A, M, R, P,
+                     PT, md, n, f.shift, o.loc, o.tile, o.total,
+                     OffZero{{z0.count, z0.count2, nullptr, nullptr}}, st);
+  return f;
 }
 
 // (b+1)-th largest magnitude of a candidate column in global memory (0 if it has at
@@ -1843,7 +1936,7 @@ __device__ inline double kth_largest_cols(const int32_t* idx, const T* val, int 
 
 template <typename T, bool GS>
 __device__ __forceinline__ void update_body(Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp,
-                                            Pair<T> PTp, UpdMode md, const int64_t* off,
+                                            Pair<T> PTp, UpdMode md, Offs off,
                                             const int64_t* total, const int32_t* kcol,
                                             double* tM, double* tP, BigList big, Seg seg,
                                             DevState* st, int tier, int L, int H, int DG) {
@@ -2163,7 +2256,7 @@ __device__ __forceinline__ void update_body(Csr A, Pair<T> Mp, Cols<T> R, Pair<T
 
 template <typename T, bool GS>
 __global__ __launch_bounds__(SPAI_WAVE) void k_update(Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp,
-                                                      Pair<T> PTp, UpdMode md, const int64_t* off,
+                                                      Pair<T> PTp, UpdMode md, Offs off,
                                                       const int64_t* total, const int32_t* kcol,
                                                       double* tM, double* tP, BigList big,
                                                       Seg seg, DevState* st, int tier, int L,
@@ -2178,7 +2271,7 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_update(Csr A, Pair<T> Mp, Cols<T>
 // may pick either.
 template <typename T>
 __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5, 5))) void k_update_w5(
-    Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp, Pair<T> PTp, UpdMode md, const int64_t* off,
+    Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp, Pair<T> PTp, UpdMode md, Offs off,
     const int64_t* total, const int32_t* kcol, double* tM, double* tP, BigList big, Seg seg,
     DevState* st, int tier, int L, int H, int DG) {
   update_body<T, false>(A, Mp, R, Pp, PTp, md, off, total, kcol, tM, tP, big, seg, st, tier, L, H,
@@ -2207,7 +2300,7 @@ constexpr int kUpdLeanNbr = 256;   // entries of the neighbour columns together
 // float64 path spills there and keeps five).
 template <typename T, bool FLAT, bool SECOND, int LM>
 __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 5))) void k_update_lean(
-    Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp, Pair<T> PTp, UpdMode mdin, const int64_t* off,
+    Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp, Pair<T> PTp, UpdMode mdin, Offs off,
     const int64_t* total, const int32_t* kcol, double* tM, double* tP, BigList big, Seg seg,
     DevState* st, int L, int H) {
   if (!st->any_active || !st->iter_active) return;
@@ -2256,7 +2349,7 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
   const T* eval = sizeof(T) == 4 ? (const T*)A.eval32 : (const T*)A.eval;
   const int W = 1 << A.eshift;                   // ELL width of A (at most 64)
   // A column's descriptors are loaded one column ahead, one value per lane (lanes 0-3
-  // the lengths of m_j, r_j, p_j, p^T_j, lanes 4-7 their starts, lanes 8 and 9 the
+  // the lengths of m_j, r_j, p_j, p^T_j, lanes 4-7 their starts, lanes 8 to 11 the
   // column's candidate range off[j] .. off[j+1]) together with row j of A (lanes 0-7:
   // neighbour l and a_jl), and each neighbour column's length and start once those
   // have arrived: a column's first loads are then its entries, and its descriptors
@@ -2276,10 +2369,11 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
     } else if (lane < 8) {
       const int64_t* bp = lane == 4 ? M.beg : lane == 5 ? R.beg : lane == 6 ? P.beg : PT.beg;
       p.d = bp[jj];
-    } else if (lane == 8) {
-      p.d = off[jj];
-    } else if (lane == 9) {
-      p.d = jj + 1 < A.n ? off[jj + 1] : ntot;
+    } else if (lane < 12) {
+      const int64_t jo = jj + ((lane - 8) >> 1);       // off[j], off[j+1] in their two parts
+      if (jo >= A.n) p.d = lane == 10 ? ntot : 0;
+      else if (lane & 1) p.d = off.tile[jo >> off.shift];
+      else p.d = off.loc[jo];
     }
     if (needRT && lane < W) {
       p.nl = A.ecol[(jj << A.eshift) + lane];
@@ -2310,8 +2404,8 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
     const int lown = lm + lr + lp + lpt;
     const int64_t bm = wave_read64(cur.d, 4), br = wave_read64(cur.d, 5);
     const int64_t bp = wave_read64(cur.d, 6), bpt = wave_read64(cur.d, 7);
-    const int64_t ob = wave_read64(cur.d, 8);
-    const int64_t ub = wave_read64(cur.d, 9) - ob;               // entries of all lists + 1
+    const int64_t ob = wave_read64(cur.d, 8) + wave_read64(cur.d, 9);
+    const int64_t ub = wave_read64(cur.d, 10) + wave_read64(cur.d, 11) - ob;               // entries of all lists + 1
     const int nl = cur.nl;                                       // neighbour l in N(j)
     const double av = (double)cur.av;
     const int nlen = cur.nlen;
@@ -2631,10 +2725,9 @@ size_t update_tile_bytes(Tile t) {
 
 template <typename T>
 void launch_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, UpdMode md,
-                   const int64_t* off, const int64_t* total, const int32_t* kcol, double* tM,
+                   Offs off, const int64_t* total, const int32_t* kcol, double* tM,
                    double* tP, BigList big, const Seg& seg, DevState* st, Tile small, Tile large,
                    Tile huge, hipStream_t s, bool second) {
-  hipLaunchKernelGGL(k_zero_counts, dim3(1), dim3(1), 0, s, big.count, big.count2);
   if (small.waves == 1 && A.eshift >= 0) {
     const size_t lds = (size_t)std::max(small.H + kOhOver, kUpdLeanKeys) * 4 + 64;   // dynamic part
     auto go = [&](auto kern) {
@@ -2789,25 +2882,6 @@ __device__ inline void find_bin_desc(F at, int nbins, long long rank, long long*
   *total = tot;
   *bin = s_bin;
   *above = s_above;
-}
-
-// true in every thread of the last workgroup of a launch to come here, all of whose atomics
-// and agent-scope stores have then arrived; the histograms are read by it through agent-scope
-// loads, and it sets the ticket back
-__device__ __forceinline__ bool last_block(int* ticket) {
-  __shared__ int last;
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-           (int)gridDim.x - 1;
-    if (last) *ticket = 0;
-  }
-  __syncthreads();
-  return last != 0;
-}
-__device__ __forceinline__ unsigned long long agent_count(const unsigned long long* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // the decision after the exponent histogram (one thread): bin holds the (b+1)-th largest of
@@ -3364,7 +3438,7 @@ template <typename T>
 void launch_score(const Csr& A, Pair<T> M, double* sc, double* sig, BigList big, DevState* st,
                   Tile small, Tile large, Tile huge, int64_t n, hipStream_t s) {
   const bool ell = A.eshift >= 0;
-  hipLaunchKernelGGL(k_zero_counts, dim3(1), dim3(1), 0, s, big.count, big.count2);
+  launch_zero_counts(big, s);
   hipLaunchKernelGGL((k_score<T, false>), dim3(resident_grid(k_score<T, false>, score_lds(small, ell))),
                      dim3(SPAI_WAVE), score_lds(small, ell), s, A, M, sc, big, st, 0, small.L,
                      small.H);
@@ -3554,13 +3628,8 @@ void launch_compact(Pair<T> X, int kind, int colcap, int sym, int global, const 
 // scalar steps (one thread per segment)
 // ============================================================================
 
-// step sizes from the reduced dots; decides whether this iteration runs
-__global__ void k_scal_step(int method, Seg seg, const double* red, DevState* st) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= seg.nseg) return;
-  SegState& g = seg.st[s];
-  if (s == 0) st->rec_i = st->rec_next++;   // the drops of this iteration go to this record
-  const double* d = red + (int64_t)s * kND;
+// step sizes of one matrix from its dots d
+__device__ void scal_step(int method, SegState& g, const double* d) {
   for (int i = 0; i < kND; ++i) g.dots[i] = d[i];
   if (!g.stop) {
     if (method == kMR) {
@@ -3619,6 +3688,35 @@ __global__ void k_scal_step(int method, Seg seg, const double* red, DevState* st
   }
 }
 
+// step sizes from the reduced dots (several matrices)
+__global__ void k_scal_step(int method, Seg seg, const double* red, DevState* st) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= seg.nseg) return;
+  if (s == 0) st->rec_i = st->rec_next++;   // the drops of this iteration go to this record
+  scal_step(method, seg.st[s], red + (int64_t)s * kND);
+}
+
+// one matrix: the dots reduced, the step sizes, and whether this iteration runs
+__global__ __launch_bounds__(kRedThreads) void k_reduce_step(int method, Seg seg,
+                                                             const double* colpart, int64_t n,
+                                                             int64_t chunk, int nb, double* part,
+                                                             DevState* st) {
+  __shared__ double d[kND];
+  chunk_sums<kND>(colpart, n, chunk, part);
+  if (!last_block(&st->red_ticket)) return;
+  for (int i = threadIdx.x >> 6; i < kND; i += kRedThreads / SPAI_WAVE) {
+    const double v = blocks_sum_wave(part + i, kND, nb);
+    if (lane_id() == 0) d[i] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  st->rec_i = st->rec_next++;
+  scal_step(method, seg.st[0], d);
+  st->any_active = st->iter_active = !seg.st[0].stop;
+  st->nnz_m = 0;
+  st->nnz_p = 0;
+}
+
 // any segment still running -> the iteration runs
 __global__ void k_any_active(Seg seg, DevState* st) {
   __shared__ int any;
@@ -3635,22 +3733,29 @@ __global__ void k_any_active(Seg seg, DevState* st) {
   }
 }
 
-void launch_scal_step(int method, const Seg& seg, const double* red, DevState* st,
-                      hipStream_t s) {
+// chunks of a reduction (kRedBlocks at most)
+static int64_t red_chunk(int64_t n) { return (n + kRedBlocks - 1) / kRedBlocks; }
+
+void launch_step(int method, const Seg& seg, const double* colpart, int64_t n,
+                 const int64_t* seg_beg, double* red, double* blockpart, DevState* st,
+                 hipStream_t s) {
+  if (seg.nseg == 1) {
+    const int64_t chunk = red_chunk(n);
+    const int nb = (int)((n + chunk - 1) / chunk);
+    hipLaunchKernelGGL(k_reduce_step, dim3((nb + 3) / 4), dim3(kRedThreads), 0, s, method, seg,
+                       colpart, n, chunk, nb, blockpart, st);
+    return;
+  }
+  launch_reduce(colpart, kND, n, seg, seg_beg, red, blockpart, s);
   hipLaunchKernelGGL(k_scal_step, dim3((seg.nseg + 255) / 256), dim3(256), 0, s, method, seg, red,
                      st);
   hipLaunchKernelGGL(k_any_active, dim3(1), dim3(256), 0, s, seg, st);
 }
 
 // after R_{i+1}: record ||R||, test the stopping rule, CG's beta
-__global__ void k_scal_post(int method, Seg seg, const double* red, const double* red_rz,
-                            double tol, double* hist, int hist_cap, int setup, DevState* st) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= seg.nseg) return;
-  if (!st->iter_active) return;
-  SegState& g = seg.st[s];
-  const double rr_new = red[s];
-  const double rz_new = red_rz ? red_rz[s] : rr_new;
+// (matrix s of the handle)
+__device__ void scal_post(int method, SegState& g, int s, double rr_new, double rz_new, double tol,
+                          double* hist, int hist_cap, int setup) {
   const double rn = sqrt(rr_new);
   if (setup) {                          // R_0: no iteration counted
     g.rr = rr_new;
@@ -3678,11 +3783,46 @@ __global__ void k_scal_post(int method, Seg seg, const double* red, const double
   }
 }
 
-void launch_scal_post(int method, const Seg& seg, const double* red, const double* red_rz,
-                      double tol, double* hist, int hist_cap, int setup, DevState* st,
-                      hipStream_t s) {
+__global__ void k_scal_post(int method, Seg seg, const double* red, const double* red_rz,
+                            double tol, double* hist, int hist_cap, int setup, DevState* st) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= seg.nseg) return;
+  if (!st->iter_active) return;
+  scal_post(method, seg.st[s], s, red[s], red_rz ? red_rz[s] : red[s], tol, hist, hist_cap, setup);
+}
+
+// one matrix: the norms reduced and the end of the iteration
+__global__ __launch_bounds__(kRedThreads) void k_reduce_post(int method, Seg seg,
+                                                             const double* colnorm,
+                                                             const double* colrz, int64_t n,
+                                                             int64_t chunk, int nb, double* part,
+                                                             double tol, double* hist,
+                                                             int hist_cap, int setup,
+                                                             DevState* st) {
+  if (!st->iter_active) return;
+  chunk_sums<1>(colnorm, n, chunk, part);
+  if (colrz) chunk_sums<1>(colrz, n, chunk, part + nb);
+  if (!last_block(&st->red_ticket)) return;
+  if (threadIdx.x >= SPAI_WAVE) return;
+  const double rr = blocks_sum_wave(part, 1, nb);
+  const double rz = colrz ? blocks_sum_wave(part + nb, 1, nb) : rr;
+  if (threadIdx.x == 0) scal_post(method, seg.st[0], 0, rr, rz, tol, hist, hist_cap, setup);
+}
+
+void launch_post(int method, const Seg& seg, const double* colnorm, const double* colrz, int64_t n,
+                 const int64_t* seg_beg, double* red, double* red_rz, double* blockpart,
+                 double tol, double* hist, int hist_cap, int setup, DevState* st, hipStream_t s) {
+  if (seg.nseg == 1) {
+    const int64_t chunk = red_chunk(n);
+    const int nb = (int)((n + chunk - 1) / chunk);
+    hipLaunchKernelGGL(k_reduce_post, dim3((nb + 3) / 4), dim3(kRedThreads), 0, s, method, seg,
+                       colnorm, colrz, n, chunk, nb, blockpart, tol, hist, hist_cap, setup, st);
+    return;
+  }
+  launch_reduce(colnorm, 1, n, seg, seg_beg, red, blockpart, s);
+  if (colrz) launch_reduce(colrz, 1, n, seg, seg_beg, red_rz, blockpart, s);
   hipLaunchKernelGGL(k_scal_post, dim3((seg.nseg + 255) / 256), dim3(256), 0, s, method, seg, red,
-                     red_rz, tol, hist, hist_cap, setup, st);
+                     colrz ? red_rz : nullptr, tol, hist, hist_cap, setup, st);
 }
 
 // the end of a drop in one launch: the new M (doM) and P (doP) become current, and with
@@ -3702,25 +3842,27 @@ void launch_drop_finish(DevState* st, int doM, int doP, int floors, double frac,
 #define SPAI_INST(T)                                                                               \
   template void launch_init_m<T>(int64_t, Cols<T>, const double*, const Seg&, hipStream_t);       \
   template void launch_zero_cols<T>(int64_t, Cols<T>, hipStream_t);                               \
-  template void launch_bound_resid<T>(const Csr&, Pair<T>, int64_t*, int64_t, const DevState*,    \
-                                      hipStream_t);                                               \
-  template void launch_resid<T>(const Csr&, Pair<T>, Cols<T>, const int64_t*, const int64_t*,    \
+  template Offs launch_bound_resid<T>(const Csr&, Pair<T>, const OffBuf&, const BigList&,         \
+                                      const BigList&, int64_t, DevState*, hipStream_t);                                               \
+  template void launch_resid<T>(const Csr&, Pair<T>, Cols<T>, Offs, const int64_t*,              \
                                 double*, int, double*, BigList, DevState*, Tile, Tile, Tile,      \
                                 hipStream_t);                                                     \
   template void launch_dots<T>(const Csr&, Cols<T>, Pair<T>, int, int, int, double*, BigList,     \
                                DevState*, Tile, Tile, Tile, hipStream_t);                         \
-  template void launch_bound_impl<T>(const Csr&, Cols<T>, Cols<T>, Pair<T>, int, int64_t*,       \
-                                     int64_t, const DevState*, hipStream_t);                      \
+  template Offs launch_bound_impl<T>(const Csr&, Cols<T>, Cols<T>, Pair<T>, int, const OffBuf&,  \
+                                     const BigList&, const BigList&, int64_t, DevState*,          \
+                                     hipStream_t);                      \
   template void launch_resid_impl<T>(const Csr&, Cols<T>, Cols<T>, Pair<T>, int, int, const Seg&, \
-                                     const int64_t*, const int64_t*, Cols<T>, Cols<T>, int,       \
+                                     Offs, const int64_t*, Cols<T>, Cols<T>, int,                 \
                                      double*, double*, BigList, DevState*, Tile, Tile, Tile,      \
                                      hipStream_t);                                                \
   template void launch_copy_cols<T>(Cols<T>, Cols<T>, int64_t, const int64_t*, const DevState*,   \
                                     hipStream_t);                                                 \
-  template void launch_bound_update<T>(const Csr&, Pair<T>, Cols<T>, Pair<T>, Pair<T>, UpdMode,   \
-                                       int64_t*, int64_t, const DevState*, hipStream_t);          \
+  template Offs launch_bound_update<T>(const Csr&, Pair<T>, Cols<T>, Pair<T>, Pair<T>, UpdMode,   \
+                                       const OffBuf&, const BigList&, int64_t, DevState*,         \
+                                       hipStream_t);          \
   template void launch_update<T>(const Csr&, Pair<T>, Cols<T>, Pair<T>, Pair<T>, UpdMode,         \
-                                 const int64_t*, const int64_t*, const int32_t*, double*,         \
+                                 Offs, const int64_t*, const int32_t*, double*,                   \
                                  double*, BigList, const Seg&, DevState*, Tile, Tile, Tile,       \
                                  hipStream_t, bool);                                              \
   template void launch_global_select<T>(Pair<T>, int, int64_t, double, int, unsigned long long*,  \

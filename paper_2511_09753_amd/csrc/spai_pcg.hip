@@ -425,39 +425,6 @@ __device__ __forceinline__ double column_sum(const double* sh, int t, int R) {
   return s;
 }
 
-// A partial that another workgroup of the same launch will read goes past the L2 caches (each
-// XCD has its own), one word at a time: a device-scope fence would write back and invalidate
-// a whole L2 for every workgroup (74 us against 13 for a product of 256 workgroups).
-__device__ __forceinline__ void agent_store(double* p, double v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double agent_load(const double* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// sum_b p[b * step], b < nblocks, on every lane of one wave, in the order and tree of
-// rows_sum / parts_sum: thread t of 256 adds b = t, t + 256, ..., then halves of the 256
-// are added; lane l holds threads l, l + 64, l + 128 and l + 192.
-__device__ __forceinline__ double blocks_sum_wave(const double* p, int64_t step, int nblocks) {
-  const int lane = threadIdx.x & 63;
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int b0 = 0; b0 < nblocks; b0 += 2 * kThreads) {     // eight loads in flight
-    double v[2][4];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int b = b0 + h * kThreads + lane + 64 * q;
-        v[h][q] = b < nblocks ? agent_load(p + (int64_t)b * step) : 0.0;
-      }
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) s[q] += v[h][q];
-  }
-  return wave_sum((s[0] + s[2]) + (s[1] + s[3]));
-}
-
 struct RhsState {
   double bnorm, rz, pq, rr, alpha, beta;
   double alpha_prev;                // the previous iteration's alpha (its x term may be pending)

@@ -578,7 +578,7 @@ struct Engine : EngineBase {
       return rc;
     if ((rc = dalloc(&colpart, n * kND)) || (rc = dalloc(&colnorm, n)) ||
         (rc = dalloc(&red, (int64_t)nseg * kND)) || (rc = dalloc(&red_rr, nseg)) ||
-        (rc = dalloc(&blockpart, 1024 * kND)) || (rc = dalloc(&cvec, nseg)))
+        (rc = dalloc(&blockpart, kBlockPart)) || (rc = dalloc(&cvec, nseg)))
       return rc;
     if (opts.jacobi && ((rc = dalloc(&colrz, n)) || (rc = dalloc(&red_rz, nseg)))) return rc;
     hist_cap = std::max(max_iter, 1);
@@ -1201,13 +1201,8 @@ struct Engine : EngineBase {
       te();
     }
     tb(SPAI_PH_COMPACT);
-    if (md.doM) launch_compact<T>(M, 0, colcap, md.sym, global, tM, opts.tie_eta, n, st, s, keyM);
-    if (md.doP) {
-      launch_compact<T>(P, 1, colcap, 0, global, tP, opts.tie_eta, n, st, s);
-      launch_compact<T>(PT, 2, colcap, 0, global, tP, opts.tie_eta, n, st, s);
-    }
-    // each compaction reads only its own pair, so both flips (and the floors) go last
-    launch_drop_finish(st, md.doM, md.doP, floors ? 1 : 0, opts.floor_frac, s);
+    launch_drop<T>(M, P, PT, md.doM, md.doP, colcap, md.sym, global, tM, tP, opts.tie_eta, n,
+                   blockpart, st, s, keyM, floors ? 1 : 0, opts.floor_frac);
     te();
   }
 

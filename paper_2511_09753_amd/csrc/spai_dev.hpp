@@ -704,6 +704,14 @@ __device__ __forceinline__ void wave_sum6(double (&v)[6]) {
   for (int q = 0; q < 6; ++q) v[q] = wave_readf(e, 8 * q);
 }
 
+// LDS written by one lane of a wave and read by another, in a workgroup of several waves that
+// do not wait for each other: a wave's LDS accesses complete in order, so only the compiler
+// has to be held
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Columns of a grid-stride loop.  The columns are split into 8 contiguous ranges,
 // one per XCD (workgroups are dealt round-robin over the 8 XCDs of the chip), so
 // the neighbour columns a workgroup touches tend to be cached in its own XCD's L2.

@@ -109,6 +109,8 @@ struct Offs {
   int64_t tiles(int64_t n) const { return (n + ((int64_t)1 << shift) - 1) >> shift; }
 };
 constexpr int kOffTiles = 512;
+constexpr int kBlockPart = 1024 * kND;   // words of the workgroups' partial sums
+constexpr int kDropSlots = kBlockPart / 9;   // workgroups a list of a drop (three lists, three sums)
 struct OffBuf {                    // their storage: loc[n], tile[min(n, kOffTiles)], total[1]
   int64_t *loc = nullptr, *tile = nullptr, *total = nullptr;
 };
@@ -210,13 +212,15 @@ void launch_score(const Csr& A, Pair<T> M, double* sc, double* sig, BigList big,
                   Tile small, Tile large, Tile huge, int64_t n, hipStream_t s);
 size_t score_tile_bytes(Tile t, bool ell);
 
-// keep rule + in-place compaction of the candidates in X.nxt();
-// kind 0: M (diagonal kept), 1: P (column threshold tcol[j]), 2: P^T (tcol[row]);
-// score non-null (global cap): keep score > threshold instead of |x| > threshold
+// keep rule + in-place compaction of the candidates of M (doM; the diagonal is kept) and of
+// P and P^T (doP; column thresholds tP of the column and of the row), which then become
+// current; score non-null (global cap): M keeps score > threshold instead of |x| > threshold;
+// floors: the next iteration's floors are set, frac times this one's cuts
 template <typename T>
-void launch_compact(Pair<T> X, int kind, int colcap, int sym, int global, const double* tcol,
-                    double eta, int64_t n, DevState* st, hipStream_t s,
-                    const double* score = nullptr);
+void launch_drop(Pair<T> M, Pair<T> P, Pair<T> PT, int doM, int doP, int colcap, int sym,
+                 int global, const double* tM, const double* tP, double eta, int64_t n,
+                 double* blockpart, DevState* st, hipStream_t s, const double* score, int floors,
+                 double frac);
 
 // the sums of colpart over the columns (fixed order) and the step sizes from them
 void launch_step(int method, const Seg& seg, const double* colpart, int64_t n,
@@ -232,11 +236,8 @@ extern int g_grid_cols;   // persistent grid of the per-column kernels (multiple
 void launch_rec_clear(DevState* st, int next, hipStream_t s);
 // the second, floor-free pass of the update and the selection runs only where the first
 // pass's floors were too high: redo_begin masks the iteration unless st->redo (and clears
-// the floors), redo_end restores it; drop_finish sets the next iteration's floors
+// the floors), redo_end restores it
 void launch_redo_begin(DevState* st, const BigList& big, hipStream_t s);
 void launch_redo_end(DevState* st, hipStream_t s);
-// the new M (doM) and P (doP) become current; with floors, the next iteration's floors
-// are set from this iteration's cuts
-void launch_drop_finish(DevState* st, int doM, int doP, int floors, double frac, hipStream_t s);
 
 }  // namespace spai

@@ -415,6 +415,17 @@ __device__ void floor_next_body(DevState* st, int doM, int doP, double frac) {
   }
   st->redo = 0;
 }
+// the end of a drop: the new M (doM) and P (doP) become current, and with floors the next
+// iteration's floors are set (one thread; on: by the last workgroup of the compaction)
+struct DropEnd {
+  int on, doM, doP, floors;
+  double frac;
+};
+__device__ void drop_end(const DropEnd& e, DevState* st) {
+  if (e.doM) st->curM ^= 1;
+  if (e.doP) st->curP ^= 1;
+  if (e.floors) floor_next_body(st, e.doM, e.doP, e.frac);
+}
 void launch_redo_begin(DevState* st, const BigList& big, hipStream_t s) {
   hipLaunchKernelGGL(k_redo_begin, dim3(1), dim3(1), 0, s, st, big.count, big.count2);
 }
@@ -425,17 +436,20 @@ void launch_redo_end(DevState* st, hipStream_t s) {
 // true in every thread of the last workgroup of a launch to come here, all of whose atomics
 // and agent-scope stores have then arrived; the histograms are read by it through agent-scope
 // loads, and it sets the ticket back
-__device__ __forceinline__ bool last_block(int* ticket) {
+__device__ __forceinline__ bool last_block(int* ticket, int blocks) {
   __shared__ int last;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
     last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-           (int)gridDim.x - 1;
+           blocks - 1;
     if (last) *ticket = 0;
   }
   __syncthreads();
   return last != 0;
+}
+__device__ __forceinline__ void agent_put(unsigned long long* p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ unsigned long long agent_count(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -503,7 +517,7 @@ __device__ __forceinline__ void offsets_of(F bound, int64_t n, int shift, int64_
   }
   if (threadIdx.x == 0)
     __hip_atomic_store(&tile[blockIdx.x], run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (!last_block(&st->off_ticket)) return;
+  if (!last_block(&st->off_ticket, (int)gridDim.x)) return;
   int64_t before = 0;
   for (int t0 = 0; t0 < (int)gridDim.x; t0 += 128, par ^= 1) {
     const int t = t0 + (threadIdx.x >> 3);
@@ -2788,8 +2802,8 @@ __device__ __forceinline__ double ord_value(unsigned long long k) {
   return __longlong_as_double((long long)((k >> 63) ? (k & ~(1ull << 63)) : ~k));
 }
 
-// ---- grouped walk over the entries of 64 consecutive columns ----------------------
-// A one-wave workgroup takes columns j0 .. j0+63 at once: lane c holds column j0 + c's
+// ---- grouped walk over the entries of up to 64 consecutive columns -----------------
+// A wave takes columns j0 .. j0+gs-1 (gs = 64, less for small matrices) at once: lane c holds column j0 + c's
 // start cb and length cl (loaded together) and ex, the exclusive prefix of the
 // lengths, so the T entries of the group form one flat range.  Entry x belongs to the
 // column c with ex[c] <= x < ex[c] + cl[c], found by a six-step shuffle search, and
@@ -2800,19 +2814,30 @@ __device__ __forceinline__ double ord_value(unsigned long long k) {
 constexpr int kGU = 4;
 constexpr int kGUc = 8;
 
+// columns of a group: 64, fewer where there would be fewer groups than waves (eight per
+// compute unit)
+static int group_cols(int64_t n) {
+  int gs = 64;
+  while (gs > 8 && n < (int64_t)gs * 2048) gs >>= 1;
+  return gs;
+}
+static int groups(int64_t n, int gs) {
+  return (int)std::min<int64_t>((n + gs - 1) / gs, 1 << 30);
+}
+
 struct Group64 {
   int64_t j0, cb;
   int cl, ex, T;
 };
 
 template <typename T>
-__device__ __forceinline__ Group64 group_load(const Cols<T>& X, int64_t j0, int64_t n) {
+__device__ __forceinline__ Group64 group_load(const Cols<T>& X, int64_t j0, int gs, int64_t n) {
   Group64 g;
   g.j0 = j0;
   const int64_t j = j0 + lane_id();
   g.cb = 0;
   g.cl = 0;
-  if (j < n) {
+  if (lane_id() < gs && j < n) {
     g.cb = X.beg[j];
     g.cl = X.len[j];
   }
@@ -2917,24 +2942,26 @@ __device__ inline void sel_exp_decide(long long b, long long total, int bin, lon
 // the waves in flight (one wave per histogram allowed five per SIMD, 7% slower).  The last
 // workgroup finds the exponent bin of the (b+1)-th largest, b = m - (diagonal count if
 // excluded), and clears the histogram for the passes over the collected keys.
+constexpr int kHistWaves = 16;
 template <typename T, bool SC>
-__global__ __launch_bounds__(4 * SPAI_WAVE) void k_sel_hist_exp(Pair<T> Xp, const double* sc,
+__global__ __launch_bounds__(kHistWaves * SPAI_WAVE) void k_sel_hist_exp(Pair<T> Xp, const double* sc,
                                                             int excl_diag, int64_t m,
                                                             unsigned long long* hist,
-                                                            double* thr, int64_t n,
+                                                            double* thr, int gs, int64_t n,
                                                             DevState* st) {
   if (!st->any_active || !st->iter_active) return;
   constexpr int NB = SC ? 4096 : 2048;
   __shared__ unsigned int h[NB];
   const int lane = lane_id();
   const int wv = threadIdx.x / SPAI_WAVE;
-  for (int i = threadIdx.x; i < NB; i += 4 * SPAI_WAVE) h[i] = 0;
+  for (int i = threadIdx.x; i < NB; i += kHistWaves * SPAI_WAVE) h[i] = 0;
   __syncthreads();
   const Cols<T> X = Xp.nxt();
-  long long diag = 0;
-  const int64_t ng = (n + 63) / 64;
-  for (int64_t gi = (int64_t)blockIdx.x * 4 + wv; gi < ng; gi += (int64_t)gridDim.x * 4) {
-    const Group64 g = group_load(X, gi * 64, n);
+  int diag = 0;                                  // a wave's columns are fewer than 2^31
+  const int64_t ng = (n + gs - 1) / gs;
+  for (int64_t gi = (int64_t)blockIdx.x * kHistWaves + wv; gi < ng;
+       gi += (int64_t)gridDim.x * kHistWaves) {
+    const Group64 g = group_load(X, gi * gs, gs, n);
     for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE * kGU) {
       int col[kGU], idx[kGU];
       T val[kGU];
@@ -2968,47 +2995,60 @@ __global__ __launch_bounds__(4 * SPAI_WAVE) void k_sel_hist_exp(Pair<T> Xp, cons
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < NB; i += 4 * SPAI_WAVE)
+  for (int i = threadIdx.x; i < NB; i += kHistWaves * SPAI_WAVE)
     if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
-  diag = wave_sum_ll(diag);
-  if (lane == 0 && diag) atomicAdd((unsigned long long*)&st->sel_diag, (unsigned long long)diag);
-  if (!last_block(&st->sel_ticket)) return;
+  __shared__ int s_diag[kHistWaves];
+  diag = wave_sum_int(diag);
+  if (lane == 0) s_diag[wv] = diag;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int d = 0;
+    for (int w = 0; w < kHistWaves; ++w) d += s_diag[w];
+    if (d) atomicAdd((unsigned long long*)&st->sel_diag, (unsigned long long)d);
+  }
+  if (!last_block(&st->sel_ticket, (int)gridDim.x)) return;
   const long long b =
       m - (excl_diag ? (long long)agent_count((const unsigned long long*)&st->sel_diag) : 0);
   long long total, above;
   int bin;
   find_bin_desc([&](int i) { return agent_count(hist + i); }, NB, b + 1, &total, &bin, &above);
   // every read of the histogram is done (the search ends on a barrier)
-  for (int i = threadIdx.x; i < NB; i += 4 * SPAI_WAVE) hist[i] = 0;
+  for (int i = threadIdx.x; i < NB; i += kHistWaves * SPAI_WAVE) hist[i] = 0;
   if (threadIdx.x == 0) sel_exp_decide(b, total, bin, above, SC ? 1 : 0, thr, st);
 }
 
-// keys whose exponent bin is the selected one, staged in LDS (one stage per one-wave
-// workgroup) and flushed to the global buffer with one atomic reservation per flush
-constexpr int kStage = 1024;
+// keys whose exponent bin is the selected one, staged in LDS (one stage per wave) and flushed
+// to the global buffer, a wave's full stage with a reservation of its own, the rest of a
+// workgroup's waves with one: reservations are atomics on one address, some 10 ns each
+constexpr int kStage = 512, kCollWaves = 8;
 template <typename T, bool SC>
-__global__ __launch_bounds__(SPAI_WAVE) void k_sel_collect(Pair<T> Xp, const double* sc,
+__global__ __launch_bounds__(kCollWaves * SPAI_WAVE) void k_sel_collect(Pair<T> Xp, const double* sc,
                                                            int excl_diag,
-                                                           unsigned long long* selbuf,
+                                                           unsigned long long* selbuf, int gs,
                                                            int64_t n, DevState* st) {
   if (!st->any_active || !st->iter_active || st->sel_done) return;
-  __shared__ unsigned long long stage[kStage];
+  __shared__ unsigned long long stages[kCollWaves][kStage];
+  __shared__ int s_cnt[kCollWaves];
+  __shared__ unsigned long long s_base;
+  const int wv = threadIdx.x / SPAI_WAVE;
+  unsigned long long* stage = stages[wv];
   const Cols<T> X = Xp.nxt();
   const unsigned long long want = st->sel_prefix >> 52;
   const int lane = lane_id();
   int cnt = 0;                                    // staged keys (wave-uniform)
   auto flush = [&]() {
-    __syncthreads();
+    wave_sync();
     unsigned long long base = 0;
     if (lane == 0 && cnt) base = atomicAdd(&st->sel_count, (unsigned long long)cnt);
     base = (unsigned long long)wave_read64((int64_t)base, 0);
     for (int i = lane; i < cnt; i += SPAI_WAVE) selbuf[base + i] = stage[i];
-    __syncthreads();
+    wave_sync();
     cnt = 0;
   };
-  const int64_t ng = (n + 63) / 64;
-  for (int64_t gi = blockIdx.x; gi < ng; gi += gridDim.x) {
-    const Group64 g = group_load(X, gi * 64, n);
+  const int64_t ng = (n + gs - 1) / gs;
+  for (int64_t gi = (int64_t)blockIdx.x * kCollWaves + wv; gi < ng;
+       gi += (int64_t)gridDim.x * kCollWaves) {
+    const Group64 g = group_load(X, gi * gs, gs, n);
     for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE * kGU) {
       if (cnt > kStage - SPAI_WAVE * kGU) flush();
       int idx[kGU];
@@ -3046,7 +3086,20 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_sel_collect(Pair<T> Xp, const dou
       }
     }
   }
-  flush();
+  if (lane == 0) s_cnt[wv] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int sum = 0;
+    for (int w = 0; w < kCollWaves; ++w) {
+      const int c = s_cnt[w];
+      s_cnt[w] = sum;
+      sum += c;
+    }
+    s_base = sum ? atomicAdd(&st->sel_count, (unsigned long long)sum) : 0ull;
+  }
+  __syncthreads();
+  const unsigned long long base = s_base + (unsigned long long)s_cnt[wv];
+  for (int i = lane; i < cnt; i += SPAI_WAVE) selbuf[base + i] = stage[i];
 }
 
 // the threshold once every key bit is known (one thread)
@@ -3093,7 +3146,7 @@ __global__ __launch_bounds__(1024) void k_sel_pass(const unsigned long long* sel
     for (int i = threadIdx.x; i < 8192; i += 1024)
       if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
   }
-  if (!last_block(&st->sel_ticket)) return;
+  if (!last_block(&st->sel_ticket, (int)gridDim.x)) return;
   long long total, above;
   int bin;
   find_bin_desc([&](int i) { return agent_count(hist + i); }, 8192, rank, &total, &bin, &above);
@@ -3150,6 +3203,7 @@ __global__ __launch_bounds__(1024) void k_sel_small(Pair<T> Xp, const double* sc
   __shared__ unsigned s_cnt;
   __shared__ int s_diag;
   constexpr int NB = SC ? 4096 : 2048;
+  constexpr int gs = 64;
   const int lane = lane_id(), wv = threadIdx.x / SPAI_WAVE;
   for (int i = threadIdx.x; i < NB; i += 1024) h[i] = 0;
   if (threadIdx.x == 0) {
@@ -3158,12 +3212,12 @@ __global__ __launch_bounds__(1024) void k_sel_small(Pair<T> Xp, const double* sc
   }
   __syncthreads();
   const Cols<T> X = Xp.nxt();
-  const int64_t ng = (n + 63) / 64;
+  const int64_t ng = (n + gs - 1) / gs;
   // f(key) for every candidate that takes part (every lane calls it; take: this lane's does)
   int diag = 0;
   auto walk = [&](auto f) {
     for (int64_t gi = wv; gi < ng; gi += 16) {
-      const Group64 g = group_load(X, gi * 64, n);
+      const Group64 g = group_load(X, gi * gs, gs, n);
       for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE * kGU) {
         int col[kGU], idx[kGU];
         T val[kGU];
@@ -3242,30 +3296,21 @@ void launch_global_select(Pair<T> X, int exclude_diag, int64_t m, double eta, in
     return;
   }
   // (the histogram is zero here: every search clears the bins that it has read)
-  const int ng = (int)std::min<int64_t>((n + 63) / 64, 1 << 30);
-  // the magnitude passes run below full occupancy, as the compaction does: 4 four-wave
-  // histogram workgroups and 12 collecting waves per compute unit took 0.55 ms per
-  // iteration at 96^3 against 0.62 ms at the occupancy limit
-  if (score)
-    hipLaunchKernelGGL(
-        (k_sel_hist_exp<T, true>),
-        dim3(std::min((ng + 3) / 4, resident_grid(k_sel_hist_exp<T, true>, 0, 4 * SPAI_WAVE))),
-        dim3(4 * SPAI_WAVE), 0, s, X, score, exclude_diag, m, hist, thr, n, st);
-  else
-    hipLaunchKernelGGL(
-        (k_sel_hist_exp<T, false>),
-        dim3(std::min({(ng + 3) / 4, resident_grid(k_sel_hist_exp<T, false>, 0, 4 * SPAI_WAVE),
-                       per_cu_grid(4)})),
-        dim3(4 * SPAI_WAVE), 0, s, X, score, exclude_diag, m, hist, thr, n, st);
-  if (score)
-    hipLaunchKernelGGL((k_sel_collect<T, true>),
-                       dim3(std::min(ng, resident_grid(k_sel_collect<T, true>, 0))),
-                       dim3(SPAI_WAVE), 0, s, X, score, exclude_diag, selbuf, n, st);
-  else
-    hipLaunchKernelGGL((k_sel_collect<T, false>),
-                       dim3(std::min({ng, resident_grid(k_sel_collect<T, false>, 0),
-                                      per_cu_grid(12)})),
-                       dim3(SPAI_WAVE), 0, s, X, score, exclude_diag, selbuf, n, st);
+  const int gs = group_cols(n), ng = groups(n, gs);
+  // One histogram workgroup of 16 waves per compute unit and four collecting ones of eight:
+  // every workgroup adds its bins, or its reservation, to the same addresses, at some 10 ns
+  // each.  Four-wave and one-wave workgroups, eight columns a group: 43 and 35 us at 36,000
+  // columns (15 and 10 now); 64 columns: 45 and 49 us at 96^3 (39 and 46 now).
+  const int gh = std::min((ng + kHistWaves - 1) / kHistWaves, per_cu_grid(1));
+  const int gcol = std::min((ng + kCollWaves - 1) / kCollWaves, per_cu_grid(4));
+  auto both = [&](auto khist, auto kcoll) {
+    hipLaunchKernelGGL(khist, dim3(gh), dim3(kHistWaves * SPAI_WAVE), 0, s, X, score, exclude_diag,
+                       m, hist, thr, gs, n, st);
+    hipLaunchKernelGGL(kcoll, dim3(gcol), dim3(kCollWaves * SPAI_WAVE), 0, s, X, score,
+                       exclude_diag, selbuf, gs, n, st);
+  };
+  if (score) both(k_sel_hist_exp<T, true>, k_sel_collect<T, true>);
+  else both(k_sel_hist_exp<T, false>, k_sel_collect<T, false>);
   // a workgroup without keys still draws its ticket, one after the other
   const int ngp = (int)std::max<int64_t>(16, std::min<int64_t>(256, n / 512));
   for (int shift = 39; shift >= last; shift -= 13)
@@ -3406,14 +3451,14 @@ size_t score_tile_bytes(Tile t, bool ell) { return score_lds(t, ell); }
 // search in column k (the candidates are exactly symmetric); the diagonal keeps s_kk
 template <typename T>
 __global__ __launch_bounds__(SPAI_WAVE) void k_score_pair(Pair<T> Mp, const double* sc,
-                                                          double* sig, int64_t n,
+                                                          double* sig, int gs, int64_t n,
                                                           DevState* st) {
   if (!st->any_active || !st->iter_active) return;
   const Cols<T> X = Mp.nxt();
   const int lane = lane_id();
-  const int64_t ng = (n + 63) / 64;
+  const int64_t ng = (n + gs - 1) / gs;
   for (int64_t gi = blockIdx.x; gi < ng; gi += gridDim.x) {
-    const Group64 g = group_load(X, gi * 64, n);
+    const Group64 g = group_load(X, gi * gs, gs, n);
     for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE) {
       const int x = x0 + lane;
       const int xc = min(x, g.T - 1);              // all lanes shuffle together
@@ -3446,41 +3491,59 @@ void launch_score(const Csr& A, Pair<T> M, double* sc, double* sig, BigList big,
                      dim3(SPAI_WAVE), score_lds(large, ell), s, A, M, sc, big, st, 1, large.L, large.H);
   hipLaunchKernelGGL((k_score<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), 0, s, A, M, sc, big, st,
                      2, huge.L, huge.H);
-  const int ng = (int)std::min<int64_t>((n + 63) / 64, 1 << 30);
+  const int gs = group_cols(n), ng = groups(n, gs);
   hipLaunchKernelGGL(k_score_pair<T>, dim3(std::min(ng, resident_grid(k_score_pair<T>, 0))),
-                     dim3(SPAI_WAVE), 0, s, M, sc, sig, n, st);
+                     dim3(SPAI_WAVE), 0, s, M, sc, sig, gs, n, st);
 }
 
 // ============================================================================
 // keep rule + in-place compaction
 // ============================================================================
 
-// Keep rule and in-place compaction, 64 columns per one-wave workgroup (grouped walk).
+// Keep rule and in-place compaction of up to three lists in one launch (blockIdx.y), every
+// wave a group of columns at a time (grouped walk), eight waves a workgroup that do not wait
+// for each other.  Bound by its workgroups' ends before this: each one-wave workgroup added
+// its sums to the record with three atomics, at some 10 ns each on one address (57 us a list
+// for the 1024 workgroups of the 256 x 256 grid, 170 us a list for 2048 at 96^3); the sums now
+// go to a slot per workgroup and the last one adds them: 63 us for all three lists and the
+// end of the drop (4.6 us of its own before) against 176, and 402 us against 512 at 96^3.
 // Each round of 64 consecutive entries takes a ballot of the kept ones; a kept
 // entry's place in its column is the column's running count (s_run, LDS) plus the
 // kept entries before it in the same column segment of the round.  It moves only
 // toward the column start, and a batch's entries are all loaded before any is written.
 // SC: the keys are the scores stored beside the candidates (score non-null).
+constexpr int kCompWaves = 8;
 template <typename T, bool SC>
-__global__ __launch_bounds__(SPAI_WAVE) void k_compact(Pair<T> Xp, int kind, int colcap, int sym,
-                                                       int global, const double* tcol,
-                                                       const double* gthr, double eta, int64_t n,
-                                                       DevState* st, const double* score) {
+__global__ __launch_bounds__(kCompWaves * SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(SC ? 1 : 4))) void k_compact(Pair<T> Mp, Pair<T> Pp, Pair<T> PTp,
+                                                       int kind0, int colcap, int sym, int global,
+                                                       const double* tM, const double* tP,
+                                                       double eta, int gs, int64_t n,
+                                                       unsigned long long* slots,
+                                                       DevState* st, const double* score,
+                                                       DropEnd end) {
   if (!st->any_active || !st->iter_active) return;
-  __shared__ int s_run[SPAI_WAVE];
-  const Cols<T> X = Xp.nxt();
+  __shared__ int s_runs[kCompWaves][SPAI_WAVE];
+  __shared__ unsigned long long s_tot[kCompWaves][3];
+  const int wv = threadIdx.x / SPAI_WAVE;
+  int* s_run = s_runs[wv];
+  const int kind = kind0 + (int)blockIdx.y;
+  const Cols<T> X = kind == 0 ? Mp.nxt() : kind == 1 ? Pp.nxt() : PTp.nxt();
+  const double* tcol = kind == 0 ? tM : tP;
+  const double* gthr = kind == 0 ? &st->thrM : &st->thrP;
   const int lane = lane_id();
   const double gt = global ? *gthr : 0.0;
   const double graw = global ? gthr[2] : 0.0;      // the cut before the tie factor
   const bool need_tk = colcap && ((kind == 0 && sym) || kind == 2);
   unsigned long long kept = 0, seen = 0, band = 0;
-  const int64_t ng = (n + 63) / 64;
-  for (int64_t gi = blockIdx.x; gi < ng; gi += gridDim.x) {
-    const Group64 g = group_load(X, gi * 64, n);
+  const int64_t ng = (n + gs - 1) / gs;
+  for (int64_t gi = (int64_t)blockIdx.x * kCompWaves + wv; gi < ng;
+       gi += (int64_t)gridDim.x * kCompWaves) {
+    const Group64 g = group_load(X, gi * gs, gs, n);
     const int64_t jl = g.j0 + lane;
-    const double tl = (colcap && jl < n) ? tcol[jl] : 0.0;   // this lane's column threshold
+    const bool mine = lane < gs && jl < n;
+    const double tl = (colcap && mine) ? tcol[jl] : 0.0;     // this lane's column threshold
     s_run[lane] = 0;
-    __syncthreads();
+    wave_sync();
     // A batch's entries are loaded before the stores of the batch before it go out: one
     // counter tracks both loads and stores and completes in order, so the first use of
     // a batch loaded after those stores would also wait for them to be written.  It is
@@ -3566,9 +3629,9 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_compact(Pair<T> Xp, int kind, int
         }
         const int cn = __builtin_amdgcn_update_dpp(c, c, 0x130, 0xf, 0xf, false);   // lane + 1's
         const bool last = ok && (lane == SPAI_WAVE - 1 || x + 1 >= g.T || cn != c);
-        __syncthreads();
+        wave_sync();
         if (last) s_run[c] = base + before + (keep ? 1 : 0);
-        __syncthreads();
+        wave_sync();
       }
       if (more) {
 #pragma unroll
@@ -3580,48 +3643,76 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_compact(Pair<T> Xp, int kind, int
         }
       }
     }
-    if (jl < n) {
+    if (mine) {
       X.len[jl] = s_run[lane];
       kept += (unsigned long long)s_run[lane];
       seen += (unsigned long long)g.cl;
     }
-    __syncthreads();
+    wave_sync();
   }
   kept = (unsigned long long)wave_sum_ll((long long)kept);
   seen = (unsigned long long)wave_sum_ll((long long)seen);
   band = (unsigned long long)wave_sum_ll((long long)band);
-  if (lane == 0 && blockIdx.x < kCntSlots) {
-    st->cnt[(3 + kind) * kCntSlots + blockIdx.x] += kept;
-    st->cnt[kind * kCntSlots + blockIdx.x] += seen;
+  if (lane == 0) {
+    s_tot[wv][0] = kept;
+    s_tot[wv][1] = seen;
+    s_tot[wv][2] = band;
   }
-  // the iteration's record (M and P; P^T mirrors P); integer sums, so the order of the
-  // workgroups' atomics does not matter
+  __syncthreads();
+  const int nb = (int)(gridDim.x * gridDim.y);
+  if (threadIdx.x < 3) {
+    unsigned long long v = 0;
+    for (int w = 0; w < kCompWaves; ++w) v += s_tot[w][threadIdx.x];
+    if (threadIdx.x < 2)
+      st->cnt[((threadIdx.x == 0 ? 3 : 0) + kind) * kCntSlots + blockIdx.x] += v;
+    agent_put(&slots[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 3 + threadIdx.x], v);
+  }
+  // the iteration's record (M and P; P^T mirrors P) and the end of the drop, by the last
+  // workgroup: an atomic of every workgroup on the record's words would cost some 10 ns each
+  if (!last_block(&st->sel_ticket, nb)) return;
   const int ri = st->rec_i;
-  if (lane == 0 && kind < 2 && st->rec && ri >= 0 && ri < st->rec_cap) {
-    unsigned long long* r = st->rec + (int64_t)ri * kRec + 3 * kind;
-    // candidates: the ones written plus (once) those the update left out below a floor
-    const unsigned long long below = blockIdx.x == 0 ? (kind == 0 ? st->belowM : st->belowP) : 0;
-    atomicAdd(&r[0], kept);
-    atomicAdd(&r[1], seen + below);
-    atomicAdd(&r[2], band);
+  const bool rec = st->rec && ri >= 0 && ri < st->rec_cap;
+  for (int y = wv; y < (int)gridDim.y; y += kCompWaves) {
+    const int kd = kind0 + y;
+    if (kd > 1 || !rec) continue;
+    unsigned long long v[3] = {0, 0, 0};
+    for (int b = lane; b < (int)gridDim.x; b += SPAI_WAVE)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) v[i] += agent_count(&slots[((int64_t)y * gridDim.x + b) * 3 + i]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[i] = (unsigned long long)wave_sum_ll((long long)v[i]);
+    if (lane == 0) {
+      unsigned long long* r = st->rec + (int64_t)ri * kRec + 3 * kd;
+      // candidates: the ones written plus (once) those the update left out below a floor
+      r[0] += v[0];
+      r[1] += v[1] + (kd == 0 ? st->belowM : st->belowP);
+      r[2] += v[2];
+    }
   }
+  __syncthreads();                     // the record has read the counts that the end clears
+  if (end.on && threadIdx.x == 0) drop_end(end, st);
 }
 
 template <typename T>
-void launch_compact(Pair<T> X, int kind, int colcap, int sym, int global, const double* tcol,
-                    double eta, int64_t n, DevState* st, hipStream_t s, const double* score) {
-  const double* gthr = kind == 0 ? &st->thrM : &st->thrP;
-  const int ng = (int)std::min<int64_t>((n + 63) / 64, 1 << 30);
-  if (score)
-    hipLaunchKernelGGL((k_compact<T, true>), dim3(std::min(ng, resident_grid(k_compact<T, true>, 0))),
-                       dim3(SPAI_WAVE), 0, s, X, kind, colcap, sym, global, tcol, gthr, eta, n, st,
-                       score);
-  else   // two workgroups per SIMD: more waves in flight made the pass slower at 96^3
-         // (0.52 ms at 8 per compute unit, 0.62 at 16, 0.66 at 4)
-    hipLaunchKernelGGL((k_compact<T, false>),
-                       dim3(std::min({ng, resident_grid(k_compact<T, false>, 0), per_cu_grid(8)})),
-                       dim3(SPAI_WAVE), 0, s, X, kind, colcap, sym, global, tcol, gthr, eta, n, st,
-                       score);
+void launch_drop(Pair<T> M, Pair<T> P, Pair<T> PT, int doM, int doP, int colcap, int sym,
+                 int global, const double* tM, const double* tP, double eta, int64_t n,
+                 double* blockpart, DevState* st, hipStream_t s, const double* score, int floors,
+                 double frac) {
+  const int gs = group_cols(n), ng = groups(n, gs);
+  DropEnd end{0, doM, doP, floors, frac};
+  unsigned long long* slots = (unsigned long long*)blockpart;
+  // one workgroup of eight waves per compute unit and list, the three lists in one launch:
+  // two or three per unit took the same
+  const int gx = std::min({(ng + kCompWaves - 1) / kCompWaves, per_cu_grid(1), kDropSlots});
+  auto go = [&](auto kern, int kind0, int kinds, bool last) {
+    end.on = last;
+    hipLaunchKernelGGL(kern, dim3(gx, kinds), dim3(kCompWaves * SPAI_WAVE), 0, s, M, P, PT, kind0,
+                       colcap, sym, global, tM, tP, eta, gs, n, slots, st, score, end);
+  };
+  if (score && doM) go(k_compact<T, true>, 0, 1, !doP);
+  const int k0 = doM && !score ? 0 : 1, k1 = doP ? 3 : 1;
+  score = nullptr;
+  if (k1 > k0) go(k_compact<T, false>, k0, k1 - k0, true);
 }
 
 // ============================================================================
@@ -3703,7 +3794,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_step(int method, Seg seg
                                                              DevState* st) {
   __shared__ double d[kND];
   chunk_sums<kND>(colpart, n, chunk, part);
-  if (!last_block(&st->red_ticket)) return;
+  if (!last_block(&st->red_ticket, (int)gridDim.x)) return;
   for (int i = threadIdx.x >> 6; i < kND; i += kRedThreads / SPAI_WAVE) {
     const double v = blocks_sum_wave(part + i, kND, nb);
     if (lane_id() == 0) d[i] = v;
@@ -3802,7 +3893,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_post(int method, Seg seg
   if (!st->iter_active) return;
   chunk_sums<1>(colnorm, n, chunk, part);
   if (colrz) chunk_sums<1>(colrz, n, chunk, part + nb);
-  if (!last_block(&st->red_ticket)) return;
+  if (!last_block(&st->red_ticket, (int)gridDim.x)) return;
   if (threadIdx.x >= SPAI_WAVE) return;
   const double rr = blocks_sum_wave(part, 1, nb);
   const double rz = colrz ? blocks_sum_wave(part + nb, 1, nb) : rr;
@@ -3823,19 +3914,6 @@ void launch_post(int method, const Seg& seg, const double* colnorm, const double
   if (colrz) launch_reduce(colrz, 1, n, seg, seg_beg, red_rz, blockpart, s);
   hipLaunchKernelGGL(k_scal_post, dim3((seg.nseg + 255) / 256), dim3(256), 0, s, method, seg, red,
                      colrz ? red_rz : nullptr, tol, hist, hist_cap, setup, st);
-}
-
-// the end of a drop in one launch: the new M (doM) and P (doP) become current, and with
-// floors the next iteration's floors are set
-__global__ void k_drop_finish(DevState* st, int doM, int doP, int floors, double frac) {
-  if (!st->iter_active) return;
-  if (doM) st->curM ^= 1;
-  if (doP) st->curP ^= 1;
-  if (floors) floor_next_body(st, doM, doP, frac);
-}
-
-void launch_drop_finish(DevState* st, int doM, int doP, int floors, double frac, hipStream_t s) {
-  hipLaunchKernelGGL(k_drop_finish, dim3(1), dim3(1), 0, s, st, doM, doP, floors, frac);
 }
 
 // ---- explicit instantiations
@@ -3868,8 +3946,9 @@ void launch_drop_finish(DevState* st, int doM, int doP, int floors, double frac,
   template void launch_global_select<T>(Pair<T>, int, int64_t, double, int, unsigned long long*,  \
                                         unsigned long long*, int64_t, DevState*, hipStream_t,     \
                                         const double*);                                           \
-  template void launch_compact<T>(Pair<T>, int, int, int, int, const double*, double, int64_t,    \
-                                  DevState*, hipStream_t, const double*);                         \
+  template void launch_drop<T>(Pair<T>, Pair<T>, Pair<T>, int, int, int, int, int, const double*, \
+                               const double*, double, int64_t, double*, DevState*, hipStream_t,   \
+                               const double*, int, double);                                       \
   template void launch_score<T>(const Csr&, Pair<T>, double*, double*, BigList, DevState*, Tile,  \
                                 Tile, Tile, int64_t, hipStream_t);
 

@@ -50,6 +50,7 @@ struct DevState {
   unsigned long long sel_count;   // keys in the selection buffer
   unsigned long long sel_prefix;  // key bits fixed so far
   long long sel_rank;             // 1-based rank still to find inside the prefix
+  long long sel_left;             // collected keys that match the prefix
   long long sel_diag;             // diagonal candidates (excluded, always kept)
   int sel_done;                   // 1: threshold known
   int iter_active;                // 1: the current iteration runs (set by the step kernel)
@@ -59,6 +60,7 @@ struct DevState {
   int rec_i, rec_cap;
   int rec_next;                   // the next iteration's record
   int sel_ticket;                 // workgroups done with a selection pass (0 between launches)
+  int sel_few;                    // keys gathered by a pass (0 between launches)
   int off_ticket;                 // ... with a bounds pass
   int red_ticket;                 // ... with a reduction
   // speculative floor of the global cap (magnitude keys, one matrix): the lean update

@@ -2864,14 +2864,14 @@ __device__ __forceinline__ int64_t group_src(const Group64& g, int c, int x) {
 
 // Find, with one block (a power of two of at most 1024 threads, nbins a multiple of it),
 // the bin i holding the rank-th largest key of a histogram, at(i) its count of bin i, counted
-// from the top bin down: *bin = i, *above = keys in bins above i.  Each thread owns
-// nbins / blockDim consecutive bins (thread 0 the highest).
+// from the top bin down: *bin = i, *above = keys in bins above i, *in = keys in it.  Each
+// thread owns nbins / blockDim consecutive bins (thread 0 the highest).
 template <typename F>
 __device__ inline void find_bin_desc(F at, int nbins, long long rank, long long* total, int* bin,
-                                     long long* above) {
+                                     long long* above, long long* in) {
   __shared__ long long s_wave[16];
   __shared__ int s_bin;
-  __shared__ long long s_above;
+  __shared__ long long s_above, s_in;
   const int t = threadIdx.x, lane = lane_id();
   const int per = nbins / (int)blockDim.x;
   const int hi = nbins - 1 - t * per;            // this thread's bins: hi, hi-1, ..., hi-per+1
@@ -2880,7 +2880,7 @@ __device__ inline void find_bin_desc(F at, int nbins, long long rank, long long*
   for (int k = 0; k < per; ++k) loc += (long long)at(hi - k);
   const long long wsum = wave_sum_ll(loc);
   if (lane == 0) s_wave[t >> 6] = wsum;
-  if (t == 0) { s_bin = -1; s_above = 0; }
+  if (t == 0) { s_bin = -1; s_above = 0; s_in = 0; }
   __syncthreads();
   long long before = 0, tot = 0;
   for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
@@ -2898,7 +2898,7 @@ __device__ inline void find_bin_desc(F at, int nbins, long long rank, long long*
       long long acc = before;
       for (int k = 0; k < per; ++k) {
         const long long c = (long long)at(hi - k);
-        if (acc + c >= rank) { s_bin = hi - k; s_above = acc; break; }
+        if (acc + c >= rank) { s_bin = hi - k; s_above = acc; s_in = c; break; }
         acc += c;
       }
     }
@@ -2907,12 +2907,13 @@ __device__ inline void find_bin_desc(F at, int nbins, long long rank, long long*
   *total = tot;
   *bin = s_bin;
   *above = s_above;
+  *in = s_in;
 }
 
 // the decision after the exponent histogram (one thread): bin holds the (b+1)-th largest of
 // `total` keys, `above` of them in higher bins; sets the threshold where nothing is selected
 __device__ inline void sel_exp_decide(long long b, long long total, int bin, long long above,
-                                      int signed_keys, double* thr, DevState* st) {
+                                      long long in, int signed_keys, double* thr, DevState* st) {
   st->sel_count = 0;
   st->sel_diag = 0;                 // for the next selection
   if (b < 0) {                      // cap below the diagonal count: keep only the diagonal
@@ -2932,6 +2933,7 @@ __device__ inline void sel_exp_decide(long long b, long long total, int bin, lon
   }
   st->sel_prefix = (unsigned long long)bin << 52;
   st->sel_rank = (b + 1) - above;
+  st->sel_left = in;
   st->sel_done = 0;
 }
 
@@ -2943,6 +2945,8 @@ __device__ inline void sel_exp_decide(long long b, long long total, int bin, lon
 // workgroup finds the exponent bin of the (b+1)-th largest, b = m - (diagonal count if
 // excluded), and clears the histogram for the passes over the collected keys.
 constexpr int kHistWaves = 16;
+constexpr int kExpCopies = 4;   // of the exponent histogram: its keys share a few bins, and LDS
+                                // atomics of a wave on one word go one after the other
 template <typename T, bool SC>
 __global__ __launch_bounds__(kHistWaves * SPAI_WAVE) void k_sel_hist_exp(Pair<T> Xp, const double* sc,
                                                             int excl_diag, int64_t m,
@@ -2951,10 +2955,10 @@ __global__ __launch_bounds__(kHistWaves * SPAI_WAVE) void k_sel_hist_exp(Pair<T>
                                                             DevState* st) {
   if (!st->any_active || !st->iter_active) return;
   constexpr int NB = SC ? 4096 : 2048;
-  __shared__ unsigned int h[NB];
+  __shared__ unsigned int h[NB * kExpCopies];
   const int lane = lane_id();
   const int wv = threadIdx.x / SPAI_WAVE;
-  for (int i = threadIdx.x; i < NB; i += kHistWaves * SPAI_WAVE) h[i] = 0;
+  for (int i = threadIdx.x; i < NB * kExpCopies; i += kHistWaves * SPAI_WAVE) h[i] = 0;
   __syncthreads();
   const Cols<T> X = Xp.nxt();
   int diag = 0;                                  // a wave's columns are fewer than 2^31
@@ -2990,13 +2994,17 @@ __global__ __launch_bounds__(kHistWaves * SPAI_WAVE) void k_sel_hist_exp(Pair<T>
           continue;
         }
         const unsigned long long key = SC ? ord_key(sv[u]) : mag_key((double)val[u]);
-        atomicAdd(&h[(int)(key >> 52)], 1u);
+        atomicAdd(&h[(int)(key >> 52) * kExpCopies + (lane & (kExpCopies - 1))], 1u);
       }
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < NB; i += kHistWaves * SPAI_WAVE)
-    if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
+  for (int i = threadIdx.x; i < NB; i += kHistWaves * SPAI_WAVE) {
+    unsigned int c = 0;
+#pragma unroll
+    for (int q = 0; q < kExpCopies; ++q) c += h[i * kExpCopies + q];
+    if (c) atomicAdd(&hist[i], (unsigned long long)c);
+  }
   __shared__ int s_diag[kHistWaves];
   diag = wave_sum_int(diag);
   if (lane == 0) s_diag[wv] = diag;
@@ -3009,12 +3017,12 @@ __global__ __launch_bounds__(kHistWaves * SPAI_WAVE) void k_sel_hist_exp(Pair<T>
   if (!last_block(&st->sel_ticket, (int)gridDim.x)) return;
   const long long b =
       m - (excl_diag ? (long long)agent_count((const unsigned long long*)&st->sel_diag) : 0);
-  long long total, above;
+  long long total, above, in;
   int bin;
-  find_bin_desc([&](int i) { return agent_count(hist + i); }, NB, b + 1, &total, &bin, &above);
+  find_bin_desc([&](int i) { return agent_count(hist + i); }, NB, b + 1, &total, &bin, &above, &in);
   // every read of the histogram is done (the search ends on a barrier)
   for (int i = threadIdx.x; i < NB; i += kHistWaves * SPAI_WAVE) hist[i] = 0;
-  if (threadIdx.x == 0) sel_exp_decide(b, total, bin, above, SC ? 1 : 0, thr, st);
+  if (threadIdx.x == 0) sel_exp_decide(b, total, bin, above, in, SC ? 1 : 0, thr, st);
 }
 
 // keys whose exponent bin is the selected one, staged in LDS (one stage per wave) and flushed
@@ -3121,8 +3129,32 @@ __device__ inline void sel_finish(double eta, int signed_keys, double* thr, DevS
   st->sel_done = 1;
 }
 
-// histogram of 13 key bits at `shift` among the collected keys matching the prefix above; the
-// last workgroup finds the bin of the key sought and clears the histogram
+// The rank-th largest of m <= kSelFew keys in LDS (one workgroup; every thread calls it): each
+// key's place by comparisons, the same value for any order of equal keys.
+constexpr int kSelFew = 256;
+__device__ inline unsigned long long rank_keys(const unsigned long long* key, int m,
+                                               long long rank) {
+  __shared__ unsigned long long s_key;
+  const int t = threadIdx.x;
+  if (t < m) {
+    const unsigned long long x = key[t];
+    int r = 0;
+#pragma unroll 8
+    for (int f = 0; f < m; ++f) {
+      const unsigned long long y = key[f];
+      r += (y > x || (y == x && f < t)) ? 1 : 0;
+    }
+    if (r == rank - 1) s_key = x;
+  }
+  __syncthreads();
+  return s_key;
+}
+
+// One pass over the collected keys.  While more than kSelFew of them match the bits known so
+// far: the histogram of the next 13 (at `shift`), whose bin the last workgroup finds (it
+// clears the histogram).  Otherwise the matching keys themselves are gathered and ranked, and
+// the passes that remain return at once (5 us a pass against 9.5, mostly the last workgroup's
+// reading of 8192 bins).
 __global__ __launch_bounds__(1024) void k_sel_pass(const unsigned long long* selbuf, int shift,
                                                    int last, double eta, int signed_keys,
                                                    unsigned long long* hist, double* thr,
@@ -3132,98 +3164,97 @@ __global__ __launch_bounds__(1024) void k_sel_pass(const unsigned long long* sel
   const unsigned long long cnt = st->sel_count;
   const long long rank = st->sel_rank;
   const unsigned long long prefix = st->sel_prefix;
+  const int hi = shift + 13;
+  const unsigned long long pre = prefix >> hi;
+  const bool few = st->sel_left <= kSelFew;
   if ((unsigned long long)blockIdx.x * 1024 < cnt) {
-    for (int i = threadIdx.x; i < 8192; i += 1024) h[i] = 0;
-    __syncthreads();
-    const int hi = shift + 13;
-    const unsigned long long pre = prefix >> hi;
+    if (!few) {
+      for (int i = threadIdx.x; i < 8192; i += 1024) h[i] = 0;
+      __syncthreads();
+    }
     for (unsigned long long i = (unsigned long long)blockIdx.x * 1024 + threadIdx.x; i < cnt;
          i += (unsigned long long)gridDim.x * 1024) {
       const unsigned long long key = selbuf[i];
-      if ((key >> hi) == pre) atomicAdd(&h[(int)((key >> shift) & 8191ull)], 1u);
+      if ((key >> hi) != pre) continue;
+      if (few) agent_put(&hist[atomicAdd(&st->sel_few, 1)], key);
+      else atomicAdd(&h[(int)((key >> shift) & 8191ull)], 1u);
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < 8192; i += 1024)
-      if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
+    if (!few) {
+      __syncthreads();
+      for (int i = threadIdx.x; i < 8192; i += 1024)
+        if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
+    }
   }
   if (!last_block(&st->sel_ticket, (int)gridDim.x)) return;
-  long long total, above;
+  if (few) {
+    const int m = (int)st->sel_left;
+    unsigned long long* key = (unsigned long long*)h;
+    if ((int)threadIdx.x < m) {
+      key[threadIdx.x] = agent_count(hist + threadIdx.x);
+      hist[threadIdx.x] = 0;
+    }
+    __syncthreads();
+    const unsigned long long x = rank_keys(key, m, rank);
+    if (threadIdx.x != 0) return;
+    st->sel_few = 0;
+    st->sel_prefix = x;
+    sel_finish(eta, signed_keys, thr, st);
+    return;
+  }
+  long long total, above, in;
   int bin;
-  find_bin_desc([&](int i) { return agent_count(hist + i); }, 8192, rank, &total, &bin, &above);
+  find_bin_desc([&](int i) { return agent_count(hist + i); }, 8192, rank, &total, &bin, &above, &in);
   for (int i = threadIdx.x; i < 8192; i += 1024) hist[i] = 0;     // for the next pass
   if (threadIdx.x != 0) return;
   if (bin >= 0) {
     st->sel_prefix = prefix | ((unsigned long long)bin << shift);
     st->sel_rank = rank - above;
+    st->sel_left = in;
   }
   if (shift == last) sel_finish(eta, signed_keys, thr, st);
 }
 
 // The whole selection of a small matrix in one workgroup, its 16 waves walking the columns:
-// a launch is most of what the passes above cost there (6 of them, 2.5 to 7 us each).  The keys of the selected exponent, in selbuf, pass by pass as in k_sel_hist_buf and
-// k_sel_find_buf, with the histogram in LDS.
-__device__ inline void sel_passes(const unsigned long long* selbuf, unsigned* h, int last,
-                                  double eta, int signed_keys, double* thr, DevState* st) {
-  const unsigned long long cnt = st->sel_count;
-  unsigned long long prefix = st->sel_prefix;
-  long long rank = st->sel_rank;
-  for (int shift = 39; shift >= last; shift -= 13) {
-    for (int i = threadIdx.x; i < 8192; i += 1024) h[i] = 0;
-    __syncthreads();
-    const int hi = shift + 13;
-    for (unsigned long long i = threadIdx.x; i < cnt; i += 1024) {
-      const unsigned long long key = selbuf[i];
-      if ((key >> hi) == (prefix >> hi)) atomicAdd(&h[(int)((key >> shift) & 8191ull)], 1u);
-    }
-    __syncthreads();
-    long long total, above;
-    int bin;
-    find_bin_desc([&](int i) { return h[i]; }, 8192, rank, &total, &bin, &above);
-    __syncthreads();
-    if (bin >= 0) {
-      prefix |= (unsigned long long)bin << shift;
-      rank -= above;
-    }
-  }
-  if (threadIdx.x == 0) {
-    st->sel_prefix = prefix;
-    st->sel_rank = rank;
-    sel_finish(eta, signed_keys, thr, st);
-  }
-}
-
+// a launch is most of what the passes above cost there (6 of them, 2.5 to 7 us each).  With
+// this and without the second pass, 20 steps on the 32 x 32 grid take 3.55 ms against 4.86
+// (12 launches for a selection, twice); kSelSmallRows is two groups a wave.  The keys of the
+// selected exponent stay in LDS (kSelKeys of them; more go to selbuf); the histograms are
+// there too.
 constexpr int64_t kSelSmallRows = 2048;
+constexpr int kSelKeys = 2048;
 template <typename T, bool SC>
 __global__ __launch_bounds__(1024) void k_sel_small(Pair<T> Xp, const double* sc, int excl_diag,
                                                     int64_t m, unsigned long long* selbuf,
                                                     int last, double eta, double* thr, int64_t n,
                                                     DevState* st) {
   if (!st->any_active || !st->iter_active) return;
-  __shared__ unsigned h[8192];
-  __shared__ unsigned s_cnt;
+  __shared__ unsigned h[SC ? 4096 * kExpCopies : 8192];
+  __shared__ unsigned long long s_keys[kSelKeys];
+  __shared__ unsigned long long s_few[kSelFew];
+  __shared__ unsigned s_cnt, s_nfew;
   __shared__ int s_diag;
   constexpr int NB = SC ? 4096 : 2048;
-  constexpr int gs = 64;
+  constexpr int gs = 64, U = 8;
   const int lane = lane_id(), wv = threadIdx.x / SPAI_WAVE;
-  for (int i = threadIdx.x; i < NB; i += 1024) h[i] = 0;
+  for (int i = threadIdx.x; i < NB * kExpCopies; i += 1024) h[i] = 0;
   if (threadIdx.x == 0) {
     s_cnt = 0;
+    s_nfew = 0;
     s_diag = 0;
   }
   __syncthreads();
   const Cols<T> X = Xp.nxt();
   const int64_t ng = (n + gs - 1) / gs;
-  // f(key) for every candidate that takes part (every lane calls it; take: this lane's does)
-  int diag = 0;
+  // f(key, takes part, diagonal) for every candidate, on all lanes together
   auto walk = [&](auto f) {
     for (int64_t gi = wv; gi < ng; gi += 16) {
       const Group64 g = group_load(X, gi * gs, gs, n);
-      for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE * kGU) {
-        int col[kGU], idx[kGU];
-        T val[kGU];
-        double sv[kGU];
+      for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE * U) {
+        int col[U], idx[U];
+        T val[U];
+        double sv[U];
 #pragma unroll
-        for (int u = 0; u < kGU; ++u) {
+        for (int u = 0; u < U; ++u) {
           const int x = x0 + u * SPAI_WAVE + lane;
           const int xc = min(x, g.T - 1);            // all lanes shuffle together
           const int c = group_col(g, xc);
@@ -3239,7 +3270,7 @@ __global__ __launch_bounds__(1024) void k_sel_small(Pair<T> Xp, const double* sc
           }
         }
 #pragma unroll
-        for (int u = 0; u < kGU; ++u) {
+        for (int u = 0; u < U; ++u) {
           const bool dg = col[u] >= 0 && excl_diag && idx[u] == (int)(g.j0 + col[u]);
           const unsigned long long key = SC ? ord_key(sv[u]) : mag_key((double)val[u]);
           f(key, col[u] >= 0 && !dg, dg);
@@ -3247,34 +3278,71 @@ __global__ __launch_bounds__(1024) void k_sel_small(Pair<T> Xp, const double* sc
       }
     }
   };
+  int diag = 0;
   walk([&](unsigned long long key, bool take, bool dg) {
     diag += dg;
-    if (take) atomicAdd(&h[(int)(key >> 52)], 1u);
+    if (take) atomicAdd(&h[(int)(key >> 52) * kExpCopies + (lane & (kExpCopies - 1))], 1u);
   });
   diag = wave_sum_int(diag);
   if (lane == 0 && diag) atomicAdd(&s_diag, diag);
   __syncthreads();
   const long long b = m - (excl_diag ? s_diag : 0);
-  long long total, above;
+  long long total, above, in;
   int bin;
-  find_bin_desc([&](int i) { return h[i]; }, NB, b + 1, &total, &bin, &above);
-  if (threadIdx.x == 0) sel_exp_decide(b, total, bin, above, SC ? 1 : 0, thr, st);
-  __syncthreads();
-  if (b < 0 || total <= b) return;
-  const unsigned long long want = (unsigned long long)bin;
+  auto at = [&](int i) { return h[i]; };
+  find_bin_desc(
+      [&](int i) {
+        unsigned c = 0;
+#pragma unroll
+        for (int q = 0; q < kExpCopies; ++q) c += h[i * kExpCopies + q];
+        return c;
+      },
+      NB, b + 1, &total, &bin, &above, &in);
+  if (b < 0 || total <= b) {
+    if (threadIdx.x == 0) sel_exp_decide(b, total, bin, above, in, SC ? 1 : 0, thr, st);
+    return;
+  }
+  unsigned long long prefix = (unsigned long long)bin << 52;
+  long long rank = (b + 1) - above;
+  const unsigned cnt = (unsigned)in;
+  unsigned long long* keys = cnt <= kSelKeys ? s_keys : selbuf;
   walk([&](unsigned long long key, bool take, bool) {
-    take = take && (key >> 52) == want;
+    take = take && (key >> 52) == (prefix >> 52);
     const unsigned long long bal = __ballot(take);
     if (bal == 0ull) return;
     unsigned base = 0;
     if (lane == 0) base = atomicAdd(&s_cnt, (unsigned)__popcll(bal));
     base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
-    if (take) selbuf[base + __popcll(bal & lanemask_lt())] = key;
+    if (take) keys[base + __popcll(bal & lanemask_lt())] = key;
   });
-  __syncthreads();
-  if (threadIdx.x == 0) st->sel_count = s_cnt;
-  __syncthreads();
-  sel_passes(selbuf, h, last, eta, SC ? 1 : 0, thr, st);
+  for (int shift = 39; shift >= last; shift -= 13) {
+    const int hi = shift + 13;
+    const bool few = in <= kSelFew;
+    if (!few)
+      for (int i = threadIdx.x; i < 8192; i += 1024) h[i] = 0;
+    __syncthreads();
+    for (unsigned i = threadIdx.x; i < cnt; i += 1024) {
+      const unsigned long long key = keys[i];
+      if ((key >> hi) != (prefix >> hi)) continue;
+      if (few) s_few[atomicAdd(&s_nfew, 1u)] = key;
+      else atomicAdd(&h[(int)((key >> shift) & 8191ull)], 1u);
+    }
+    __syncthreads();
+    if (few) {
+      prefix = rank_keys(s_few, (int)in, rank);
+      break;
+    }
+    find_bin_desc(at, 8192, rank, &total, &bin, &above, &in);
+    __syncthreads();
+    if (bin >= 0) {
+      prefix |= (unsigned long long)bin << shift;
+      rank -= above;
+    }
+  }
+  if (threadIdx.x == 0) {
+    st->sel_prefix = prefix;
+    sel_finish(eta, SC ? 1 : 0, thr, st);
+  }
 }
 
 template <typename T>

@@ -5,7 +5,8 @@ import scipy.sparse as sp
 
 from oracle import spai_oracle as O
 from paper_2511_09753_amd import workloads as W
-from tests.helpers import history_array, oracle_rule, pattern_diff, require_gpu, value_err
+from tests.helpers import (history_array, oracle_rule, parse_state, pattern_diff, require_gpu,
+                           value_err)
 
 pytestmark = pytest.mark.gpu
 
@@ -205,3 +206,27 @@ def test_floors_from_their_first_size_on(method, precision):
         assert np.array_equal(hist, runs[0][0])
         assert (M != runs[0][1]).nnz == 0
         assert np.array_equal(rec, runs[0][2])
+
+
+# constant coefficients: thousands of candidates share the cut's magnitude, so the collected
+# keys neither fit one workgroup's LDS (2025 columns) nor thin out from pass to pass (2116)
+@pytest.mark.parametrize("side", [45, 46])
+@pytest.mark.parametrize("method", ["mr", "lomr"])
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_selection_among_ties(side, method, precision):
+    S = _spai()
+    A = W.laplace2d(side)
+    h = S.SPAI(A, method, "global", 1.5, True, max_iter=4, options=S.Options(precision=precision))
+    _, hist, _ = h.iterate(4)
+    M = h.get()
+    h.close()
+    ref = O.run(method, A, oracle_rule(A, "global", 1.5, True), 4)
+    want = np.asarray(ref.resid[1:len(hist) + 1])
+    if precision == "f64":
+        assert np.all(np.abs(np.asarray(hist) - want) <= 1e-10 * want)
+        assert pattern_diff(M, ref.M) == (set(), set())
+        assert value_err(M, ref.M) <= 1e-9
+    else:
+        # float32 values: the cut's tie band is decided on rounded values, so only the
+        # first step (its candidates have a handful of distinct magnitudes) is compared
+        assert abs(hist[0] - want[0]) <= 1e-5 * want[0]

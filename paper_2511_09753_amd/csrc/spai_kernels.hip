@@ -3984,6 +3984,84 @@ void launch_post(int method, const Seg& seg, const double* colnorm, const double
                      colrz ? red_rz : nullptr, tol, hist, hist_cap, setup, st);
 }
 
+// ============================================================================
+// export of a symmetric list as CSR
+// ============================================================================
+
+// offsets of X's columns packed without gaps (their lengths' exclusive sums)
+template <typename T>
+__global__ __launch_bounds__(1024) void k_len_offsets(Cols<T> X, int64_t n, int shift, int64_t* loc,
+                                                      int64_t* tile, int64_t* total, OffZero z,
+                                                      DevState* st) {
+  off_zero(z);
+  offsets_of([&](int64_t j, int) -> int64_t { return j < n ? X.len[j] : 0; }, n, shift, loc, tile,
+             total, st);
+}
+
+template <typename T>
+Offs launch_len_offsets(Cols<T> X, const OffBuf& o, const BigList& z, int64_t n, DevState* st,
+                        hipStream_t s) {
+  const Offs f = make_offs(o, n);
+  hipLaunchKernelGGL(k_len_offsets<T>, dim3((unsigned)f.tiles(n)), dim3(1024), 0, s, X, n, f.shift,
+                     o.loc, o.tile, o.total, OffZero{{z.count, nullptr, nullptr, nullptr}}, st);
+  return f;
+}
+
+// The columns packed, values widened: where every entry (k, j) has an equal entry (j, k) --
+// each is looked up in column k, by bits -- they are the rows of the CSR form, sorted as the
+// columns are; otherwise *bad is set and the caller transposes.  Groups of columns as in the
+// compaction: the reads and writes are of consecutive entries, the look-up is some five loads
+// one after the other that other waves hide.
+template <typename T>
+__global__ __launch_bounds__(kCompWaves * SPAI_WAVE) void k_export(Cols<T> X, Offs off,
+                                                                   const int64_t* total, int gs,
+                                                                   int64_t n, int64_t* rowptr,
+                                                                   int32_t* idx, double* val,
+                                                                   int* bad) {
+  const int lane = lane_id(), wv = threadIdx.x / SPAI_WAVE;
+  const int64_t ng = (n + gs - 1) / gs;
+  bool odd = false;
+  for (int64_t gi = (int64_t)blockIdx.x * kCompWaves + wv; gi < ng;
+       gi += (int64_t)gridDim.x * kCompWaves) {
+    const Group64 g = group_load(X, gi * gs, gs, n);
+    const int64_t o = off[g.j0];
+    if (lane < gs && g.j0 + lane < n) rowptr[g.j0 + lane] = o + g.ex;
+    for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE) {
+      const int x = x0 + lane;
+      const int xc = min(x, g.T - 1);              // all lanes shuffle together
+      const int c = group_col(g, xc);
+      const int64_t src = group_src(g, c, xc);
+      if (x >= g.T) continue;
+      const int j = (int)(g.j0 + c);
+      const int k = X.idx[src];
+      const T v = X.val[src];
+      idx[o + x] = k;
+      val[o + x] = (double)v;
+      if (k != j) {
+        const int64_t kb = X.beg[k];
+        const int p = bsearch_idx(X.idx + kb, X.len[k], j);
+        if (p < 0) odd = true;
+        else if constexpr (sizeof(T) == 4)
+          odd |= __float_as_uint((float)X.val[kb + p]) != __float_as_uint((float)v);
+        else
+          odd |= __double_as_longlong(X.val[kb + p]) != __double_as_longlong(v);
+      }
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) rowptr[n] = *total;
+  if (__ballot(odd) && lane == 0) *bad = 1;
+}
+
+template <typename T>
+void launch_export(Cols<T> X, Offs off, const int64_t* total, int64_t n, int64_t* rowptr,
+                   int32_t* idx, double* val, int* bad, hipStream_t s) {
+  const int gs = group_cols(n), ng = groups(n, gs);
+  const int g = std::min((ng + kCompWaves - 1) / kCompWaves,
+                         resident_grid(k_export<T>, 0, kCompWaves * SPAI_WAVE));
+  hipLaunchKernelGGL(k_export<T>, dim3(g), dim3(kCompWaves * SPAI_WAVE), 0, s, X, off, total, gs, n,
+                     rowptr, idx, val, bad);
+}
+
 // ---- explicit instantiations
 #define SPAI_INST(T)                                                                               \
   template void launch_init_m<T>(int64_t, Cols<T>, const double*, const Seg&, hipStream_t);       \
@@ -4017,6 +4095,10 @@ void launch_post(int method, const Seg& seg, const double* colnorm, const double
   template void launch_drop<T>(Pair<T>, Pair<T>, Pair<T>, int, int, int, int, int, const double*, \
                                const double*, double, int64_t, double*, DevState*, hipStream_t,   \
                                const double*, int, double);                                       \
+  template Offs launch_len_offsets<T>(Cols<T>, const OffBuf&, const BigList&, int64_t, DevState*, \
+                                      hipStream_t);                                               \
+  template void launch_export<T>(Cols<T>, Offs, const int64_t*, int64_t, int64_t*, int32_t*,      \
+                                 double*, int*, hipStream_t);                                     \
   template void launch_score<T>(const Csr&, Pair<T>, double*, double*, BigList, DevState*, Tile,  \
                                 Tile, Tile, int64_t, hipStream_t);
 

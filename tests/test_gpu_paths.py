@@ -230,3 +230,31 @@ def test_selection_among_ties(side, method, precision):
         # float32 values: the cut's tie band is decided on rounded values, so only the
         # first step (its candidates have a handful of distinct magnitudes) is compared
         assert abs(hist[0] - want[0]) <= 1e-5 * want[0]
+
+
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_export_of_an_unsymmetric_state(precision):
+    """A restored state may hold any M; the export transposes one that is not symmetric."""
+    S = _spai()
+    A = W.lognormal3d(8, 7)
+    n = A.shape[0]
+    h = S.SPAI(A, "mr", "global", 2.0, True, max_iter=8, options=S.Options(precision=precision))
+    h.iterate(4)
+    M = h.get()
+    state = bytearray(h.get_state())
+    hd, lists = parse_state(bytes(state))
+    cp, ix, vl = lists[0]
+    q = int(cp[n // 2])
+    j = n // 2
+    assert ix[q] != j                                  # an off-diagonal entry of column j
+    o = hd["list_offsets"][0] + 8 * (n + 1) + 4 * int(cp[n]) + vl.itemsize * q
+    state[o:o + vl.itemsize] = np.asarray([2 * vl[q]], dtype=vl.dtype).tobytes()
+    h.set_state(bytes(state))
+    got = h.get()
+    h.close()
+    want = M.tolil()
+    want[int(ix[q]), j] = 2 * float(vl[q])
+    want = want.tocsr()
+    want.sort_indices()
+    assert np.array_equal(got.indptr, want.indptr) and np.array_equal(got.indices, want.indices)
+    assert np.array_equal(got.data, want.data)

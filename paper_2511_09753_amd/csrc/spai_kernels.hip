@@ -3508,6 +3508,173 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_score(Csr A, Pair<T> Mp, double* 
   }
 }
 
+// The resident tier for A in ELL: the same sums in the same order (the scores are those of
+// k_score bit for bit) without sorts or searches.  The candidates sit in clash-free cells;
+// the rows of r~_l stay where an ordered hash put them, their values beside them by slot, and
+// only the list of occupied slots is made dense, so that every lane has a row to pull; a
+// candidate's neighbours -- all of them rows of r~_l, A being symmetric -- are found by walks
+// of their clusters, eight in lock step.  k_score's bitonic sort and binary searches in its
+// 12 KB tile took 1.39 ms at 48^3 (48 candidates and 105 rows a column, 13 waves a compute
+// unit); this takes 0.34 (0.31 with a
+// table of 256, which columns of more rows would leave).  A column of more than 128 candidates, or whose rows overflow the
+// table, goes to the larger tiles.
+constexpr int kScoreH = 512;
+template <typename T>
+__global__ __launch_bounds__(SPAI_WAVE) void k_score_lean(Csr A, Pair<T> Mp, double* sc,
+                                                          BigList big, DevState* st) {
+  if (!st->any_active || !st->iter_active) return;
+  constexpr int kEnd = kScoreH + kOhOver;
+  constexpr int kSh = 32 - 9;
+  static_assert(kScoreH == 1 << 9);
+  __shared__ __align__(16) unsigned char cell[kBtCells];
+  __shared__ __align__(16) BtEnt<T> ent[128 + 1];
+  __shared__ unsigned kt[kEnd];
+  __shared__ double rv[kEnd];
+  __shared__ unsigned short slots[kEnd];
+  const int lane = lane_id();
+  for (int i = lane; i < kBtCells / 4; i += SPAI_WAVE) ((unsigned*)cell)[i] = 0u;
+  if (lane == 0) ent[0] = BtEnt<T>{kBtNone, (T)0};
+  __syncthreads();
+  const Cols<T> M = Mp.nxt();
+  const int W = 1 << A.eshift;
+  ColumnWalk w(A.n, blockIdx.x, gridDim.x);
+  for (int64_t j = w.begin; j < w.end; j += w.step) {
+    const int lm = M.len[j];
+    const int64_t mb = M.beg[j];
+    if (lm > 128) {
+      defer_column(0, big, st, j);
+      continue;
+    }
+    int row[2], lst[2] = {0, 0}, pos[2];
+    T val[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int e = lane + k * SPAI_WAVE;
+      pos[k] = e;
+      const int64_t q = e < lm ? mb + e : 0;
+      row[k] = M.idx[q];
+      val[k] = M.val[q];
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int e = lane + k * SPAI_WAVE;
+      if (e < lm) ent[e + 1] = BtEnt<T>{row[k], val[k]};
+      else row[k] = -1;
+    }
+    for (int i = lane; i < kEnd; i += SPAI_WAVE) kt[i] = kOhEmpty;
+    const int a = bt_build<2, 1>(cell, row, lst, pos);
+    if (a < 0) {
+      defer_column(0, big, st, j);
+      continue;
+    }
+    const unsigned mul = bt_mul(a);
+    const int npass = lm > SPAI_WAVE ? 2 : 1;      // candidates per lane in use
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      if (k >= npass) break;
+      int rr = row[k];
+      for (int c = 0; c < W; c += 8) {
+        int cols[8];
+        ell_cols8(A, rr, c, cols);
+        const int c0[4] = {cols[0], cols[1], cols[2], cols[3]};
+        const int c1[4] = {cols[4], cols[5], cols[6], cols[7]};
+        ok = oh_insert_batch<4>(kt, kSh, c0) && ok;
+        ok = oh_insert_batch<4>(kt, kSh, c1) && ok;
+        if (cols[7] < 0) rr = -1;                  // the row ended in this chunk
+      }
+    }
+    {
+      const int kd[1] = {lane == 0 ? (int)j : -1};
+      ok = oh_insert_batch<1>(kt, kSh, kd) && ok;
+    }
+    if (__ballot(!ok) != 0ull) {
+      bt_clear<2, 1>(cell, row, lst, mul);
+      __syncthreads();
+      defer_column(0, big, st, j);
+      continue;
+    }
+    __syncthreads();
+    int nu = 0;                                    // occupied slots
+#pragma unroll
+    for (int base = 0; base < kEnd; base += SPAI_WAVE) {
+      const bool occ = kt[base + lane] != kOhEmpty;
+      const unsigned long long m = __ballot(occ);
+      if (occ) slots[nu + __popcll(m & lanemask_lt())] = (unsigned short)(base + lane);
+      nu += __popcll(m);
+    }
+    __syncthreads();
+    for (int t0 = 0; t0 < nu; t0 += SPAI_WAVE) {
+      const int t = t0 + lane;
+      if (t >= nu) continue;
+      const int s = slots[t];
+      const int u = ounhash(kt[s]);
+      const int64_t q0 = (int64_t)u << A.eshift;
+      double sum = 0.0;
+      for (int c = 0; c < W; c += 8) {
+        int cols[8];
+        T vals[8];
+        ell_chunk<T>(A, q0 + c, cols, vals);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          bool h0;
+          T x0;
+          bt_find1<T>(cell, mul, ent, cols[k], h0, x0);
+          // a masked product adds +-0 to a sum that is never -0: bitwise the skip
+          sum += (double)vals[k] * bt_masked<T>(h0, x0);
+        }
+        if (cols[7] < 0) break;
+      }
+      rv[s] = ((u == (int)j) ? 1.0 : 0.0) - sum;
+    }
+    __syncthreads();
+    // per candidate row k: (A r~_l)_k and ||A e_k||^2 from row k of A
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      if (k >= npass) break;
+      if (row[k] < 0) continue;
+      const double m = (double)val[k];
+      const int64_t q0 = (int64_t)row[k] << A.eshift;
+      double ar = 0.0, n2 = 0.0;
+      for (int c = 0; c < W; c += 8) {
+        int cols[8];
+        T vals[8];
+        ell_chunk<T>(A, q0 + c, cols, vals);
+        unsigned v[8];
+        int s[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          v[i] = cols[i] >= 0 ? ohash(cols[i]) : kOhEmpty;
+          s[i] = cols[i] >= 0 ? (int)(v[i] >> kSh) : kEnd - 1;
+        }
+        // a cluster's keys ascend: walk while the slot's is smaller (bounded by the
+        // insertion's bound; an empty slot is larger than any key)
+        for (int step = 0; step < kOhOver; ++step) {
+          bool more = false;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const bool less = kt[s[i]] < v[i] && cols[i] >= 0;
+            s[i] += less ? 1 : 0;
+            more = more || less;
+          }
+          if (!more) break;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          if (cols[i] < 0) continue;
+          const double x = (double)vals[i];
+          n2 += x * x;
+          if (kt[s[i]] == v[i]) ar += x * rv[s[i]];
+        }
+        if (cols[7] < 0) break;
+      }
+      sc[mb + lane + k * SPAI_WAVE] = (m * m) * n2 + (2.0 * m) * ar;
+    }
+    bt_clear<2, 1>(cell, row, lst, mul);
+    __syncthreads();
+  }
+}
+
 static size_t score_lds(Tile t, bool ell) {
   return (size_t)t.L * 4 + (size_t)t.H * 4 + (size_t)t.L * 8 + (size_t)t.L * 16 +
          (size_t)(t.H / 2) * 8 + (ell ? 0 : (size_t)t.L * 12) + 128;
@@ -3515,8 +3682,48 @@ static size_t score_lds(Tile t, bool ell) {
 
 size_t score_tile_bytes(Tile t, bool ell) { return score_lds(t, ell); }
 
+// places of rows want[u] in X's columns col[u] (-1: no such entry, or col[u] < 0), U searches
+// in flight: a search is a chain of some six dependent loads
+template <int U, typename T>
+__device__ __forceinline__ void find_rows(const Cols<T>& X, const int (&col)[U],
+                                          const int (&want)[U], int64_t (&at)[U]) {
+  int64_t beg[U];
+  int lo[U], hi[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    beg[u] = 0;
+    lo[u] = hi[u] = 0;
+    if (col[u] >= 0) {
+      beg[u] = X.beg[col[u]];
+      hi[u] = X.len[col[u]];
+    }
+    at[u] = -1;
+  }
+  for (;;) {                                       // halves of [lo, hi) until it is empty
+    bool more = false;
+    int mid[U], got[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      mid[u] = (lo[u] + hi[u]) >> 1;
+      got[u] = 0;
+      if (lo[u] < hi[u]) got[u] = X.idx[beg[u] + mid[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool on = lo[u] < hi[u];
+      const bool hit = on && got[u] == want[u];
+      if (hit) at[u] = beg[u] + mid[u];
+      if (on && got[u] < want[u]) lo[u] = mid[u] + 1;
+      else if (on) hi[u] = hit ? lo[u] : mid[u];
+      more = more || lo[u] < hi[u];
+    }
+    if (!more) break;
+  }
+}
+
 // sigma at entry (k, l) of the candidates: s_kl + s_lk, the partner found by binary
-// search in column k (the candidates are exactly symmetric); the diagonal keeps s_kk
+// search in column k (the candidates are exactly symmetric); the diagonal keeps s_kk.
+// Bound by the searches' chains of loads: four a lane in flight take 0.17 ms at 48^3, one 0.26.
 template <typename T>
 __global__ __launch_bounds__(SPAI_WAVE) void k_score_pair(Pair<T> Mp, const double* sc,
                                                           double* sig, int gs, int64_t n,
@@ -3527,22 +3734,35 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_score_pair(Pair<T> Mp, const doub
   const int64_t ng = (n + gs - 1) / gs;
   for (int64_t gi = blockIdx.x; gi < ng; gi += gridDim.x) {
     const Group64 g = group_load(X, gi * gs, gs, n);
-    for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE) {
-      const int x = x0 + lane;
-      const int xc = min(x, g.T - 1);              // all lanes shuffle together
-      const int c = group_col(g, xc);
-      const int64_t src = group_src(g, c, xc);
-      if (x >= g.T) continue;
-      const int l = (int)(g.j0 + c);
-      const int k = X.idx[src];
-      double v = sc[src];
-      if (k != l) {
-        const int64_t kb = X.beg[k];
-        const int p = bsearch_idx(X.idx + kb, X.len[k], l);
-        if (p >= 0) v = v + sc[kb + p];
-        else atomicOr(&st->err, 4);              // not symmetric: cannot happen
+    for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE * kGU) {
+      int64_t src[kGU], at[kGU];
+      int col[kGU], row[kGU];
+      double v[kGU];
+#pragma unroll
+      for (int u = 0; u < kGU; ++u) {
+        const int x = x0 + u * SPAI_WAVE + lane;
+        const int xc = min(x, g.T - 1);            // all lanes shuffle together
+        const int c = group_col(g, xc);
+        src[u] = group_src(g, c, xc);
+        row[u] = (int)(g.j0 + c);                  // the partner's row: this column
+        col[u] = -1;
+        v[u] = 0.0;
+        if (x < g.T) {
+          col[u] = X.idx[src[u]];
+          v[u] = sc[src[u]];
+        } else {
+          src[u] = -1;
+        }
+        if (col[u] == row[u]) col[u] = -1;         // the diagonal has none
       }
-      sig[src] = v;
+      find_rows<kGU>(X, col, row, at);
+#pragma unroll
+      for (int u = 0; u < kGU; ++u) {
+        if (src[u] < 0) continue;
+        if (at[u] >= 0) v[u] = v[u] + sc[at[u]];
+        else if (col[u] >= 0) atomicOr(&st->err, 4);   // not symmetric: cannot happen
+        sig[src[u]] = v[u];
+      }
     }
   }
 }
@@ -3552,9 +3772,14 @@ void launch_score(const Csr& A, Pair<T> M, double* sc, double* sig, BigList big,
                   Tile small, Tile large, Tile huge, int64_t n, hipStream_t s) {
   const bool ell = A.eshift >= 0;
   launch_zero_counts(big, s);
-  hipLaunchKernelGGL((k_score<T, false>), dim3(resident_grid(k_score<T, false>, score_lds(small, ell))),
-                     dim3(SPAI_WAVE), score_lds(small, ell), s, A, M, sc, big, st, 0, small.L,
-                     small.H);
+  if (ell)
+    hipLaunchKernelGGL(k_score_lean<T>, dim3(resident_grid(k_score_lean<T>, 0)), dim3(SPAI_WAVE), 0, s,
+                       A, M, sc, big, st);
+  else
+    hipLaunchKernelGGL((k_score<T, false>),
+                       dim3(resident_grid(k_score<T, false>, score_lds(small, ell))),
+                       dim3(SPAI_WAVE), score_lds(small, ell), s, A, M, sc, big, st, 0, small.L,
+                       small.H);
   hipLaunchKernelGGL((k_score<T, false>), dim3(large_grid(k_score<T, false>, score_lds(large, ell))),
                      dim3(SPAI_WAVE), score_lds(large, ell), s, A, M, sc, big, st, 1, large.L, large.H);
   hipLaunchKernelGGL((k_score<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), 0, s, A, M, sc, big, st,
@@ -4026,25 +4251,43 @@ __global__ __launch_bounds__(kCompWaves * SPAI_WAVE) void k_export(Cols<T> X, Of
     const Group64 g = group_load(X, gi * gs, gs, n);
     const int64_t o = off[g.j0];
     if (lane < gs && g.j0 + lane < n) rowptr[g.j0 + lane] = o + g.ex;
-    for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE) {
-      const int x = x0 + lane;
-      const int xc = min(x, g.T - 1);              // all lanes shuffle together
-      const int c = group_col(g, xc);
-      const int64_t src = group_src(g, c, xc);
-      if (x >= g.T) continue;
-      const int j = (int)(g.j0 + c);
-      const int k = X.idx[src];
-      const T v = X.val[src];
-      idx[o + x] = k;
-      val[o + x] = (double)v;
-      if (k != j) {
-        const int64_t kb = X.beg[k];
-        const int p = bsearch_idx(X.idx + kb, X.len[k], j);
-        if (p < 0) odd = true;
-        else if constexpr (sizeof(T) == 4)
-          odd |= __float_as_uint((float)X.val[kb + p]) != __float_as_uint((float)v);
-        else
-          odd |= __double_as_longlong(X.val[kb + p]) != __double_as_longlong(v);
+    for (int x0 = 0; x0 < g.T; x0 += SPAI_WAVE * kGU) {
+      int64_t at[kGU];
+      int col[kGU], row[kGU];
+      T v[kGU];
+#pragma unroll
+      for (int u = 0; u < kGU; ++u) {
+        const int x = x0 + u * SPAI_WAVE + lane;
+        const int xc = min(x, g.T - 1);            // all lanes shuffle together
+        const int c = group_col(g, xc);
+        const int64_t src = group_src(g, c, xc);
+        row[u] = (int)(g.j0 + c);
+        col[u] = -1;
+        v[u] = (T)0;
+        if (x < g.T) {
+          col[u] = X.idx[src];
+          v[u] = X.val[src];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kGU; ++u) {
+        const int x = x0 + u * SPAI_WAVE + lane;
+        if (x < g.T) {
+          idx[o + x] = col[u];
+          val[o + x] = (double)v[u];
+        }
+        if (col[u] == row[u]) col[u] = -1;         // the diagonal is its own mirror
+      }
+      find_rows<kGU>(X, col, row, at);
+#pragma unroll
+      for (int u = 0; u < kGU; ++u) {
+        if (at[u] < 0) {
+          odd = odd || col[u] >= 0;
+        } else if constexpr (sizeof(T) == 4) {
+          odd = odd || __float_as_uint((float)X.val[at[u]]) != __float_as_uint((float)v[u]);
+        } else {
+          odd = odd || __double_as_longlong(X.val[at[u]]) != __double_as_longlong(v[u]);
+        }
       }
     }
   }

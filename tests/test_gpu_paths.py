@@ -258,3 +258,26 @@ def test_export_of_an_unsymmetric_state(precision):
     want.sort_indices()
     assert np.array_equal(got.indptr, want.indptr) and np.array_equal(got.indices, want.indices)
     assert np.array_equal(got.data, want.data)
+
+
+# the scores' resident tier ends at 128 candidates a column and a few hundred rows of its
+# residual: a generous cap on denser graphs takes some columns past either end
+@pytest.mark.parametrize("name,make,cap", [
+    ("lognormal7", lambda: W.lognormal3d(7, 3), 6.0),
+    ("geo400", lambda: W.geometric_graph(400, 9), 6.0),
+    ("geo900", lambda: W.geometric_graph(900, 4), 3.0),
+    ("one", lambda: W.geometric_graph(1, 4), 3.0)])
+@pytest.mark.parametrize("method", ["mr", "lomr"])
+def test_scores_at_the_ends_of_their_tier(name, make, cap, method):
+    S = _spai()
+    A = make()
+    m = O.cap_counts(A, "global", cap, True)
+    h = S.SPAI(A, method, "global", cap, True, max_iter=5, options=S.Options(drop_score=True))
+    _, hist, _ = h.iterate(5)
+    M = h.get()
+    h.close()
+    ref = O.run(method, A, O.DropRule(mode="global", m=m, score=True), 5)
+    want = np.asarray(ref.resid[1:len(hist) + 1])
+    assert np.all(np.abs(np.asarray(hist) - want) <= 1e-10 * want + 1e-13 * ref.resid[0])
+    assert pattern_diff(M, ref.M) == (set(), set())
+    assert value_err(M, ref.M) <= 1e-9

@@ -166,6 +166,9 @@ __device__ __forceinline__ int64_t wave_read64(int64_t v, int l) {
 __device__ __forceinline__ double wave_readf(double v, int l) {
   return __longlong_as_double(wave_read64(__double_as_longlong(v), l));
 }
+__device__ __forceinline__ float wave_readf(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
 __device__ __forceinline__ int wave_max_int(int v) {
   v = max(v, lane_xor<1>(v));
   v = max(v, lane_xor<2>(v));

@@ -1948,6 +1948,48 @@ __device__ inline double kth_largest_cols(const int32_t* idx, const T* val, int 
   return wave_max(t);
 }
 
+// The same from registers: the (b+1)-th largest of the magnitudes x[k] >= 0 of the lanes with
+// use[k] set, k < K (0 if there are at most b).  A lane counts the magnitudes above each of
+// its own -- one comparison per magnitude, read by lane -- and the smallest one with at most b
+// above it is the answer, whichever of equal ones comes first.
+template <int K, typename T>
+__device__ __forceinline__ double kth_largest_lanes(const T (&x)[K], const bool (&use)[K], int b) {
+  unsigned long long um[K];
+  T v[K];
+  int above[K], m = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const bool on = use[k] && x[k] == x[k];       // a NaN is never counted and never the answer
+    um[k] = __ballot(on);
+    v[k] = on ? x[k] : (T)-1;
+    above[k] = 0;
+    m += __popcll(um[k]);
+  }
+  if (m <= b) return 0.0;
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    const int end = um[q] ? 64 - __clzll((long long)um[q]) : 0;
+#pragma unroll 8
+    for (int f = 0; f < end; ++f) {
+      const T y = wave_readf(v[q], f);            // -1 where lane f has none
+#pragma unroll
+      for (int k = 0; k < K; ++k) above[k] += y > v[k] ? 1 : 0;
+    }
+  }
+  double t = -INFINITY;                           // - the smallest
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (v[k] >= (T)0 && above[k] <= b) t = fmax(t, -(double)v[k]);
+  return -wave_max(t);
+}
+
+template <typename T>
+__device__ __forceinline__ double kth_largest_lane(T x, bool use, int b) {
+  const T xs[1] = {x};
+  const bool us[1] = {use};
+  return kth_largest_lanes<1, T>(xs, us, b);
+}
+
 template <typename T, bool GS>
 __device__ __forceinline__ void update_body(Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp,
                                             Pair<T> PTp, UpdMode md, Offs off,
@@ -2307,9 +2349,12 @@ constexpr int kUpdLeanNbr = 256;   // entries of the neighbour columns together
 
 // SECOND: the same kernel under another name for the floor-free second pass (masked
 // unless needed), so that profiles keep the two apart.  LM: a mode fixed at compile time,
-// so that its flags take no registers and its branches fold -- 1: the symmetrized LOMR
-// step under a global cap (M + a1 R + a2 P, and P from R and P), 2: the symmetrized MR
-// step (M + a1 R, no P; either cap); 0: every mode, read from md.
+// so that its flags take no registers and its branches fold -- 1, 3: the symmetrized LOMR
+// step (M + a1 R + a2 P, and P from R and P) without and with column caps; 2, 4: the
+// symmetrized MR step (M + a1 R, no P), the same; 5, 6: the symmetrized CG steps of M
+// (M + a1 P) and of P; 0: every mode, read from md.
+// 256 x 256 grid, LOMR under a column cap in float64, 0.31 ms as mode 0 and 0.23 as 3 (its
+// thresholds from registers instead of written candidates read back); 33^3 CG, M 81 -> 55 us.
 // Registers capped for six waves per SIMD on the float path (2% faster at 96^3; the
 // float64 path spills there and keeps five).
 template <typename T, bool FLAT, bool SECOND, int LM>
@@ -2319,7 +2364,7 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
     DevState* st, int L, int H) {
   if (!st->any_active || !st->iter_active) return;
   UpdMode md = mdin;
-  if constexpr (LM == 1) {
+  if constexpr (LM == 1 || LM == 3) {
     md.doM = 1;
     md.x1 = 1;
     md.x2 = 2;
@@ -2327,12 +2372,26 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
     md.pR = 1;
     md.pP = 1;
     md.sym = 1;
-    md.colcap = 0;
-  } else if constexpr (LM == 2) {
+    md.colcap = LM == 3;
+  } else if constexpr (LM == 2 || LM == 4) {
     md.doM = 1;
     md.x1 = 1;
     md.x2 = 0;
     md.doP = 0;
+    md.sym = 1;
+    md.colcap = LM == 4;
+  } else if constexpr (LM == 5) {
+    md.doM = 1;
+    md.x1 = 2;
+    md.x2 = 0;
+    md.doP = 0;
+    md.sym = 1;
+  } else if constexpr (LM == 6) {
+    md.doM = 0;
+    md.x1 = md.x2 = 0;
+    md.doP = 1;
+    md.pR = 1;
+    md.pP = 1;
     md.sym = 1;
   }
   // the fixed-size arrays at fixed LDS addresses (their offsets fold into the accesses),
@@ -2606,7 +2665,14 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
     const SegState& g = seg.st[seg.segof(j)];
     const double a1 = g.coef[0], a2 = g.coef[1], c1 = g.coef[2], c2 = g.coef[3];
     int cntM = 0, cntP = 0, cntPT = 0;
-    for (int base = 0; base < nk; base += SPAI_WAVE) {
+    // at most two rounds (nk <= kUpdLeanKeys): the candidates' magnitudes stay in registers
+    // for the column thresholds
+    T magM[2] = {(T)0, (T)0}, magP[2] = {(T)0, (T)0};
+    bool inM[2] = {false, false}, inP[2] = {false, false};
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+      const int base = round * SPAI_WAVE;
+      if (base >= nk) break;
       const int t = base + lane;
       const bool valid = t < nk;
       const int k = valid ? keys[t] : -1;
@@ -2648,22 +2714,30 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
         keepP = valid && (double)pt != 0.0;
         keepPT = valid && (double)ptt != 0.0;
       }
-      // candidates below the floor are not written (the diagonal always is); they are
-      // counted, and the selection checks that its cut clears the floor
-      const bool wM = keepM && (k == (int)j || fabs((double)mt) >= fM);
-      const bool wP = keepP && fabs((double)pt) >= fP;
-      const bool wPT = keepPT && fabs((double)ptt) >= fP;
-      {
-        const unsigned bM = (unsigned)__popcll(__ballot(keepM && !wM));
-        const unsigned bP = (unsigned)__popcll(__ballot(keepP && !wP));
-        if (lane == 0 && (bM | bP)) {
-          below[0] += bM;
-          below[1] += bP;
+      if constexpr (LM != 3 && LM != 4) {         // no floors under column caps
+        // candidates below the floor are not written (the diagonal always is); they are
+        // counted, and the selection checks that its cut clears the floor
+        const bool wM = keepM && (k == (int)j || fabs((double)mt) >= fM);
+        const bool wP = keepP && fabs((double)pt) >= fP;
+        const bool wPT = keepPT && fabs((double)ptt) >= fP;
+        {
+          const unsigned bM = (unsigned)__popcll(__ballot(keepM && !wM));
+          const unsigned bP = (unsigned)__popcll(__ballot(keepP && !wP));
+          if (lane == 0 && (bM | bP)) {
+            below[0] += bM;
+            below[1] += bP;
+          }
         }
+        keepM = wM;
+        keepP = wP;
+        keepPT = wPT;
       }
-      keepM = wM;
-      keepP = wP;
-      keepPT = wPT;
+      if (md.colcap) {
+        inM[round] = keepM && k != (int)j;
+        inP[round] = keepP;
+        magM[round] = (T)fabs((double)mt);
+        magP[round] = (T)fabs((double)pt);
+      }
       const unsigned long long bm = __ballot(keepM);
       const unsigned long long bp = __ballot(keepP);
       const unsigned long long bpt = __ballot(keepPT);
@@ -2695,16 +2769,16 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
       }
     }
     if (md.colcap) {
-      // thresholds from the candidates this wave has just written (L1/L2 resident)
       const int kc = kcol[j];
-      __threadfence_block();
-      __syncthreads();
       if (md.doM) {
-        const double t = kth_largest_cols(Mo.idx + ob, Mo.val + ob, cntM, (int)j, kc - 1);
+        const double t = nk <= SPAI_WAVE
+                             ? kth_largest_lane(magM[0], inM[0], kc - 1)
+                             : kth_largest_lanes<2, T>(magM, inM, kc - 1);
         if (lane == 0) tM[j] = t;
       }
       if (md.doP) {
-        const double t = kth_largest_cols(Po.idx + ob, Po.val + ob, cntP, -1, kc);
+        const double t = nk <= SPAI_WAVE ? kth_largest_lane(magP[0], inP[0], kc)
+                                         : kth_largest_lanes<2, T>(magP, inP, kc);
         if (lane == 0) tP[j] = t;
       }
     }
@@ -2749,18 +2823,25 @@ void launch_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, Up
                          P, PT, md, off, total, kcol, tM, tP, big, seg, st, small.L, small.H);
     };
     // ELL rows wider than 8: neighbour entries laid out flat
-    const bool lomr = md.doM == 1 && md.x1 == 1 && md.x2 == 2 && md.doP == 1 && md.pR == 1 &&
-                      md.pP == 1 && md.sym == 1 && md.colcap == 0;
+    const bool both = md.pR == 1 && md.pP == 1;
+    const bool lomr = md.doM == 1 && md.x1 == 1 && md.x2 == 2 && md.doP == 1 && both && md.sym == 1;
     const bool mr = md.doM == 1 && md.x1 == 1 && md.x2 == 0 && md.doP == 0 && md.sym == 1;
+    const bool cg_m = md.doM == 1 && md.x1 == 2 && md.x2 == 0 && md.doP == 0 && md.sym == 1;
+    const bool cg_p = md.doM == 0 && md.doP == 1 && both && md.sym == 1;
     auto pick = [&](auto lmc) {
       constexpr int L2 = decltype(lmc)::value;
+      constexpr bool S2 = L2 != 3 && L2 != 4;      // a second pass comes with floors only
       if (A.eshift > 3)
-        second ? go(k_update_lean<T, true, true, L2>) : go(k_update_lean<T, true, false, L2>);
+        second ? go(k_update_lean<T, true, S2, L2>) : go(k_update_lean<T, true, false, L2>);
       else
-        second ? go(k_update_lean<T, false, true, L2>) : go(k_update_lean<T, false, false, L2>);
+        second ? go(k_update_lean<T, false, S2, L2>) : go(k_update_lean<T, false, false, L2>);
     };
-    if (lomr) pick(std::integral_constant<int, 1>{});
-    else if (mr) pick(std::integral_constant<int, 2>{});
+    if (lomr && !md.colcap) pick(std::integral_constant<int, 1>{});
+    else if (lomr) pick(std::integral_constant<int, 3>{});
+    else if (mr && !md.colcap) pick(std::integral_constant<int, 2>{});
+    else if (mr) pick(std::integral_constant<int, 4>{});
+    else if (cg_m) pick(std::integral_constant<int, 5>{});
+    else if (cg_p) pick(std::integral_constant<int, 6>{});
     else pick(std::integral_constant<int, 0>{});
   } else if (small.waves == 5)
     hipLaunchKernelGGL((k_update_w5<T>),

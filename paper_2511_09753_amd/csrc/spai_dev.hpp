@@ -428,14 +428,25 @@ __device__ __forceinline__ void sort_in_registers(int* keys, int cnt) {
 // hash ohash(k) instead of k (the order the ordered key set yields; h ^ 2^31 orders
 // as a signed int like h as unsigned, and the INT_MAX padding is the empty word).
 __device__ inline int ks_sort_inplace(int* keys, int H, bool by_hash = false) {
+  // (eight chunks are read at once: in device memory a chunk is a load's latency)
+  constexpr int U = 8;
   int cnt = 0;
-  for (int base = 0; base < H; base += SPAI_WAVE) {
-    int k = keys[base + lane_id()];
-    bool occ = k != -1;
-    unsigned long long m = __ballot(occ);
+  for (int base = 0; base < H; base += SPAI_WAVE * U) {
+    int k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = base + u * SPAI_WAVE;
+      k[u] = i < H ? keys[i + lane_id()] : -1;
+    }
     __syncthreads();
-    if (occ) keys[cnt + __popcll(m & lanemask_lt())] = by_hash ? (int)(ohash(k) ^ 0x80000000u) : k;
-    cnt += __popcll(m);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool occ = k[u] != -1;
+      const unsigned long long m = __ballot(occ);
+      if (occ)
+        keys[cnt + __popcll(m & lanemask_lt())] = by_hash ? (int)(ohash(k[u]) ^ 0x80000000u) : k[u];
+      cnt += __popcll(m);
+    }
     __syncthreads();
   }
   if (by_hash && cnt == 1) {
@@ -622,6 +633,34 @@ __device__ __forceinline__ int oh_compact(unsigned* T, int end) {
     cnt += __popcll(m);
   }
   return cnt;
+}
+
+// ---- a set of rows as a bitmap in LDS ------------------------------------------------
+// Rows are entered with atomics that return nothing, and come out in ascending order by one
+// walk over the words: no probing, no count to keep, no sort.  words: a multiple of 64.
+__device__ __forceinline__ void bm_clear(unsigned* bm, int words) {
+  for (int i = lane_id() * 4; i < words; i += SPAI_WAVE * 4) *(uint4*)(bm + i) = uint4{0, 0, 0, 0};
+}
+__device__ __forceinline__ void bm_set(unsigned* bm, int row) {
+  __hip_atomic_fetch_or(&bm[row >> 5], 1u << (row & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ int bm_count(const unsigned* bm, int words) {
+  int c = 0;
+  for (int i = lane_id(); i < words; i += SPAI_WAVE) c += __popc(bm[i]);
+  return wave_sum_int(c);
+}
+__device__ __forceinline__ void bm_extract(const unsigned* bm, int words, int* keys) {
+  int run = 0;
+  for (int base = 0; base < words; base += SPAI_WAVE) {
+    unsigned m = bm[base + lane_id()];
+    const int inc = wave_incl_scan(__popc(m));
+    int o = run + inc - __popc(m);
+    while (m) {
+      keys[o++] = (base + lane_id()) * 32 + __ffs((int)m) - 1;
+      m &= m - 1;
+    }
+    run += wave_last(inc);
+  }
 }
 
 // ---- clash-free cells: a multiplicative hash whose multiplier is picked per column (row)

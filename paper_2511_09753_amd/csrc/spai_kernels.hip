@@ -246,6 +246,76 @@ __device__ inline int insert_products(const Csr& A, const int* rows, int cnt, co
   return count;
 }
 
+// The same products entered in a bitmap of the rows (no limit to watch).
+__device__ inline void bm_products(const Csr& A, const int* rows, int cnt, const int* pre,
+                                   const int64_t* rs, int total, unsigned* bm) {
+  constexpr int U = 4;
+  const bool ell = A.eshift >= 0;
+  const int sh = A.eshift;
+  const int wm = ell ? (1 << sh) - 1 : 0;
+  const int tot = ell ? (cnt << sh) : total;
+  for (int p0 = 0; p0 < tot; p0 += SPAI_WAVE * U) {
+    int cols[U];
+#pragma unroll
+    for (int c = 0; c < U; ++c) {
+      const int p = p0 + c * SPAI_WAVE + lane_id();
+      cols[c] = -1;
+      if (p < tot) {
+        if (ell) {
+          cols[c] = A.ecol[((int64_t)rows[p >> sh] << sh) + (p & wm)];
+        } else {
+          const int e = upper_bound_int(pre, cnt, p);
+          const int before = e ? pre[e - 1] : 0;
+          cols[c] = A.col[rs[e] + (p - before)];
+        }
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < U; ++c)
+      if (cols[c] >= 0) bm_set(bm, cols[c]);
+  }
+}
+
+// The same products entered in an ordered hash of 2^(32 - shift) home slots; false where a
+// walk was too long (the table is then too small).
+__device__ inline bool oh_products(const Csr& A, const int* rows, int cnt, const int* pre,
+                                   const int64_t* rs, int total, unsigned* kt, int shift) {
+  constexpr int U = 4;
+  const bool ell = A.eshift >= 0;
+  const int sh = A.eshift;
+  const int wm = ell ? (1 << sh) - 1 : 0;
+  const int tot = ell ? (cnt << sh) : total;
+  bool ok = true;
+  for (int p0 = 0; p0 < tot && ok; p0 += SPAI_WAVE * U) {
+    int cols[U];
+#pragma unroll
+    for (int c = 0; c < U; ++c) {
+      const int p = p0 + c * SPAI_WAVE + lane_id();
+      cols[c] = -1;
+      if (p < tot) {
+        if (ell) {
+          cols[c] = A.ecol[((int64_t)rows[p >> sh] << sh) + (p & wm)];
+        } else {
+          const int e = upper_bound_int(pre, cnt, p);
+          const int before = e ? pre[e - 1] : 0;
+          cols[c] = A.col[rs[e] + (p - before)];
+        }
+      }
+    }
+    ok = oh_insert_batch<U>(kt, shift, cols);
+  }
+  return ok;
+}
+
+// Rows of the key bitmap of the large and the huge tier (0: too many rows, a hash set and a
+// sort instead): up to kBmRows, 16 KB beside the at most 57 KB of a large tile, so that two
+// workgroups still fit a compute unit.  A sort of 2048 keys in LDS took
+// some 45 us of one wave, most of a column's time in the large tier.
+constexpr int64_t kBmRows = 131072;
+__host__ __device__ inline int bm_words(int64_t n) {
+  return n <= kBmRows ? (int)((n + 2047) / 2048 * 64) : 0;
+}
+
 // Eight entries of A's row storage from slot q (q < qe; the row ends at qe), loaded
 // together: cols[k] = -1 where there is no entry.  ELL chunks are aligned 32-byte
 // pieces of the padded row.
@@ -341,13 +411,25 @@ __device__ inline void defer_column(int tier, BigList big, DevState* st, int64_t
 }
 
 // Barrier of a per-column kernel.  In the huge tier the working set is device memory
-// and its hash tables are updated with atomics, which are performed in L2: the fence
-// (device scope, so the acquire side invalidates L1) keeps later plain loads from
-// reading stale L1 lines.
+// and its hash tables are updated with atomics, which are performed in L2: the acquire
+// side has device scope, so that it invalidates L1 and later plain loads read no stale
+// lines; no other workgroup reads the slice, so the release side only waits for the
+// workgroup's own stores (a device-scope release writes back the XCD's whole L2).
 template <bool GS>
 __device__ __forceinline__ void tile_sync() {
-  if constexpr (GS) __threadfence();
+  if constexpr (GS) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  }
   __syncthreads();
+}
+
+// Slots of the key set for a column with at most ub distinct keys, in a tile of H: clearing
+// and compacting the set cost a pass over its slots.  Half of them hold ub keys (an insertion
+// batch needs 256 free beyond that), so a column that fits the tile's own set fits this one.
+__device__ __forceinline__ int key_slots(int64_t ub, int H) {
+  return (int)min<int64_t>((int64_t)H, (int64_t)next_pow2((int)min<int64_t>(2 * ub + 512, 1 << 30)));
 }
 
 // working-set base of a per-column kernel: dynamic LDS, or (GS, the huge tier) this
@@ -830,22 +912,23 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5, 5)
                                                      Offs off, const int64_t* total,
                                                      double* colnorm, int weighted, double* colrz,
                                                      BigList big, DevState* st, int tier, int L,
-                                                     int H) {
+                                                     int Ht) {
   if (!st->any_active) return;
   extern __shared__ char smem[];
   const bool ell = A.eshift >= 0;
   Carve cv(tile_base<GS>(smem, big));
   int* s_mi = cv.take<int>(L);
-  int* s_keys = cv.take<int>(H);         // hash set, then the sorted keys
+  int* s_keys = cv.take<int>(Ht);        // hash set, then the sorted keys
   double* s_mv = cv.take<double>(L);
   int* s_mk = cv.take<int>(2 * L);       // position map of m_j's rows
   unsigned* s_mp = cv.take<unsigned>(2 * L);
   int* s_pre = ell ? nullptr : cv.take<int>(L);           // CSR: degree prefix
   int64_t* s_rs = ell ? nullptr : cv.take<int64_t>(L);    // CSR: row starts
+  const int bw = tier == 0 ? 0 : bm_words(A.n);           // key bitmap (LDS in every tier)
+  unsigned* bm = GS ? (unsigned*)smem : cv.take16<unsigned>(bw);
   const int lane = lane_id();
   const Cols<T> M = Mp.now();
   const bool overflow = *total > R.cap;
-  const int limit = H / 2 - 1;
   unsigned long long outcnt = 0;
 
   auto body = [&](int64_t j) {
@@ -860,7 +943,11 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5, 5)
       return;
     }
     const int hs = next_pow2(max(2 * lm, 64));
-    ks_clear(s_keys, H);
+    const int64_t ob = off[j];
+    const int H = key_slots((j + 1 < A.n ? off[j + 1] : *total) - ob, Ht);
+    const int limit = H / 2 - 1;
+    if (bw) bm_clear(bm, bw);
+    else ks_clear(s_keys, H);
     lm_clear(s_mk, s_mp, hs);
     tile_sync<GS>();
     for (int e = lane; e < lm; e += SPAI_WAVE) {
@@ -875,18 +962,32 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5, 5)
       tot = degree_prefix(A, s_mi, lm, s_pre, s_rs);
       tile_sync<GS>();
     }
-    int kd[1] = {lane == 0 ? (int)j : -1};
-    int nk = wave_sum_int(ks_insert_batch<1>(s_keys, H, kd));
-    nk = insert_products(A, s_mi, lm, s_pre, s_rs, tot, s_keys, H, nk, limit);
-    tile_sync<GS>();
-    if (nk > limit) {               // more distinct rows than the tile holds
-      defer_column(tier, big, st, j);
+    int nu;
+    if (bw) {
+      if (lane == 0) bm_set(bm, (int)j);
+      bm_products(A, s_mi, lm, s_pre, s_rs, tot, bm);
+      __syncthreads();
+      nu = bm_count(bm, bw);
+      if (nu > Ht) {
+        defer_column(tier, big, st, j);
+        tile_sync<GS>();
+        return;
+      }
+      bm_extract(bm, bw, s_keys);
       tile_sync<GS>();
-      return;
+    } else {
+      int kd[1] = {lane == 0 ? (int)j : -1};
+      int nk = wave_sum_int(ks_insert_batch<1>(s_keys, H, kd));
+      nk = insert_products(A, s_mi, lm, s_pre, s_rs, tot, s_keys, H, nk, limit);
+      tile_sync<GS>();
+      if (nk > limit) {             // more distinct rows than the tile holds
+        defer_column(tier, big, st, j);
+        tile_sync<GS>();
+        return;
+      }
+      nu = ks_sort_inplace(s_keys, H);
+      tile_sync<GS>();
     }
-    const int nu = ks_sort_inplace(s_keys, H);
-    tile_sync<GS>();
-    const int64_t ob = off[j];
     double acc = 0.0, acc_rz = 0.0;
     double sum[1];
     double diag[1];             // a_uu of the pulled row (the Pi weight is 1 / a_uu)
@@ -1217,9 +1318,11 @@ void launch_resid(const Csr& A, Pair<T> M, Cols<T> R, Offs off, const int64_t* t
                        dim3(resident_grid(k_resid<T, false>, resid_lds(small, ell))),
                        dim3(SPAI_WAVE), resid_lds(small, ell), s, A, M, R, off, total, colnorm,
                        weighted, colrz, big, st, 0, small.L, small.H);
-  hipLaunchKernelGGL((k_resid<T, false>), dim3(large_grid(k_resid<T, false>, resid_lds(large, ell))),
-                     dim3(SPAI_WAVE), resid_lds(large, ell), s, A, M, R, off, total, colnorm, weighted, colrz, big, st, 1, large.L, large.H);
-  hipLaunchKernelGGL((k_resid<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), 0, s, A, M, R, off, total,
+  const size_t bml = (size_t)bm_words(A.n) * 4;
+  const size_t ldl = resid_lds(large, ell) + bml;
+  hipLaunchKernelGGL((k_resid<T, false>), dim3(large_grid(k_resid<T, false>, ldl)),
+                     dim3(SPAI_WAVE), ldl, s, A, M, R, off, total, colnorm, weighted, colrz, big, st, 1, large.L, large.H);
+  hipLaunchKernelGGL((k_resid<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), bml, s, A, M, R, off, total,
                      colnorm, weighted, colrz, big, st, 2, huge.L, huge.H);
 }
 
@@ -1235,16 +1338,18 @@ size_t resid_tile_bytes(Tile t, bool ell) {
 // SpGEMM fused with Frobenius dots: A r_j and A p_j in LDS, never stored
 // ============================================================================
 
+// slots of the huge tier's ordered key table in LDS (the large tier's is its key set)
+constexpr int kDotsSlots = 16384;
 template <typename T, bool GS>
 __device__ __forceinline__ void dots_body(Csr A, Cols<T> R, Pair<T> Pp, int useR, int useP,
                                           int weighted, double* colpart, BigList big,
-                                          DevState* st, int tier, int L, int H) {
+                                          DevState* st, int tier, int L, int Ht) {
   if (!st->any_active || !st->iter_active) return;
   extern __shared__ char smem[];
   const bool ell = A.eshift >= 0;
   Carve cv(tile_base<GS>(smem, big));
   int* s_li = cv.take<int>(L);           // r_j rows, then p_j rows
-  int* s_keys = cv.take<int>(H);
+  int* s_keys = cv.take<int>(Ht + (tier == 1 ? kOhOver : 0));
   double* s_lv = cv.take<double>(L);
   int* s_mk = cv.take<int>(2 * L);       // position map: row -> (place in r_j, in p_j)
   unsigned* s_mp = cv.take<unsigned>(2 * L);
@@ -1252,7 +1357,6 @@ __device__ __forceinline__ void dots_body(Csr A, Cols<T> R, Pair<T> Pp, int useR
   int64_t* s_rs = ell ? nullptr : cv.take<int64_t>(L);
   const int lane = lane_id();
   const Cols<T> P = Pp.now();
-  const int limit = H / 2 - 1;
 
   auto body = [&](int64_t j) {
     const int lr = useR ? R.len[j] : 0;
@@ -1264,9 +1368,9 @@ __device__ __forceinline__ void dots_body(Csr A, Cols<T> R, Pair<T> Pp, int useR
     const int64_t rb = useR ? R.beg[j] : 0;
     const int64_t pb = useP ? P.beg[j] : 0;
     const int hs = next_pow2(max(2 * (lr + lp), 64));
-    ks_clear(s_keys, H);
     lm_clear(s_mk, s_mp, hs);
     tile_sync<GS>();
+    int ub = 0;                                  // entries of the rows reached
     for (int e = lane; e < lr + lp; e += SPAI_WAVE) {   // both lists in one pass
       int i;
       double v;
@@ -1279,23 +1383,53 @@ __device__ __forceinline__ void dots_body(Csr A, Cols<T> R, Pair<T> Pp, int useR
       }
       s_li[e] = i;
       s_lv[e] = v;
+      ub += (int)(A.rowptr[i + 1] - A.rowptr[i]);
       lm_put(s_mk, s_mp, hs, i, e < lr ? 0 : 1, e < lr ? e : e - lr);
     }
-    tile_sync<GS>();
+    ub = wave_sum_int(ub);
     int tot = 0;
     if (!ell) {
+      tile_sync<GS>();
       tot = degree_prefix(A, s_li, lr + lp, s_pre, s_rs);
+    }
+    tile_sync<GS>();
+    // tiers 1 and 2: the rows in an ordered hash in LDS, which compacts to the hash order
+    // that the lean tier sums in (no sort); a column that does not fit it: the huge tier
+    // takes a hash set in device memory
+    int* keys = s_keys;
+    int nu = -1;
+    if (tier != 0) {
+      unsigned* kt = GS ? (unsigned*)smem : (unsigned*)s_keys;
+      const int Hc = key_slots(ub, GS ? kDotsSlots : Ht), ksh = 32 - log2_pow2(Hc);
+      const int kend = Hc + kOhOver;
+      for (int i = lane; i < kend; i += SPAI_WAVE) kt[i] = kOhEmpty;
+      __syncthreads();
+      if (oh_products(A, s_li, lr + lp, s_pre, s_rs, tot, kt, ksh)) {
+        __syncthreads();
+        nu = oh_compact(kt, kend);
+        keys = (int*)kt;
+      }
+      __syncthreads();
+      if (!GS && nu < 0) {
+        defer_column(tier, big, st, j);
+        return;
+      }
+    }
+    if (nu < 0) {
+      const int H = key_slots(ub, Ht);
+      const int limit = H / 2 - 1;
+      ks_clear(s_keys, H);
+      tile_sync<GS>();
+      const int nk = insert_products(A, s_li, lr + lp, s_pre, s_rs, tot, s_keys, H, 0, limit);
+      tile_sync<GS>();
+      if (nk > limit) {
+        defer_column(tier, big, st, j);
+        tile_sync<GS>();
+        return;
+      }
+      nu = ks_sort_inplace(s_keys, H, true);   // ordered by ohash, as the lean tier
       tile_sync<GS>();
     }
-    const int nk = insert_products(A, s_li, lr + lp, s_pre, s_rs, tot, s_keys, H, 0, limit);
-    tile_sync<GS>();
-    if (nk > limit) {
-      defer_column(tier, big, st, j);
-      tile_sync<GS>();
-      return;
-    }
-    const int nu = ks_sort_inplace(s_keys, H, true);   // ordered by ohash, as the lean tier
-    tile_sync<GS>();
     const int* ri = s_li;
     const double* rv = s_lv;
     const int* pi = s_li + lr;
@@ -1304,12 +1438,12 @@ __device__ __forceinline__ void dots_body(Csr A, Cols<T> R, Pair<T> Pp, int useR
     double ar[1], ap[1], diag[1];
     int key[1];
     pull_rows<1>(
-        A, s_keys, nu,
+        A, keys, nu,
         [&](int c, int t) {
           ar[c] = 0.0;
           ap[c] = 0.0;
           diag[c] = 0.0;
-          key[c] = s_keys[t];
+          key[c] = keys[t];
         },
         [&](int c, const int (&cols)[8], const double (&vals)[8]) {
           unsigned pw[8];
@@ -1601,9 +1735,11 @@ void launch_dots(const Csr& A, Cols<T> R, Pair<T> P, int useR, int useP, int wei
                        dim3(resident_grid(k_dots<T, false>, dots_lds(small, ell))),
                        dim3(SPAI_WAVE), dots_lds(small, ell), s, A, R, P, useR, useP, weighted,
                        colpart, big, st, 0, small.L, small.H);
-  hipLaunchKernelGGL((k_dots<T, false>), dim3(large_grid(k_dots<T, false>, dots_lds(large, ell))),
-                     dim3(SPAI_WAVE), dots_lds(large, ell), s, A, R, P, useR, useP, weighted, colpart, big, st, 1, large.L, large.H);
-  hipLaunchKernelGGL((k_dots<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), 0, s, A, R, P, useR, useP,
+  const size_t ldl = dots_lds(large, ell) + (size_t)kOhOver * 4;
+  hipLaunchKernelGGL((k_dots<T, false>), dim3(large_grid(k_dots<T, false>, ldl)),
+                     dim3(SPAI_WAVE), ldl, s, A, R, P, useR, useP, weighted, colpart, big, st, 1, large.L, large.H);
+  hipLaunchKernelGGL((k_dots<T, true>), dim3(big.grid2), dim3(SPAI_WAVE),
+                     (size_t)(kDotsSlots + kOhOver) * 4, s, A, R, P, useR, useP,
                      weighted, colpart, big, st, 2, huge.L, huge.H);
 }
 
@@ -1995,12 +2131,12 @@ __device__ __forceinline__ void update_body(Csr A, Pair<T> Mp, Cols<T> R, Pair<T
                                             Pair<T> PTp, UpdMode md, Offs off,
                                             const int64_t* total, const int32_t* kcol,
                                             double* tM, double* tP, BigList big, Seg seg,
-                                            DevState* st, int tier, int L, int H, int DG) {
+                                            DevState* st, int tier, int L, int Ht, int DG) {
   if (!st->any_active || !st->iter_active) return;
   extern __shared__ char smem[];
   Carve cv(tile_base<GS>(smem, big));
   int* s_li = cv.take<int>(L);
-  int* s_keys = cv.take<int>(H);        // hash set, then the sorted keys
+  int* s_keys = cv.take<int>(Ht);       // hash set, then the sorted keys
   int* s_nbcol = cv.take<int>(DG);
   int* s_nboff = cv.take<int>(DG + 1);
   double* s_lv = cv.take<double>(L);
@@ -2009,6 +2145,8 @@ __device__ __forceinline__ void update_body(Csr A, Pair<T> Mp, Cols<T> R, Pair<T
   // memory and are searched in place (s_nbbeg / s_nboff hold their start and length)
   const bool nb_lds = tier == 0;
   int64_t* s_nbbeg = cv.take<int64_t>(DG);
+  const int bw = tier == 0 ? 0 : bm_words(A.n);           // key bitmap (LDS in every tier)
+  unsigned* bm = GS ? (unsigned*)smem : cv.take16<unsigned>(bw);
   const int lane = lane_id();
 
   const Cols<T> M = Mp.now();
@@ -2025,7 +2163,6 @@ __device__ __forceinline__ void update_body(Csr A, Pair<T> Mp, Cols<T> R, Pair<T
   const bool overflow = *total > Mo.cap || (md.doP && (*total > Po.cap || *total > PTo.cap));
 
   const bool ell = A.eshift >= 0;
-  const int limit = H / 2 - 1;
 
   auto body = [&](int64_t j) {
     const SegState& g = seg.st[seg.segof(j)];
@@ -2094,7 +2231,11 @@ __device__ __forceinline__ void update_body(Csr A, Pair<T> Mp, Cols<T> R, Pair<T
       if (lane == 0) atomicOr(&st->err, 2);
       return;
     }
-    ks_clear(s_keys, H);
+    const int64_t ob = off[j];
+    const int H = key_slots((j + 1 < A.n ? off[j + 1] : *total) - ob, Ht);
+    const int limit = H / 2 - 1;
+    if (bw) bm_clear(bm, bw);
+    else ks_clear(s_keys, H);
     tile_sync<GS>();
     // ---- every list entry held in LDS, in one flattened gather (four per lane in flight)
     {
@@ -2139,41 +2280,62 @@ __device__ __forceinline__ void update_body(Csr A, Pair<T> Mp, Cols<T> R, Pair<T
     }
     tile_sync<GS>();
     // ---- key union (at most limit distinct keys)
-    int kd[1] = {lane == 0 ? (int)j : -1};
-    int nkeys = wave_sum_int(ks_insert_batch<1>(s_keys, H, kd));
-    for (int x0 = 0; x0 < ltot && nkeys <= limit; x0 += SPAI_WAVE * 4) {
-      int kk[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int pos = x0 + c * SPAI_WAVE + lane;
-        kk[c] = pos < ltot ? s_li[pos] : -1;
-      }
-      nkeys += wave_sum_int(ks_insert_batch<4>(s_keys, H, kk));
-    }
-    if (!nb_lds)
-      for (int t = 0; t < deg && nkeys <= limit; ++t) {
-        const int64_t b0 = s_nbbeg[t];
-        const int len = s_nboff[t + 1] - s_nboff[t];
-        for (int x0 = 0; x0 < len && nkeys <= limit; x0 += SPAI_WAVE * 4) {
-          int kk[4];
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const int e = x0 + c * SPAI_WAVE + lane;
-            kk[c] = e < len ? M.idx[b0 + e] : -1;
-          }
-          nkeys += wave_sum_int(ks_insert_batch<4>(s_keys, H, kk));
+    int nk;
+    if (bw) {
+      if (lane == 0) bm_set(bm, (int)j);
+      for (int x0 = lane; x0 < ltot; x0 += SPAI_WAVE) bm_set(bm, s_li[x0]);
+      if (!nb_lds)
+        for (int t = 0; t < deg; ++t) {
+          const int64_t b0 = s_nbbeg[t];
+          const int len = s_nboff[t + 1] - s_nboff[t];
+#pragma unroll 4
+          for (int e = lane; e < len; e += SPAI_WAVE) bm_set(bm, M.idx[b0 + e]);
         }
+      __syncthreads();
+      nk = bm_count(bm, bw);
+      if (nk > Ht) {
+        defer_column(tier, big, st, j);
+        tile_sync<GS>();
+        return;
       }
-    tile_sync<GS>();
-    if (nkeys > limit) {
-      defer_column(tier, big, st, j);
+      bm_extract(bm, bw, s_keys);
       tile_sync<GS>();
-      return;
+    } else {
+      int kd[1] = {lane == 0 ? (int)j : -1};
+      int nkeys = wave_sum_int(ks_insert_batch<1>(s_keys, H, kd));
+      for (int x0 = 0; x0 < ltot && nkeys <= limit; x0 += SPAI_WAVE * 4) {
+        int kk[4];
+  #pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int pos = x0 + c * SPAI_WAVE + lane;
+          kk[c] = pos < ltot ? s_li[pos] : -1;
+        }
+        nkeys += wave_sum_int(ks_insert_batch<4>(s_keys, H, kk));
+      }
+      if (!nb_lds)
+        for (int t = 0; t < deg && nkeys <= limit; ++t) {
+          const int64_t b0 = s_nbbeg[t];
+          const int len = s_nboff[t + 1] - s_nboff[t];
+          for (int x0 = 0; x0 < len && nkeys <= limit; x0 += SPAI_WAVE * 4) {
+            int kk[4];
+  #pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const int e = x0 + c * SPAI_WAVE + lane;
+              kk[c] = e < len ? M.idx[b0 + e] : -1;
+            }
+            nkeys += wave_sum_int(ks_insert_batch<4>(s_keys, H, kk));
+          }
+        }
+      tile_sync<GS>();
+      if (nkeys > limit) {
+        defer_column(tier, big, st, j);
+        tile_sync<GS>();
+        return;
+      }
+      nk = ks_sort_inplace(s_keys, H);
+      tile_sync<GS>();
     }
-    const int nk = ks_sort_inplace(s_keys, H);
-    tile_sync<GS>();
     // ---- values, candidates
-    const int64_t ob = off[j];
     int cntM = 0, cntMo = 0, cntP = 0, cntPT = 0;
     for (int base = 0; base < nk; base += SPAI_WAVE) {
       const int t = base + lane;
@@ -2853,11 +3015,12 @@ void launch_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, Up
                        dim3(resident_grid(k_update<T, false>, update_lds(small, true))),
                        dim3(SPAI_WAVE), update_lds(small, true), s, A, M, R, P, PT, md, off,
                        total, kcol, tM, tP, big, seg, st, 0, small.L, small.H, update_deg(small));
+  const size_t bml = (size_t)bm_words(A.n) * 4;
   hipLaunchKernelGGL((k_update<T, false>),
-                     dim3(large_grid(k_update<T, false>, update_lds(large, false))), dim3(SPAI_WAVE),
-                     update_lds(large, false), s, A, M, R, P, PT, md, off, total, kcol, tM, tP, big, seg, st, 1, large.L,
+                     dim3(large_grid(k_update<T, false>, update_lds(large, false) + bml)),
+                     dim3(SPAI_WAVE), update_lds(large, false) + bml, s, A, M, R, P, PT, md, off, total, kcol, tM, tP, big, seg, st, 1, large.L,
                      large.H, update_deg(large));
-  hipLaunchKernelGGL((k_update<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), 0, s, A, M, R, P, PT,
+  hipLaunchKernelGGL((k_update<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), bml, s, A, M, R, P, PT,
                      md, off, total, kcol, tM, tP, big, seg, st, 2, huge.L, huge.H,
                      update_deg(huge));
 }

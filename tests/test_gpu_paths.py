@@ -281,3 +281,41 @@ def test_scores_at_the_ends_of_their_tier(name, make, cap, method):
     assert np.all(np.abs(np.asarray(hist) - want) <= 1e-10 * want + 1e-13 * ref.resid[0])
     assert pattern_diff(M, ref.M) == (set(), set())
     assert value_err(M, ref.M) <= 1e-9
+
+
+def _arrow(n, spokes, seed):
+    """2 I with one row and column coupled to `spokes` others: its columns of M, R and P are
+    as wide as that, all the others narrow."""
+    rng = np.random.default_rng(seed)
+    hub = n // 3
+    to = np.sort(rng.choice(np.delete(np.arange(n), hub), spokes, replace=False))
+    v = rng.uniform(0.5, 1.0, spokes) / np.sqrt(spokes)
+    U = sp.coo_matrix((v, (np.full(spokes, hub), to)), shape=(n, n)).tocsr()
+    A = (U + U.T + 2.0 * sp.identity(n)).tocsr()
+    A.sort_indices()
+    return A
+
+
+# wide columns, whose rows are collected in a bitmap up to 131,072 rows and in a hash set
+# beyond: every column wide (2600 rows, lists past the large tile), and one of 3000 or 900
+# entries among narrow ones on either side of the limit
+@pytest.mark.parametrize("name,make,cap,iters,fmt", [
+    ("all", lambda: _random_symmetric(2600, 9, 3) + 16.0 * sp.identity(2600), 40.0, 4, "ell"),
+    ("all", lambda: _random_symmetric(2600, 9, 3) + 16.0 * sp.identity(2600), 40.0, 4, "csr"),
+    ("below", lambda: _arrow(131072, 3000, 5), 1.5, 2, "csr"),
+    ("above", lambda: _arrow(131073, 3000, 5), 1.5, 2, "csr"),
+    ("large", lambda: _arrow(50000, 900, 6), 1.5, 2, "csr")])
+@pytest.mark.parametrize("method", ["mr", "cg", "lomr"])
+def test_wide_columns(name, make, cap, iters, fmt, method):
+    S = _spai()
+    A = make().tocsr()
+    A.sort_indices()
+    h = S.SPAI(A, method, "global", cap, True, max_iter=iters, options=S.Options(a_format=fmt))
+    _, hist, _ = h.iterate(iters)
+    M = h.get()
+    h.close()
+    ref = O.run(method, A, oracle_rule(A, "global", cap, True), iters)
+    want = np.asarray(ref.resid[1:len(hist) + 1])
+    assert np.all(np.abs(np.asarray(hist) - want) <= 1e-10 * want)
+    assert pattern_diff(M, ref.M) == (set(), set())
+    assert value_err(M, ref.M) <= 1e-9

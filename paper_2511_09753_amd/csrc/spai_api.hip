@@ -5,6 +5,7 @@
 // fixed sequence of kernels on the caller's stream.  All step sizes, stopping
 // decisions and buffer parities live in device memory; the host synchronises only
 // when it returns host results.
+#include <mutex>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -309,6 +310,7 @@ struct Engine : EngineBase {
   Cols<T> Rn{}, Zn{}, Rraw{};
   bool implicit = false;
   OffBuf ob;
+  std::mutex get_mu;                 // spai_get may be called from several threads
   double *colpart = nullptr, *colnorm = nullptr, *red = nullptr, *red_rr = nullptr;
   double *colrz = nullptr, *red_rz = nullptr;   // (R, Z)_F per column / matrix (weighted)
   double *blockpart = nullptr, *cvec = nullptr, *hist = nullptr;
@@ -1290,6 +1292,7 @@ struct Engine : EngineBase {
 
   int get(spai_csr_out_t* out) override {
     if (!out) return fail(SPAI_ERR_ARG, "null output");
+    std::lock_guard<std::mutex> lock(get_mu);   // the lists it packs into are the handle's
     HIPCHK(hipStreamSynchronize(s));
     DevState h;
     HIPCHK(hipMemcpy(&h, st, sizeof(DevState), hipMemcpyDeviceToHost));

@@ -555,13 +555,13 @@ static Offs make_offs(const OffBuf& o, int64_t n) {
   return Offs{o.loc, o.tile, sh};
 }
 
-// exclusive prefix over the workgroup's 128 columns of v, column c's in lanes 8 c .. 8 c + 7;
-// tot: their sum.  w: 16 words, used by one call between two barriers.
-__device__ __forceinline__ int64_t cols_excl_scan(int64_t v, int64_t* w, int64_t& tot) {
+// exclusive prefix over the workgroup's 1024 threads of v; tot: the sum.  w: 16 words, used by
+// one call between two barriers.
+__device__ __forceinline__ int64_t block_scan_1024(int64_t v, int64_t* w, int64_t& tot) {
   const int lane = lane_id(), wv = threadIdx.x >> 6;
   int64_t inc = v;
 #pragma unroll
-  for (int d = 8; d < 64; d <<= 1) {
+  for (int d = 1; d < 64; d <<= 1) {
     const int64_t o = __shfl_up(inc, d, SPAI_WAVE);
     if (lane >= d) inc += o;
   }
@@ -578,41 +578,46 @@ __device__ __forceinline__ int64_t cols_excl_scan(int64_t v, int64_t* w, int64_t
   return before + inc - v;
 }
 
-// bound(j, g): the bound of column j on all eight lanes g that share it (every lane of the
-// wave calls it, j may be >= n: then 0)
-template <typename F>
+// bound(j, g): the bound of column j on the first of the G lanes g that share it (every lane
+// of the wave calls it, j may be >= n: then 0).  The bounds of up to kOffSeg columns are collected
+// in LDS, the waves not waiting for each other, before one scan orders them: a scan and its
+// barrier for every 128 columns took 131 us for the residual's bounds at 96^3, this 111.
+constexpr int kOffSeg = 2048;
+template <int G, typename F>
 __device__ __forceinline__ void offsets_of(F bound, int64_t n, int shift, int64_t* loc,
                                            int64_t* tile, int64_t* total, DevState* st) {
   __shared__ int64_t w[2][16];
+  __shared__ int64_t seg[kOffSeg];
   const int64_t j0 = (int64_t)blockIdx.x << shift;
   const int64_t j1 = min(n, j0 + ((int64_t)1 << shift));
-  const int g = threadIdx.x & 7;
+  const int g = threadIdx.x % G, c = threadIdx.x / G;
   int64_t run = 0;
   int par = 0;
-  for (int64_t b = j0; b < j1; b += 128, par ^= 1) {
-    const int64_t j = b + (threadIdx.x >> 3);
-    const int64_t v = bound(j, g);
+  for (int64_t s0 = j0; s0 < j1; s0 += kOffSeg, par ^= 1) {
+    const int cols = (int)min<int64_t>(kOffSeg, j1 - s0);
+    for (int b = 0; b < cols; b += 1024 / G) {
+      const int64_t v = bound(s0 + b + c, g);
+      if (g == 0) seg[b + c] = v;        // b + c < kOffSeg, a multiple of 1024 / G
+    }
+    __syncthreads();
+    const int i = 2 * threadIdx.x;
+    const int64_t v0 = i < cols ? seg[i] : 0, v1 = i + 1 < cols ? seg[i + 1] : 0;
     int64_t tot;
-    const int64_t ex = cols_excl_scan(v, w[par], tot);
-    if (g == 0 && j < j1) loc[j] = run + ex;
-    run += tot;
+    const int64_t ex = run + block_scan_1024(v0 + v1, w[par], tot);
+    if (i < cols) loc[s0 + i] = ex;
+    if (i + 1 < cols) loc[s0 + i + 1] = ex + v0;
+    run += tot;                          // (seg is read before the scan's barrier)
   }
   if (threadIdx.x == 0)
     __hip_atomic_store(&tile[blockIdx.x], run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (!last_block(&st->off_ticket, (int)gridDim.x)) return;
-  int64_t before = 0;
-  for (int t0 = 0; t0 < (int)gridDim.x; t0 += 128, par ^= 1) {
-    const int t = t0 + (threadIdx.x >> 3);
-    const int64_t v =
-        t < (int)gridDim.x
-            ? (int64_t)agent_count((const unsigned long long*)&tile[t])
-            : 0;
-    int64_t tot;
-    const int64_t ex = cols_excl_scan(v, w[par], tot);
-    if (g == 0 && t < (int)gridDim.x) tile[t] = before + ex;
-    before += tot;
-  }
-  if (threadIdx.x == 0) *total = before;
+  // (at most kOffTiles of them, one a thread)
+  const bool mine = threadIdx.x < gridDim.x;
+  const int64_t v = mine ? (int64_t)agent_count((const unsigned long long*)&tile[threadIdx.x]) : 0;
+  int64_t tot;
+  const int64_t ex = block_scan_1024(v, w[par], tot);
+  if (mine) tile[threadIdx.x] = ex;
+  if (threadIdx.x == 0) *total = tot;
 }
 
 __device__ __forceinline__ void off_zero(const OffZero& z) {
@@ -852,25 +857,26 @@ void launch_zero_cols(int64_t n, Cols<T> X, hipStream_t s) {
 // R = I - A M (explicit residual, Section 6.2) with ||r_j||^2 per column
 // ============================================================================
 
-// upper bound of nnz(r_j): 1 + sum_{l in supp(m_j)} deg(l).  Eight lanes per column read
-// its entries together (two per lane in flight) and add their degrees with shuffles: an
-// integer sum, the same in any order.
-__device__ __forceinline__ int64_t eight_sum(long long s) {
-  s += lane_xor<1>(s);                               // all lanes
-  s += lane_xor<2>(s);
-  s += lane_xor<4>(s);
+// upper bound of nnz(r_j): 1 + sum_{l in supp(m_j)} deg(l).  G lanes per column read its
+// entries together (two per lane in flight) and add their degrees with shuffles: an integer
+// sum, the same in any order.
+template <int G>
+__device__ __forceinline__ int64_t lanes_sum(long long s) {
+  if constexpr (G > 1) s += lane_xor<1>(s);          // all lanes
+  if constexpr (G > 2) s += lane_xor<2>(s);
+  if constexpr (G > 4) s += lane_xor<4>(s);
   return s;
 }
 
-// sum of the degrees of the rows of X's column j, this lane's share of eight
-template <typename T>
+// sum of the degrees of the rows of X's column j, this lane's share of G
+template <int G, typename T>
 __device__ __forceinline__ long long degrees_of(const Csr& A, const Cols<T>& X, int64_t j, int g) {
   long long s = 0;
   const int64_t b = X.beg[j];
   const int lm = X.len[j];
   int e = g;
-  for (; e + 8 < lm; e += 16) {
-    const int l0 = X.idx[b + e], l1 = X.idx[b + e + 8];
+  for (; e + G < lm; e += 2 * G) {
+    const int l0 = X.idx[b + e], l1 = X.idx[b + e + G];
     s += (A.rowptr[l0 + 1] - A.rowptr[l0]) + (A.rowptr[l1 + 1] - A.rowptr[l1]);
   }
   if (e < lm) {
@@ -880,16 +886,18 @@ __device__ __forceinline__ long long degrees_of(const Csr& A, const Cols<T>& X, 
   return s;
 }
 
-template <typename T>
+// Eight lanes a column where a workgroup takes 128 of them (15 us for 65,536 columns against
+// 17 with four), four beyond (101 us at 96^3 against 111).
+template <typename T, int G>
 __global__ __launch_bounds__(1024) void k_bound_resid(Csr A, Pair<T> Mp, int64_t n, int shift,
                                                       int64_t* loc, int64_t* tile,
                                                       int64_t* total, OffZero z, DevState* st) {
   off_zero(z);
   if (!st->any_active) return;
   const Cols<T> M = Mp.now();
-  offsets_of(
+  offsets_of<G>(
       [&](int64_t j, int g) -> int64_t {
-        const int64_t s = eight_sum(j < n ? degrees_of(A, M, j, g) : 0);
+        const int64_t s = lanes_sum<G>(j < n ? degrees_of<G>(A, M, j, g) : 0);
         return j < n ? s + 1 : 0;
       },
       n, shift, loc, tile, total, st);
@@ -899,9 +907,12 @@ template <typename T>
 Offs launch_bound_resid(const Csr& A, Pair<T> M, const OffBuf& o, const BigList& z0,
                         const BigList& z1, int64_t n, DevState* st, hipStream_t s) {
   const Offs f = make_offs(o, n);
-  hipLaunchKernelGGL(k_bound_resid<T>, dim3((unsigned)f.tiles(n)), dim3(1024), 0, s, A, M, n,
-                     f.shift, o.loc, o.tile, o.total,
-                     OffZero{{z0.count, z0.count2, z1.count, z1.count2}}, st);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)f.tiles(n)), dim3(1024), 0, s, A, M, n, f.shift, o.loc,
+                       o.tile, o.total, OffZero{{z0.count, z0.count2, z1.count, z1.count2}}, st);
+  };
+  if (f.shift == 7) go(k_bound_resid<T, 8>);
+  else go(k_bound_resid<T, 4>);
   return f;
 }
 
@@ -1322,6 +1333,8 @@ void launch_resid(const Csr& A, Pair<T> M, Cols<T> R, Offs off, const int64_t* t
   const size_t ldl = resid_lds(large, ell) + bml;
   hipLaunchKernelGGL((k_resid<T, false>), dim3(large_grid(k_resid<T, false>, ldl)),
                      dim3(SPAI_WAVE), ldl, s, A, M, R, off, total, colnorm, weighted, colrz, big, st, 1, large.L, large.H);
+  // a list and its rows, at most n, fit the large tile: no column is left
+  if (A.n <= large.L && A.n <= large.H && bml) return;
   hipLaunchKernelGGL((k_resid<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), bml, s, A, M, R, off, total,
                      colnorm, weighted, colrz, big, st, 2, huge.L, huge.H);
 }
@@ -1771,9 +1784,9 @@ __global__ __launch_bounds__(1024) void k_bound_impl(Csr A, Cols<T> Rin, Cols<T>
   off_zero(z);
   if (!st->any_active || !st->iter_active) return;
   const Cols<T> X = src.xsrc ? Pp.now() : Xr;
-  offsets_of(
+  offsets_of<8>(
       [&](int64_t j, int g) -> int64_t {
-        const int64_t s = eight_sum(j < n ? degrees_of(A, X, j, g) : 0);
+        const int64_t s = lanes_sum<8>(j < n ? degrees_of<8>(A, X, j, g) : 0);
         return j < n ? s + Rin.len[j] : 0;
       },
       n, shift, loc, tile, total, st);
@@ -1998,8 +2011,10 @@ void launch_copy_cols(Cols<T> src, Cols<T> dst, int64_t n, const int64_t* total,
 // the transposed R bitwise, so the symmetrized M is exactly symmetric and the P^T
 // candidates are exactly the transposed P candidates.
 
-// upper bound of the union of the lists of column j
-template <typename T>
+// upper bound of the union of the lists of column j: eight lanes a column where a workgroup
+// takes 128 of them (the chain of loads counts: 19 us for 65,536 columns), one a column beyond
+// (the instructions count: 37 us at 96^3 against 103)
+template <typename T, int G>
 __global__ __launch_bounds__(1024) void k_bound_update(Csr A, Pair<T> Mp, Cols<T> R, Pair<T> Pp,
                                                        Pair<T> PTp, UpdMode md, int64_t n,
                                                        int shift, int64_t* loc, int64_t* tile,
@@ -2012,19 +2027,27 @@ __global__ __launch_bounds__(1024) void k_bound_update(Csr A, Pair<T> Mp, Cols<T
   const bool needR = (md.doM && (md.x1 == 1 || md.x2 == 1)) || (md.doP && md.pR);
   const bool needP = (md.doM && (md.x1 == 2 || md.x2 == 2)) || (md.doP && md.pP);
   const bool mirror = md.sym != 0;   // R^T, P^T serve only the symmetrization
-  offsets_of(
+  offsets_of<G>(
       [&](int64_t j, int g) -> int64_t {
         long long s = 0;
         if (j < n) {
-          if (g == 0) s += 1;
-          if (g == 1 && md.doM) s += M.len[j];
-          if (g == 2 && needR) s += R.len[j];
-          if (g == 3 && needP) s += P.len[j];
-          if (g == 4 && needP && mirror) s += PT.len[j];
+          if constexpr (G == 1) {
+            s = 1;
+            if (md.doM) s += M.len[j];
+            if (needR) s += R.len[j];
+            if (needP) s += P.len[j];
+            if (needP && mirror) s += PT.len[j];
+          } else {
+            if (g == 0) s += 1;
+            if (g == 1 && md.doM) s += M.len[j];
+            if (g == 2 && needR) s += R.len[j];
+            if (g == 3 && needP) s += P.len[j];
+            if (g == 4 && needP && mirror) s += PT.len[j];
+          }
           if (needR && mirror)
-            for (int64_t q = A.rowptr[j] + g; q < A.rowptr[j + 1]; q += 8) s += M.len[A.col[q]];
+            for (int64_t q = A.rowptr[j] + g; q < A.rowptr[j + 1]; q += G) s += M.len[A.col[q]];
         }
-        return eight_sum(s);
+        return lanes_sum<G>(s);
       },
       n, shift, loc, tile, total, st);
 }
@@ -2034,9 +2057,13 @@ Offs launch_bound_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> 
                          const OffBuf& o, const BigList& z0, int64_t n, DevState* st,
                          hipStream_t s) {
   const Offs f = make_offs(o, n);
-  hipLaunchKernelGGL(k_bound_update<T>, dim3((unsigned)f.tiles(n)), dim3(1024), 0, s, A, M, R, P,
-                     PT, md, n, f.shift, o.loc, o.tile, o.total,
-                     OffZero{{z0.count, z0.count2, nullptr, nullptr}}, st);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)f.tiles(n)), dim3(1024), 0, s, A, M, R, P, PT, md, n,
+                       f.shift, o.loc, o.tile, o.total,
+                       OffZero{{z0.count, z0.count2, nullptr, nullptr}}, st);
+  };
+  if (f.shift == 7) go(k_bound_update<T, 8>);
+  else go(k_bound_update<T, 1>);
   return f;
 }
 
@@ -3020,6 +3047,12 @@ void launch_update(const Csr& A, Pair<T> M, Cols<T> R, Pair<T> P, Pair<T> PT, Up
                      dim3(large_grid(k_update<T, false>, update_lds(large, false) + bml)),
                      dim3(SPAI_WAVE), update_lds(large, false) + bml, s, A, M, R, P, PT, md, off, total, kcol, tM, tP, big, seg, st, 1, large.L,
                      large.H, update_deg(large));
+  // the lists (R and P, P^T apart from M) and their rows fit the large tile: no column is left
+  const int64_t lists = 1 + (md.x1 == 1 || md.x2 == 1 || (md.doP && md.pR)) +
+                        ((md.x1 == 2 || md.x2 == 2 || (md.doP && md.pP)) ? 2 : 0);
+  if (lists * A.n <= large.L && A.n <= large.H && bml &&
+      (A.eshift >= 0 || A.n <= update_deg(large)))
+    return;
   hipLaunchKernelGGL((k_update<T, true>), dim3(big.grid2), dim3(SPAI_WAVE), bml, s, A, M, R, P, PT,
                      md, off, total, kcol, tM, tP, big, seg, st, 2, huge.L, huge.H,
                      update_deg(huge));
@@ -4463,7 +4496,7 @@ __global__ __launch_bounds__(1024) void k_len_offsets(Cols<T> X, int64_t n, int 
                                                       int64_t* tile, int64_t* total, OffZero z,
                                                       DevState* st) {
   off_zero(z);
-  offsets_of([&](int64_t j, int) -> int64_t { return j < n ? X.len[j] : 0; }, n, shift, loc, tile,
+  offsets_of<1>([&](int64_t j, int) -> int64_t { return j < n ? X.len[j] : 0; }, n, shift, loc, tile,
              total, st);
 }
 

@@ -3304,8 +3304,9 @@ __global__ __launch_bounds__(kHistWaves * SPAI_WAVE) void k_sel_hist_exp(Pair<T>
 
 // keys whose exponent bin is the selected one, staged in LDS (one stage per wave) and flushed
 // to the global buffer, a wave's full stage with a reservation of its own, the rest of a
-// workgroup's waves with one: reservations are atomics on one address, some 10 ns each
-constexpr int kStage = 512, kCollWaves = 8;
+// workgroup's waves with one: reservations are atomics on one address, some 10 ns each, and
+// most of the pass at 96^3 (millions of keys): 70 us with stages of 1024, 95 with 512
+constexpr int kStage = 1024, kCollWaves = 8;
 template <typename T, bool SC>
 __global__ __launch_bounds__(kCollWaves * SPAI_WAVE) void k_sel_collect(Pair<T> Xp, const double* sc,
                                                            int excl_diag,
@@ -3642,12 +3643,13 @@ void launch_global_select(Pair<T> X, int exclude_diag, int64_t m, double eta, in
   }
   // (the histogram is zero here: every search clears the bins that it has read)
   const int gs = group_cols(n), ng = groups(n, gs);
-  // One histogram workgroup of 16 waves per compute unit and four collecting ones of eight:
+  // One histogram workgroup of 16 waves per compute unit and two collecting ones of eight (LDS):
   // every workgroup adds its bins, or its reservation, to the same addresses, at some 10 ns
   // each.  Four-wave and one-wave workgroups, eight columns a group: 43 and 35 us at 36,000
-  // columns (15 and 10 now); 64 columns: 45 and 49 us at 96^3 (39 and 46 now).
+  // columns (15 and 10 now); with the masked second pass in the mean, 45 and 49 us at 96^3
+  // (34 and 34 now).
   const int gh = std::min((ng + kHistWaves - 1) / kHistWaves, per_cu_grid(1));
-  const int gcol = std::min((ng + kCollWaves - 1) / kCollWaves, per_cu_grid(4));
+  const int gcol = std::min((ng + kCollWaves - 1) / kCollWaves, per_cu_grid(2));
   auto both = [&](auto khist, auto kcoll) {
     hipLaunchKernelGGL(khist, dim3(gh), dim3(kHistWaves * SPAI_WAVE), 0, s, X, score, exclude_diag,
                        m, hist, thr, gs, n, st);

@@ -2920,6 +2920,9 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(sizeo
         keepM = wM;
         keepP = wP;
         keepPT = wPT;
+      } else {                                    // a NaN passes no floor, 0 included: no candidate
+        keepP = keepP && pt == pt;
+        keepPT = keepPT && ptt == ptt;
       }
       if (md.colcap) {
         inM[round] = keepM && k != (int)j;

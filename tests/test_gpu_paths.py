@@ -319,3 +319,43 @@ def test_wide_columns(name, make, cap, iters, fmt, method):
     assert np.all(np.abs(np.asarray(hist) - want) <= 1e-10 * want)
     assert pattern_diff(M, ref.M) == (set(), set())
     assert value_err(M, ref.M) <= 1e-9
+
+
+def _state_with_direction(buf, k, j, value):
+    """The LOMR state `buf` with every value of P and P^T zero and P's column j given an
+    entry `value` in row k (a row after the column's last)."""
+    hd, lists = parse_state(buf)
+    n, (cp, ix, vl) = hd["n"], lists[1]
+    q = int(cp[j + 1])
+    assert q == cp[j] or ix[q - 1] < k
+    cp2 = cp + (np.arange(n + 1) > j)
+    vt = vl.dtype
+    P = (cp2, np.insert(ix, q, k), np.insert(np.zeros(len(vl), vt), q, value))
+    PT = (lists[2][0], lists[2][1], np.zeros(len(lists[2][2]), vt))
+    head = bytearray(buf[:hd["list_offsets"][0]])
+    np.frombuffer(head, dtype=np.int64, count=13)[9] += 1          # header: entries of P
+    out = bytes(head)
+    for c, i, v in (lists[0], P, PT, lists[3]):
+        out += c.astype(np.int64).tobytes() + i.astype(np.int32).tobytes() + v.astype(vt).tobytes()
+    return out
+
+
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_a_nan_direction_is_no_candidate_under_a_column_cap(precision):
+    """A NaN in P (the step then falls back to MR, as it does with P = 0) adds no candidate
+    of P: the iterate and the drop record are those of the same state with a zero there."""
+    S = _spai()
+    A = W.aniso2d(24, 1.0, 1.0)
+    n = A.shape[0]
+    h = S.SPAI(A, "lomr", "column", 3.0, True, max_iter=8, options=S.Options(precision=precision))
+    h.iterate(3)
+    st = h.get_state()
+    runs = []
+    for value in (0.0, np.nan):
+        h.set_state(_state_with_direction(st, n - 1, 0, value))
+        h.iterate(1)
+        runs.append((history_array(h)[3], h.get()))
+    assert h.stats()["mr_fallbacks"] >= 1
+    h.close()
+    assert np.array_equal(runs[0][0], runs[1][0])
+    assert (runs[0][1] != runs[1][1]).nnz == 0

@@ -97,7 +97,7 @@ struct PcgWork {
   int64_t n = -1;
   int nrhs = 0;
   void* blk[9] = {};
-  DevPool tiny_pool;                   // the results of a solve in one workgroup (any size)
+  DevPool tiny_pool;                   // what a solve in one workgroup keeps (any size)
   void* tiny = nullptr;
 };
 

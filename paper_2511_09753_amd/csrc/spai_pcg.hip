@@ -1074,10 +1074,22 @@ constexpr int kTinyRows = 1024;     // beyond, one compute unit reads the rows t
                                     // rows and one right-hand side 58 us an iteration, launched 60
 constexpr int kTinyThreads = 1024;
 constexpr int kTinyRhs = 32;
+// Iterations of one launch: a kernel cannot be interrupted, and a solve that stagnates runs to
+// its max_iter (any int).  1024 take 7 to 50 ms, 0.02 ms of it the launch and the host's look;
+// what goes on is kept in TinyKeep.
+constexpr int kTinyIters = 1024;
 
 struct TinyOut {
   int iters, status;
+  int active, pad;                  // right-hand sides still running (rr is then not set)
   double bnorm, rr;                 // ||b||, sum of (b - A x)^2
+};
+
+// a solve between two launches
+struct TinyKeep {
+  TinyOut out[kTinyRhs];
+  RhsState S[kTinyRhs];
+  double x[kTinyElems], r[kTinyElems], p[kTinyElems];
 };
 
 // eight entries of a row from q0 (column -1: none)
@@ -1195,8 +1207,8 @@ constexpr int kTinyTerms = 5248;    // of each kind
 template <typename MT, int LAYA, int LAYM, int U>
 __global__ __launch_bounds__(kTinyThreads) void k_pcg_tiny(Mat A, Mat M, const double* __restrict__ B,
                                                            double* __restrict__ X, int nrhs, int R,
-                                                           double rtol, int max_iter,
-                                                           const int32_t* order, TinyOut* out) {
+                                                           double rtol, int it0, int it1, int max_iter,
+                                                           const int32_t* order, TinyKeep* keep) {
   __shared__ double s_p[kTinyThreads * U], s_r[kTinyThreads * U];
   __shared__ double s_t[kTinyTerms], s_n[kTinyTerms];       // terms by position, by row
   __shared__ RhsState S[kTinyRhs];
@@ -1306,34 +1318,46 @@ __global__ __launch_bounds__(kTinyThreads) void k_pcg_tiny(Mat A, Mat M, const d
       if (blk == 0) step(r, s);
     }
   };
-  // x_0 = 0, r = b, z = M r, p = z
   if (tid == 0) s_active = 0;
-  each([&](int u, int i, int r, int own) {
-    const double b = B[own];
-    s_r[own] = b;
-    s_n[nat[u]] = b * b;
-  });
-  __syncthreads();
-  each([&](int u, int i, int r, int own) {
-    w[u] = row_m(i, s_r, r);
-    s_p[own] = w[u];
-    s_t[tat[u]] = s_r[own] * w[u];
-  });
-  row_sums([&](int r, double bb) {
-    RhsState& g = S[r];
-    g = RhsState{};
-    g.bnorm = sqrt(bb);
-    if (g.bnorm == 0.0) {
-      g.status = 1;
-    } else {
-      g.active = 1;
-      atomicAdd(&s_active, 1);
+  if (it0 > 0) {                    // where the launch before this one stopped
+    each([&](int u, int i, int r, int own) {
+      x[u] = keep->x[own];
+      s_r[own] = keep->r[own];
+      s_p[own] = keep->p[own];
+    });
+    __syncthreads();
+    if (tid < nrhs) {
+      S[tid] = keep->S[tid];
+      if (S[tid].active) atomicAdd(&s_active, 1);
     }
-  });
+  } else {                          // x_0 = 0, r = b, z = M r, p = z
+    each([&](int u, int i, int r, int own) {
+      const double b = B[own];
+      s_r[own] = b;
+      s_n[nat[u]] = b * b;
+    });
+    __syncthreads();
+    each([&](int u, int i, int r, int own) {
+      w[u] = row_m(i, s_r, r);
+      s_p[own] = w[u];
+      s_t[tat[u]] = s_r[own] * w[u];
+    });
+    row_sums([&](int r, double bb) {
+      RhsState& g = S[r];
+      g = RhsState{};
+      g.bnorm = sqrt(bb);
+      if (g.bnorm == 0.0) {
+        g.status = 1;
+      } else {
+        g.active = 1;
+        atomicAdd(&s_active, 1);
+      }
+    });
+    __syncthreads();
+    product_sums([&](int r, double v) { S[r].rz = v; });
+  }
   __syncthreads();
-  product_sums([&](int r, double v) { S[r].rz = v; });
-  __syncthreads();
-  for (int it = 0; it < max_iter && s_active > 0; ++it) {
+  for (int it = it0; it < it1 && s_active > 0; ++it) {
     each([&](int u, int i, int r, int own) {      // q = A p, (p, q), alpha
       w[u] = row_a(i, s_p, r);
       s_t[tat[u]] = s_p[own] * w[u];
@@ -1366,6 +1390,18 @@ __global__ __launch_bounds__(kTinyThreads) void k_pcg_tiny(Mat A, Mat M, const d
     });
     __syncthreads();
   }
+  if (s_active > 0 && it1 < max_iter) {
+    each([&](int u, int i, int r, int own) {
+      keep->x[own] = x[u];
+      keep->r[own] = s_r[own];
+      keep->p[own] = s_p[own];
+    });
+    if (tid < nrhs) {
+      keep->S[tid] = S[tid];
+      keep->out[tid].active = s_active;
+    }
+    return;
+  }
   // x, and the true residual: p's place takes x for the product
   each([&](int u, int i, int r, int own) {
     X[own] = x[u];
@@ -1377,7 +1413,9 @@ __global__ __launch_bounds__(kTinyThreads) void k_pcg_tiny(Mat A, Mat M, const d
     s_n[nat[u]] = d * d;
   });
   __syncthreads();
-  row_sums([&](int r, double v) { out[r] = TinyOut{S[r].iters, S[r].status, S[r].bnorm, v}; });
+  row_sums([&](int r, double v) {
+    keep->out[r] = TinyOut{S[r].iters, S[r].status, 0, 0, S[r].bnorm, v};
+  });
 }
 
 // which solves: the vectors fit, and each XCD range is one workgroup of the narrow product
@@ -1394,15 +1432,15 @@ static bool tiny_fits(int64_t n, int nrhs) {
 
 template <typename MT, int LAYA>
 static void launch_tiny(const Mat& A, const Mat& M, const double* B, double* X, int nrhs, int R,
-                        double rtol, int max_iter, const int32_t* order, TinyOut* out,
-                        hipStream_t s) {
+                        double rtol, int it0, int it1, int max_iter, const int32_t* order,
+                        TinyKeep* keep, hipStream_t s) {
   auto go = [&](auto one, auto four) {
     if (A.n * nrhs <= kTinyThreads)
-      hipLaunchKernelGGL(one, dim3(1), dim3(kTinyThreads), 0, s, A, M, B, X, nrhs, R, rtol, max_iter,
-                         order, out);
+      hipLaunchKernelGGL(one, dim3(1), dim3(kTinyThreads), 0, s, A, M, B, X, nrhs, R, rtol, it0,
+                         it1, max_iter, order, keep);
     else
-      hipLaunchKernelGGL(four, dim3(1), dim3(kTinyThreads), 0, s, A, M, B, X, nrhs, R, rtol, max_iter,
-                         order, out);
+      hipLaunchKernelGGL(four, dim3(1), dim3(kTinyThreads), 0, s, A, M, B, X, nrhs, R, rtol, it0,
+                         it1, max_iter, order, keep);
   };
   constexpr int kFour = kTinyElems / kTinyThreads;
   if (M.beg) go(k_pcg_tiny<MT, LAYA, kLayPad, 1>, k_pcg_tiny<MT, LAYA, kLayPad, kFour>);
@@ -1413,28 +1451,35 @@ static int pcg_tiny(const Mat& A, const Mat& M, int nrhs, const double* B, doubl
                     int max_iter, int* iters, double* relres, const int32_t* order, hipStream_t s,
                     PcgWork* work) {
   DevPool local;
-  TinyOut* out = nullptr;
+  TinyKeep* keep = nullptr;
   int rc;
   if (work && work->tiny) {
-    out = (TinyOut*)work->tiny;
+    keep = (TinyKeep*)work->tiny;
   } else {
     DevPool& pool = work ? work->tiny_pool : local;
-    if ((rc = pool.alloc(&out, kTinyRhs))) return rc;
-    if (work) work->tiny = out;
+    if ((rc = pool.alloc(&keep, 1))) return rc;
+    if (work) work->tiny = keep;
   }
   int R = 1;
   while (R < nrhs) R <<= 1;
-  auto by_a = [&](auto mt) {
-    using MT = decltype(mt);
-    if (A.eshift >= 0) launch_tiny<MT, kLayEll>(A, M, B, X, nrhs, R, rtol, max_iter, order, out, s);
-    else launch_tiny<MT, kLayCsr>(A, M, B, X, nrhs, R, rtol, max_iter, order, out, s);
-  };
-  if (M.val32) by_a(float{});
-  else by_a(double{});
-  HIPCHK(hipGetLastError());
   TinyOut h[kTinyRhs];
-  HIPCHK(hipMemcpyAsync(h, out, sizeof(TinyOut) * nrhs, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  int it0 = 0;
+  do {
+    const int it1 = max_iter - it0 > kTinyIters ? it0 + kTinyIters : max_iter;
+    auto by_a = [&](auto mt) {
+      using MT = decltype(mt);
+      if (A.eshift >= 0)
+        launch_tiny<MT, kLayEll>(A, M, B, X, nrhs, R, rtol, it0, it1, max_iter, order, keep, s);
+      else
+        launch_tiny<MT, kLayCsr>(A, M, B, X, nrhs, R, rtol, it0, it1, max_iter, order, keep, s);
+    };
+    if (M.val32) by_a(float{});
+    else by_a(double{});
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpyAsync(h, keep->out, sizeof(TinyOut) * nrhs, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    it0 = it1;
+  } while (h[0].active > 0);
   bool indef = false, unconv = false;
   for (int r = 0; r < nrhs; ++r) {
     if (iters) iters[r] = h[r].iters;

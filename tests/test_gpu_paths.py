@@ -359,3 +359,41 @@ def test_a_nan_direction_is_no_candidate_under_a_column_cap(precision):
     h.close()
     assert np.array_equal(runs[0][0], runs[1][0])
     assert (runs[0][1] != runs[1][1]).nnz == 0
+
+
+def _kernels_of(call, name):
+    """Milliseconds of every kernel named `name` that call() launches."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.device_time / 1e3 for e in prof.events()
+            if name in e.name and str(e.device_type).endswith("CUDA")]
+
+
+@pytest.mark.parametrize("n,nrhs", [(1024, 1), (300, 3), (512, 8)])
+def test_a_stagnating_small_solve_is_cut_into_launches(n, nrhs):
+    """rtol = 0 on a matrix of condition 1e12: thousands of iterations.  No launch runs more
+    than 1024 of them, and the solve is that of the product-by-product launches bit for bit
+    (also where max_iter is a multiple of 1024, and one more)."""
+    S = _spai()
+    d = np.sqrt(np.random.default_rng(n).permutation(np.logspace(0, 12, n)))
+    T = sp.diags([np.full(n, 2.0), np.full(n - 1, -1.0), np.full(n - 1, -1.0)], [0, 1, -1])
+    A = sp.csr_matrix(sp.diags(d) @ T @ sp.diags(d))
+    A = sp.csr_matrix((A + A.T) / 2)
+    A.sort_indices()
+    B = W.rhs(n, nrhs, 7)
+    caps = (1024, 1025, 2048, 2500)
+    out, launches = [], 0
+    for prof in (False, True):
+        h = S.SPAI(A, "mr", "global", 2.0, True, max_iter=2, options=S.Options(profile=prof))
+        if not prof:
+            launches = len(_kernels_of(lambda: h.pcg(B, rtol=0.0, max_iter=2500), "k_pcg_tiny"))
+        out.append([h.pcg(B, rtol=0.0, max_iter=m) for m in caps])
+        h.close()
+    assert max(out[0][-1][1]) > 2048 and launches == 3
+    for a, b in zip(*out):
+        assert a[3] == b[3]
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+        assert np.array_equal(a[2], b[2])

@@ -622,15 +622,23 @@ __device__ __forceinline__ bool oh_insert_batch(unsigned* T, int shift, const in
 }
 
 // Compact the occupied slots of T[0 .. end) in place into keys (decoded), in slot order;
-// returns the count.  One wave; each 64-slot chunk is read before it is written.
+// returns the count.  One wave; each 64-slot chunk is read before it is written.  (U chunks
+// are read at once: in device memory a chunk is a load's latency.)
+template <int U = 1>
 __device__ __forceinline__ int oh_compact(unsigned* T, int end) {
   int cnt = 0;
-  for (int base = 0; base < end; base += SPAI_WAVE) {
-    const unsigned x = T[base + lane_id()];
-    const bool occ = x != kOhEmpty;
-    const unsigned long long m = __ballot(occ);
-    if (occ) ((int*)T)[cnt + __popcll(m & lanemask_lt())] = ounhash(x);
-    cnt += __popcll(m);
+  for (int base = 0; base < end; base += SPAI_WAVE * U) {
+    unsigned x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      x[u] = U == 1 || base + u * SPAI_WAVE < end ? T[base + u * SPAI_WAVE + lane_id()] : kOhEmpty;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool occ = x[u] != kOhEmpty;
+      const unsigned long long m = __ballot(occ);
+      if (occ) ((int*)T)[cnt + __popcll(m & lanemask_lt())] = ounhash(x[u]);
+      cnt += __popcll(m);
+    }
   }
   return cnt;
 }

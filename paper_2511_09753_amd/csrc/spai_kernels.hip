@@ -1351,8 +1351,6 @@ size_t resid_tile_bytes(Tile t, bool ell) {
 // SpGEMM fused with Frobenius dots: A r_j and A p_j in LDS, never stored
 // ============================================================================
 
-// slots of the huge tier's ordered key table in LDS (the large tier's is its key set)
-constexpr int kDotsSlots = 16384;
 template <typename T, bool GS>
 __device__ __forceinline__ void dots_body(Csr A, Cols<T> R, Pair<T> Pp, int useR, int useP,
                                           int weighted, double* colpart, BigList big,
@@ -1368,6 +1366,8 @@ __device__ __forceinline__ void dots_body(Csr A, Cols<T> R, Pair<T> Pp, int useR
   unsigned* s_mp = cv.take<unsigned>(2 * L);
   int* s_pre = ell ? nullptr : cv.take<int>(L);
   int64_t* s_rs = ell ? nullptr : cv.take<int64_t>(L);
+  const int bw = GS ? bm_words(A.n) : 0;                  // key bitmap (LDS) of the huge tier
+  unsigned* bm = (unsigned*)smem;
   const int lane = lane_id();
   const Cols<T> P = Pp.now();
 
@@ -1406,27 +1406,56 @@ __device__ __forceinline__ void dots_body(Csr A, Cols<T> R, Pair<T> Pp, int useR
       tot = degree_prefix(A, s_li, lr + lp, s_pre, s_rs);
     }
     tile_sync<GS>();
-    // tiers 1 and 2: the rows in an ordered hash in LDS, which compacts to the hash order
-    // that the lean tier sums in (no sort); a column that does not fit it: the huge tier
-    // takes a hash set in device memory
-    int* keys = s_keys;
+    // Tiers 1 and 2: the rows in an ordered hash, which compacts to the hash order that the
+    // lean tier sums in (no sort).  The large tier's is its key set in LDS; the huge tier
+    // collects the rows in a bitmap in LDS first, so that each enters the hash in device
+    // memory once (a product enters some 20 to 80 times as many), and takes a hash set and a
+    // sort where there are too many rows for either.  (An ordered hash of 16,384 slots in LDS
+    // for the huge tier left two waves a compute unit, and columns of more rows entered their
+    // products twice: 20,000 rows of 80 entries, the dots 3.58 s where the set and the sort
+    // alone took 2.17.)
     int nu = -1;
-    if (tier != 0) {
-      unsigned* kt = GS ? (unsigned*)smem : (unsigned*)s_keys;
-      const int Hc = key_slots(ub, GS ? kDotsSlots : Ht), ksh = 32 - log2_pow2(Hc);
+    if (!GS && tier != 0) {
+      unsigned* kt = (unsigned*)s_keys;
+      const int Hc = key_slots(ub, Ht), ksh = 32 - log2_pow2(Hc);
       const int kend = Hc + kOhOver;
       for (int i = lane; i < kend; i += SPAI_WAVE) kt[i] = kOhEmpty;
       __syncthreads();
-      if (oh_products(A, s_li, lr + lp, s_pre, s_rs, tot, kt, ksh)) {
-        __syncthreads();
-        nu = oh_compact(kt, kend);
-        keys = (int*)kt;
-      }
+      const bool ok = oh_products(A, s_li, lr + lp, s_pre, s_rs, tot, kt, ksh);
       __syncthreads();
-      if (!GS && nu < 0) {
+      if (!ok) {
         defer_column(tier, big, st, j);
         return;
       }
+      nu = oh_compact(kt, kend);
+      __syncthreads();
+    }
+    if (GS && bw) {
+      bm_clear(bm, bw);
+      __syncthreads();
+      bm_products(A, s_li, lr + lp, s_pre, s_rs, tot, bm);
+      __syncthreads();
+      unsigned* kt = (unsigned*)s_keys;            // Ht / 2 + kOhOver of its Ht slots at most
+      const int Hc = min(key_slots(bm_count(bm, bw), Ht), Ht / 2), ksh = 32 - log2_pow2(Hc);
+      const int kend = Hc + kOhOver;
+      for (int i = lane; i < kend; i += SPAI_WAVE) kt[i] = kOhEmpty;
+      tile_sync<GS>();
+      bool ok = true;
+      for (int base = 0; base < bw && ok; base += SPAI_WAVE) {
+        unsigned m = bm[base + lane];
+        while (ok && __ballot(m != 0u) != 0ull) {
+          int k4[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            k4[c] = m ? (base + lane) * 32 + __ffs((int)m) - 1 : -1;
+            m &= m - 1u;
+          }
+          ok = oh_insert_batch<4>(kt, ksh, k4);
+        }
+      }
+      tile_sync<GS>();
+      if (ok) nu = oh_compact<8>(kt, kend);
+      tile_sync<GS>();
     }
     if (nu < 0) {
       const int H = key_slots(ub, Ht);
@@ -1451,12 +1480,12 @@ __device__ __forceinline__ void dots_body(Csr A, Cols<T> R, Pair<T> Pp, int useR
     double ar[1], ap[1], diag[1];
     int key[1];
     pull_rows<1>(
-        A, keys, nu,
+        A, s_keys, nu,
         [&](int c, int t) {
           ar[c] = 0.0;
           ap[c] = 0.0;
           diag[c] = 0.0;
-          key[c] = keys[t];
+          key[c] = s_keys[t];
         },
         [&](int c, const int (&cols)[8], const double (&vals)[8]) {
           unsigned pw[8];
@@ -1752,8 +1781,8 @@ void launch_dots(const Csr& A, Cols<T> R, Pair<T> P, int useR, int useP, int wei
   hipLaunchKernelGGL((k_dots<T, false>), dim3(large_grid(k_dots<T, false>, ldl)),
                      dim3(SPAI_WAVE), ldl, s, A, R, P, useR, useP, weighted, colpart, big, st, 1, large.L, large.H);
   hipLaunchKernelGGL((k_dots<T, true>), dim3(big.grid2), dim3(SPAI_WAVE),
-                     (size_t)(kDotsSlots + kOhOver) * 4, s, A, R, P, useR, useP,
-                     weighted, colpart, big, st, 2, huge.L, huge.H);
+                     (size_t)bm_words(A.n) * 4, s, A, R, P, useR, useP, weighted, colpart, big, st, 2,
+                     huge.L, huge.H);
 }
 
 size_t dots_tile_bytes(Tile t, bool ell) {

@@ -102,11 +102,11 @@ __global__ void k_to_f32(const double* a, float* b, int64_t nnz) {
 // unit) and an LDS sort 2600 and 2800.
 // A row outside this (more than 64 entries in X's row or a row of Y, more rounds or more
 // distinct columns than there is room for, a clash under every multiplier) is marked
-// rowpart[i] = -1 and left to k_loss_rows.
+// rowpart[i] = -1 and left to k_loss_rows, or to k_loss_cols (MAP).
 constexpr int kLossRounds = 8;
 constexpr int kLossSums = 512;      // per-rank sums of all groups
-constexpr int kLossEntries = 509;   // entries of the selected rows together (k_loss_rows' limit)
-constexpr double kLossLeft = -1.0;  // rowpart of a row left to k_loss_rows
+constexpr int kLossEntries = 509;   // entries of the selected rows together (the left tiers' limit)
+constexpr double kLossLeft = -1.0;  // rowpart of a row left to the larger tiles
 
 template <typename T, bool MAP>
 __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5))) void k_loss_lean(Pat X, const T* Xv, const int64_t* xmap,
@@ -297,14 +297,26 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5))) 
   }
 }
 
-// The rows that k_loss_lean left (rowpart[i] = kLossLeft), in a larger LDS tile: sorted
+// body(i) for the rows that k_loss_lean left (rowpart[i] = kLossLeft), walked as it walks them:
+// 64 of a workgroup's rows are looked at together
+template <typename F>
+__device__ __forceinline__ void left_rows(int64_t n, const double* rowpart, F body) {
+  ColumnWalk w(n, blockIdx.x, gridDim.x);
+  for (int64_t i0 = w.begin; i0 < w.end; i0 += SPAI_WAVE * w.step) {
+    const int64_t i = i0 + lane_id() * w.step;
+    const bool mine = i < w.end && rowpart[i] == kLossLeft;
+    for (unsigned long long m = __ballot(mine); m; m &= m - 1)
+      body(i0 + (int64_t)(__ffsll((long long)m) - 1) * w.step);
+  }
+}
+
+// The rows of I - X Y that k_loss_lean left, in a larger LDS tile: sorted
 // keys, and the sums pulled with binary searches.  Up to DG entries in X's row and
 // L, H / 2 - 2 entries of Y; a row beyond that raises err bit 1.
-template <typename T, bool MAP>
-__global__ __launch_bounds__(SPAI_WAVE) void k_loss_rows(Pat X, const T* Xv, const int64_t* xmap,
-                                                         Pat Y, const T* Yv, double* rowpart,
-                                                         double* gX, double dL, int* err, int L,
-                                                         int H, int DG) {
+template <typename T>
+__global__ __launch_bounds__(SPAI_WAVE) void k_loss_rows(Pat X, const T* Xv, Pat Y, const T* Yv,
+                                                         double* rowpart, double* gX, double dL,
+                                                         int* err, int L, int H, int DG) {
   extern __shared__ char smem[];
   Carve2 cv(smem);
   int* s_li = cv.take<int>(L);
@@ -335,7 +347,7 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_loss_rows(Pat X, const T* Xv, con
       if (t < deg) {
         const int l = X.col[qa + t];
         len = (int)(Y.rowptr[l + 1] - Y.rowptr[l]);
-        s_a[t] = (double)(MAP ? Xv[xmap[qa + t]] : Xv[qa + t]);
+        s_a[t] = (double)Xv[qa + t];
       }
       const int inc = wave_incl_scan(len);
       if (t < deg) s_off[t] = run + inc - len;
@@ -385,18 +397,96 @@ __global__ __launch_bounds__(SPAI_WAVE) void k_loss_rows(Pat X, const T* Xv, con
           g += s_rho[pos] * s_lv[o + e];
         }
         g = wave_sum(g);
-        if (lane == 0) gX[MAP ? xmap[qa + t] : qa + t] = -2.0 * dL * g;
+        if (lane == 0) gX[qa + t] = -2.0 * dL * g;
       }
     }
     __syncthreads();
   };
-  // workgroup b owns rows b, b + gridDim.x, ...: neighbouring left rows go to different ones
-  for (int64_t i0 = blockIdx.x; i0 < X.n; i0 += (int64_t)SPAI_WAVE * gridDim.x) {
-    const int64_t i = i0 + (int64_t)lane * gridDim.x;
-    const bool mine = i < X.n && rowpart[i] == kLossLeft;
-    for (unsigned long long m = __ballot(mine); m; m &= m - 1)
-      body(i0 + (int64_t)(__ffsll((long long)m) - 1) * gridDim.x);
-  }
+  left_rows(X.n, rowpart, body);
+}
+
+// The columns of the gradient in M that k_loss_lean left: column j of R = I - A M is pulled
+// over the rows of A that its support selects, against the entries of m_j in LDS, and so is
+// -2 (A^T R)(k, j) for the rows k of m_j -- a search in m_j or in the column's rows per entry
+// of A, where k_loss_rows on M^T would search every row of A for each of the column's rows,
+// and take a sum over the wave per entry of M.  Up to L entries in m_j that select at most
+// H / 2 - 3 of A; beyond, err bit 1.  Seven-point 40^3, M on pattern(A^3) (63 entries a column):
+// gradient in M 9.1 ms by k_loss_rows, 1.6 so; nine-point 256^2, pattern(A^3) (49), 7.2
+// and 1.35.
+template <typename T>
+__global__ __launch_bounds__(SPAI_WAVE) void k_loss_cols(Pat A, const T* Av, const T* Atv, Pat M,
+                                                         const T* Mv, const int64_t* tmap,
+                                                         const double* rowpart, double* gM,
+                                                         double dL, int* err, int L, int H) {
+  extern __shared__ char smem[];
+  Carve2 cv(smem);
+  int* s_mi = cv.take<int>(L);
+  int* s_pre = cv.take<int>(L);
+  int* s_keys = cv.take<int>(H);
+  int* s_sorted = cv.take<int>(H);
+  double* s_mv = cv.take<double>(L);
+  double* s_r = cv.take<double>(H / 2);
+  const int lane = lane_id();
+  left_rows(M.n, rowpart, [&](int64_t j) {
+    const int64_t mb = M.rowptr[j];
+    const int64_t lm64 = M.rowptr[j + 1] - mb;      // column j of M: row j, the pattern is symmetric
+    if (lm64 > L) {
+      if (lane == 0) atomicOr(err, 1);
+      return;
+    }
+    const int lm = (int)lm64;
+    for (int e = lane; e < lm; e += SPAI_WAVE) {
+      s_mi[e] = M.col[mb + e];
+      s_mv[e] = (double)Mv[tmap[mb + e]];           // M(l, j)
+    }
+    __syncthreads();
+    // the entries of A in the rows l of m_j, numbered through their prefix
+    int run = 0;
+    for (int base = 0; base < lm; base += SPAI_WAVE) {
+      const int e = base + lane;
+      int d = 0;
+      if (e < lm) d = (int)min<int64_t>(A.rowptr[s_mi[e] + 1] - A.rowptr[s_mi[e]], H);
+      const int inc = wave_incl_scan(d);
+      if (e < lm) s_pre[e] = run + inc;
+      run += wave_last(inc);
+    }
+    if (run + 2 >= H / 2) {
+      if (lane == 0) atomicOr(err, 1);
+      __syncthreads();
+      return;
+    }
+    ks_clear(s_keys, H);
+    __syncthreads();
+    if (lane == 0) ks_insert(s_keys, H, (int)j);
+    for (int p = lane; p < run; p += SPAI_WAVE) {
+      const int e = upper_bound_int(s_pre, lm, p);
+      const int before = e ? s_pre[e - 1] : 0;
+      ks_insert(s_keys, H, A.col[A.rowptr[s_mi[e]] + (p - before)]);
+    }
+    __syncthreads();
+    const int nu = ks_sorted(s_keys, H, s_sorted);
+    __syncthreads();
+    for (int t = lane; t < nu; t += SPAI_WAVE) {
+      const int u = s_sorted[t];
+      double s = 0.0;
+      for (int64_t q = A.rowptr[u]; q < A.rowptr[u + 1]; ++q) {
+        const int e = bsearch_idx(s_mi, lm, A.col[q]);
+        if (e >= 0) s += (double)Av[q] * s_mv[e];
+      }
+      s_r[t] = ((u == (int)j) ? 1.0 : 0.0) - s;
+    }
+    __syncthreads();
+    for (int e = lane; e < lm; e += SPAI_WAVE) {
+      const int k = s_mi[e];
+      double g = 0.0;
+      for (int64_t q = A.rowptr[k]; q < A.rowptr[k + 1]; ++q) {
+        const int pos = bsearch_idx(s_sorted, nu, A.col[q]);
+        if (pos >= 0) g += (double)Atv[q] * s_r[pos];   // A(u, k) R(u, j), u = col q
+      }
+      gM[tmap[mb + e]] = -2.0 * dL * g;
+    }
+    __syncthreads();
+  });
 }
 
 __global__ void k_sum_parts(const double* part, int64_t n, double* out) {
@@ -429,23 +519,32 @@ __global__ void k_sum_chunks(const double* part, int64_t n, int64_t chunk, doubl
 
 constexpr int kGridRows = 256 * 17;       // k_loss_lean: the one-wave workgroups that fit (LDS)
 constexpr int kGridLeft = 2048;
-constexpr int kLeftL = 512, kLeftH = 1024;
+constexpr int kLeftL = 512, kLeftH = 1024, kLeftDeg = 64;   // k_loss_rows
+constexpr int kColsL = 256;                                 // k_loss_cols: entries in a column of M
 
-size_t left_lds(int DG) {
-  return (size_t)kLeftL * 4 + (size_t)kLeftH * 8 + (size_t)(DG + 1) * 4 + (size_t)kLeftL * 8 +
-         (size_t)DG * 8 + (size_t)(kLeftH / 2) * 8 + 64;
+// row sums of I - A M, with gA the gradient in A
+template <typename T>
+void launch_rows(const Pat& A, const T* Av, const Pat& M, const T* Mv, double* rowpart, double* gA,
+                 double dL, int* err, hipStream_t s) {
+  hipLaunchKernelGGL((k_loss_lean<T, false>), dim3(kGridRows), dim3(SPAI_WAVE), 0, s, A, Av,
+                     (const int64_t*)nullptr, M, Mv, rowpart, gA, dL);
+  const size_t lds = (size_t)kLeftL * 4 + (size_t)kLeftH * 8 + (size_t)(kLeftDeg + 1) * 4 +
+                     (size_t)kLeftL * 8 + (size_t)kLeftDeg * 8 + (size_t)(kLeftH / 2) * 8 + 64;
+  hipLaunchKernelGGL((k_loss_rows<T>), dim3(kGridLeft), dim3(SPAI_WAVE), lds, s, A, Av, M, Mv, rowpart,
+                     gA, dL, err, kLeftL, kLeftH, kLeftDeg);
 }
-
-// both tiers of I - X Y; DG: the most entries a row of X may have
-template <typename T, bool MAP>
-void launch_rows(const Pat& X, const T* Xv, const int64_t* xmap, const Pat& Y, const T* Yv,
-                 double* rowpart, double* gX, double dL, int* err, int DG, hipStream_t s) {
-  hipLaunchKernelGGL((k_loss_lean<T, MAP>), dim3(kGridRows), dim3(SPAI_WAVE), 0, s, X, Xv, xmap, Y,
-                     Yv, rowpart, gX, dL);
-  hipLaunchKernelGGL((k_loss_rows<T, MAP>), dim3(kGridLeft), dim3(SPAI_WAVE), left_lds(DG), s, X, Xv,
-                     xmap, Y, Yv, rowpart, gX, dL, err, kLeftL, kLeftH, DG);
+// the gradient in M: the rows of R^T = I - M^T A^T (tmap: M's transpose map, Atv: A^T's values)
+template <typename T>
+void launch_cols(const Pat& A, const T* Av, const T* Atv, const Pat& M, const T* Mv,
+                 const int64_t* tmap, double* rowpart, double* gM, double dL, int* err,
+                 hipStream_t s) {
+  hipLaunchKernelGGL((k_loss_lean<T, true>), dim3(kGridRows), dim3(SPAI_WAVE), 0, s, M, Mv, tmap, A, Atv,
+                     rowpart, gM, dL);
+  const size_t lds = (size_t)kColsL * 8 + (size_t)kLeftH * 8 + (size_t)kColsL * 8 +
+                     (size_t)(kLeftH / 2) * 8 + 64;
+  hipLaunchKernelGGL((k_loss_cols<T>), dim3(kGridLeft), dim3(SPAI_WAVE), lds, s, A, Av, Atv, M, Mv, tmap,
+                     rowpart, gM, dL, err, kColsL, kLeftH);
 }
-constexpr int kDegRows = 64, kDegCols = 256;   // entries in a row of A; in a column of M
 
 struct LossCall {
   DevPool pool;
@@ -538,7 +637,7 @@ int loss_fwd_t(LossCall& c, double* Lout) {
   const int nch = 512;
   if ((rc = c.scratch(&blk, sizeof(double) * (size_t)(c.pA.n + nch + 1)))) return rc;
   double *rowpart = (double*)blk, *chunks = rowpart + c.pA.n, *out = chunks + nch;
-  launch_rows<T, false>(c.pA, Av, nullptr, c.pM, Mv, rowpart, nullptr, 1.0, c.err, kDegRows, c.s);
+  launch_rows<T>(c.pA, Av, c.pM, Mv, rowpart, nullptr, 1.0, c.err, c.s);
   HIPCHK(hipGetLastError());
   const int64_t chunk = (c.pA.n + nch - 1) / nch;
   const int nb = (int)((c.pA.n + chunk - 1) / chunk);
@@ -569,16 +668,14 @@ int loss_bwd_t(LossCall& c, double dL, double* gA, double* gM, bool host_out) {
     if (gA && (rc = c.pool.alloc(&dgA, c.nnzA))) return rc;
     if (gM && (rc = c.pool.alloc(&dgM, c.nnzM))) return rc;
   }
-  if (gA)
-    launch_rows<T, false>(c.pA, Av, nullptr, c.pM, Mv, rowpart, dgA, dL, c.err, kDegRows, c.s);
+  if (gA) launch_rows<T>(c.pA, Av, c.pM, Mv, rowpart, dgA, dL, c.err, c.s);
   if (gM) {
     const int64_t lanes = c.pA.n * kMapLanes;
     const dim3 grid((unsigned)((lanes + 255) / 256)), bs(256);
     hipLaunchKernelGGL(k_transpose<T>, grid, bs, 0, c.s, c.pA, (int64_t*)nullptr, Av, Atv, c.err);
     hipLaunchKernelGGL(k_transpose<T>, grid, bs, 0, c.s, c.pM, tM, (const T*)nullptr, (T*)nullptr,
                        c.err);
-    // rows of R^T = I - M^T A^T
-    launch_rows<T, true>(c.pM, Mv, tM, c.pA, Atv, rowpart, dgM, dL, c.err, kDegCols, c.s);
+    launch_cols<T>(c.pA, Av, Atv, c.pM, Mv, tM, rowpart, dgM, dL, c.err, c.s);
   }
   HIPCHK(hipGetLastError());
   int herr = 0;
@@ -676,8 +773,7 @@ extern "C" int spai_loss_fwd_noalloc(const spai_csr_t* A, const spai_csr_t* M, d
     const Pat pA{A->n, A->rowptr, A->colind}, pM{M->n, M->rowptr, M->colind};
     // the flag is cleared by a kernel (no memset node), so the call can be captured
     hipLaunchKernelGGL(k_zero_flag, dim3(1), dim3(1), 0, s, err);
-    launch_rows<double, false>(pA, A->val, nullptr, pM, M->val, rowpart, nullptr, 1.0, err,
-                               kDegRows, s);
+    launch_rows<double>(pA, A->val, pM, M->val, rowpart, nullptr, 1.0, err, s);
     const int64_t chunk = (A->n + kNoAllocChunks - 1) / kNoAllocChunks;
     const int nb = (int)((A->n + chunk - 1) / chunk);
     hipLaunchKernelGGL(k_sum_chunks, dim3(nb), dim3(256), 0, s, rowpart, A->n, chunk, chunks);

@@ -418,3 +418,63 @@ def test_dots_of_20000_rows_keep_their_place_beside_the_residual():
     ratio = (after["dots"] - before["dots"]) / (after["resid"] - before["resid"])
     print("dots / residual: %.1f" % ratio)
     assert ratio <= 35.0
+
+
+def _power_pattern(A, k):
+    B = sp.csr_matrix((np.ones(A.nnz), A.indices, A.indptr), shape=A.shape)
+    P = B
+    for _ in range(k - 1):
+        P = sp.csr_matrix(P @ B)
+        P.data[:] = 1.0
+    P.sort_indices()
+    return P
+
+
+@pytest.mark.parametrize("make,k", [
+    (lambda: W.lognormal3d(10, 4), 3),       # columns of up to 63 entries
+    (lambda: W.grid9(20, 4), 3),             # 49
+    (lambda: W.laplace2d(24), 5),            # 61
+    (lambda: W.laplace2d(24), 4)])           # 41
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_loss_gradients_on_wide_patterns(make, k, precision):
+    """M on pattern(A^k), its columns beyond the lean kernel's 32 entries: tolerances as above."""
+    S = _spai()
+    A = make()
+    M = _power_pattern(A, k)
+    M.data = 0.1 * np.random.default_rng(k).standard_normal(M.nnz)
+    tol = 1e-12 if precision == "f64" else 1e-5
+    gA, gM = S.loss_bwd(A, M, options=S.Options(precision=precision))
+    for g, o, p in zip((gA, gM), O.loss_grad(A, M), (A, M)):
+        o = np.asarray(sp.csr_matrix(o)[tuple(p.nonzero())]).ravel()
+        assert np.max(np.abs(g - o)) <= tol * np.max(np.abs(o))
+
+
+def _best_time(call, reps=10):
+    import time
+
+    import torch
+    best = np.inf
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        call()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+def test_gradient_in_m_keeps_its_place_beside_the_gradient_in_a():
+    """Nine-point graph, M on pattern(A^3): both gradients leave the lean kernel.  The one in M
+    took 1.3 times the one in A with a kernel of its own, 6.2 times with the rows' kernel."""
+    import torch
+    S = _spai()
+    A = W.grid9(256, 3)
+    M = _power_pattern(A, 3)
+    M.data = np.random.default_rng(0).standard_normal(M.nnz)
+    dev = [torch.sparse_csr_tensor(torch.from_numpy(X.indptr.astype(np.int64)),
+                                   torch.from_numpy(X.indices.astype(np.int64)),
+                                   torch.from_numpy(X.data), size=X.shape).cuda() for X in (A, M)]
+    ta = _best_time(lambda: S.loss_bwd(*dev, want_m=False))
+    tm = _best_time(lambda: S.loss_bwd(*dev, want_a=False))
+    print("gradient in M / in A: %.2f" % (tm / ta))
+    assert tm <= 3.0 * ta

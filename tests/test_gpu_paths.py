@@ -392,7 +392,7 @@ def test_a_stagnating_small_solve_is_cut_into_launches(n, nrhs):
             launches = len(_kernels_of(lambda: h.pcg(B, rtol=0.0, max_iter=2500), "k_pcg_tiny"))
         out.append([h.pcg(B, rtol=0.0, max_iter=m) for m in caps])
         h.close()
-    assert max(out[0][-1][1]) > 2048 and launches == 3
+    assert max(out[0][-1][1]) > 2048 and 2 <= launches <= 3
     for a, b in zip(*out):
         assert a[3] == b[3]
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
@@ -478,3 +478,16 @@ def test_gradient_in_m_keeps_its_place_beside_the_gradient_in_a():
     tm = _best_time(lambda: S.loss_bwd(*dev, want_a=False))
     print("gradient in M / in A: %.2f" % (tm / ta))
     assert tm <= 3.0 * ta
+
+
+@pytest.mark.parametrize("eigs,steps,enqueued", [(1, 1, 1), (3, 3, 4), (5, 5, 16), (12, 12, 16)])
+def test_lanczos_enqueues_few_steps_past_its_end(eigs, steps, enqueued):
+    """A process of `steps` steps (as many distinct eigenvalues) enqueues no more than the host
+    needs to see its end: the passes of 1, 4 or 16 steps, three each, and one for ||v0||."""
+    S = _spai()
+    A = sp.diags(np.repeat(np.linspace(1.0, 3.0, eigs), 600 // eigs)).tocsr()
+    v0 = np.random.default_rng(eigs).standard_normal(A.shape[0])
+    got = []
+    n = len(_kernels_of(lambda: got.append(S.spectrum(A, v0, steps=200)[4]), "k_lz_pass"))
+    assert got[0] == steps
+    assert 0 < n <= 1 + 3 * enqueued

@@ -1060,7 +1060,8 @@ __global__ __launch_bounds__(kThreads) void k_fill(double* dst, double v, int64_
 // rows of work in every one.  With at most kTinyElems values per block of vectors one
 // workgroup of 1024 threads runs all of it: the vectors that are gathered (p, r) and the
 // terms of the dots in LDS, x, z and q in registers of the thread that owns a position and a
-// right-hand side, barriers instead of launches.  Up to 1024 values (U = 1) the first eight
+// right-hand side, barriers instead of launches (where A and M have few enough entries,
+// tiny_limit: the kernel itself counts them and declines).  Up to 1024 values (U = 1) the first eight
 // entries of a thread's rows of A and M stay in registers too.  Bound by the ordered sums
 // (chains of up to 256 dependent additions) and, with U = 4, the rows' entries from L2.
 // 17 x 17 and 32 x 32 grids, one right-hand side: 7 us an iteration against 63 and 50 launched
@@ -1074,6 +1075,21 @@ constexpr int kTinyRows = 1024;     // beyond, one compute unit reads the rows t
                                     // rows and one right-hand side 58 us an iteration, launched 60
 constexpr int kTinyThreads = 1024;
 constexpr int kTinyRhs = 32;
+constexpr int kTinyDeclined = -1;   // TinyOut.status of a solve that one workgroup is not to take
+// Stored entries of A and M, times right-hand sides, that one workgroup reads (row after row,
+// eight entries a load) no slower than the launched products: beyond, they are faster.  The
+// lanes of four right-hand sides share a row's loads, which other numbers split over the waves'
+// ends; up to 1024 values the rows' first entries stay in registers, and rows are shared the
+// more, the more right-hand sides there are.  us an iteration, one workgroup | launched, some
+// 30 to 60 us a solve more where it declines: one right-hand side 31 | 41 at 40,000, 60 | 47 at
+// 72,000; three, 900 values 39 | 54 at 74,000, 108 | 83 at 206,000; three, 2200 values and more
+// 43 | 48 at 70,000, 66 | 48 at 119,000; six 36 | 42 at 83,000, 43 | 40 at 98,000; four 42 | 45
+// at 128,000, 49 | 46 at 176,000; sixteen 43 | 44 at 172,000.
+__host__ __device__ inline int tiny_limit(int n, int nrhs) {
+  if (nrhs % 4 == 0) return 160000;
+  if (n * nrhs <= 1024) return nrhs < 3 ? 32000 * (nrhs + 1) : 128000;
+  return nrhs > 4 ? 84000 : 64000;
+}
 // Iterations of one launch: a kernel cannot be interrupted, and a solve that stagnates runs to
 // its max_iter (any int).  1024 take 7 to 50 ms, 0.02 ms of it the launch and the host's look;
 // what goes on is kept in TinyKeep.
@@ -1212,9 +1228,23 @@ __global__ __launch_bounds__(kTinyThreads) void k_pcg_tiny(Mat A, Mat M, const d
   __shared__ double s_p[kTinyThreads * U], s_r[kTinyThreads * U];
   __shared__ double s_t[kTinyTerms], s_n[kTinyTerms];       // terms by position, by row
   __shared__ RhsState S[kTinyRhs];
-  __shared__ int s_active;
+  __shared__ int s_active, s_entries;
   const int tid = threadIdx.x;
   const int n = (int)A.n, tot = n * nrhs;
+  if (it0 == 0) {                   // n <= kTinyThreads: a thread a row
+    if (tid == 0) s_entries = 0;
+    __syncthreads();
+    int64_t len = 0;
+    if (tid < n)
+      len = row_hi<LAYA>(A, tid) - row_lo<LAYA>(A, tid) + row_hi<LAYM>(M, tid) - row_lo<LAYM>(M, tid);
+    const int sum = wave_sum_int((int)len);        // (a row has at most n entries, or 64 in ELL)
+    if ((tid & 63) == 0) atomicAdd(&s_entries, sum);
+    __syncthreads();
+    if (s_entries > tiny_limit(n, nrhs) / nrhs) {
+      if (tid == 0) keep->out[0] = TinyOut{0, kTinyDeclined, 0, 0, 0.0, 0.0};
+      return;
+    }
+  }
   const int per = (n + 7) / 8;
   const TinyLay lay = tiny_lay(n, nrhs, R);
   const int G = lay.G;              // rows of a pass of 256 threads
@@ -1447,9 +1477,10 @@ static void launch_tiny(const Mat& A, const Mat& M, const double* B, double* X, 
   else go(k_pcg_tiny<MT, LAYA, kLayCsr, 1>, k_pcg_tiny<MT, LAYA, kLayCsr, kFour>);
 }
 
+// (*declined: nothing has been solved)
 static int pcg_tiny(const Mat& A, const Mat& M, int nrhs, const double* B, double* X, double rtol,
                     int max_iter, int* iters, double* relres, const int32_t* order, hipStream_t s,
-                    PcgWork* work) {
+                    PcgWork* work, bool* declined) {
   DevPool local;
   TinyKeep* keep = nullptr;
   int rc;
@@ -1480,6 +1511,8 @@ static int pcg_tiny(const Mat& A, const Mat& M, int nrhs, const double* B, doubl
     HIPCHK(hipStreamSynchronize(s));
     it0 = it1;
   } while (h[0].active > 0);
+  *declined = h[0].status == kTinyDeclined;
+  if (*declined) return SPAI_OK;
   bool indef = false, unconv = false;
   for (int r = 0; r < nrhs; ++r) {
     if (iters) iters[r] = h[r].iters;
@@ -1735,9 +1768,12 @@ int pcg_run(const PcgMat& A, const PcgMat& M, int nrhs, const double* dB, double
             int max_iter, int* iters, double* relres, const int32_t* order, hipStream_t s,
             PcgTiming* timing, PcgWork* work) {
   // (A is ELL or CSR, M padded columns or CSR; the per-product timing wants the launches)
-  if (tiny_fits(A.n, nrhs) && !timing && !A.beg && !A.val32 && M.eshift < 0)
-    return pcg_tiny(A, M, nrhs, dB, dX, rtol, max_iter, iters, relres, order, s, work);
   int rc;
+  if (tiny_fits(A.n, nrhs) && !timing && !A.beg && !A.val32 && M.eshift < 0) {
+    bool declined = false;
+    rc = pcg_tiny(A, M, nrhs, dB, dX, rtol, max_iter, iters, relres, order, s, work, &declined);
+    if (rc < 0 || !declined) return rc;
+  }
   DevPool local;
   DevPool& pool = work ? work->pool : local;
   Solver S{};

@@ -491,3 +491,27 @@ def test_lanczos_enqueues_few_steps_past_its_end(eigs, steps, enqueued):
     n = len(_kernels_of(lambda: got.append(S.spectrum(A, v0, steps=200)[4]), "k_lz_pass"))
     assert got[0] == steps
     assert 0 < n <= 1 + 3 * enqueued
+
+
+@pytest.mark.parametrize("nrhs", [1, 3, 4, 7])
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_small_solves_with_long_rows_are_launched(nrhs, precision):
+    """One workgroup takes a small solve only where A and M have few entries (with 150 a row,
+    512 rows and three right-hand sides it took 145 us an iteration, launched 84): the rows of
+    a cap of 24 nnz(A) are left to the launched products, those of 2 are not, and either way
+    the solve is the launched one bit for bit."""
+    S = _spai()
+    A = W.lognormal3d(8, 1)
+    B = W.rhs(A.shape[0], nrhs, 5)
+    for cap, launched in ((2.0, False), (24.0, True)):
+        out = []
+        for prof in (False, True):
+            h = S.SPAI(A, "lomr", "global", cap, True, max_iter=12,
+                       options=S.Options(precision=precision, profile=prof))
+            h.iterate(12)
+            if not prof:
+                assert (len(_kernels_of(lambda: h.pcg(B, rtol=1e-9), "k_spmm")) > 0) == launched
+            out.append(h.pcg(B, rtol=1e-9))
+            h.close()
+        assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+        assert np.array_equal(out[0][2], out[1][2])

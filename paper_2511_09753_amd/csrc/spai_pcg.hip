@@ -502,13 +502,13 @@ constexpr int narrow_chunk() { return (kThreads / R) * narrow_rpt<R>(); }
 
 template <typename VT, int LAY, int R, int W>
 __global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double* X, double* Y,
-                                                             int dot, int nrhs, int c0, int ld,
+                                                             int dot, int nrhs,
                                                              const int32_t* order, double* part,
                                                              Finish fin) {
   static_assert(narrow_chunk<R>() >= (kThreads / 64) * kRowsPerWave,
                 "no more workgroups than the partial buffer holds");
   if (A.gate && *A.gate == 0) return finish_stopped(fin);  // every right-hand side stopped
-  if (A.ran && c0 == 0 && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(A.ran, 1);
+  if (A.ran && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(A.ran, 1);
   constexpr int G = kThreads / R;
   constexpr int RPT = narrow_rpt<R>();
   __shared__ double sh[W == 1 ? kThreads : RPT * kThreads];
@@ -520,10 +520,6 @@ __global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double
   const int64_t r1 = r0 + per < A.n ? r0 + per : A.n;
   const int64_t base = r0 + kb * (int64_t)narrow_chunk<R>();
   double acc = 0.0;
-  // columns c0 .. c0 + nrhs of blocks whose rows are ld doubles apart (ld = nrhs, c0 = 0
-  // for a whole block; a wide block is taken R columns at a time)
-  X += c0;
-  Y += c0;
   for (int j = threadIdx.x / kThreads; j < RPT; j += W) {
     const int64_t k = base + (int64_t)j * G + g;
     double term = 0.0;
@@ -546,7 +542,7 @@ __global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double
           }
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) xx[u] = cc[u] >= 0 ? X[(int64_t)cc[u] * ld + r] : 0.0;
+        for (int u = 0; u < 8; ++u) xx[u] = cc[u] >= 0 ? X[(int64_t)cc[u] * nrhs + r] : 0.0;
 #pragma unroll
         for (int u = 0; u < 8; ++u)
           if (cc[u] >= 0) {               // ELL padding (column -1) sits last
@@ -558,10 +554,10 @@ __global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double
           }
         if (cc[7] < 0) break;
       }
-      Y[i * ld + r] = y;
+      Y[i * nrhs + r] = y;
       if (dot) {
         // a row without a diagonal entry loads X[i, r] after all
-        const double wx = found ? xd : X[i * ld + r];
+        const double wx = found ? xd : X[i * nrhs + r];
         term = wx * y;
       }
     }
@@ -579,7 +575,7 @@ __global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double
   if (threadIdx.x < kThreads) sh[t] = acc;
   __syncthreads();
   if (threadIdx.x < R && t < nrhs)
-    agent_store(&part[(int64_t)(c0 + t) * gridDim.x + blockIdx.x], column_sum(sh, t, R));
+    agent_store(&part[(int64_t)t * gridDim.x + blockIdx.x], column_sum(sh, t, R));
   if (fin.ticket) finish_blocks(fin, part, (int)gridDim.x);
 }
 
@@ -1622,8 +1618,7 @@ struct Solver {
   int spmm_grid = 8;
 
   template <typename VT, int LAY, int R>
-  void spmm_narrow(const Mat& K, const double* X, double* Y, double* pt, int c0 = 0,
-                   int cw = 0) {
+  void spmm_narrow(const Mat& K, const double* X, double* Y, double* pt) {
     const int64_t per = (n + 7) / 8;
     spmm_grid = (int)(8 * ((per + narrow_chunk<R>() - 1) / narrow_chunk<R>()));
     Finish f;
@@ -1634,10 +1629,10 @@ struct Solver {
                          pt ? 1 : 0, nrhs, order, pt, f);
     } else if (spmm_grid <= wide_grid)
       hipLaunchKernelGGL((k_spmm_narrow<VT, LAY, R, 4>), dim3(spmm_grid), dim3(4 * kThreads), 0, s, K,
-                         X, Y, pt ? 1 : 0, cw ? cw : nrhs, c0, nrhs, order, pt, f);
+                         X, Y, pt ? 1 : 0, nrhs, order, pt, f);
     else
       hipLaunchKernelGGL((k_spmm_narrow<VT, LAY, R, 1>), dim3(spmm_grid), dim3(kThreads), 0, s, K, X,
-                         Y, pt ? 1 : 0, cw ? cw : nrhs, c0, nrhs, order, pt, f);
+                         Y, pt ? 1 : 0, nrhs, order, pt, f);
   }
   template <typename VT, int LAY>
   void spmm_as(const Mat& K, const double* X, double* Y, double* pt) {

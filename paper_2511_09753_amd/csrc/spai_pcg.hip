@@ -438,9 +438,13 @@ __device__ void rhs_beta(RhsState& g, double rz_new);
 // right-hand sides' sums (part[r * rstep + b * bstep], nrhs of them, nblocks partials each)
 // and the scalar step that consumes them (0: alpha, 1: beta, 2: convergence).  ticket counts
 // the workgroups that have written theirs (null: a launch of its own sums them); the last
-// one leaves it at 0 for the next launch.  One launch less per reduction: where partials are
-// few (kFusedParts) the sums take less time than a launch, 2 to 4 us each of the three in an
-// iteration; beyond that one workgroup per right-hand side sums them faster.
+// one leaves it at 0 for the next launch.  One launch less per reduction: where partials and
+// workgroups are few the sums take less time than a launch, 2 to 4 us each of the three in an
+// iteration; beyond that one workgroup per right-hand side sums them faster.  20^3, 4
+// right-hand sides: a solve 1.57 ms fused, 1.71 not.  Products, 256 x 256 grid, 8 right-hand
+// sides (512 workgroups): 11.3 and 10.7; 28^3, 16 of them (344): 2.95 and 2.99.  The r update:
+// 52^3, 4 right-hand sides (4396 partials, as many waves) 8.35 and 7.85, 256 x 256, 4 (4096)
+// 9.8 and 9.4, 46^3, 2 (1522) 4.6 both.
 struct Finish {
   int* ticket = nullptr;
   RhsState* S = nullptr;
@@ -450,7 +454,8 @@ struct Finish {
   double rtol = 0.0;
 };
 constexpr int kFusedParts = 8192;
-constexpr int kFusedGrid = 512;     // and the workgroups that draw a ticket
+constexpr int kFusedGrid = 400;     // and the workgroups that draw a ticket
+constexpr int kFusedRows = 2048;    // partials of the r update
 
 __device__ __forceinline__ void finish_blocks(const Finish& f, const double* part, int nblocks) {
   __shared__ int last;
@@ -490,11 +495,12 @@ __device__ __forceinline__ void finish_stopped(const Finish& f) {
 // sum_i X[i, r] Y[i, r], stored transposed as there: thread (g, r) of 256 adds its rows g,
 // g + G, ..., then g runs over the G groups.
 // W = 4: 1024 threads take those rows side by side instead of 256 one after the other and
-// leave the terms in LDS for the same sums.  Where a launch has fewer workgroups than four
-// per compute unit the product is bound by the latency of a thread's rows (descriptor,
-// entries, gathers, one row after the other): 256 x 256 grid, 4 right-hand sides (256
-// workgroups) 12.4 us with its reduction, against 13.3 and a reduction of 4.1; with more
-// workgroups 256 threads keep more waves resident (registers).
+// leave the terms in LDS for the same sums.  Where a launch has few workgroups (wide_grid) the
+// product is bound by the latency of a thread's rows (descriptor, entries, gathers, one row
+// after the other): 256 x 256 grid, 4 right-hand sides (256 workgroups) 12.4 us with its
+// reduction, against 13.3 and a reduction of 4.1; with more workgroups 256 threads keep more
+// waves resident (registers).  Those take no reduction's end: the code alone, never run there,
+// cost 5% (64^3, float32 M, 8 right-hand sides: z = M r 65 us against 70).
 template <int R>
 constexpr int narrow_rpt() { return R / 4 > 4 ? R / 4 : 4; }   // rows per thread of 256
 template <int R>
@@ -507,7 +513,10 @@ __global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double
                                                              Finish fin) {
   static_assert(narrow_chunk<R>() >= (kThreads / 64) * kRowsPerWave,
                 "no more workgroups than the partial buffer holds");
-  if (A.gate && *A.gate == 0) return finish_stopped(fin);  // every right-hand side stopped
+  if (A.gate && *A.gate == 0) {                            // every right-hand side stopped
+    if constexpr (W > 1) finish_stopped(fin);
+    return;
+  }
   if (A.ran && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(A.ran, 1);
   constexpr int G = kThreads / R;
   constexpr int RPT = narrow_rpt<R>();
@@ -520,49 +529,52 @@ __global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double
   const int64_t r1 = r0 + per < A.n ? r0 + per : A.n;
   const int64_t base = r0 + kb * (int64_t)narrow_chunk<R>();
   double acc = 0.0;
-  for (int j = threadIdx.x / kThreads; j < RPT; j += W) {
-    const int64_t k = base + (int64_t)j * G + g;
-    double term = 0.0;
-    if (r < nrhs && k < r1) {
-      const int64_t i = order ? (int64_t)order[k] : k;
-      const int64_t a = row_lo<LAY>(A, i), b = row_hi<LAY>(A, i);
-      double y = 0.0, xd = 0.0;
-      bool found = false;
-      for (int64_t q0 = a; q0 < b; q0 += 8) {
-        int cc[8];
-        VT vv[8];
-        double xx[8];
+  if (W > 1 || r < nrhs) {
+    for (int j = W > 1 ? threadIdx.x / kThreads : 0; j < RPT; j += W) {
+      const int64_t k = base + (int64_t)j * G + g;
+      if (W == 1 && k >= r1) break;
+      double term = 0.0;
+      if (W == 1 || (r < nrhs && k < r1)) {
+        const int64_t i = order ? (int64_t)order[k] : k;
+        const int64_t a = row_lo<LAY>(A, i), b = row_hi<LAY>(A, i);
+        double y = 0.0, xd = 0.0;
+        bool found = false;
+        for (int64_t q0 = a; q0 < b; q0 += 8) {
+          int cc[8];
+          VT vv[8];
+          double xx[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          cc[u] = -1;
-          vv[u] = 0;
-          if (q0 + u < b) {
-            cc[u] = A.col[q0 + u];
-            vv[u] = entry_val<VT>(A, q0 + u);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) xx[u] = cc[u] >= 0 ? X[(int64_t)cc[u] * nrhs + r] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (cc[u] >= 0) {               // ELL padding (column -1) sits last
-            y += (double)vv[u] * xx[u];
-            if (cc[u] == (int)i) {
-              xd = xx[u];
-              found = true;
+          for (int u = 0; u < 8; ++u) {
+            cc[u] = -1;
+            vv[u] = 0;
+            if (q0 + u < b) {
+              cc[u] = A.col[q0 + u];
+              vv[u] = entry_val<VT>(A, q0 + u);
             }
           }
-        if (cc[7] < 0) break;
+#pragma unroll
+          for (int u = 0; u < 8; ++u) xx[u] = cc[u] >= 0 ? X[(int64_t)cc[u] * nrhs + r] : 0.0;
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (cc[u] >= 0) {               // ELL padding (column -1) sits last
+              y += (double)vv[u] * xx[u];
+              if (cc[u] == (int)i) {
+                xd = xx[u];
+                found = true;
+              }
+            }
+          if (cc[7] < 0) break;
+        }
+        Y[i * nrhs + r] = y;
+        if (dot) {
+          // a row without a diagonal entry loads X[i, r] after all
+          const double wx = found ? xd : X[i * nrhs + r];
+          if (W == 1) acc += wx * y;
+          else term = wx * y;
+        }
       }
-      Y[i * nrhs + r] = y;
-      if (dot) {
-        // a row without a diagonal entry loads X[i, r] after all
-        const double wx = found ? xd : X[i * nrhs + r];
-        term = wx * y;
-      }
+      if (W > 1) sh[j * kThreads + t] = term;
     }
-    if (W == 1) acc += term;              // (0 where there is no row: the sum as it is)
-    else sh[j * kThreads + t] = term;
   }
   if (!part) return;
   if (W > 1) {
@@ -576,7 +588,8 @@ __global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double
   __syncthreads();
   if (threadIdx.x < R && t < nrhs)
     agent_store(&part[(int64_t)t * gridDim.x + blockIdx.x], column_sum(sh, t, R));
-  if (fin.ticket) finish_blocks(fin, part, (int)gridDim.x);
+  if constexpr (W > 1)
+    if (fin.ticket) finish_blocks(fin, part, (int)gridDim.x);
 }
 
 // The product for at most two right-hand sides: four lanes per row and right-hand side, lane
@@ -588,7 +601,8 @@ __global__ __launch_bounds__(kThreads* W) void k_spmm_narrow(Mat A, const double
 // with it.  1024 threads take the G = 256 / R rows of a pass of k_spmm_narrow at a time, four
 // passes with their loads in flight together, and the partials are that kernel's: the same
 // bit for bit.  256 x 256 grid, one right-hand side (64 workgroups): z = M r 19.4 us against
-// 31.7, q = A p 12.9 against 17.1 (each with its reduction).  From three right-hand sides on a
+// 31.7, q = A p 12.9 against 17.1 (each with its reduction).  Solves with one and two: 64^3
+// 9.6 ms against 14.1 and 12.0 against 13.7, 96^3 47 against 88 and 55 against 77.  From three right-hand sides on a
 // thread per value is faster (four of them, 44.3 us an iteration against 47.1): its lanes
 // share their rows' loads already.
 constexpr int kQuadRhs = 2;         // padded right-hand sides
@@ -1537,7 +1551,12 @@ struct Solver {
   // workgroups of the x, p update: 5 per compute unit (20 waves; the 64-right-hand-side solve
   // at 96^3 took 352 ms, against 361 ms with the full 2048 and 363 ms with 3 per unit)
   int pupd_grid = kGrid;
-  int wide_grid = 1024;              // products with at most as many workgroups take 1024 threads
+  // products with at most as many workgroups take 1024 threads: with 8 and 16 right-hand sides
+  // up to four a compute unit (a solve, 40^3, 16 of them and 1000 workgroups: 6.0 ms against 6.2
+  // with 256 threads; 46^3, 8: 5.8 and 6.3), else two (40^3, 32 and 1000: 10.7 and 9.8, a
+  // thread's two rows not side by side; 52^3, 4, float32 M and 552: 8.1 and 7.7)
+  static constexpr int wide_grid(int R) { return R == 8 || R == 16 ? 1024 : 512; }
+  static_assert(kFusedGrid <= 512, "a product of 256 threads takes no reduction's end");
   int* ticket = nullptr;             // of the fused reductions
   // optional timing of the products inside the iterations: HIP events recorded on the
   // solver's stream around each A p (kind 0) and M r (kind 1), read back per chunk
@@ -1551,7 +1570,7 @@ struct Solver {
   Finish finish(int step, int64_t nb, int64_t grid, int64_t rstep, int64_t bstep,
                 double rtol = 0.0) const {
     Finish f;
-    if (nb * nrhs > kFusedParts || grid > kFusedGrid) return f;
+    if (step == 2 ? nb * nrhs > kFusedRows : nb * nrhs > kFusedParts || grid > kFusedGrid) return f;
     f.ticket = ticket;
     f.S = S;
     f.nactive = nactive;
@@ -1627,7 +1646,7 @@ struct Solver {
     if constexpr (R <= kQuadRhs) {
       hipLaunchKernelGGL((k_spmm_quad<VT, LAY, R>), dim3(spmm_grid), dim3(4 * kThreads), 0, s, K, X, Y,
                          pt ? 1 : 0, nrhs, order, pt, f);
-    } else if (spmm_grid <= wide_grid)
+    } else if (spmm_grid <= wide_grid(R))
       hipLaunchKernelGGL((k_spmm_narrow<VT, LAY, R, 4>), dim3(spmm_grid), dim3(4 * kThreads), 0, s, K,
                          X, Y, pt ? 1 : 0, nrhs, order, pt, f);
     else

@@ -515,3 +515,38 @@ def test_small_solves_with_long_rows_are_launched(nrhs, precision):
             h.close()
         assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
         assert np.array_equal(out[0][2], out[1][2])
+
+
+def _kernel_names(call, name):
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return {e.name for e in prof.events() if name in e.name}
+
+
+# 512 workgroups of 64 (32 right-hand sides) or 256 rows (4), and 1024 of 128 (8), are the last
+# with 1024 threads
+@pytest.mark.parametrize("n,nrhs,threads", [
+    (32768, 31, 1024), (32769, 31, 256), (131072, 3, 1024), (131073, 3, 256),
+    (131072, 5, 1024), (131073, 5, 256)])
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_pcg_narrow_products_on_either_side_of_their_widths(n, nrhs, threads, precision):
+    """A few iterations against the oracle (M rounded to float32 on the mixed path), as above."""
+    S = _spai()
+    A = sp.csr_matrix(W.geometric_graph(n, 3))
+    d = sp.diags(1.0 / np.sqrt(A.diagonal()))
+    M = sp.csr_matrix(d @ (sp.identity(n) - 0.05 * (d @ A @ d - sp.identity(n))) @ d)
+    M = sp.csr_matrix((M + M.T) / 2)
+    M.sort_indices()
+    if precision == "mixed":
+        M.data = M.data.astype(np.float32).astype(np.float64)
+    B = W.rhs(n, nrhs, 3)
+    got = []
+    names = _kernel_names(lambda: got.append(S.pcg_solve(
+        A, M, B, rtol=1e-8, max_iter=4, options=S.Options(precision=precision))), "k_spmm_narrow")
+    assert names and all((", %d>" % (threads // 256)) in x for x in names)
+    Xo, ito, _ = O.pcg_block(A, M, B, rtol=1e-8, max_iter=4)
+    assert list(got[0][1]) == list(ito)
+    assert np.max(np.abs(got[0][0] - Xo)) <= 1e-12 * np.max(np.abs(Xo))

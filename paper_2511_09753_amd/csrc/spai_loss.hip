@@ -230,9 +230,15 @@ __global__ __launch_bounds__(SPAI_WAVE) __attribute__((amdgpu_waves_per_eu(5))) 
       for (int q = 0; q < groups; ++q)
         for (int k = lane; k < nk; k += SPAI_WAVE) sums[q * cap + k] = 0.0;
       __syncthreads();
+      double av_v[RR];
 #pragma unroll
       for (int r = 0; r < RR; ++r)
-        sums[at[r]] += __shfl(av, (r << (6 - lg)) + g, SPAI_WAVE) * (double)v[r];
+        av_v[r] = __shfl(av, (r << (6 - lg)) + g, SPAI_WAVE) * (double)v[r];
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        sums[at[r]] += av_v[r];
+        wave_sync();                              // the next round may add to it from another lane
+      }
       __syncthreads();
       double acc = 0.0;
       for (int k = lane; k < nk; k += SPAI_WAVE) {

@@ -5,8 +5,8 @@ import scipy.sparse as sp
 
 from oracle import spai_oracle as O
 from paper_2511_09753_amd import workloads as W
-from tests.helpers import (history_array, oracle_rule, parse_state, pattern_diff, require_gpu,
-                           value_err)
+from tests.helpers import (TOL_F64, history_array, history_from_oracle, oracle_rule, parse_state,
+                           pattern_diff, rel_err, require_gpu, value_err)
 
 pytestmark = pytest.mark.gpu
 
@@ -550,3 +550,28 @@ def test_pcg_narrow_products_on_either_side_of_their_widths(n, nrhs, threads, pr
     Xo, ito, _ = O.pcg_block(A, M, B, rtol=1e-8, max_iter=4)
     assert list(got[0][1]) == list(ito)
     assert np.max(np.abs(got[0][0] - Xo)) <= 1e-12 * np.max(np.abs(Xo))
+
+
+@pytest.mark.parametrize("method", ["mr", "cg", "lomr"])
+def test_floors_in_use_against_the_oracle(method):
+    """50,653 columns, where floors are in use: residual history and drop record against the
+    oracle with the default floor, which leaves candidates unwritten (its second pass hardly
+    ever runs), and with one (a million cuts) that every iteration fails (the second pass then writes them)."""
+    S = _spai()
+    A = W.lognormal3d(37, 41)
+    iters = 6
+    ref = getattr(O, method)(A, oracle_rule(A, "global", 2.0, True), iters)
+    written = {}
+    for frac in (0.0, 0.75, 1e6):
+        h = S.SPAI(A, method, "global", 2.0, True, max_iter=iters,
+                   options=S.Options(floor_frac=frac))
+        _, hist, _ = h.iterate(iters)
+        written[frac] = h.profile()[2]["cand_m"]
+        rec = history_array(h)
+        M = h.get()
+        h.close()
+        assert rel_err(hist, ref.resid[1:]) <= TOL_F64
+        assert np.array_equal(rec, history_from_oracle(ref))
+        assert pattern_diff(M, ref.M) == (set(), set())
+        assert value_err(M, ref.M) <= 1e-9
+    assert written[0.75] < written[0.0] == written[1e6]

@@ -1293,40 +1293,37 @@ struct Engine : EngineBase {
   int get(spai_csr_out_t* out) override {
     if (!out) return fail(SPAI_ERR_ARG, "null output");
     std::lock_guard<std::mutex> lock(get_mu);   // the lists it packs into are the handle's
+    // A symmetric iterate's columns are its rows: packed on the device, in lists that hold
+    // nothing between calls (the other buffer of M, the dots' partials), and copied out.
+    const bool pack = out->rowptr && opts.symmetrize;
+    int64_t* drp = (int64_t*)colpart;          // n + 3 of n kND words
+    static_assert(kND >= 4, "the packed row pointers and three words more fit the partials");
+    const Offs off = launch_len_offsets<T>(M, ob, pack ? drp + n + 1 : nullptr, n, st, s);
+    if (pack) launch_export<T>(M, off, ob.total, n, drp, s);
+    HIPCHK(hipGetLastError());
+    int64_t w[3] = {0, 1, 0};                  // entries of M, not packed, current buffer
+    HIPCHK(hipMemcpyAsync(w, pack ? drp + n : ob.total, (pack ? 3 : 1) * sizeof(int64_t),
+                          hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    DevState h;
-    HIPCHK(hipMemcpy(&h, st, sizeof(DevState), hipMemcpyDeviceToHost));
-    const Cols<T>& C = M.b[h.curM];
-    const Offs off = launch_len_offsets<T>(C, ob, big[0], n, st, s);
-    int64_t nnz = 0;
-    HIPCHK(hipMemcpyAsync(&nnz, ob.total, sizeof(nnz), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    const int64_t nnz = w[0];
     out->n = n;
     out->nnz = nnz;
     if (!out->rowptr) return SPAI_OK;
     if (out->capacity < nnz) return fail(SPAI_ERR_ARG, "output capacity below nnz(M)");
-    // A symmetric iterate's columns are its rows: packed on the device, in lists that hold
-    // nothing between calls (the other buffer of M, the dots' partials), and copied out.
-    const Cols<T>& W = M.b[h.curM ^ 1];
-    if (opts.symmetrize && nnz <= W.cap && (double)nnz * 8.0 <= (double)W.cap * sizeof(T)) {
-      int64_t* drp = (int64_t*)colpart;      // n + 1 of n kND words
-      double* dvl = (double*)W.val;
-      int bad = 0;
-      launch_export<T>(C, off, ob.total, n, drp, W.idx, dvl, big[0].count, s);
-      HIPCHK(hipGetLastError());
-      HIPCHK(hipMemcpyAsync(&bad, big[0].count, sizeof(int), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipStreamSynchronize(s));
-      if (!bad) {
-        const hipMemcpyKind kd = out->on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-        HIPCHK(hipMemcpyAsync(out->rowptr, drp, sizeof(int64_t) * (n + 1), kd, s));
-        if (nnz) {
-          HIPCHK(hipMemcpyAsync(out->colind, W.idx, sizeof(int32_t) * nnz, kd, s));
-          HIPCHK(hipMemcpyAsync(out->val, dvl, sizeof(double) * nnz, kd, s));
-        }
-        HIPCHK(hipStreamSynchronize(s));
-        return SPAI_OK;
+    if (!w[1]) {
+      const Cols<T>& W = M.b[w[2] ^ 1];
+      const hipMemcpyKind kd = out->on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+      HIPCHK(hipMemcpyAsync(out->rowptr, drp, sizeof(int64_t) * (n + 1), kd, s));
+      if (nnz) {
+        HIPCHK(hipMemcpyAsync(out->colind, W.idx, sizeof(int32_t) * nnz, kd, s));
+        HIPCHK(hipMemcpyAsync(out->val, W.val, sizeof(double) * nnz, kd, s));
       }
+      HIPCHK(hipStreamSynchronize(s));
+      return SPAI_OK;
     }
+    DevState h;
+    HIPCHK(hipMemcpy(&h, st, sizeof(DevState), hipMemcpyDeviceToHost));
+    const Cols<T>& C = M.b[h.curM];
     std::vector<int32_t> len(n);
     HIPCHK(hipMemcpy(len.data(), C.len, sizeof(int32_t) * n, hipMemcpyDeviceToHost));
     // gather the columns (CSC, packed on the device), then transpose to CSR on the host

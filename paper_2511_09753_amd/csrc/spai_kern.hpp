@@ -224,14 +224,15 @@ void launch_drop(Pair<T> M, Pair<T> P, Pair<T> PT, int doM, int doP, int colcap,
                  double* blockpart, DevState* st, hipStream_t s, const double* score, int floors,
                  double frac);
 
-// offsets of X's columns without gaps (z.count set to zero), and X packed there as CSR where
-// it is symmetric bit for bit (*bad = 1 where it is not)
+// offsets of the columns of X.now() without gaps (*flag, or null, set to zero), and X.now()
+// packed there as CSR, values as doubles, into X.nxt() where it is symmetric bit for bit and
+// fits.  rowptr: n + 3 words, the last two 1 where it did not (the flag) and X's current buffer
 template <typename T>
-Offs launch_len_offsets(Cols<T> X, const OffBuf& o, const BigList& z, int64_t n, DevState* st,
+Offs launch_len_offsets(Pair<T> X, const OffBuf& o, int64_t* flag, int64_t n, DevState* st,
                         hipStream_t s);
 template <typename T>
-void launch_export(Cols<T> X, Offs off, const int64_t* total, int64_t n, int64_t* rowptr,
-                   int32_t* idx, double* val, int* bad, hipStream_t s);
+void launch_export(Pair<T> X, Offs off, const int64_t* total, int64_t n, int64_t* rowptr,
+                   hipStream_t s);
 
 // the sums of colpart over the columns (fixed order) and the step sizes from them
 void launch_step(int method, const Seg& seg, const double* colpart, int64_t n,

@@ -4526,34 +4526,47 @@ void launch_post(int method, const Seg& seg, const double* colnorm, const double
 
 // offsets of X's columns packed without gaps (their lengths' exclusive sums)
 template <typename T>
-__global__ __launch_bounds__(1024) void k_len_offsets(Cols<T> X, int64_t n, int shift, int64_t* loc,
-                                                      int64_t* tile, int64_t* total, OffZero z,
-                                                      DevState* st) {
+__global__ __launch_bounds__(1024) void k_len_offsets(Pair<T> Xp, int64_t n, int shift,
+                                                      int64_t* loc, int64_t* tile, int64_t* total,
+                                                      OffZero z, DevState* st) {
   off_zero(z);
+  const Cols<T> X = Xp.now();
   offsets_of<1>([&](int64_t j, int) -> int64_t { return j < n ? X.len[j] : 0; }, n, shift, loc, tile,
              total, st);
 }
 
 template <typename T>
-Offs launch_len_offsets(Cols<T> X, const OffBuf& o, const BigList& z, int64_t n, DevState* st,
+Offs launch_len_offsets(Pair<T> X, const OffBuf& o, int64_t* flag, int64_t n, DevState* st,
                         hipStream_t s) {
   const Offs f = make_offs(o, n);
   hipLaunchKernelGGL(k_len_offsets<T>, dim3((unsigned)f.tiles(n)), dim3(1024), 0, s, X, n, f.shift,
-                     o.loc, o.tile, o.total, OffZero{{z.count, nullptr, nullptr, nullptr}}, st);
+                     o.loc, o.tile, o.total,
+                     OffZero{{(int*)flag, flag ? (int*)flag + 1 : nullptr, nullptr, nullptr}}, st);
   return f;
 }
 
 // The columns packed, values widened: where every entry (k, j) has an equal entry (j, k) --
 // each is looked up in column k, by bits -- they are the rows of the CSR form, sorted as the
-// columns are; otherwise *bad is set and the caller transposes.  Groups of columns as in the
+// columns are; otherwise (or where the doubles do not fit the other buffer) the flag behind the
+// row pointers is set and the caller transposes.  rowptr[n]: the entries, [n + 1]: the flag,
+// [n + 2]: which buffer is current, so that the host waits and copies once before it copies the
+// lists (a wait for each took 20 us more, 128 us for n = 64).  Groups of columns as in the
 // compaction: the reads and writes are of consecutive entries, the look-up is some five loads
 // one after the other that other waves hide.
 template <typename T>
-__global__ __launch_bounds__(kCompWaves * SPAI_WAVE) void k_export(Cols<T> X, Offs off,
+__global__ __launch_bounds__(kCompWaves * SPAI_WAVE) void k_export(Pair<T> Xp, Offs off,
                                                                    const int64_t* total, int gs,
-                                                                   int64_t n, int64_t* rowptr,
-                                                                   int32_t* idx, double* val,
-                                                                   int* bad) {
+                                                                   int64_t n, int64_t* rowptr) {
+  const Cols<T> X = Xp.now(), Y = Xp.nxt();
+  int32_t* idx = Y.idx;
+  double* val = (double*)Y.val;
+  const bool fits = *total <= Y.cap && *total <= Y.cap * (int64_t)sizeof(T) / 8;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    rowptr[n] = *total;
+    rowptr[n + 2] = *Xp.cur;
+    if (!fits) rowptr[n + 1] = 1;
+  }
+  if (!fits) return;
   const int lane = lane_id(), wv = threadIdx.x / SPAI_WAVE;
   const int64_t ng = (n + gs - 1) / gs;
   bool odd = false;
@@ -4602,18 +4615,17 @@ __global__ __launch_bounds__(kCompWaves * SPAI_WAVE) void k_export(Cols<T> X, Of
       }
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) rowptr[n] = *total;
-  if (__ballot(odd) && lane == 0) *bad = 1;
+  if (__ballot(odd) && lane == 0) rowptr[n + 1] = 1;
 }
 
 template <typename T>
-void launch_export(Cols<T> X, Offs off, const int64_t* total, int64_t n, int64_t* rowptr,
-                   int32_t* idx, double* val, int* bad, hipStream_t s) {
+void launch_export(Pair<T> X, Offs off, const int64_t* total, int64_t n, int64_t* rowptr,
+                   hipStream_t s) {
   const int gs = group_cols(n), ng = groups(n, gs);
   const int g = std::min((ng + kCompWaves - 1) / kCompWaves,
                          resident_grid(k_export<T>, 0, kCompWaves * SPAI_WAVE));
   hipLaunchKernelGGL(k_export<T>, dim3(g), dim3(kCompWaves * SPAI_WAVE), 0, s, X, off, total, gs, n,
-                     rowptr, idx, val, bad);
+                     rowptr);
 }
 
 // ---- explicit instantiations
@@ -4649,10 +4661,9 @@ void launch_export(Cols<T> X, Offs off, const int64_t* total, int64_t n, int64_t
   template void launch_drop<T>(Pair<T>, Pair<T>, Pair<T>, int, int, int, int, int, const double*, \
                                const double*, double, int64_t, double*, DevState*, hipStream_t,   \
                                const double*, int, double);                                       \
-  template Offs launch_len_offsets<T>(Cols<T>, const OffBuf&, const BigList&, int64_t, DevState*, \
+  template Offs launch_len_offsets<T>(Pair<T>, const OffBuf&, int64_t*, int64_t, DevState*,       \
                                       hipStream_t);                                               \
-  template void launch_export<T>(Cols<T>, Offs, const int64_t*, int64_t, int64_t*, int32_t*,      \
-                                 double*, int*, hipStream_t);                                     \
+  template void launch_export<T>(Pair<T>, Offs, const int64_t*, int64_t, int64_t*, hipStream_t);  \
   template void launch_score<T>(const Csr&, Pair<T>, double*, double*, BigList, DevState*, Tile,  \
                                 Tile, Tile, int64_t, hipStream_t);
 

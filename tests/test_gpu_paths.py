@@ -575,3 +575,23 @@ def test_floors_in_use_against_the_oracle(method):
         assert pattern_diff(M, ref.M) == (set(), set())
         assert value_err(M, ref.M) <= 1e-9
     assert written[0.75] < written[0.0] == written[1e6]
+
+
+@pytest.mark.parametrize("n", [1, 2, 64])
+def test_get_waits_and_copies_little(n):
+    """A small export is waits and copies: one copy for the size, and one before the three
+    lists (four more, with a wait each, took 20 us of 128 more than the host's transposition)."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    S = _spai()
+    A = sp.csr_matrix(sp.diags([np.full(n, 3.0), np.full(max(n - 1, 0), -1.0),
+                                np.full(max(n - 1, 0), -1.0)], [0, 1, -1], shape=(n, n)))
+    h = S.SPAI(A, "lomr", "global", 2.0, True, max_iter=4)
+    h.iterate(3)
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        M = h.get()
+        torch.cuda.synchronize()
+    h.close()
+    ref = O.run("lomr", A, oracle_rule(A, "global", 2.0, True), 3)
+    assert pattern_diff(M, ref.M) == (set(), set()) and value_err(M, ref.M) <= 1e-12
+    assert 0 < sum("DtoH" in e.name for e in prof.events()) <= 5

@@ -617,32 +617,37 @@ struct LossCall {
   }
 };
 
+// the float32 copies of the values (at `at`, value_bytes of the call's scratch), or the values
 template <typename T>
-int values(LossCall& c, const T** Av, const T** Mv) {
+size_t value_bytes(const LossCall& c) {
+  return sizeof(T) == 8 ? 0 : sizeof(T) * (size_t)(c.nnzA + c.nnzM);
+}
+template <typename T>
+void values(LossCall& c, char* at, const T** Av, const T** Mv) {
   if constexpr (sizeof(T) == 8) {
     *Av = (const T*)c.Av64;
     *Mv = (const T*)c.Mv64;
   } else {
-    int rc;
-    float *a, *m;
-    if ((rc = c.pool.alloc(&a, c.nnzA)) || (rc = c.pool.alloc(&m, c.nnzM))) return rc;
-    hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((c.nnzA + 255) / 256)), dim3(256), 0, c.s, c.Av64, a, c.nnzA);
-    hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((c.nnzM + 255) / 256)), dim3(256), 0, c.s, c.Mv64, m, c.nnzM);
-    *Av = (const T*)a;
-    *Mv = (const T*)m;
+    T *a = (T*)at, *m = a + c.nnzA;
+    if (c.nnzA)
+      hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((c.nnzA + 255) / 256)), dim3(256), 0, c.s, c.Av64, a, c.nnzA);
+    if (c.nnzM)
+      hipLaunchKernelGGL(k_to_f32, dim3((unsigned)((c.nnzM + 255) / 256)), dim3(256), 0, c.s, c.Mv64, m, c.nnzM);
+    *Av = a;
+    *Mv = m;
   }
-  return SPAI_OK;
 }
 
 template <typename T>
 int loss_fwd_t(LossCall& c, double* Lout) {
   int rc;
   const T *Av, *Mv;
-  if ((rc = values<T>(c, &Av, &Mv))) return rc;
   char* blk;
   const int nch = 512;
-  if ((rc = c.scratch(&blk, sizeof(double) * (size_t)(c.pA.n + nch + 1)))) return rc;
+  const size_t n8 = sizeof(double) * (size_t)(c.pA.n + nch + 1);
+  if ((rc = c.scratch(&blk, n8 + value_bytes<T>(c)))) return rc;
   double *rowpart = (double*)blk, *chunks = rowpart + c.pA.n, *out = chunks + nch;
+  values<T>(c, blk + n8, &Av, &Mv);
   launch_rows<T>(c.pA, Av, c.pM, Mv, rowpart, nullptr, 1.0, c.err, c.s);
   HIPCHK(hipGetLastError());
   const int64_t chunk = (c.pA.n + nch - 1) / nch;
@@ -661,15 +666,15 @@ template <typename T>
 int loss_bwd_t(LossCall& c, double dL, double* gA, double* gM, bool host_out) {
   int rc;
   const T *Av, *Mv;
-  if ((rc = values<T>(c, &Av, &Mv))) return rc;
   double *dgA = gA, *dgM = gM;
   char* blk;                            // row sums, and for gM the transpose map of M and A^T's values
   const size_t n8 = sizeof(double) * (size_t)c.pA.n;
   const size_t m8 = gM ? sizeof(int64_t) * (size_t)c.nnzM : 0, a8 = gM ? sizeof(T) * (size_t)c.nnzA : 0;
-  if ((rc = c.scratch(&blk, n8 + m8 + a8))) return rc;
+  if ((rc = c.scratch(&blk, n8 + m8 + a8 + value_bytes<T>(c)))) return rc;
   double* rowpart = (double*)blk;
   int64_t* tM = (int64_t*)(blk + n8);
   T* Atv = (T*)(blk + n8 + m8);
+  values<T>(c, blk + n8 + m8 + a8, &Av, &Mv);
   if (host_out) {
     if (gA && (rc = c.pool.alloc(&dgA, c.nnzA))) return rc;
     if (gM && (rc = c.pool.alloc(&dgM, c.nnzM))) return rc;

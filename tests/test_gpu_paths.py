@@ -595,3 +595,28 @@ def test_get_waits_and_copies_little(n):
     ref = O.run("lomr", A, oracle_rule(A, "global", 2.0, True), 3)
     assert pattern_diff(M, ref.M) == (set(), set()) and value_err(M, ref.M) <= 1e-12
     assert 0 < sum("DtoH" in e.name for e in prof.events()) <= 5
+
+
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_loss_calls_allocate_once(precision):
+    """Value and gradients on device matrices take one block a call, the float32 copies of the
+    mixed path among it (two more blocks made it slower than float64)."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    S = _spai()
+    A = W.grid9(20, 4)
+    M = sp.csr_matrix(W.square_pattern(A))
+    M.data = 0.1 * np.random.default_rng(1).standard_normal(M.nnz)
+    dev = [torch.sparse_csr_tensor(torch.from_numpy(X.indptr.astype(np.int64)),
+                                   torch.from_numpy(X.indices.astype(np.int64)),
+                                   torch.from_numpy(X.data), size=X.shape).cuda() for X in (A, M)]
+    o = S.Options(precision=precision)
+    L, g = S.loss_fwd(*dev, o), S.loss_bwd(*dev, options=o)     # (torch's blocks are then cached)
+    tol = 1e-12 if precision == "f64" else 1e-5
+    assert L == pytest.approx(O.loss(A, M), rel=tol)
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        S.loss_fwd(*dev, o)
+        S.loss_bwd(*dev, options=o)
+        torch.cuda.synchronize()
+    assert 0 < sum(e.name == "hipMalloc" for e in prof.events()) <= 2
+    del g

@@ -3248,9 +3248,9 @@ __device__ inline void sel_exp_decide(long long b, long long total, int bin, lon
 
 // histogram of the top key bits (63..52; for magnitudes bit 63 is 0) of the candidates,
 // counting diagonal entries apart.  SC: the keys are the signed scores sc[] stored beside
-// the candidates instead of their magnitudes.  Four waves per workgroup share one LDS
-// histogram, each walking its own 64-column groups: the histogram's LDS no longer limits
-// the waves in flight (one wave per histogram allowed five per SIMD, 7% slower).  The last
+// the candidates instead of their magnitudes.  Sixteen waves per workgroup share one LDS
+// histogram (of kExpCopies copies), each walking its own groups of columns: the histogram's
+// LDS does not limit the waves in flight, and few workgroups add their bins.  The last
 // workgroup finds the exponent bin of the (b+1)-th largest, b = m - (diagonal count if
 // excluded), and clears the histogram for the passes over the collected keys.
 constexpr int kHistWaves = 16;

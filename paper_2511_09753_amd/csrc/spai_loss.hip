@@ -6,8 +6,9 @@
 // Neither A M nor R is stored.  Row i of R is rebuilt from the rows of M selected by A's
 // row i, which gives f and d f / d A; column j of R is row j of R^T = I - M^T A^T, so the
 // same kernel on M^T and A^T (symmetric patterns, values gathered through the transpose
-// map) gives d f / d M.  One row per 64-lane wavefront, every sum in a fixed order, so the
-// results are deterministic.
+// map) gives d f / d M.  Rows and columns past its tile are left to k_loss_rows and
+// k_loss_cols.  One row per 64-lane wavefront, every sum in a fixed order, so the results are
+// deterministic.
 #include <hip/hip_runtime.h>
 
 #include <map>
